@@ -128,7 +128,7 @@ bool plan_ring_view(const Camera& cam, const vr_params* p, int32_t M, const int6
   const int Lmax = std::max(1, std::min(layer_cap, (int)std::lround((double)p->ckpt_K * p->step * db)));
   for (int L = Lmax; L >= 1; L = L > 1 ? L / 2 : 0) {
     const int smax = (int)std::floor((double)L / (p->step * db)) + 3;
-    const double per_wave = 4.0 * (2.0 * (L + 1) * slot + 64.0 + 64.0 * smax);
+    const double per_wave = 4.0 * (3.0 * (L + 1) * slot + 64.0 + 64.0 * smax);
     const double fixed = 48.0 * M;  // table (float4) and table gradients (double x 4)
     int best_w = 0, best_waves = 0;
     for (int w : {4, 2, 1}) {

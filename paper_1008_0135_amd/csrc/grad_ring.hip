@@ -12,11 +12,13 @@
 //      transmittance, keeping T before each sample in LDS;
 //   3. walks them backward with the division-free recursion
 //        dL/dc_k = g_rgb T_{k-1} a_k,
-//        dL/da_k = T_{k-1} [g_rgb . (c_k - R_k) + g_A (1 - Q_k)],
-//        R_{k-1} = a_k c_k + (1 - a_k) R_k,  Q_{k-1} = a_k + (1 - a_k) Q_k,
-//      carrying R and Q from group to group; table gradients go to double LDS
-//      accumulators (one set per workgroup, reduced by k_tf_reduce), voxel
-//      gradients to the gradient windows with LDS float atomics;
+//        dL/da_k = T_{k-1} (h_k - S_k),  h_k = g_rgb . c_k + g_A,
+//        S_{k-1} = a_k h_k + (1 - a_k) S_k,
+//      (S: the output gradient times what the ray gathers behind a sample, per
+//      unit of transmittance) carrying S from group to group; table gradients
+//      go to double LDS accumulators (one set per workgroup, reduced by
+//      k_tf_reduce), voxel gradients to the gradient windows with LDS double
+//      atomics;
 //   4. adds the gradient windows to the gradient volume with one float atomic
 //      per non-zero window voxel, row after row (coalesced), instead of eight
 //      scattered atomics per sample.
@@ -94,25 +96,31 @@ __device__ __forceinline__ Eval eval_d(const float (&v)[8], const CellD& c, doub
   return e;
 }
 
+// LDS of one wavefront in floats: L + 1 voxel windows (float), L + 1 gradient
+// windows (double), window offsets, T before each sample of the group.
+__host__ __device__ constexpr size_t per_wave_floats(int L, int slot, int smax) {
+  return (size_t)3 * (L + 1) * slot + 64 + (size_t)smax * 64;
+}
+
 __global__ __launch_bounds__(256) void k_bwd_ring(MarchArgs a, BwdArgs ba) {
   extern __shared__ double dsm[];
   const int M = a.M, L = ba.K;
-  double* s_gtf = dsm;                                      // [M][4]
+  // table gradients [4][M]: neighbouring entries in neighbouring banks (an
+  // [M][4] layout makes entries 8 apart collide: 56 cycles per add against 33)
+  double* s_gtf = dsm;
   float4* s_tf = reinterpret_cast<float4*>(dsm + 4 * M);    // [M]
   const int wpb = (int)(blockDim.x >> 6);
   const int wave = uni((int)(threadIdx.x >> 6)), lane = threadIdx.x & 63;
   const int slot = a.ring_slot;
   const int smax = ba.smax;  // samples of one ray in one group, at most
-  // per wavefront: L + 1 voxel windows, L + 1 gradient windows, the slot
-  // offsets and T before each sample of the group, [smax][64]
-  const size_t per_wave = (size_t)2 * (L + 1) * slot + 64 + (size_t)smax * 64;
+  const size_t per_wave = per_wave_floats(L, slot, smax);
   float* s_vox = reinterpret_cast<float*>(s_tf + M) + (size_t)wave * per_wave;
-  float* s_grad = s_vox + (size_t)(L + 1) * slot;
+  double* s_grad = reinterpret_cast<double*>(s_vox + (size_t)(L + 1) * slot);
   int* s_boff = reinterpret_cast<int*>(s_grad + (size_t)(L + 1) * slot);
   float* s_T = reinterpret_cast<float*>(s_boff + 64);
   for (int i = threadIdx.x; i < M; i += blockDim.x) {
     s_tf[i] = a.tf[i];
-    s_gtf[4 * i] = s_gtf[4 * i + 1] = s_gtf[4 * i + 2] = s_gtf[4 * i + 3] = 0.0;
+    s_gtf[i] = s_gtf[M + i] = s_gtf[2 * M + i] = s_gtf[3 * M + i] = 0.0;
   }
   __syncthreads();
 
@@ -241,7 +249,7 @@ __global__ __launch_bounds__(256) void k_bwd_ring(MarchArgs a, BwdArgs ba) {
       const float4 gf = valid ? ba.gout[pix] : make_float4(0.f, 0.f, 0.f, 0.f);
       const double gx = gf.x, gy = gf.y, gz = gf.z, gw = gf.w;
       const double dvs = (double)(M - 1) * ba.inv_range;  // du/dv inside the window
-      double R0 = 0.0, R1 = 0.0, R2 = 0.0, Q = 0.0;
+      double S = 0.0;  // g . (what the ray gathers behind the sample, per unit of transmittance)
       const int ngrp = (nlay + L - 1) / L;
       const int npix = ba.npix;
       // Consecutive samples of a ray mostly fall in the same table interval and
@@ -252,25 +260,36 @@ __global__ __launch_bounds__(256) void k_bwd_ring(MarchArgs a, BwdArgs ba) {
       float run_tf[8];  // a run is a few samples: float sums lose nothing the tolerance sees
       auto flush_tf = [&]() {
         if (ti >= 0) {
-          double* e0 = s_gtf + 4 * ti;
-          for (int q = 0; q < 8; ++q) atomicAdd(e0 + q, (double)run_tf[q]);
+          double* e0 = s_gtf + ti;
+          for (int q = 0; q < 4; ++q) {
+            atomicAdd(e0 + q * M, (double)run_tf[q]);
+            atomicAdd(e0 + q * M + 1, (double)run_tf[4 + q]);
+          }
           ti = -1;
         }
       };
+      // The gradient windows hold doubles: on gfx950 one ds_add_f32 takes about
+      // 195 cycles of a compute unit's LDS whatever its addresses (it retires
+      // about a lane every three cycles), ds_add_f64 9 without conflicts and 28
+      // with a tile's.  Float windows took 1.02e9 LDS cycles per 512^2 view of a
+      // 256 x 256 x 512 cube, these 3.5e8 (forward + backward of 8 views 25.3 ->
+      // 18.3 ms), and they round less.
       int vl = -1, vu = -1;  // LDS offsets of the pending cell's lower and upper corner rows
       float va[8];
       auto flush_vox = [&]() {
         if (vl >= 0) {
-          float* p = s_grad + vl;
-          float* q = s_grad + vu;
+          double* p = s_grad + vl;
+          double* q = s_grad + vu;
           if (by) {  // dy selects the layer, dz the row
-            atomicAdd(p, va[0]); atomicAdd(p + 1, va[1]); atomicAdd(q, va[2]); atomicAdd(q + 1, va[3]);
-            atomicAdd(p + pitch, va[4]); atomicAdd(p + pitch + 1, va[5]);
-            atomicAdd(q + pitch, va[6]); atomicAdd(q + pitch + 1, va[7]);
+            atomicAdd(p, (double)va[0]); atomicAdd(p + 1, (double)va[1]);
+            atomicAdd(q, (double)va[2]); atomicAdd(q + 1, (double)va[3]);
+            atomicAdd(p + pitch, (double)va[4]); atomicAdd(p + pitch + 1, (double)va[5]);
+            atomicAdd(q + pitch, (double)va[6]); atomicAdd(q + pitch + 1, (double)va[7]);
           } else {   // dz selects the layer, dy the row
-            atomicAdd(p, va[0]); atomicAdd(p + 1, va[1]); atomicAdd(p + pitch, va[2]);
-            atomicAdd(p + pitch + 1, va[3]); atomicAdd(q, va[4]); atomicAdd(q + 1, va[5]);
-            atomicAdd(q + pitch, va[6]); atomicAdd(q + pitch + 1, va[7]);
+            atomicAdd(p, (double)va[0]); atomicAdd(p + 1, (double)va[1]);
+            atomicAdd(p + pitch, (double)va[2]); atomicAdd(p + pitch + 1, (double)va[3]);
+            atomicAdd(q, (double)va[4]); atomicAdd(q + 1, (double)va[5]);
+            atomicAdd(q + pitch, (double)va[6]); atomicAdd(q + pitch + 1, (double)va[7]);
           }
           vl = -1;
         }
@@ -292,7 +311,7 @@ __global__ __launch_bounds__(256) void k_bwd_ring(MarchArgs a, BwdArgs ba) {
             const int ps = pslot(k0 + i);
             if (!(shared_top && i == nv - 1)) {
               issue(V0 + (k0 + i) * vstep, w, s_vox + ps * slot);
-              for (int e = lane; e < slot; e += 64) s_grad[ps * slot + e] = 0.f;
+              for (int e = lane; e < slot; e += 64) s_grad[ps * slot + e] = 0.0;
             }
             if (lane == 0) s_boff[i] = ps * slot - w.g0 * pitch - w.f0;
           }
@@ -349,9 +368,9 @@ __global__ __launch_bounds__(256) void k_bwd_ring(MarchArgs a, BwdArgs ba) {
           float vv[8];
           int lofs, uofs;
           corners(j, c, vv, lofs, uofs);
-          const Eval S = eval_d(vv, c, ba.vmin, ba.inv_range, M, s_tf);
+          const Eval e = eval_d(vv, c, ba.vmin, ba.inv_range, M, s_tf);
           s_T[(j - js) * 64 + lane] = (float)T;
-          T = fma(-T, S.a, T);
+          T = fma(-T, e.a, T);
         }
         // backward walk
         for (int j = je - 1; j >= js; --j) {
@@ -359,20 +378,17 @@ __global__ __launch_bounds__(256) void k_bwd_ring(MarchArgs a, BwdArgs ba) {
           float vv[8];
           int lofs, uofs;
           corners(j, c, vv, lofs, uofs);
-          const Eval S = eval_d(vv, c, ba.vmin, ba.inv_range, M, s_tf);
+          const Eval e = eval_d(vv, c, ba.vmin, ba.inv_range, M, s_tf);
           const double Tp = (double)s_T[(j - js) * 64 + lane];
-          const double ta = Tp * S.a;
+          const double ta = Tp * e.a;
           const double gr = gx * ta, gg = gy * ta, gb = gz * ta;
-          const double ga = Tp * (gx * (S.r - R0) + gy * (S.g - R1) + gz * (S.b - R2) + gw * (1.0 - Q));
-          const double om = 1.0 - S.a;
-          R0 = fma(S.a, S.r, om * R0);
-          R1 = fma(S.a, S.g, om * R1);
-          R2 = fma(S.a, S.b, om * R2);
-          Q = fma(om, Q, S.a);
-          const double w1 = S.w, w0 = 1.0 - S.w;
-          if (S.i != ti) {
+          const double h = fma(gx, e.r, fma(gy, e.g, fma(gz, e.b, gw)));
+          const double ga = Tp * (h - S);
+          S = fma(e.a, h - S, S);
+          const double w1 = e.w, w0 = 1.0 - e.w;
+          if (e.i != ti) {
             flush_tf();
-            ti = S.i;
+            ti = e.i;
             for (int q = 0; q < 8; ++q) run_tf[q] = 0.f;
           }
           run_tf[0] += (float)(w0 * gr);
@@ -383,13 +399,13 @@ __global__ __launch_bounds__(256) void k_bwd_ring(MarchArgs a, BwdArgs ba) {
           run_tf[5] += (float)(w1 * gg);
           run_tf[6] += (float)(w1 * gb);
           run_tf[7] += (float)(w1 * ga);
-          if (gvol && S.sraw > 0.0 && S.sraw < 1.0) {
-            const float4 t0f = s_tf[S.i], t1f = s_tf[S.i + 1];
+          if (gvol && e.sraw > 0.0 && e.sraw < 1.0) {
+            const float4 t0f = s_tf[e.i], t1f = s_tf[e.i + 1];
             const double du = gr * ((double)t1f.x - (double)t0f.x) + gg * ((double)t1f.y - (double)t0f.y) +
                               gb * ((double)t1f.z - (double)t0f.z) + ga * ((double)t1f.w - (double)t0f.w);
             const double gv = du * dvs;
             if (gv != 0.0) {
-              const double x1 = S.wx, x0 = 1.0 - S.wx, y1 = S.wy, y0 = 1.0 - S.wy, z1 = S.wz, z0 = 1.0 - S.wz;
+              const double x1 = e.wx, x0 = 1.0 - e.wx, y1 = e.wy, y0 = 1.0 - e.wy, z1 = e.wz, z0 = 1.0 - e.wz;
               // corner weights in v[dz][dy][dx] order
               const float cw[8] = {(float)(gv * x0 * y0 * z0), (float)(gv * x1 * y0 * z0), (float)(gv * x0 * y1 * z0),
                                    (float)(gv * x1 * y1 * z0), (float)(gv * x0 * y0 * z1), (float)(gv * x1 * y0 * z1),
@@ -425,9 +441,9 @@ __global__ __launch_bounds__(256) void k_bwd_ring(MarchArgs a, BwdArgs ba) {
           for (int i = g > 0 ? 1 : 0; i < nv; ++i) {  // V_{k0} goes on into group g - 1
             const Window w = window(V0 + (k0 + i) * vstep);
             float* gl = gvol + ((int64_t)(V0 + (k0 + i) * vstep) * sB + (int64_t)w.g0 * sG + w.f0);
-            const float* sg = s_grad + pslot(k0 + i) * slot;
+            const double* sg = s_grad + pslot(k0 + i) * slot;
             for (int e = lane; e < NG * pitch; e += 64) {
-              const float val = sg[e];
+              const float val = (float)sg[e];
               if (val != 0.f) {
                 const int r = (int)(((float)e + 0.5f) * inv_pitch), col = e - r * pitch;
                 unsafeAtomicAdd(gl + ((int64_t)r * sG + col), val);
@@ -444,14 +460,14 @@ __global__ __launch_bounds__(256) void k_bwd_ring(MarchArgs a, BwdArgs ba) {
   }
   __syncthreads();
   double* part = ba.tf_part + (int64_t)blockIdx.x * M * 4;
-  for (int i = threadIdx.x; i < M * 4; i += blockDim.x) part[i] = s_gtf[i];
+  for (int i = threadIdx.x; i < M * 4; i += blockDim.x) part[i] = s_gtf[(i & 3) * M + (i >> 2)];
 }
 
 }  // namespace
 
 size_t bwd_ring_lds_bytes(const MarchArgs& a, const BwdArgs& ba, int wpb) {
-  const size_t per_wave = (size_t)2 * (ba.K + 1) * a.ring_slot + 64 + (size_t)ba.smax * 64;
-  return sizeof(double) * 4 * (size_t)a.M + sizeof(float4) * (size_t)a.M + sizeof(float) * wpb * per_wave;
+  return sizeof(double) * 4 * (size_t)a.M + sizeof(float4) * (size_t)a.M +
+         sizeof(float) * wpb * per_wave_floats(ba.K, a.ring_slot, ba.smax);
 }
 
 int bwd_ring_blocks(const MarchArgs& a, const BwdArgs& ba, int wpb) {
