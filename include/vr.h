@@ -170,6 +170,12 @@ int vr_volume_create(vr_ctx *ctx, const float *src, int src_on_device, int64_t n
  */
 int vr_volume_wrap(vr_ctx *ctx, float *dev_ptr, int64_t n1, int64_t n2, int64_t n3, uintptr_t stream,
                    vr_volume **out);
+/*
+ * Frees the volume (waits for the device first).  Its device memory is kept
+ * for volumes created later, up to 1/32 of the device's memory in all, until
+ * the last context of the device is destroyed or an allocation of the library
+ * would fail without it.
+ */
 int vr_volume_destroy(vr_volume *vol);
 
 /* Global (min, max) over all voxels (paper Sec. 2.2).  Synchronises. */

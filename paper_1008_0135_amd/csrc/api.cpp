@@ -120,7 +120,7 @@ int ensure_device(void** p, size_t* cap, size_t need) {
     if (e != hipSuccess) return fail(VR_EHIP, "hipFree: %s", hipGetErrorString(e));
   }
   size_t bytes = std::max<size_t>(need, 256);
-  hipError_t e = hipMalloc(p, bytes);
+  hipError_t e = dev_malloc(p, bytes);
   if (e != hipSuccess) {
     *p = nullptr;
     (void)hipGetLastError();
@@ -145,7 +145,7 @@ int upload_tables(vr_ctx* ctx, hipStream_t s, const void* data, size_t bytes, vo
       sl.h = nullptr;
       return fail(VR_ENOMEM, "hipHostMalloc(%zu) failed", cap);
     }
-    if (hipMalloc(&sl.d, cap) != hipSuccess) {
+    if (dev_malloc(&sl.d, cap) != hipSuccess) {
       sl.d = nullptr;
       return fail(VR_ENOMEM, "hipMalloc(%zu) failed", cap);
     }
@@ -160,12 +160,13 @@ int upload_tables(vr_ctx* ctx, hipStream_t s, const void* data, size_t bytes, vo
 }
 
 // Global (min, max, non-finite count) of n floats at x, read back to the host.
-int reduce_minmax(vr_ctx* ctx, const float* x, int64_t n, hipStream_t s, float out3[3]) {
+// dst: also copy them there (16-byte aligned, as x then is; null: no copy).
+int reduce_minmax(vr_ctx* ctx, const float* x, int64_t n, hipStream_t s, float out3[3], float* dst) {
   int32_t nb = (int32_t)std::min<int64_t>(2048, std::max<int64_t>(1, n / (256 * 16)));
   VR_TRY(ensure_device(&ctx->d_small, &ctx->small_bytes, (size_t)nb * 16 + 64));
   float* part = reinterpret_cast<float*>(ctx->d_small);
   float* res = reinterpret_cast<float*>(reinterpret_cast<char*>(ctx->d_small) + (size_t)nb * 16);
-  VR_HIP(launch_minmax(x, n, part, nb, s));
+  VR_HIP(launch_minmax(x, n, dst, part, nb, s));
   VR_HIP(launch_minmax_final(part, nb, res, s));
   VR_HIP(hipMemcpyAsync(out3, res, 3 * sizeof(float), hipMemcpyDeviceToHost, s));
   VR_HIP(hipStreamSynchronize(s));
@@ -220,14 +221,18 @@ int resolve_window(vr_ctx* ctx, vr_volume* vol, hipStream_t s, double& vmin, dou
   return VR_OK;
 }
 
-int volume_range(vr_volume* vol, hipStream_t s) {
-  if (vol->have_range) return VR_OK;
-  float r[3];
-  VR_TRY(reduce_minmax(vol->ctx, vol->data, vol->n[0] * vol->n[1] * vol->n[2], s, r));
+static void set_range(vr_volume* vol, const float r[3]) {
   vol->vmin = r[0];
   vol->vmax = r[1];
   vol->nonfinite = (int64_t)r[2];
   vol->have_range = true;
+}
+
+int volume_range(vr_volume* vol, hipStream_t s) {
+  if (vol->have_range) return VR_OK;
+  float r[3];
+  VR_TRY(reduce_minmax(vol->ctx, vol->data, vol->n[0] * vol->n[1] * vol->n[2], s, r));
+  set_range(vol, r);
   return VR_OK;
 }
 
@@ -249,11 +254,13 @@ void fill_march_common(MarchArgs& a, const vr_volume* vol, const vr_params* p, d
 }
 
 // (Re)build the macrocell grid of edge mc over the whole volume (mc = 0: drop it).
-int build_macrocells(vr_volume* vol, int32_t mc, hipStream_t s) {
+// src: the volume this one is the permuted copy of, whose macrocells are the
+// same cells in permuted order (read 4 B x voxels less); null: from the voxels.
+int build_macrocells(vr_volume* vol, int32_t mc, const vr_volume* src, hipStream_t s) {
   if (vol->d_mc_mm || vol->d_mc_clear) {
-    VR_HIP(hipStreamSynchronize(s));
-    if (vol->d_mc_mm) VR_HIP(hipFree(vol->d_mc_mm));
-    if (vol->d_mc_clear) VR_HIP(hipFree(vol->d_mc_clear));
+    VR_HIP(hipDeviceSynchronize());  // renders of other streams may still read them
+    dev_give(vol->d_mc_mm, vol->mc_mm_bytes);
+    dev_give(vol->d_mc_clear, vol->mc_clear_bytes);
   }
   vol->d_mc_mm = nullptr;
   vol->d_mc_clear = nullptr;
@@ -268,16 +275,18 @@ int build_macrocells(vr_volume* vol, int32_t mc, hipStream_t s) {
   const int64_t count = c[0] * c[1] * c[2];
   if (count >= ((int64_t)1 << 31)) return fail(VR_EINVAL, "%lld macrocells: too many", (long long)count);
   const size_t cbytes = ((size_t)count + 255) & ~(size_t)255;  // flags, then the clear-cell counter
-  if (hipMalloc(&vol->d_mc_mm, (size_t)count * 8) != hipSuccess ||
-      hipMalloc(&vol->d_mc_clear, cbytes + 256) != hipSuccess) {
+  if (dev_take(&vol->d_mc_mm, (size_t)count * 8, &vol->mc_mm_bytes) != hipSuccess ||
+      dev_take(&vol->d_mc_clear, cbytes + 256, &vol->mc_clear_bytes) != hipSuccess) {
     (void)hipGetLastError();
-    if (vol->d_mc_mm) (void)hipFree(vol->d_mc_mm);
+    dev_give(vol->d_mc_mm, vol->mc_mm_bytes);
     vol->d_mc_mm = nullptr;
+    vol->d_mc_clear = nullptr;
     vol->d_mc_clear = nullptr;
     return fail(VR_ENOMEM, "hipMalloc for %lld macrocells failed", (long long)count);
   }
   vol->d_mc_count = reinterpret_cast<unsigned int*>(vol->d_mc_clear + cbytes);
-  VR_HIP(launch_mc_minmax(vol->data, vol->n, mc, c, vol->d_mc_mm, s));
+  if (src && src->mc == mc) VR_HIP(launch_mc_permute(src->d_mc_mm, src->mcn, vol->d_mc_mm, s));
+  else VR_HIP(launch_mc_minmax(vol->data, vol->n, mc, c, vol->d_mc_mm, s));
   VR_HIP(hipStreamSynchronize(s));
   vol->mc = mc;
   for (int i = 0; i < 3; i++) vol->mcn[i] = c[i];
@@ -429,6 +438,8 @@ int vr_create(int device, vr_ctx** out) {
     vr_destroy(ctx);
     return fail(VR_ENOMEM, "pinned staging for the allocation-free batch failed");
   }
+  pool_enter(device);
+  ctx->pooled = true;
   *out = ctx;
   return VR_OK;
 }
@@ -465,6 +476,7 @@ int vr_destroy(vr_ctx* ctx) {
   if (ctx->aux_fork_ev) (void)hipEventDestroy(ctx->aux_fork_ev);
   if (ctx->na_host) (void)hipHostFree(ctx->na_host);
   if (ctx->na_copied) (void)hipEventDestroy(ctx->na_copied);
+  if (ctx->pooled) pool_leave(ctx->device);
   delete ctx;
   return VR_OK;
 }
@@ -556,7 +568,7 @@ int vr_volume_create(vr_ctx* ctx, const float* src, int src_on_device, int64_t n
   const int64_t count = dn[0] * dn[1] * dn[2];
   const size_t bytes = (size_t)count * sizeof(float);
   // 64 floats of slack after the voxels: staged loads may read past a row's end
-  if (hipMalloc(&vol->data, bytes + 256) != hipSuccess) {
+  if (dev_take(&vol->data, bytes + 256, &vol->data_bytes) != hipSuccess) {
     (void)hipGetLastError();
     delete vol;
     return fail(VR_ENOMEM, "hipMalloc(%zu bytes) for the volume failed", bytes);
@@ -564,8 +576,14 @@ int vr_volume_create(vr_ctx* ctx, const float* src, int src_on_device, int64_t n
   vol->owned = true;
   int rc = VR_OK;
   hipError_t e = hipSuccess;
+  float range[3] = {0.f, 0.f, 0.f};
+  bool ranged = false;
   const bool whole = !sub_origin || (so[0] == 0 && so[1] == 0 && so[2] == 0 && dn[0] == n1 && dn[1] == n2 && dn[2] == n3);
-  if (whole) {
+  if (whole && src_on_device && ((uintptr_t)src & 15) == 0) {
+    // copied and reduced in one pass (read once)
+    rc = reduce_minmax(ctx, src, count, s, range, vol->data);
+    ranged = rc == VR_OK;
+  } else if (whole) {
     e = hipMemcpyAsync(vol->data, src, bytes, src_on_device ? hipMemcpyDeviceToDevice : hipMemcpyHostToDevice, s);
   } else if (src_on_device) {
     e = launch_copy_box(src, sn, so, vol->data, dn, s);
@@ -577,6 +595,7 @@ int vr_volume_create(vr_ctx* ctx, const float* src, int src_on_device, int64_t n
     }
   }
   if (e != hipSuccess) rc = fail(VR_EHIP, "volume upload: %s", hipGetErrorString(e));
+  if (ranged) set_range(vol, range);
   if (rc == VR_OK) rc = volume_range(vol, s);
   if (rc == VR_OK && vol->nonfinite > 0)
     rc = fail(VR_ENONFINITE, "volume holds %lld non-finite voxels", (long long)vol->nonfinite);
@@ -623,11 +642,11 @@ int vr_volume_destroy(vr_volume* vol) {
   if (!vol) return VR_OK;
   DeviceGuard g(vol->ctx->device);
   (void)hipDeviceSynchronize();
-  if (vol->owned && vol->data) (void)hipFree(vol->data);
-  if (vol->d_bricks) (void)hipFree(vol->d_bricks);
-  if (vol->d_store) (void)hipFree(vol->d_store);
-  if (vol->d_mc_mm) (void)hipFree(vol->d_mc_mm);
-  if (vol->d_mc_clear) (void)hipFree(vol->d_mc_clear);
+  if (vol->owned) dev_give(vol->data, vol->data_bytes);
+  dev_give(vol->d_bricks, vol->bricks_bytes);
+  dev_give(vol->d_store, vol->store_bytes);
+  dev_give(vol->d_mc_mm, vol->mc_mm_bytes);
+  dev_give(vol->d_mc_clear, vol->mc_clear_bytes);
   if (vol->twin) vr_volume_destroy(vol->twin);
   delete vol;
   return VR_OK;
@@ -656,7 +675,10 @@ int vr_volume_dims(const vr_volume* vol, int64_t n[3]) {
 
 // Brick records, storage and ranges of partition P for vol (and its
 // macrocells); the caller holds the context's call order.
-static int brick_volume(vr_volume* vol, Partition& P, bool materialize, int32_t macrocell, hipStream_t s) {
+// src: the volume vol is the permuted copy of, already bricked (else null), and
+// src_brick the brick of src each brick of P is.
+static int brick_volume(vr_volume* vol, Partition& P, bool materialize, int32_t macrocell, const vr_volume* src,
+                        const std::vector<int32_t>& src_brick, hipStream_t s) {
   vr_ctx* ctx = vol->ctx;
   const int32_t nb = (int32_t)P.boxes.size();
   const int64_t* n = vol->n;
@@ -676,8 +698,8 @@ static int brick_volume(vr_volume* vol, Partition& P, bool materialize, int32_t 
   }
   // free previous partition storage
   if (vol->d_store) {
-    VR_HIP(hipStreamSynchronize(s));
-    VR_HIP(hipFree(vol->d_store));
+    VR_HIP(hipDeviceSynchronize());  // renders of other streams may still read it
+    dev_give(vol->d_store, vol->store_bytes);
     vol->d_store = nullptr;
   }
   std::vector<int64_t> store_off((size_t)nb, 0);
@@ -690,7 +712,7 @@ static int brick_volume(vr_volume* vol, Partition& P, bool materialize, int32_t 
       total += (c + 63) & ~(int64_t)63;
     }
     total += 64;  // slack after the last brick
-    if (hipMalloc(&vol->d_store, (size_t)total * sizeof(float)) != hipSuccess) {
+    if (dev_take(&vol->d_store, (size_t)total * sizeof(float), &vol->store_bytes) != hipSuccess) {
       (void)hipGetLastError();
       vol->d_store = nullptr;
       return fail(VR_ENOMEM, "hipMalloc(%lld floats) for materialised bricks failed", (long long)total);
@@ -701,21 +723,30 @@ static int brick_volume(vr_volume* vol, Partition& P, bool materialize, int32_t 
       VR_HIP(launch_copy_box(vol->data, n, so, vol->d_store + store_off[b], dn, s));
     }
   }
-  // per-brick (min, max) over stored voxels
-  int zper = 4, zmax = 1;
-  for (int32_t b = 0; b < nb; b++) zmax = std::max<int>(zmax, (int)(sboxes[6 * b + 5] - sboxes[6 * b + 2] + 1));
-  const int zgroups = (zmax + zper - 1) / zper;
-  const size_t need = (size_t)nb * 48 + (size_t)nb * zgroups * 8 + (size_t)nb * 8 + 1024;
-  VR_TRY(ensure_device(&ctx->d_scratch, &ctx->scratch_bytes, need));
-  char* sc = reinterpret_cast<char*>(ctx->d_scratch);
-  int64_t* d_boxes = reinterpret_cast<int64_t*>(sc);
-  float* d_part = reinterpret_cast<float*>(sc + (size_t)nb * 48);
-  float* d_mm = reinterpret_cast<float*>(sc + (size_t)nb * 48 + (size_t)nb * zgroups * 8);
-  VR_HIP(hipMemcpyAsync(d_boxes, sboxes.data(), (size_t)nb * 48, hipMemcpyHostToDevice, s));
-  VR_HIP(launch_brick_minmax_parts(vol->data, n, d_boxes, nb, zgroups, zper, d_part, d_mm, s));
+  // per-brick (min, max) over stored voxels; the permuted copy's bricks hold
+  // the same voxels as the source's
   std::vector<float> mm(2 * (size_t)nb);
-  VR_HIP(hipMemcpyAsync(mm.data(), d_mm, (size_t)nb * 8, hipMemcpyDeviceToHost, s));
-  VR_HIP(hipStreamSynchronize(s));
+  if (src) {
+    for (int32_t b = 0; b < nb; b++) {
+      mm[2 * b] = src->bdesc[src_brick[b]].vmin;
+      mm[2 * b + 1] = src->bdesc[src_brick[b]].vmax;
+    }
+  } else {
+    const int zper = kBrickRangePlanes;
+    int zmax = 1;
+    for (int32_t b = 0; b < nb; b++) zmax = std::max<int>(zmax, (int)(sboxes[6 * b + 5] - sboxes[6 * b + 2] + 1));
+    const int zgroups = (zmax + zper - 1) / zper;
+    const size_t need = (size_t)nb * 48 + (size_t)nb * zgroups * 8 + (size_t)nb * 8 + 1024;
+    VR_TRY(ensure_device(&ctx->d_scratch, &ctx->scratch_bytes, need));
+    char* sc = reinterpret_cast<char*>(ctx->d_scratch);
+    int64_t* d_boxes = reinterpret_cast<int64_t*>(sc);
+    float* d_part = reinterpret_cast<float*>(sc + (size_t)nb * 48);
+    float* d_mm = reinterpret_cast<float*>(sc + (size_t)nb * 48 + (size_t)nb * zgroups * 8);
+    VR_HIP(hipMemcpyAsync(d_boxes, sboxes.data(), (size_t)nb * 48, hipMemcpyHostToDevice, s));
+    VR_HIP(launch_brick_minmax_parts(vol->data, n, d_boxes, nb, zgroups, zper, d_part, d_mm, s));
+    VR_HIP(hipMemcpyAsync(mm.data(), d_mm, (size_t)nb * 8, hipMemcpyDeviceToHost, s));
+    VR_HIP(hipStreamSynchronize(s));
+  }
   // brick records
   std::vector<DevBrick> recs((size_t)nb);
   vol->bdesc.assign((size_t)nb, vr_brick_desc());
@@ -758,10 +789,11 @@ static int brick_volume(vr_volume* vol, Partition& P, bool materialize, int32_t 
     d.vmax = r.vmax;
   }
   if (vol->d_bricks) {
-    VR_HIP(hipFree(vol->d_bricks));
+    VR_HIP(hipDeviceSynchronize());
+    dev_give(vol->d_bricks, vol->bricks_bytes);
     vol->d_bricks = nullptr;
   }
-  if (hipMalloc(&vol->d_bricks, sizeof(DevBrick) * (size_t)nb) != hipSuccess) {
+  if (dev_take(&vol->d_bricks, sizeof(DevBrick) * (size_t)nb, &vol->bricks_bytes) != hipSuccess) {
     (void)hipGetLastError();
     vol->d_bricks = nullptr;
     return fail(VR_ENOMEM, "hipMalloc for the brick table failed");
@@ -772,7 +804,7 @@ static int brick_volume(vr_volume* vol, Partition& P, bool materialize, int32_t 
   vol->bricked = true;
   vol->materialized = mat;
   vol->version++;
-  return build_macrocells(vol, macrocell, s);
+  return build_macrocells(vol, macrocell, src, s);
 }
 
 static void destroy_twin(vr_volume* vol) {
@@ -794,7 +826,7 @@ static int make_twin(vr_volume* vol, int32_t macrocell, hipStream_t s) {
     t->n[1] = n[2];
     t->n[2] = n[0];
     t->spectral_axis = 1;  // the volume's axis 3 is the copy's axis 2
-    if (hipMalloc(&t->data, sizeof(float) * (size_t)(n[0] * n[1] * n[2]) + 256) != hipSuccess) {
+    if (dev_take(&t->data, sizeof(float) * (size_t)(n[0] * n[1] * n[2]) + 256, &t->data_bytes) != hipSuccess) {
       (void)hipGetLastError();
       delete t;
       return fail(VR_ENOMEM, "hipMalloc for the permuted copy (%lld floats) failed", (long long)(n[0] * n[1] * n[2]));
@@ -809,8 +841,9 @@ static int make_twin(vr_volume* vol, int32_t macrocell, hipStream_t s) {
   t->nonfinite = vol->nonfinite;
   VR_TRY(make_whole_brick(t));
   Partition P;
-  permute_partition(vol->part, t->n, P);
-  VR_TRY(brick_volume(t, P, false, macrocell, s));
+  std::vector<int32_t> src_brick;
+  permute_partition(vol->part, t->n, P, src_brick);
+  VR_TRY(brick_volume(t, P, false, macrocell, vol, src_brick, s));
   t->version++;
   return VR_OK;
 }
@@ -835,7 +868,7 @@ int vr_volume_brick(vr_volume* vol, const vr_brick_spec* spec, uintptr_t stream)
   DeviceGuard g(ctx->device);
   hipStream_t s = (hipStream_t)stream;
   VR_TRY(ctx_begin(ctx, s));
-  VR_TRY(brick_volume(vol, P, spec->materialize != 0, spec->macrocell, s));
+  VR_TRY(brick_volume(vol, P, spec->materialize != 0, spec->macrocell, nullptr, {}, s));
   if (spec->twin) {
     VR_TRY(make_twin(vol, spec->macrocell, s));
   } else if (vol->twin) {
@@ -895,7 +928,7 @@ int vr_mask_set(vr_ctx* ctx, const float* mask, int32_t n, int src_on_device, ui
     if (ctx->d_mask) VR_HIP(hipFree(ctx->d_mask));
     ctx->d_mask = nullptr;
     ctx->mask_cap = 0;
-    if (hipMalloc(&ctx->d_mask, sizeof(float) * (size_t)n) != hipSuccess) {
+    if (dev_malloc(&ctx->d_mask, sizeof(float) * (size_t)n) != hipSuccess) {
       (void)hipGetLastError();
       ctx->d_mask = nullptr;
       return fail(VR_ENOMEM, "hipMalloc for the mask failed");
@@ -932,7 +965,7 @@ int vr_tf_set(vr_ctx* ctx, const float* rgba, int32_t m, double vmin, double vma
   if (m > ctx->tf_cap) {
     if (ctx->d_tf) VR_HIP(hipFree(ctx->d_tf));
     ctx->d_tf = nullptr;
-    if (hipMalloc(&ctx->d_tf, sizeof(float4) * (size_t)m) != hipSuccess) {
+    if (dev_malloc(&ctx->d_tf, sizeof(float4) * (size_t)m) != hipSuccess) {
       (void)hipGetLastError();
       ctx->d_tf = nullptr;
       ctx->tf_cap = 0;
@@ -946,7 +979,7 @@ int vr_tf_set(vr_ctx* ctx, const float* rgba, int32_t m, double vmin, double vma
   if (m + 1 > ctx->tf_nz_cap) {
     if (ctx->d_tf_nz) VR_HIP(hipFree(ctx->d_tf_nz));
     ctx->d_tf_nz = nullptr;
-    if (hipMalloc(&ctx->d_tf_nz, sizeof(int32_t) * ((size_t)m + 1)) != hipSuccess) {
+    if (dev_malloc(&ctx->d_tf_nz, sizeof(int32_t) * ((size_t)m + 1)) != hipSuccess) {
       (void)hipGetLastError();
       ctx->d_tf_nz = nullptr;
       ctx->tf_nz_cap = 0;
@@ -1099,7 +1132,8 @@ int vr_plan_cells(const int64_t dims[3], const vr_brick_spec* spec, const vr_vie
     n[1] = dims[2];
     n[2] = dims[0];
     Partition Q;
-    permute_partition(P, n, Q);
+    std::vector<int32_t> src;
+    permute_partition(P, n, Q, src);
     P = Q;
   }
   Camera cam;

@@ -216,7 +216,7 @@ int render_batch(vr_ctx* ctx, const vr_request* reqs, int32_t n, const vr_params
     b->total_items = items;
     b->max_M = maxM;
     const size_t bytes = sizeof(BatchReq) * (size_t)std::max(n, 1);
-    if (hipMalloc(&b->d_reqs, bytes) != hipSuccess || hipMalloc(&b->d_counter, 256) != hipSuccess ||
+    if (dev_malloc(&b->d_reqs, bytes) != hipSuccess || dev_malloc(&b->d_counter, 256) != hipSuccess ||
         hipHostMalloc(&b->h_reqs, bytes, hipHostMallocDefault) != hipSuccess) {
       (void)hipGetLastError();
       batch_free(b);

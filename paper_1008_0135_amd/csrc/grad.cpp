@@ -219,8 +219,8 @@ int render_with_state(vr_ctx* ctx, vr_volume* vol, const vr_view* views, int32_t
     st->ckpt_bytes = ck_bytes;
     st->ckpt_j_bytes = ckj_bytes;
     st->nused_bytes = nu_bytes;
-    if (hipMalloc(&st->d_ckpt, ck_bytes) != hipSuccess || hipMalloc(&st->d_nused, nu_bytes) != hipSuccess ||
-        (ckj_bytes > 0 && hipMalloc(&st->d_ckpt_j, ckj_bytes) != hipSuccess)) {
+    if (dev_malloc(&st->d_ckpt, ck_bytes) != hipSuccess || dev_malloc(&st->d_nused, nu_bytes) != hipSuccess ||
+        (ckj_bytes > 0 && dev_malloc(&st->d_ckpt_j, ckj_bytes) != hipSuccess)) {
       (void)hipGetLastError();
       vr_state_destroy(st);
       return fail(VR_ENOMEM, "hipMalloc for %zu bytes of checkpoints failed", ck_bytes);

@@ -43,6 +43,7 @@ struct DeviceGuard {
 
 struct vr_ctx {
   int device = 0;
+  bool pooled = false;  // counted among the device pool's contexts
   // transfer function slot
   float4* d_tf = nullptr;
   int32_t tf_cap = 0, tf_m = 0;
@@ -161,6 +162,8 @@ struct vr_volume {
   std::vector<vr_brick_desc> bdesc;
   vr::DevBrick* d_bricks = nullptr;
   float* d_store = nullptr;  // materialised brick storage
+  // sizes of the blocks above and below as the pool gave them
+  size_t data_bytes = 0, bricks_bytes = 0, store_bytes = 0, mc_mm_bytes = 0, mc_clear_bytes = 0;
   // macrocells (empty-space skipping): edge in cells, counts, (min, max), and the
   // per-table "opacity is 0 over the range" flags with the table they were made for
   int32_t mc = 0;
@@ -188,9 +191,27 @@ int stage_begin(vr_ctx* ctx, int stage, hipStream_t s);
 int aux_fork(vr_ctx* ctx, hipStream_t s);
 int aux_join(vr_ctx* ctx, hipStream_t s);
 int stage_end(vr_ctx* ctx, hipStream_t s);
+// Device memory (pool.cpp; the device is current).  dev_malloc: hipMalloc, and
+// once more after the pool gave its memory back if that fails.  dev_take /
+// dev_give: a block of at least `bytes` from the pool or newly allocated (its
+// size in *got), and back to the pool once no stream uses it any more.
+hipError_t dev_malloc(void** p, size_t bytes);
+template <class T>
+inline hipError_t dev_malloc(T** p, size_t bytes) {
+  return dev_malloc(reinterpret_cast<void**>(p), bytes);
+}
+hipError_t dev_take(void** p, size_t bytes, size_t* got);
+template <class T>
+inline hipError_t dev_take(T** p, size_t bytes, size_t* got) {
+  return dev_take(reinterpret_cast<void**>(p), bytes, got);
+}
+void dev_give(void* p, size_t bytes);
+// contexts of a device: the last one to leave frees the device's pool
+void pool_enter(int device);
+void pool_leave(int device);
 int ensure_device(void** p, size_t* cap, size_t need);
 int upload_tables(vr_ctx* ctx, hipStream_t s, const void* data, size_t bytes, void** dev);
-int reduce_minmax(vr_ctx* ctx, const float* x, int64_t n, hipStream_t s, float out3[3]);
+int reduce_minmax(vr_ctx* ctx, const float* x, int64_t n, hipStream_t s, float out3[3], float* dst = nullptr);
 int volume_range(vr_volume* vol, hipStream_t s);
 int check_view(const vr_view* v, const int64_t n[3]);
 int check_params(const vr_params* p);

@@ -114,7 +114,7 @@ int vr_autotune(vr_ctx* ctx, const vr_volume* cvol, const vr_view* view, const v
   DeviceGuard g(ctx->device);
   hipStream_t s = (hipStream_t)stream;
   float* img = nullptr;
-  if (hipMalloc(&img, sizeof(float) * 4 * (size_t)view->W * view->H) != hipSuccess) {
+  if (dev_malloc(&img, sizeof(float) * 4 * (size_t)view->W * view->H) != hipSuccess) {
     (void)hipGetLastError();
     return fail(VR_ENOMEM, "hipMalloc for the tuning image failed");
   }

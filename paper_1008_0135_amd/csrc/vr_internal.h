@@ -374,8 +374,10 @@ size_t bwd_ring_lds_bytes(const MarchArgs& a, const BwdArgs& ba, int wpb);
 int bwd_ring_blocks(const MarchArgs& a, const BwdArgs& ba, int wpb);
 hipError_t launch_march_lds(const MarchArgs& a, hipStream_t s);
 hipError_t launch_composite(const CompArgs& a, hipStream_t s);
-hipError_t launch_minmax(const float* x, int64_t n, float* partial, int32_t nblocks, hipStream_t s);
+// partials of x; dst non-null: also copies x there (both 16-byte aligned)
+hipError_t launch_minmax(const float* x, int64_t n, float* dst, float* partial, int32_t nblocks, hipStream_t s);
 hipError_t launch_minmax_final(const float* partial, int32_t nblocks, float* out3, hipStream_t s);
+constexpr int kBrickRangePlanes = 2;  // z-planes of one workgroup of the brick ranges
 // Per-brick (min, max) over stored voxel boxes: boxes is a device array of
 // nb x (slo1, slo2, slo3, shi1, shi2, shi3); each brick's z range is split into
 // zgroups groups of zper planes; scratch holds nb*zgroups float2 partials.
@@ -396,6 +398,8 @@ hipError_t launch_twin(const float* src, const int64_t n[3], float* dst, hipStre
 // Macrocell (min, max) pairs [c3][c2][c1] of edge `mc` over the volume (mc in [2, 1024]).
 hipError_t launch_mc_minmax(const float* vol, const int64_t n[3], int mc, const int64_t c[3], float* out2,
                             hipStream_t s);
+// The permuted copy's macrocells from the source's ([c3][c2][c1] pairs, counts c): [c1][c3][c2].
+hipError_t launch_mc_permute(const float* mm2, const int64_t c[3], float* out2, hipStream_t s);
 // clear[i] = 1 when the table's opacity is 0 over every entry macrocell i can reach
 // (nz: [M + 1] prefix count of entries with opacity != 0); *nclear = number of such cells.
 hipError_t launch_mc_classify(const float* mm2, int64_t count, const int32_t* nz, int M, double vmin, double vmax,
