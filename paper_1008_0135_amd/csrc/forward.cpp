@@ -29,8 +29,52 @@ constexpr int32_t kRingMinWaves = 2;
 // register-staged cells march: its registers leave room for 4 wavefronts per SIMD
 constexpr int32_t kRingRegWaves = 16;
 constexpr int32_t kLdsPerCu = 160 * 1024;
+// perspective views with rays closer than this many voxels (on the plane
+// through the box centre): cells hold 20 rays on average there (their sizes
+// follow the brick's densest point) and gathers are as fast (two views of
+// 1024 x 1024 x 768 at 1.6 voxels: 8.4 ms against 8.8); at 3.2 voxels the
+// cells take 11.9 ms per view of the 24 GiB cube, gathers 14.7
+constexpr double kPerspCellPitch = 1.8;
+// whole-ray termination, views whose gathers are estimated below this: every
+// ray through all its bricks in one launch (0.3 ms per 200^2 view of 64 bricks
+// against 1.6 ms in 10 launches); above, launches per front of bricks, in
+// which a launch works on a compact part of the volume
+constexpr double kThruBelow = 0.4e-3;
 
 }  // namespace
+
+// Estimated times of a view (seconds) by the cell march with the shape fs
+// (infinite when null) and by gathers, for boxes marched side by side.
+//   gathers: 182 G samples/s with rays 1.2 voxels apart or closer (the cache
+//     lookups of four row pairs per sample bind), falling as 1 / pitch (60 at
+//     4.2 voxels, 86 measured on the 24 GiB cube at 3.2);
+//   cells: the larger of 300 G samples/s (vector instructions), 2.3 times the
+//     boxes' bytes at 7.2 TB/s (window traffic), and the chain of one wavefront
+//     (1.3 us a layer, more with the wide windows of sparse rays), which no
+//     number of wavefronts shortens.  Rays less than 0.75 voxels apart, where
+//     the narrowest cells hold more than 64 of them, are left to the gathers
+//     (300^3 at 1024^2, 0.5 voxels: 6.0 ms by cells, 2.1 by gathers).
+MarchTimes march_times(const Camera& cam, const std::vector<Box>& boxes, double step, const FootShape* fs) {
+  MarchTimes t;
+  t.pitch = cam.S / (double)cam.W;
+  double samples = 0.0, bytes = 0.0;
+  int64_t layers = 0;
+  const double* d = cam.e3;
+  for (const Box& b : boxes) {
+    const double e[3] = {(double)(b.hi[0] - b.lo[0]), (double)(b.hi[1] - b.lo[1]), (double)(b.hi[2] - b.lo[2])};
+    const double vol = e[0] * e[1] * e[2];
+    const double area = std::fabs(d[0]) * e[1] * e[2] + std::fabs(d[1]) * e[0] * e[2] + std::fabs(d[2]) * e[0] * e[1];
+    const double rays = std::min(area / (t.pitch * t.pitch), (double)cam.W * cam.H);
+    samples += rays * vol / std::max(area, 1.0) / step;
+    bytes += 4.0 * vol;
+    if (fs) layers = std::max(layers, b.hi[fs->axis] - b.lo[fs->axis]);
+  }
+  t.gather = 20e-6 + samples * std::max(1.0, t.pitch / 1.2) / 182e9;
+  if (!fs || t.pitch < 0.75) return t;
+  const double chain = (double)layers * 1.3e-6 * (1.0 + std::max(0.0, t.pitch - 4.0) / 4.0);
+  t.cells = std::max(std::max(samples / 300e9, 2.3 * bytes / 7.2e12), chain);
+  return t;
+}
 
 bool pick_foot(const Camera& cam, const int64_t n[3], int32_t M, bool plain, bool reg_on, int32_t nslots,
                double rays, int32_t pad, int32_t kmax, FootShape& fs, int32_t max_px) {
@@ -136,6 +180,15 @@ int render_forward(vr_ctx* ctx, vr_volume* vol, const vr_view* views, int32_t nv
   // opacity tested over the whole ray: bricks marched in front-to-back waves
   // straight into the frame, each ray carrying its state from brick to brick
   const bool global = bricked && out && !extras && !base.mip && p->ert_scope == VR_ERT_GLOBAL;
+  // the march is chosen per view (the default shapes and no forced march)
+  const bool pick = !extras && (mode == 0 || mode == 3) && tw == 8;
+  if (pick && base.mc > 0) {
+    // few clear macrocells: what the walk from macrocell to macrocell and the
+    // 16-sample blocks around the others cost outweighs the samples saved (a
+    // block-gathered sample costs about twice a sample of the cell march)
+    const int64_t cells = vol->mcn[0] * vol->mcn[1] * vol->mcn[2];
+    if (2 * vol->mc_nclear < cells) base.mc = 0;
+  }
 
   std::vector<ViewPlan> plans((size_t)nviews);
   std::vector<Camera> cams((size_t)nviews);
@@ -160,150 +213,173 @@ int render_forward(vr_ctx* ctx, vr_volume* vol, const vr_view* views, int32_t nv
       vp.pixels = (int64_t)W * H;
     }
   }
-  // perspective views on the ring march: rays from the eye spread with depth,
-  // so the 8 x 8 tiles of far bricks need windows about twice those of near
-  // ones, and one slot sized for nearly all tiles leaves the near bricks at a
-  // fraction of the wavefronts their windows allow.  Bricks are grouped into
-  // classes of similar window (about equal tile counts), launched one class
-  // at a time with a slot of its own.
-  // bricks of a view grouped into ncls classes of about equal work by a size
-  // key (the window), launched one class at a time; items(b): the work items
-  // (tiles or cells) of brick view b
-  auto group_classes = [&](ViewPlan& vp, const std::vector<double>& key, int32_t ncls, auto items) {
-    std::vector<int32_t> idx(vp.bv.size());
-    int64_t total = 0;
-    for (int32_t i = 0; i < (int32_t)vp.bv.size(); i++) {
-      idx[i] = i;
-      total += items(vp.bv[i]);
+  // work items of a view marched by gathers: 64 / D pixels each (8 x 8 with
+  // macrocell skipping)
+  auto gather_tiles = [](ViewPlan& vp, int32_t first, int32_t last, int32_t w, int32_t h) {
+    int32_t t = 0;
+    for (int32_t i = first; i < last; i++) {
+      DevBrickView& b = vp.bv[i];
+      b.tiles_x = (b.w + w - 1) / w;
+      b.tile_begin = t;
+      t += b.tiles_x * ((b.h + h - 1) / h);
     }
-    std::stable_sort(idx.begin(), idx.end(), [&](int32_t x, int32_t y) { return key[x] < key[y]; });
-    // class boundaries at about equal work; within a class, brick order
-    std::vector<int32_t> cls(vp.bv.size(), 0);
-    int64_t acc = 0;
-    for (int32_t i : idx) {
-      cls[i] = (int32_t)std::min<int64_t>(ncls - 1, acc * ncls / std::max<int64_t>(1, total));
-      acc += items(vp.bv[i]);
-    }
-    std::vector<DevBrickView> nbv;
-    std::vector<int32_t> where(vp.bv.size(), -1);
-    nbv.reserve(vp.bv.size());
-    vp.class_begin.clear();
-    vp.class_tiles.clear();
-    for (int32_t c = 0; c < ncls; c++) {
-      const int32_t first = (int32_t)nbv.size();
-      int32_t t = 0;
-      for (int32_t i = 0; i < (int32_t)vp.bv.size(); i++)
-        if (cls[i] == c) {
-          DevBrickView b = vp.bv[i];
-          b.tile_begin = t;
-          t += (int32_t)items(b);
-          where[i] = (int32_t)nbv.size();
-          nbv.push_back(b);
-        }
-      if (t == 0) continue;
-      vp.class_begin.push_back(first);
-      vp.class_tiles.push_back(t);
-    }
-    vp.class_begin.push_back((int32_t)nbv.size());
-    for (int32_t& l : vp.layers_order) l = where[l];
-    vp.bv.swap(nbv);
+    return t;
   };
-  // perspective views on footprint cells sized per brick (the plain march of
-  // emission-absorption or MIP, register-staged): one slab axis for the view,
-  // the one along which the eye lies outside every brick's slab.  A view
-  // where some brick does not suit keeps the 8 x 8 tiles.
+  auto gather_view = [&](ViewPlan& vp, int32_t depth) {
+    vp.deep = depth;
+    const int32_t e = vp.skip ? 8 : depth == 16 ? 2 : 4;
+    if (global && !vp.thru)
+      for (size_t w = 0; w + 1 < vp.wave_begin.size(); w++)
+        vp.wave_tiles[w] = gather_tiles(vp, vp.wave_begin[w], vp.wave_begin[w + 1], e, e);
+    else if (vp.thru) vp.ntiles = ((W + e - 1) / e) * ((H + e - 1) / e);
+    else vp.ntiles = gather_tiles(vp, 0, (int32_t)vp.bv.size(), e, e);
+  };
+  // every ray through all its bricks in one launch: bricks front to back
+  auto thru_order = [&](int32_t v) {
+    ViewPlan& vp = plans[v];
+    plan_bricked_view(vol, cams[v], p, tw, ctx->h_tf.data(), ctx->tf_m, vmin, vmax, vp, false);
+    std::vector<DevBrickView> o;
+    for (int32_t i : vp.layers_order) o.push_back(vp.bv[i]);
+    vp.bv.swap(o);
+    vp.layers_order.clear();
+    vp.thru = true;
+  };
+  auto view_boxes = [&](const ViewPlan& vp) {
+    std::vector<Box> boxes;
+    for (const DevBrickView& b : vp.bv) {
+      if (bricked) {
+        boxes.push_back(vol->part.boxes[b.brick]);
+        continue;
+      }
+      Box w;
+      for (int i = 0; i < 3; i++) {
+        w.lo[i] = 0;
+        w.hi[i] = vol->n[i] - 1;
+        w.closed[i] = 1;
+      }
+      boxes.push_back(w);
+    }
+    return boxes;
+  };
   for (int32_t v = 0; v < nviews; v++) {
     ViewPlan& vp = plans[v];
-    vp.pfoot = false;
-    if (!bricked || global || extras || !cams[v].persp || !(mode == 0 || mode == 3) || tw != 8 ||
-        !ctx->persp_cells || base.mc != 0 || base.mask || ctx->ring_reg <= 0 || ctx->ring_nslots == 3 ||
-        vp.bv.empty())
-      continue;
-    const int first_axis = std::fabs(cams[v].e3[1]) >= std::fabs(cams[v].e3[2]) ? 1 : 2;
-    std::vector<PerspCells> pcs(vp.bv.size());
-    int axis = 0;
-    for (int tryax : {first_axis, 3 - first_axis}) {
-      bool all = true;
-      for (size_t i = 0; i < vp.bv.size() && all; i++) {
-        const DevBrickView& b = vp.bv[i];
-        Rect rc;
-        rc.x0 = b.x0;
-        rc.y0 = b.y0;
-        rc.w = b.w;
-        rc.h = b.h;
-        all = persp_cells(cams[v], tryax, vol->part.boxes[b.brick], rc, ctx->foot_rays, ctx->persp_kmax, kRingCap,
-                          kRingRegLoads, pcs[i], ctx->foot_maxpx);
+    if (!pick || vp.bv.empty()) continue;
+    if (base.mc > 0) {
+      if (global) thru_order(v);
+      vp.skip = true;
+      gather_view(vp, 16);
+    } else if (global) {
+      const MarchTimes t = march_times(cams[v], view_boxes(vp), p->step, nullptr);
+      if (t.gather < kThruBelow) {
+        thru_order(v);
+        gather_view(vp, 16);
+      } else if (base.mask || vp.wave_begin.size() > 8) {
+        gather_view(vp, t.pitch < 2.0 ? 4 : 16);
       }
-      if (all) {
-        axis = tryax;
+    }
+  }
+  // perspective views: footprint cells sized per brick (the plain march of
+  // emission-absorption or MIP, register-staged), each brick along the slab
+  // axis along which the eye lies outside its slab; the bricks neither axis
+  // suits, and views with rays less than kPerspCellPitch voxels apart, by
+  // gathers
+  for (int32_t v = 0; v < nviews; v++) {
+    ViewPlan& vp = plans[v];
+    if (!pick || !cams[v].persp || vp.bv.empty() || vp.deep || global) continue;
+    const bool cells = bricked && ctx->persp_cells && !base.mask && ctx->ring_reg > 0 && ctx->ring_nslots != 3 &&
+                       cams[v].S / W >= kPerspCellPitch;
+    const int first_axis = std::fabs(cams[v].e3[1]) >= std::fabs(cams[v].e3[2]) ? 1 : 2;
+    std::vector<int32_t> axis(vp.bv.size(), 0);
+    bool any = false;
+    for (size_t i = 0; cells && i < vp.bv.size(); i++) {
+      DevBrickView& b = vp.bv[i];
+      Rect rc;
+      rc.x0 = b.x0;
+      rc.y0 = b.y0;
+      rc.w = b.w;
+      rc.h = b.h;
+      for (int tryax : {first_axis, 3 - first_axis}) {
+        PerspCells pc;
+        if (!persp_cells(cams[v], tryax, vol->part.boxes[b.brick], rc, ctx->foot_rays, ctx->persp_kmax, kRingCap,
+                         kRingRegLoads, pc, ctx->foot_maxpx))
+          continue;
+        axis[i] = tryax;
+        any = true;
+        b.tiles_x = pc.ncf;
+        b.cf0 = pc.cf0;
+        b.cg0 = pc.cg0;
+        b.blocks_x = pc.ncg;  // cells along g (the cell count is tiles_x x blocks_x)
+        b.pTf = pc.Tf;
+        b.pTg = pc.Tg;
+        b.ppitch = pc.pitch;
+        b.png = pc.ng;
         break;
       }
     }
-    if (axis == 0) continue;
-    std::vector<double> key(vp.bv.size());
-    for (size_t i = 0; i < vp.bv.size(); i++) {
-      DevBrickView& b = vp.bv[i];
-      const PerspCells& pc = pcs[i];
-      b.tiles_x = pc.ncf;
-      b.cf0 = pc.cf0;
-      b.cg0 = pc.cg0;
-      b.blocks_x = pc.ncg;  // cells along g (the cell count is tiles_x x blocks_x)
-      b.pTf = pc.Tf;
-      b.pTg = pc.Tg;
-      b.ppitch = pc.pitch;
-      b.png = pc.ng;
-      key[i] = (double)pc.pitch * pc.ng;
-    }
-    // one launch: the cell shapes are chosen for the occupancy their windows
-    // allow, so their slots differ little (three launches measured slower)
-    group_classes(vp, key, 1, [](const DevBrickView& b) { return (int64_t)b.tiles_x * b.blocks_x; });
-    vp.pfoot = true;
-    vp.paxis = axis;
-    int64_t cells = 0;
-    for (int32_t t : vp.class_tiles) cells += t;
-    vp.ntiles = (int32_t)cells;
-  }
-  // perspective views on the ring march's 8 x 8 tiles: rays from the eye
-  // spread with depth, so the tiles of far bricks need windows about twice
-  // those of near ones, and one slot sized for nearly all tiles leaves the
-  // near bricks at a fraction of the wavefronts their windows allow.  Bricks
-  // are grouped into classes of similar window (about equal tile counts),
-  // launched one class at a time with a slot of its own.
-  for (int32_t v = 0; v < nviews; v++) {
-    ViewPlan& vp = plans[v];
-    if (vp.pfoot) continue;
-    vp.class_begin.clear();
-    vp.class_tiles.clear();
-    const int32_t ncls = ctx->persp_classes;
-    if (!bricked || global || extras || !cams[v].persp || !(mode == 0 || mode == 3) || tw != 8 || ncls < 2 ||
-        vp.bv.size() < (size_t)(2 * ncls))
+    if (!any) {
+      gather_view(vp, 16);
       continue;
-    std::vector<double> key(vp.bv.size());
-    for (int32_t i = 0; i < (int32_t)vp.bv.size(); i++) {
-      const DevBrickView& b = vp.bv[i];
-      TileRegion r;
-      for (int k = 0; k < 3; k++) {
-        r.lo[k] = vol->part.boxes[b.brick].lo[k];
-        r.hi[k] = vol->part.boxes[b.brick].hi[k];
-      }
-      r.x0 = b.x0;
-      r.y0 = b.y0;
-      r.w = b.w;
-      r.h = b.h;
-      key[i] = persp_region_window(cams[v], r);
     }
-    group_classes(vp, key, ncls, [th](const DevBrickView& b) { return (int64_t)b.tiles_x * ((b.h + th - 1) / th); });
+    std::vector<DevBrickView> grouped;
+    std::vector<int32_t> where(vp.bv.size(), -1);
+    for (const int32_t ax : {1, 2, 0}) {
+      const int32_t first = (int32_t)grouped.size();
+      int32_t t = 0;
+      for (size_t i = 0; i < vp.bv.size(); i++) {
+        if (axis[i] != ax) continue;
+        DevBrickView b = vp.bv[i];
+        b.tile_begin = t;
+        if (ax != 0) t += b.tiles_x * b.blocks_x;
+        where[i] = (int32_t)grouped.size();
+        grouped.push_back(b);
+      }
+      if ((int32_t)grouped.size() == first) continue;
+      vp.class_begin.push_back(first);
+      vp.class_axis.push_back(ax);
+      vp.class_tiles.push_back(t);
+    }
+    vp.class_begin.push_back((int32_t)grouped.size());
+    for (int32_t& l : vp.layers_order) l = where[l];
+    vp.bv.swap(grouped);
+    if (vp.class_axis.back() == 0)
+      vp.class_tiles.back() =
+          gather_tiles(vp, vp.class_begin[vp.class_begin.size() - 2], (int32_t)vp.bv.size(), 2, 2);
   }
   // parallel rays on the ring march: footprint cells instead of 8 x 8 pixel
   // tiles (the cell counts replace the tile counts of the plan)
   const bool plain_ring = base.mc == 0 && !base.mask;
   for (int32_t v = 0; v < nviews; v++) {
     ViewPlan& vp = plans[v];
-    if (extras || cams[v].persp || !ctx->foot || !(mode == 0 || mode == 3) || tw != 8) continue;
+    if (!pick || cams[v].persp || vp.deep) continue;
     FootShape fs;
-    if (!pick_foot(cams[v], vol->n, base.M, plain_ring, ctx->ring_reg > 0, ctx->ring_nslots, ctx->foot_rays,
-                   ctx->foot_pad, ctx->foot_kmax, fs, ctx->foot_maxpx))
-      continue;
+    // gathers for certain: their estimate is below the cells' best (the slab
+    // axis with fewer layers), without sizing the cells on the host (80 us)
+    if (!global && ctx->foot && !vp.bv.empty()) {
+      const std::vector<Box> boxes = view_boxes(vp);
+      bool sure = true;
+      for (int axis : {1, 2}) {
+        FootShape any;
+        any.axis = axis;
+        const MarchTimes t = march_times(cams[v], boxes, p->step, &any);
+        sure = sure && t.gather < t.cells;
+      }
+      if (sure) {
+        gather_view(vp, 16);
+        continue;
+      }
+    }
+    const bool cells = ctx->foot && pick_foot(cams[v], vol->n, base.M, plain_ring, ctx->ring_reg > 0, ctx->ring_nslots,
+                                              ctx->foot_rays, ctx->foot_pad, ctx->foot_kmax, fs, ctx->foot_maxpx);
+    if (!global && ctx->foot && !vp.bv.empty()) {
+      const MarchTimes t = march_times(cams[v], view_boxes(vp), p->step, cells ? &fs : nullptr);
+      if (ctx->debug_plan)
+        std::fprintf(stderr, "[vr] view %d: estimated cells %.0f us, gathers %.0f us\n", v, t.cells * 1e6, t.gather * 1e6);
+      if (t.gather < t.cells) {
+        gather_view(vp, 16);
+        continue;
+      }
+    }
+    if (!cells) continue;
     Box whole;
     for (int i = 0; i < 3; i++) {
       whole.lo[i] = 0;
@@ -365,8 +441,8 @@ int render_forward(vr_ctx* ctx, vr_volume* vol, const vr_view* views, int32_t nv
       foot_tiles = std::max<int64_t>(foot_tiles, vp.ntiles * per);
       for (int32_t t : vp.wave_tiles) foot_tiles = std::max<int64_t>(foot_tiles, t * per);
     }
-    if (vp.pfoot)
-      for (int32_t t : vp.class_tiles) foot_tiles = std::max<int64_t>(foot_tiles, t);
+    for (size_t c = 0; c < vp.class_tiles.size(); c++)
+      if (vp.class_axis[c] != 0) foot_tiles = std::max<int64_t>(foot_tiles, vp.class_tiles[c]);
   }
   const size_t ovf_stride = align16(256 + 4 * (size_t)foot_tiles);
   if (foot_tiles > 0) VR_TRY(ensure_device(&ctx->d_ovf, &ctx->ovf_bytes, ovf_stride * vr_ctx::kAux));
@@ -405,48 +481,9 @@ int render_forward(vr_ctx* ctx, vr_volume* vol, const vr_view* views, int32_t nv
   // views with the opacity test over whole rays write disjoint frames and use
   // no shared arena: their wave sequences run side by side on the side streams
   // (small front and back waves of one view leave most of the chip idle)
-  if (global) {
-    VR_TRY(stage_begin(ctx, VR_STAGE_MARCH, s));
-    VR_TRY(aux_fork(ctx, s));
-  }
-  // LDS slot, slots per wavefront and register staging of the perspective
-  // ring march for the bricks bv[first .. first + count) of view v; false
-  // when the windows do not fit (gather march)
-  auto persp_shape = [&](int32_t v, int32_t first, int32_t count, MarchArgs& a, int& wpb) {
-    const ViewPlan& vp = plans[v];
-    std::vector<TileRegion> regs;
-    for (int32_t k = first; k < first + count; k++) {
-      const DevBrickView& b = vp.bv[k];
-      TileRegion r;
-      for (int i = 0; i < 3; i++) {
-        r.lo[i] = bricked ? vol->part.boxes[b.brick].lo[i] : 0;
-        r.hi[i] = bricked ? vol->part.boxes[b.brick].hi[i] : vol->n[i] - 1;
-      }
-      r.x0 = b.x0;
-      r.y0 = b.y0;
-      r.w = b.w;
-      r.h = b.h;
-      regs.push_back(r);
-    }
-    a.slab_axis = std::fabs(cams[v].e3[1]) >= std::fabs(cams[v].e3[2]) ? 1 : 2;
-    const bool ok = choose_ring_persp(cams[v], regs, kRingCap, a.M, kRingMaxWaves, kRingMinWaves, a.ring_slot, wpb,
-                                      ctx->persp_fit);
-    a.ring_nslots = 3;
-    a.ring_reg = 0;
-    // two slots wherever they fit more wavefronts (as for parallel rays)
-    if (ok && a.mc == 0 && !a.mask && ctx->ring_nslots != 3) {
-      int32_t waves3 = 0, waves2 = 0;
-      ring_waves_per_block(a.ring_slot, a.M, kRingMaxWaves, &waves3, 3);
-      const int32_t wpb2 = ring_waves_per_block(a.ring_slot, a.M, kRingMaxWaves, &waves2, 2);
-      if (ctx->ring_nslots == 2 || waves2 > waves3) {
-        wpb = wpb2;
-        a.ring_nslots = 2;
-      }
-    }
-    // the layer after next staged in registers (emission-absorption)
-    if (ok && a.ring_nslots == 2 && !a.mip && a.mc == 0 && !a.mask && ctx->ring_reg) a.ring_reg = 1;
-    return ok;
-  };
+  const bool side = global && nviews > 1;
+  if (global) VR_TRY(stage_begin(ctx, VR_STAGE_MARCH, s));
+  if (side) VR_TRY(aux_fork(ctx, s));
   for (int32_t v = 0; v < nviews; v++) {
     const ViewPlan& vp = plans[v];
     MarchArgs a = base;
@@ -465,6 +502,14 @@ int render_forward(vr_ctx* ctx, vr_volume* vol, const vr_view* views, int32_t nv
     bool lds = false, ring = false;
     int ring_wpb = 4;
     a.lds_budget = budget;
+    a.depth = vp.deep;
+    a.skip = vp.skip ? 1 : 0;
+    a.thru = vp.thru ? 1 : 0;
+    // fewer bricks than XCDs: the cells of one brick spread over all of them
+    // in runs (a whole volume 604 -> 553 us for two views, six bricks 1.70 ->
+    // 1.59 ms); from 8 bricks on each XCD keeps bricks of its own (2.39 ms for
+    // eight bricks against 2.66)
+    a.xcd_chunk = a.nbv < 8 ? 16 : 0;
     if (vp.foot) {
       const FootShape& fs = vp.fs;
       ring = true;
@@ -508,13 +553,7 @@ int render_forward(vr_ctx* ctx, vr_volume* vol, const vr_view* views, int32_t nv
                            bricked ? vp.pixels : (int64_t)W * H, s));
       }
     } else if (!extras && (mode == 0 || mode == 3) && a.tile_w == 8) {
-      if (cams[v].persp) {
-        if (vp.class_begin.empty()) {
-          ring = persp_shape(v, 0, (int32_t)vp.bv.size(), a, ring_wpb);
-        } else {
-          ring = true;  // shapes per class at the launch
-        }
-      } else {
+      if (!cams[v].persp && !vp.deep) {
         int32_t waves3 = 0;
         ring = choose_ring(cams[v], kRingCap, a.M, kRingMaxWaves, kRingWantWaves, kRingMinWaves, a.slab_axis,
                            a.ring_slot, ring_wpb, 3, &waves3);
@@ -548,7 +587,7 @@ int render_forward(vr_ctx* ctx, vr_volume* vol, const vr_view* views, int32_t nv
       a.tile_bw = ctx->tile_bw;
       a.tile_bh = ctx->tile_bh;
     }
-    if (!ring && !extras && mode != 1 && !a.mip && !a.mask) {  // (the slab march has no MIP and no mask)
+    if (!ring && !extras && mode != 1 && !a.mip && !a.mask && !vp.deep && vp.class_begin.empty()) {  // (the slab march has no MIP and no mask)
       lds = choose_slab(cams[v], a.tile_w, a.tile_h, budget, a.slab_axis, a.slab_T);
       // rays nearly parallel to axis 1 need a wider slab box: retry with twice the budget
       if (!lds && budget < 8192 && choose_slab(cams[v], a.tile_w, a.tile_h, 8192, a.slab_axis, a.slab_T)) {
@@ -559,10 +598,14 @@ int render_forward(vr_ctx* ctx, vr_volume* vol, const vr_view* views, int32_t nv
     if (global) {
       // waves in order, each continuing the rays the previous left in the frame
       float4* frame = reinterpret_cast<float4*>(out) + (int64_t)v * W * H;
-      hipStream_t vs = ctx->aux[v % vr_ctx::kAux];
+      hipStream_t vs = side ? ctx->aux[v % vr_ctx::kAux] : s;
       lds = false;  // the slab march does not carry state
-      a.carry = 1;
       a.img = frame;
+      if (vp.thru) {
+        VR_HIP(launch_march(a, vs));
+        continue;
+      }
+      a.carry = 1;
       VR_HIP(launch_carry(frame, (int64_t)W * H, false, vs));
       const DevBrickView* wbv = a.bv;
       for (size_t w = 0; w + 1 < vp.wave_begin.size(); w++) {
@@ -575,27 +618,32 @@ int render_forward(vr_ctx* ctx, vr_volume* vol, const vr_view* views, int32_t nv
       continue;
     }
     VR_TRY(stage_begin(ctx, VR_STAGE_MARCH, s));
-    if (vp.pfoot) {
+    if (!vp.class_begin.empty()) {
       // perspective footprint cells: the brick images' pixels without samples
-      // are not written, so the arena is cleared first; one launch per class
-      // of window size, the class's largest window as the slot
+      // are not written, so the arena is cleared first; one launch per slab
+      // axis, the largest window as the slot, then the bricks by gathers
       VR_HIP(launch_zero(arena, vp.pixels, s));
       const DevBrickView* cbv = a.bv;
       for (size_t c = 0; c + 1 < vp.class_begin.size(); c++) {
         MarchArgs ac = a;
         const int32_t first = vp.class_begin[c], count = vp.class_begin[c + 1] - first;
+        ac.bv = cbv + first;
+        ac.nbv = count;
+        ac.ntiles = vp.class_tiles[c];
+        if (vp.class_axis[c] == 0) {
+          ac.depth = 16;
+          VR_HIP(launch_march(ac, s));
+          continue;
+        }
         int32_t slot = 0, mpitch = 0, mng = 0;
         for (int32_t k = first; k < first + count; k++) {
           slot = std::max(slot, vp.bv[k].ppitch * vp.bv[k].png);
           mpitch = std::max(mpitch, vp.bv[k].ppitch);
           mng = std::max(mng, vp.bv[k].png);
         }
-        ac.bv = cbv + first;
-        ac.nbv = count;
-        ac.ntiles = vp.class_tiles[c];
         ac.foot = 1;
         ac.blk_f = ac.blk_g = 0;
-        ac.slab_axis = vp.paxis;
+        ac.slab_axis = vp.class_axis[c];
         ac.ring_slot = slot;
         ac.ring_nslots = 2;
         ac.ring_reg = 1;
@@ -613,24 +661,8 @@ int render_forward(vr_ctx* ctx, vr_volume* vol, const vr_view* views, int32_t nv
         ac.ovf_tiles = reinterpret_cast<int32_t*>(ovf + 256);
         if (ctx->debug_plan)
           std::fprintf(stderr, "[vr] view %d cells class %zu: bricks %d cells %d axis %d slot %d pitch<=%d ng<=%d wpb %d waves %d\n",
-                       v, c, count, ac.ntiles, vp.paxis, slot, mpitch, mng, cwpb, waves);
+                       v, c, count, ac.ntiles, ac.slab_axis, slot, mpitch, mng, cwpb, waves);
         VR_HIP(launch_march_ring(ac, cwpb, s));
-      }
-    } else if (!vp.class_begin.empty()) {
-      // perspective classes: one launch each, with the class's own slot
-      const DevBrickView* cbv = a.bv;
-      for (size_t c = 0; c + 1 < vp.class_begin.size(); c++) {
-        MarchArgs ac = a;
-        int cwpb = 4;
-        const int32_t first = vp.class_begin[c], count = vp.class_begin[c + 1] - first;
-        const bool cring = persp_shape(v, first, count, ac, cwpb);
-        ac.bv = cbv + first;
-        ac.nbv = count;
-        ac.ntiles = vp.class_tiles[c];
-        if (ctx->debug_plan)
-          std::fprintf(stderr, "[vr] view %d class %zu: bricks %d tiles %d ring %d slot %d nslots %d reg %d wpb %d\n", v, c,
-                       count, ac.ntiles, cring ? 1 : 0, ac.ring_slot, ac.ring_nslots, ac.ring_reg, cwpb);
-        VR_HIP(cring ? launch_march_ring(ac, cwpb, s) : launch_march(ac, s));
       }
     } else {
       VR_HIP(extras ? extras->launch(a, s)
@@ -651,10 +683,8 @@ int render_forward(vr_ctx* ctx, vr_volume* vol, const vr_view* views, int32_t nv
       VR_TRY(stage_end(ctx, s));
     }
   }
-  if (global) {
-    VR_TRY(aux_join(ctx, s));
-    VR_TRY(stage_end(ctx, s));
-  }
+  if (side) VR_TRY(aux_join(ctx, s));
+  if (global) VR_TRY(stage_end(ctx, s));
   if (extras) {
     extras->vmin = vmin;
     extras->vmax = vmax;

@@ -154,7 +154,12 @@ __global__ __launch_bounds__(256) __attribute__((amdgpu_waves_per_eu(4))) void k
   // contiguous range of cells (neighbouring cells share its L2)
   const int ngroups = (a.ntiles + wpb - 1) / wpb;
   const int per = (ngroups + 7) >> 3;
-  const int tile = ((int)(blockIdx.x & 7) * per + (int)(blockIdx.x >> 3)) * wpb + wave;
+  int grp = (int)(blockIdx.x & 7) * per + (int)(blockIdx.x >> 3);
+  if (a.xcd_chunk > 0) {
+    const int c = a.xcd_chunk, r = (int)blockIdx.x % (8 * c);
+    grp = (int)blockIdx.x - r + (r & 7) * c + (r >> 3);
+  }
+  const int tile = grp * wpb + wave;
   if (tile >= a.ntiles) return;  // this wavefront only: no barrier follows
 
   const DevBrickView bvw = a.bv[find_bv(a, tile)];
@@ -507,7 +512,8 @@ hipError_t launch_march_cells(const MarchArgs& a, int wpb, hipStream_t s) {
   if (a.ntiles <= 0) return hipSuccess;
   if ((wpb != 1 && wpb != 2 && wpb != 4) || !cells_args_ok(a, 1)) return hipErrorInvalidValue;
   const int groups = (a.ntiles + wpb - 1) / wpb;
-  const int grid = ((groups + 7) / 8) * 8;
+  const int span = 8 * std::max(1, a.xcd_chunk);
+  const int grid = ((groups + span - 1) / span) * span;
   const dim3 g(grid), b(64 * wpb);
   const size_t lds = std::max(cells_lds_bytes(a, wpb), (size_t)std::max(0, a.lds_floor));
   const bool by = a.slab_axis == 1;

@@ -17,6 +17,8 @@
 // Maximum intensity projection (paper Sec. 2.4): the march keeps the largest
 // normalised sample value M of the ray and stops once M reaches 1; pixels are
 // (M, M, M, M).
+#include <type_traits>
+
 #include "sample.h"
 #include "vr_internal.h"
 
@@ -33,48 +35,238 @@ __device__ __forceinline__ f2u ld_pair(gfloat* p) {
 }
 
 // Blocks of 256 lanes (4 wavefronts, 4 consecutive tiles).  Consecutive
-// hardware block ids go round-robin over the 8 XCDs; remap them so each XCD
-// receives one contiguous range of tiles (neighbouring tiles of the same brick
-// then share that XCD's L2).
-__device__ __forceinline__ int xcd_block(int nblk) {
-  const int per = (nblk + 7) >> 3;
-  return (int)(blockIdx.x & 7) * per + (int)(blockIdx.x >> 3);
+// hardware block ids go round-robin over the 8 XCDs; they are remapped so that
+// each XCD takes runs of kXcdRun consecutive blocks (neighbouring tiles share
+// its L2), dealt round robin: rays differ in length across the image, and one
+// contiguous eighth each left the XCDs at the image's border idle (whole
+// 201 x 187 x 333 volume 535 -> 395 us for two views; whole-ray termination
+// over 64 bricks 4.4 -> 2.5 ms).
+constexpr int kXcdRun = 8;
+__device__ __forceinline__ int xcd_block() {
+  const int r = (int)blockIdx.x % (8 * kXcdRun);
+  return (int)blockIdx.x - r + (r & 7) * kXcdRun + (r >> 3);
 }
 
-template <int TW, bool MIP, bool MASK>
-__global__ __launch_bounds__(256) void k_march(MarchArgs a) {
+// Run of samples of a ray from sample j on whose cells lie in the macrocell
+// holding sample j's: its length (at least 1; 0.001 voxel of margin at the far
+// planes against the rounding of sample positions) and whether that macrocell
+// is clear, i.e. whether each of them would add exactly nothing.
+__device__ __forceinline__ int macrocell_run(const MarchArgs& a, const DevBrick& br, int j, const float4& pos,
+                                             const float4& dir, const float4& inv, float inv_mc, bool& clear) {
+  const SamplePos q = sample_pos(j, pos.x, pos.y, pos.z, dir.x, dir.y, dir.z);
+  const Cell c = cell_of(q, br);
+  // macrocell of a cell index i >= 0 (below 2^22): floor((i + 1/2) / mc)
+  const float fmc = (float)a.mc;
+  const float mx = floorf(((float)(c.ix + br.lo[0]) + 0.5f) * inv_mc);
+  const float my = floorf(((float)(c.iy + br.lo[1]) + 0.5f) * inv_mc);
+  const float mz = floorf(((float)(c.iz + br.lo[2]) + 0.5f) * inv_mc);
+  clear = a.mc_clear[((int64_t)(int)mz * a.mcn[1] + (int)my) * a.mcn[0] + (int)mx] != 0;
+  // steps to the far plane (brick-local); inv = 1 / dir, 1e9 for a component of 0
+  auto steps = [&](float q1, float is, float m1, int lo) {
+    const float edge = fmaf(m1, fmc, is > 0.f ? fmc - 1e-3f : 1e-3f) - (float)lo;
+    return (edge - q1) * is;
+  };
+  const float n = fminf(fminf(steps(q.x, inv.x, mx, br.lo[0]), steps(q.y, inv.y, my, br.lo[1])),
+                        steps(q.z, inv.z, mz, br.lo[2]));
+  return 1 + (int)fmaxf(0.f, floorf(n));
+}
+
+// Empty-space skipping ray by ray (emission-absorption).  8 x 8 rays per
+// wavefront, two phases per 1024 samples of the rays: every lane walks its own
+// ray from macrocell to macrocell and marks the blocks of 16 samples that
+// touch one that is not clear; then 16 lanes at a time take the marked blocks
+// of a ray, 4 rays (2 x 2 pixels) side by side, as k_march<16> does.  Passed
+// samples would add nothing and leave T as it is, so the images are those of
+// the other marches.
+// Bound by the longest wavefronts' chains of blocks; what a view costs follows
+// its rays and marked samples, not the voxels of its bricks (two 1024^2 views
+// of 1024 x 1024 x 768 with 95 % of the macrocells clear: 1.13 ms, 3.48 by a
+// march that skips whole steps of a brick's layers).
+template <bool MASK, bool THRU>
+__global__ __launch_bounds__(256) void k_march_skip(MarchArgs a) {
   extern __shared__ float4 s_tf[];
+  __shared__ float4 s_pos[4][64], s_dir[4][64], s_acc[4][64];
+  __shared__ unsigned long long s_blocks[4][64];
   for (int i = threadIdx.x; i < a.M; i += 256) s_tf[i] = a.tf[i];
   __syncthreads();
 
-  constexpr int TH = 64 / TW;
   const int nblk = (a.ntiles + 3) >> 2;
-  const int lb = xcd_block(nblk);
-  if (lb >= nblk) return;
-  int tile = __builtin_amdgcn_readfirstlane(lb * 4 + (int)(threadIdx.x >> 6));
-  if (tile >= a.ntiles) return;
-
-  // brick owning this tile: last entry with tile_begin <= tile
-  int lo = 0, hi = a.nbv - 1;
+  const int lb = xcd_block();
+  const int wave = __builtin_amdgcn_readfirstlane((int)(threadIdx.x >> 6)), lane = threadIdx.x & 63;
+  const int tile = lb * 4 + wave;
+  if (lb >= nblk || tile >= a.ntiles) return;  // this wavefront only: no barrier follows
+  int lo = 0, hi = THRU ? 0 : a.nbv - 1;
   while (lo < hi) {
     int mid = (lo + hi + 1) >> 1;
     if (a.bv[mid].tile_begin <= tile) lo = mid;
     else hi = mid - 1;
   }
-  const DevBrickView bvw = a.bv[lo];
-  const DevBrick br = a.bricks[bvw.brick];
-  const int t = tile - bvw.tile_begin;
-  const int tx = t % bvw.tiles_x, ty = t / bvw.tiles_x;
-  const int lane = threadIdx.x & 63;
-  const int lx = tx * TW + (lane % TW), ly = ty * TH + (lane / TW);
-  if (lx >= bvw.w || ly >= bvw.h) return;
-  const int u = bvw.x0 + lx, v = bvw.y0 + ly;
+  const int rx = THRU ? 0 : a.bv[lo].x0, ry = THRU ? 0 : a.bv[lo].y0;
+  const int rw = THRU ? a.cam.W : a.bv[lo].w, rh = THRU ? a.cam.H : a.bv[lo].h;
+  const int t = THRU ? tile : tile - a.bv[lo].tile_begin;
+  const int tiles_x = THRU ? (rw + 7) / 8 : a.bv[lo].tiles_x;
+  const int tx = t % tiles_x, ty = t / tiles_x;
+  // ray `lane` belongs to rod lane >> 2 (2 x 2 pixels, 4 x 4 rods)
+  const int lx = tx * 8 + ((lane >> 2) & 3) * 2 + (lane & 1), ly = ty * 8 + (lane >> 4) * 2 + ((lane >> 1) & 1);
+  const bool valid = lx < rw && ly < rh;
+  const int u = rx + lx, v = ry + ly;
+  float4* const dst =
+      THRU || a.carry ? a.img + (int64_t)v * a.cam.W + u : a.img + a.bv[lo].img_off + (int64_t)ly * rw + lx;
+  float4 acc = make_float4(0.f, 0.f, 0.f, 1.f);  // colour and transmittance
+  if (!THRU && a.carry && valid) acc = *dst;
+  bool live = valid && (THRU || !a.carry || 1.f - acc.w < a.tau);
+  double o[3], d[3], tin = 0.0;
+  int64_t n = 0;
+  if (live) {
+    pixel_ray(a.cam, u, v, o, d);
+    live = ray_lattice(o, d, a.hi, a.step, tin, n);
+  }
+  s_acc[wave][lane] = acc;
+  const float inv_mc = 1.f / (float)a.mc;
+  const int dl = lane & 15;
+  bool touched = false;
+  for (int b = lo; b < (THRU ? a.nbv : lo + 1); ++b) {
+    const DevBrickView& bvw = a.bv[b];
+    if constexpr (THRU) {
+      // the tile lies outside the brick's rectangle
+      if (tx * 8 >= bvw.x0 + bvw.w || tx * 8 + 8 <= bvw.x0 || ty * 8 >= bvw.y0 + bvw.h || ty * 8 + 8 <= bvw.y0) continue;
+    }
+    const DevBrick br = a.bricks[bvw.brick];
+    float4 pos = make_float4(0.f, 0.f, 0.f, 0.f), dir = pos;
+    int cnt = 0;
+    if (live) {
+      int64_t k0, k1;
+      brick_krange(o, d, tin, a.step, n, br.lo, br.hi, br.closed, k0, k1);
+      if (k1 > k0) {
+        const double t0 = tin + ((double)k0 + 0.5) * a.step;
+        pos.x = (float)(o[0] + t0 * d[0] - (double)br.lo[0]);
+        pos.y = (float)(o[1] + t0 * d[1] - (double)br.lo[1]);
+        pos.z = (float)(o[2] + t0 * d[2] - (double)br.lo[2]);
+        dir = make_float4((float)(a.step * d[0]), (float)(a.step * d[1]), (float)(a.step * d[2]), 0.f);
+        cnt = (int)(k1 - k0);
+        touched = true;
+      }
+    }
+    if (!__any(cnt > 0)) continue;
+    pos.w = __int_as_float(cnt);
+    s_pos[wave][lane] = pos;
+    s_dir[wave][lane] = dir;
+    const float4 inv = make_float4(dir.x != 0.f ? 1.f / dir.x : 1e9f, dir.y != 0.f ? 1.f / dir.y : 1e9f,
+                                   dir.z != 0.f ? 1.f / dir.z : 1e9f, 0.f);
+    gfloat* base = (gfloat*)br.base;
+    const int ys = br.sy, zs = br.sz;
+    for (int jc = 0; __any(jc < cnt); jc += 1024) {
+      unsigned long long blocks = 0;
+      const int jend = min(cnt, jc + 1024);
+      for (int j = jc; j < jend;) {
+        bool clear;
+        const int run = macrocell_run(a, br, j, pos, dir, inv, inv_mc, clear);
+        if (!clear) {
+          const int b0 = (j - jc) >> 4, b1 = (min(j + run, jend) - 1 - jc) >> 4;
+          blocks |= (~0ull << b0) & (~0ull >> (63 - b1));
+        }
+        j += run;
+      }
+      if (!__any(blocks != 0)) continue;
+      s_blocks[wave][lane] = blocks;
+      __builtin_amdgcn_wave_barrier();
+      __builtin_amdgcn_fence(__ATOMIC_ACQ_REL, "wavefront");
+      for (int q = 0; q < 16; ++q) {
+        const int ray = 4 * q + (lane >> 4);
+        unsigned long long m = s_blocks[wave][ray];
+        if (!__any(m != 0)) continue;
+        const float4 rp = s_pos[wave][ray], rd = s_dir[wave][ray];
+        float4 c0 = s_acc[wave][ray];
+        const int rc = __float_as_int(rp.w);
+        if (1.f - c0.w >= a.tau) m = 0;
+        // the corners of the next block are loaded while one is composited
+        Cell c;
+        f2u a00, a01, a10, a11;
+        int j = 0;
+        auto load = [&]() {
+          j = jc + 16 * __builtin_ctzll(m) + dl;
+          m &= m - 1;
+          c = cell_of(sample_pos(min(j, rc - 1), rp.x, rp.y, rp.z, rd.x, rd.y, rd.z), br);
+          gfloat* p = base + (c.iz * zs + c.iy * ys + c.ix);
+          a00 = ld_pair(p);
+          a01 = ld_pair(p + ys);
+          a10 = ld_pair(p + zs);
+          a11 = ld_pair(p + zs + ys);
+        };
+        bool more = m != 0;
+        if (more) load();
+        while (more) {
+          const float val = trilerp(a00.x, a00.y, a01.x, a01.y, a10.x, a10.y, a11.x, a11.y, c);
+          Classified k = classify(val, a.vmin, a.inv_range, a.M, s_tf);
+          if constexpr (MASK) k.a *= channel_weight(a.mask, a.mask_axis, br.lo[a.mask_axis], c);
+          if (j >= rc) k.a = 0.f;  // past the ray's last sample: adds nothing
+          more = m != 0;
+          if (more) load();
+          if (accumulate_group<16>(k, a.tau, c0.x, c0.y, c0.z, c0.w)) break;
+        }
+        if (dl == 0) s_acc[wave][ray] = c0;
+      }
+      __builtin_amdgcn_wave_barrier();
+      __builtin_amdgcn_fence(__ATOMIC_ACQ_REL, "wavefront");
+      if (1.f - s_acc[wave][lane].w >= a.tau) {  // the ray has stopped
+        live = false;
+        cnt = 0;
+      }
+    }
+    if (!__any(live)) break;
+  }
+  acc = s_acc[wave][lane];
+  // carried state: only a ray with samples here owns its pixel in this wave
+  if (!valid || (!THRU && a.carry && !touched)) return;
+  *dst = make_float4(acc.x, acc.y, acc.z, !THRU && a.carry ? acc.w : 1.f - acc.w);
+}
+
+// D lanes of a wavefront share a ray and hold D consecutive samples of it
+// (D = 1: one lane per ray); TW x 64 / (D TW) pixels per wavefront.  The lanes
+// of a group read neighbouring voxels, so a load touches fewer cache lines,
+// and a ray's chain of loads is D times shorter.  Bound by the L1's tag
+// lookups (one a cycle and compute unit, 36 per load instruction at D = 4) and,
+// in small views, by the chain.  64^3 at 128^2: 25 us a call with D = 16 (128
+// by the cell march, 77 with D = 1); two 1024^2 views of 512 x 512 x 1024: 3.9
+// ms with D = 4 or 16, 14.0 with D = 1 (2.4 by the cell march).
+// THRU: tiles of the frame, every ray taken through all its bricks front to
+// back (a.bv in that order) with one opacity test over the whole ray.
+template <int D, int TW, bool MIP, bool MASK, bool THRU>
+__global__ __launch_bounds__(256) void k_march(MarchArgs a) {
+  static_assert(D == 1 || D == 4 || D == 16, "lane groups the cross-lane steps know");
+  extern __shared__ float4 s_tf[];
+  for (int i = threadIdx.x; i < a.M; i += 256) s_tf[i] = a.tf[i];
+  __syncthreads();
+
+  constexpr int TH = 64 / D / TW;
+  const int nblk = (a.ntiles + 3) >> 2;
+  const int lb = xcd_block();
+  if (lb >= nblk) return;
+  int tile = __builtin_amdgcn_readfirstlane(lb * 4 + (int)(threadIdx.x >> 6));
+  if (tile >= a.ntiles) return;
+
+  // brick owning this tile: last entry with tile_begin <= tile
+  int lo = 0, hi = THRU ? 0 : a.nbv - 1;
+  while (lo < hi) {
+    int mid = (lo + hi + 1) >> 1;
+    if (a.bv[mid].tile_begin <= tile) lo = mid;
+    else hi = mid - 1;
+  }
+  const int rx = THRU ? 0 : a.bv[lo].x0, ry = THRU ? 0 : a.bv[lo].y0;
+  const int rw = THRU ? a.cam.W : a.bv[lo].w, rh = THRU ? a.cam.H : a.bv[lo].h;
+  const int t = THRU ? tile : tile - a.bv[lo].tile_begin;
+  const int tiles_x = THRU ? (rw + TW - 1) / TW : a.bv[lo].tiles_x;
+  const int tx = t % tiles_x, ty = t / tiles_x;
+  const int ray = (threadIdx.x & 63) / D, dl = threadIdx.x & (D - 1);
+  const int lx = tx * TW + (ray % TW), ly = ty * TH + (ray / TW);
+  if (lx >= rw || ly >= rh) return;
+  const int u = rx + lx, v = ry + ly;
 
   double o[3], d[3];
   pixel_ray(a.cam, u, v, o, d);
-  float4* const dst = a.carry ? a.img + (int64_t)v * a.cam.W + u : a.img + bvw.img_off + (int64_t)ly * bvw.w + lx;
+  float4* const dst = THRU || a.carry ? a.img + (int64_t)v * a.cam.W + u : a.img + a.bv[lo].img_off + (int64_t)ly * rw + lx;
   float Cr = 0.f, Cg = 0.f, Cb = 0.f, T = 1.f, mx = 0.f;
-  if (a.carry) {
+  if (!THRU && a.carry) {
     const float4 s0 = *dst;
     if (1.f - s0.w >= a.tau) return;  // the ray stopped in a brick in front
     Cr = s0.x;
@@ -85,42 +277,76 @@ __global__ __launch_bounds__(256) void k_march(MarchArgs a) {
   double tin;
   int64_t n;
   bool touched = false;  // the ray has samples in this brick
+  bool stopped = false;
   if (ray_lattice(o, d, a.hi, a.step, tin, n)) {
-    int64_t k0, k1;
-    brick_krange(o, d, tin, a.step, n, br.lo, br.hi, br.closed, k0, k1);
-    if (k1 > k0) {
+    const float sx = (float)(a.step * d[0]), sy = (float)(a.step * d[1]), sz = (float)(a.step * d[2]);
+    for (int b = lo; b < (THRU ? a.nbv : lo + 1); ++b) {
+      const DevBrickView& bvw = a.bv[b];
+      if constexpr (THRU) {
+        // the tile lies outside the brick's rectangle (the same for all lanes)
+        if (tx * TW >= bvw.x0 + bvw.w || tx * TW + TW <= bvw.x0 || ty * TH >= bvw.y0 + bvw.h || ty * TH + TH <= bvw.y0)
+          continue;
+      }
+      const DevBrick& br = a.bricks[bvw.brick];
+      int64_t k0, k1;
+      brick_krange(o, d, tin, a.step, n, br.lo, br.hi, br.closed, k0, k1);
+      if (k1 <= k0) continue;
       touched = true;
       const double t0 = tin + ((double)k0 + 0.5) * a.step;
       const float px = (float)(o[0] + t0 * d[0] - (double)br.lo[0]);
       const float py = (float)(o[1] + t0 * d[1] - (double)br.lo[1]);
       const float pz = (float)(o[2] + t0 * d[2] - (double)br.lo[2]);
-      const float sx = (float)(a.step * d[0]), sy = (float)(a.step * d[1]), sz = (float)(a.step * d[2]);
       const int cnt = (int)(k1 - k0);
       gfloat* base = (gfloat*)br.base;
       const int ys = br.sy, zs = br.sz;
-      for (int j = 0; j < cnt; ++j) {
-        const Cell c = cell_of(sample_pos(j, px, py, pz, sx, sy, sz), br);
+      // the corners of the next samples are loaded while these are composited
+      int j;
+      Cell c;
+      f2u a00, a01, a10, a11;
+      auto load = [&](int jb) {
+        j = jb + dl;
+        c = cell_of(sample_pos(D == 1 ? j : min(j, cnt - 1), px, py, pz, sx, sy, sz), br);
         gfloat* p = base + (c.iz * zs + c.iy * ys + c.ix);
-        const f2u a00 = ld_pair(p), a01 = ld_pair(p + ys), a10 = ld_pair(p + zs), a11 = ld_pair(p + zs + ys);
+        a00 = ld_pair(p);
+        a01 = ld_pair(p + ys);
+        a10 = ld_pair(p + zs);
+        a11 = ld_pair(p + zs + ys);
+      };
+      load(0);
+      for (int jb = D;; jb += D) {
         const float val = trilerp(a00.x, a00.y, a01.x, a01.y, a10.x, a10.y, a11.x, a11.y, c);
+        [[maybe_unused]] float w = 1.f;
+        if constexpr (MASK) w = channel_weight(a.mask, a.mask_axis, br.lo[a.mask_axis], c);
+        const bool past = D > 1 && j >= cnt;
+        const bool more = jb < cnt;
+        if (more) load(jb);
         if (MIP) {
           float s = norm_value(val, a.vmin, a.inv_range);
-          if constexpr (MASK) s *= channel_weight(a.mask, a.mask_axis, br.lo[a.mask_axis], c);
+          if constexpr (MASK) s *= w;
           mx = fmaxf(mx, s);
-          if (mx >= 1.f) break;
+          stopped = mx >= 1.f;
         } else {
           Classified k = classify(val, a.vmin, a.inv_range, a.M, s_tf);
-          if constexpr (MASK) k.a *= channel_weight(a.mask, a.mask_axis, br.lo[a.mask_axis], c);
-          accumulate(k, Cr, Cg, Cb, T);
-          if (1.f - T >= a.tau) break;
+          if constexpr (MASK) k.a *= w;
+          if constexpr (D == 1) {
+            accumulate(k, Cr, Cg, Cb, T);
+            stopped = 1.f - T >= a.tau;
+          } else {
+            if (past) k.a = 0.f;  // past the ray's last sample: adds nothing
+            stopped = accumulate_group<D>(k, a.tau, Cr, Cg, Cb, T);
+          }
         }
+        if (stopped || !more) break;
       }
+      if (stopped) break;
     }
   }
   // carried state: only a ray with samples here owns its pixel in this wave
   // (another brick of the wave whose rectangle holds the pixel may update it)
-  if (a.carry && !touched) return;
-  *dst = MIP ? make_float4(mx, mx, mx, mx) : make_float4(Cr, Cg, Cb, a.carry ? T : 1.f - T);
+  if (!THRU && a.carry && !touched) return;
+  if constexpr (MIP && D > 1)
+    for (int off = D >> 1; off > 0; off >>= 1) mx = fmaxf(mx, __shfl_xor(mx, off));
+  if (dl == 0) *dst = MIP ? make_float4(mx, mx, mx, mx) : make_float4(Cr, Cg, Cb, !THRU && a.carry ? T : 1.f - T);
 }
 
 // Carried state over the frame: (C, T) = (0, 1) before the first brick, and
@@ -189,23 +415,35 @@ hipError_t launch_zero(float4* img, int64_t n, hipStream_t s) {
 hipError_t launch_march(const MarchArgs& a, hipStream_t s) {
   if (a.ntiles <= 0) return hipSuccess;
   const int nblk = (a.ntiles + 3) / 4;
-  const int grid = ((nblk + 7) / 8) * 8;
+  const int grid = (nblk + 8 * kXcdRun - 1) / (8 * kXcdRun) * (8 * kXcdRun);
   const size_t lds = sizeof(float4) * (size_t)a.M;
-#define VR_LAUNCH_GATHER(MIPV, MASKV)                                                                        \
-  switch (a.tile_w) {                                                                                     \
-    case 8: hipLaunchKernelGGL((k_march<8, MIPV, MASKV>), dim3(grid), dim3(256), lds, s, a); break;       \
-    case 16: hipLaunchKernelGGL((k_march<16, MIPV, MASKV>), dim3(grid), dim3(256), lds, s, a); break;     \
-    case 4: hipLaunchKernelGGL((k_march<4, MIPV, MASKV>), dim3(grid), dim3(256), lds, s, a); break;       \
-    default: return hipErrorInvalidValue;                                                                 \
-  }
-  if (a.mask) {
-    if (a.mip) VR_LAUNCH_GATHER(true, true)
-    else VR_LAUNCH_GATHER(false, true)
+  auto go = [&](auto kernel) { hipLaunchKernelGGL(kernel, dim3(grid), dim3(256), lds, s, a); };
+  const bool mask = a.mask != nullptr, mip = a.mip != 0;
+  if (a.skip) {
+    if (mip || a.mc < 2) return hipErrorInvalidValue;
+    if (a.thru && mask) go(k_march_skip<true, true>);
+    else if (a.thru) go(k_march_skip<false, true>);
+    else if (mask) go(k_march_skip<true, false>);
+    else go(k_march_skip<false, false>);
+  } else if (a.thru) {
+    if (mip || a.depth != 16) return hipErrorInvalidValue;
+    if (mask) go(k_march<16, 2, false, true, true>);
+    else go(k_march<16, 2, false, false, true>);
   } else {
-    if (a.mip) VR_LAUNCH_GATHER(true, false)
-    else VR_LAUNCH_GATHER(false, false)
+    auto shape = [&](auto d, auto tw) {
+      constexpr int D = decltype(d)::value, TW = decltype(tw)::value;
+      if (mask && mip) go(k_march<D, TW, true, true, false>);
+      else if (mask) go(k_march<D, TW, false, true, false>);
+      else if (mip) go(k_march<D, TW, true, false, false>);
+      else go(k_march<D, TW, false, false, false>);
+    };
+    if (a.depth == 16) shape(std::integral_constant<int, 16>{}, std::integral_constant<int, 2>{});
+    else if (a.depth == 4) shape(std::integral_constant<int, 4>{}, std::integral_constant<int, 4>{});
+    else if (a.tile_w == 8) shape(std::integral_constant<int, 1>{}, std::integral_constant<int, 8>{});
+    else if (a.tile_w == 16) shape(std::integral_constant<int, 1>{}, std::integral_constant<int, 16>{});
+    else if (a.tile_w == 4) shape(std::integral_constant<int, 1>{}, std::integral_constant<int, 4>{});
+    else return hipErrorInvalidValue;
   }
-#undef VR_LAUNCH_GATHER
   return hipGetLastError();
 }
 

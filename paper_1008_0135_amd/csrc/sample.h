@@ -107,4 +107,79 @@ __device__ __forceinline__ void accumulate(const Classified& k, float& Cr, float
   T = fmaf(-T, k.a, T);
 }
 
+template <int CTRL>
+__device__ __forceinline__ float dpp(float v) {
+  return __int_as_float(__builtin_amdgcn_update_dpp(0, __float_as_int(v), CTRL, 0xf, 0xf, true));
+}
+
+// The front-to-back steps of the D samples that D neighbouring lanes hold (one
+// each, in lane order), taken by all D lanes alike: the operations of
+// accumulate() in the same order as one lane stepping through them, the other
+// lanes' opacity and colour read as cross-lane operands.  Written out because
+// the compiler puts a move in front of every cross-lane operand (9
+// instructions a sample instead of 5; the 64-request batch 1.82 -> 1.65 ms).
+// The leading s_nop covers the two wait states a cross-lane read needs after
+// the vector instruction that wrote its register; no cross-lane operand is
+// written inside the block.
+#define VR_LANE_STEP(SEL)                                              \
+  "v_mul_f32_dpp %4, %5, %3 " SEL " row_mask:0xf bank_mask:0xf\n\t"    \
+  "v_fmac_f32_dpp %0, %6, %4 " SEL " row_mask:0xf bank_mask:0xf\n\t"   \
+  "v_fmac_f32_dpp %1, %7, %4 " SEL " row_mask:0xf bank_mask:0xf\n\t"   \
+  "v_fmac_f32_dpp %2, %8, %4 " SEL " row_mask:0xf bank_mask:0xf\n\t"   \
+  "v_fmac_f32_dpp %3, -%5, %3 " SEL " row_mask:0xf bank_mask:0xf\n\t"
+#define VR_QUAD(I) VR_LANE_STEP("quad_perm:[" #I "," #I "," #I "," #I "]")
+#define VR_ROW(I) VR_LANE_STEP("row_newbcast:" #I)
+#define VR_LANE_OPERANDS                                                                  \
+  : "+v"(Cr), "+v"(Cg), "+v"(Cb), "+v"(T), "=&v"(ta) : "v"(k.a), "v"(k.r), "v"(k.g), "v"(k.b)
+template <int D>
+__device__ __forceinline__ void accumulate_lanes(const Classified& k, float& Cr, float& Cg, float& Cb, float& T) {
+  static_assert(D == 4 || D == 16, "lane groups with a broadcast of their own");
+  float ta;
+  if constexpr (D == 4)
+    asm("s_nop 1\n\t" VR_QUAD(0) VR_QUAD(1) VR_QUAD(2) VR_QUAD(3) VR_LANE_OPERANDS);
+  else
+    asm("s_nop 1\n\t" VR_ROW(0) VR_ROW(1) VR_ROW(2) VR_ROW(3) VR_ROW(4) VR_ROW(5) VR_ROW(6) VR_ROW(7) VR_ROW(8)
+            VR_ROW(9) VR_ROW(10) VR_ROW(11) VR_ROW(12) VR_ROW(13) VR_ROW(14) VR_ROW(15) VR_LANE_OPERANDS);
+}
+#undef VR_LANE_STEP
+#undef VR_QUAD
+#undef VR_ROW
+#undef VR_LANE_OPERANDS
+
+template <int D, int I>
+__device__ __forceinline__ void accumulate_until(const Classified& k, float tau, bool& done, float& Cr, float& Cg,
+                                                 float& Cb, float& T) {
+  if constexpr (I < D) {
+    constexpr int ctrl = D == 4 ? 0x55 * I : 0x150 + I;
+    Classified q;
+    q.a = dpp<ctrl>(k.a);
+    q.r = dpp<ctrl>(k.r);
+    q.g = dpp<ctrl>(k.g);
+    q.b = dpp<ctrl>(k.b);
+    if (!done) {
+      accumulate(q, Cr, Cg, Cb, T);
+      done = 1.f - T >= tau;
+    }
+    accumulate_until<D, I + 1>(k, tau, done, Cr, Cg, Cb, T);
+  }
+}
+
+// The group's steps with early termination; true once the ray has stopped.
+// T only falls, so a stop shows after the group, which is then taken again one
+// sample at a time from its start.
+template <int D>
+__device__ __forceinline__ bool accumulate_group(const Classified& k, float tau, float& Cr, float& Cg, float& Cb,
+                                                 float& T) {
+  const float Cr0 = Cr, Cg0 = Cg, Cb0 = Cb, T0 = T;
+  accumulate_lanes<D>(k, Cr, Cg, Cb, T);
+  if (!(1.f - T >= tau)) return false;
+  Cr = Cr0;
+  Cg = Cg0;
+  Cb = Cb0;
+  T = T0;
+  bool done = false;
+  accumulate_until<D, 0>(k, tau, done, Cr, Cg, Cb, T);
+  return true;
+}
+
 }  // namespace vr

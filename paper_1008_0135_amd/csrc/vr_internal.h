@@ -229,6 +229,12 @@ struct MarchArgs {
   int32_t nbv;           // rendered bricks in this launch
   int32_t ntiles;        // total work items (tiles)
   int32_t tile_w, tile_h;
+  int32_t depth;         // gather march: lanes that share a ray, each a sample further on (1, 4 or 16);
+                         // a wavefront then holds tile_w x tile_h = 64 / depth pixels
+  int32_t xcd_chunk;     // cells march: workgroups in a row on one XCD, dealt round robin; 0 = a
+                         // contiguous eighth of them each
+  int32_t skip;          // gather march: macrocells passed over ray by ray (k_march_skip)
+  int32_t thru;          // gather march: tiles of the frame, rays taken through all bricks (see k_march)
   int32_t slab_axis;     // LDS-staged march: slab axis (1 = axis 2, 2 = axis 3); 0 = gather march
   int32_t slab_T;        // cell layers per slab
   int32_t lds_budget;    // floats of LDS for one slab's voxel box
