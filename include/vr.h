@@ -338,16 +338,19 @@ int vr_composite(vr_ctx *ctx, const vr_brick_image *imgs, int32_t n, const int32
  * save.  grad_out: [nviews][H][W][4] float32 device.  grad_tf: [m][4] float32
  * device.  grad_vol: [n3][n2][n1] float32 device or NULL.  accumulate = 0
  * overwrites the outputs, 1 adds to them.  The normalisation window is a
- * constant.  Each ray is walked back to front, recomputing each stretch
- * forward from its saved transmittance checkpoint.  ckpt_K bounds a stretch:
- * on the ring-window layout (the default where its windows fit) a stretch is
- * a group of L cell layers of the ray's 8 x 8 tile, L = round(ckpt_K step
- * |d_b|) capped at 3 layers (the environment variable VR_BWD_LAYERS sets the
- * cap, 1 to 16: longer groups need more LDS per wavefront), so a checkpoint
- * falls every min(ckpt_K, about 3 / (step |d_b|)) samples (vr_state_info
- * reports it per view); otherwise a stretch is a segment of exactly ckpt_K
- * samples.  Views run side by side on the library's side streams (forked from
- * and joined back to `stream`; VR_BWD_SIDE=0 runs them one after another).
+ * constant.  Each ray is walked back to front between its saved transmittance
+ * checkpoints: inside a stretch the transmittance follows from its end by
+ * division by the samples' 1 - alpha, or, for tables whose opacity exceeds 1/4
+ * (and on the sample-segment layout), from a replay of the stretch from its
+ * start.  ckpt_K bounds a stretch: on the ring-window layout (the default where
+ * its windows fit) a stretch is a group of L cell layers of the ray's 8 x 8
+ * tile, L = round(ckpt_K step |d_b|) capped at 3 layers (the environment
+ * variable VR_BWD_LAYERS sets the cap, 1 to 16: longer groups need more LDS per
+ * tile), so a checkpoint falls every min(ckpt_K, about 3 / (step |d_b|))
+ * samples (vr_state_info reports it per view); otherwise a stretch is a
+ * segment of exactly ckpt_K samples.  Views run side by side on the library's
+ * side streams (forked from and joined back to `stream`; VR_BWD_SIDE=0 runs
+ * them one after another).
  * Synchronises with `stream` at the end (it checks the adjoint's
  * per-group sample bound).
  * Errors: VR_EINVAL, VR_ESTATE (state from another volume, or the transfer

@@ -461,7 +461,6 @@ int vr_destroy(vr_ctx* ctx) {
   if (ctx->d_scratch) (void)hipFree(ctx->d_scratch);
   if (ctx->d_ovf) (void)hipFree(ctx->d_ovf);
   if (ctx->spare.ckpt) (void)hipFree(ctx->spare.ckpt);
-  if (ctx->spare.ckpt_j) (void)hipFree(ctx->spare.ckpt_j);
   if (ctx->spare.nused) (void)hipFree(ctx->spare.nused);
   for (auto& t : ctx->timed) {
     (void)hipEventDestroy(t.a);

@@ -21,19 +21,18 @@ struct vr_state {
   double vmin = 0.0, vmax = 0.0;
   int32_t W = 0, H = 0, nviews = 0, K = 32, nseg = 0;
   // per view: checkpoint layout.  Ring views keep, per group of L cell layers
-  // of each 8 x 8 tile, T and the sample cursor at the group's start; the
+  // of each 8 x 8 tile, T at the group's start, and at the ray's end; the
   // others keep T before every K-th sample.
   struct View {
     bool ring = false;
-    int32_t axis = 0, slot = 0, fwd_wpb = 4, bwd_wpb = 1, L = 0, smax = 0, ngrp = 0;
-    int64_t off = 0;  // offset of this view's checkpoints (floats / ints) in d_ckpt / d_ckpt_j
-    int32_t band[9] = {};  // ring adjoint: tile groups per XCD (all zero: equal counts)
+    int32_t axis = 0, slot = 0, fwd_wpb = 4, L = 0, smax = 0, ngrp = 0;
+    int64_t off = 0;  // offset of this view's checkpoints in d_ckpt
+    int32_t band[9] = {};  // ring adjoint: tiles per XCD (all zero: equal counts)
   };
   std::vector<View> vs;
   float* d_ckpt = nullptr;     // checkpoints, all views
-  int32_t* d_ckpt_j = nullptr; // ring views: sample cursors at group starts
   int32_t* d_nused = nullptr;  // [view][pixel], then the adjoint's bound flag
-  size_t ckpt_bytes = 0, ckpt_j_bytes = 0, nused_bytes = 0;  // allocated sizes
+  size_t ckpt_bytes = 0, nused_bytes = 0;  // allocated sizes
   int32_t* d_flag = nullptr;   // set by the adjoint when a group held more samples than its bound
 };
 
@@ -113,9 +112,9 @@ void xcd_bands(const std::vector<double>& cost, int wpb, int32_t band[9]) {
 }
 
 // Ring layout for the differentiable pair of one view: slab axis, window slot,
-// forward launch shape, cell layers per checkpoint group (about K samples),
-// and the adjoint's wavefronts per workgroup under 160 KB of LDS.  False when
-// the view needs the sample-segment kernels.
+// forward launch shape and cell layers per checkpoint group (about K samples,
+// the adjoint's windows of one tile within 160 KB of LDS).  False when the view
+// needs the sample-segment kernels.
 bool plan_ring_view(const Camera& cam, const vr_params* p, int32_t M, const int64_t n[3], int layer_cap,
                     vr_state::View& rv) {
   if (p->tile != 0 && p->tile != 8) return false;
@@ -128,25 +127,11 @@ bool plan_ring_view(const Camera& cam, const vr_params* p, int32_t M, const int6
   const int Lmax = std::max(1, std::min(layer_cap, (int)std::lround((double)p->ckpt_K * p->step * db)));
   for (int L = Lmax; L >= 1; L = L > 1 ? L / 2 : 0) {
     const int smax = (int)std::floor((double)L / (p->step * db)) + 3;
-    const double per_wave = 4.0 * (3.0 * (L + 1) * slot + 64.0 + 64.0 * smax);
-    const double fixed = 48.0 * M;  // table (float4) and table gradients (double x 4)
-    int best_w = 0, best_waves = 0;
-    for (int w : {4, 2, 1}) {
-      const double lds = fixed + w * per_wave;
-      if (lds > 160.0 * 1024.0) continue;
-      int blocks = (int)std::floor(160.0 * 1024.0 / lds);
-      blocks = std::min(blocks, 16 / w);  // 99 VGPRs: 4 wavefronts per SIMD
-      if (blocks * w > best_waves) {
-        best_waves = blocks * w;
-        best_w = w;
-      }
-    }
-    if (best_w == 0) continue;
+    if (bwd_ring_lds_bytes(M, L, slot, smax, true) > 160 * 1024) continue;
     rv.ring = true;
     rv.axis = axis;
     rv.slot = slot;
     rv.fwd_wpb = wpb;
-    rv.bwd_wpb = best_w;
     rv.L = L;
     rv.smax = smax;
     rv.ngrp = (int32_t)((n[axis] - 1 + L - 1) / L) + 1;
@@ -189,38 +174,32 @@ int render_with_state(vr_ctx* ctx, vr_volume* vol, const vr_view* views, int32_t
   // per-view layout and checkpoint offsets
   std::vector<Camera> cams((size_t)nviews);
   st->vs.assign((size_t)nviews, vr_state::View());
-  int64_t ck_total = 0, ckj_total = 0;
+  int64_t ck_total = 0;
   for (int32_t v = 0; v < nviews; v++) {
     make_camera(views[v], vol->n, cams[v]);
     vr_state::View& rv = st->vs[v];
     if (ctx->march_mode != 1 && plan_ring_view(cams[v], p, ctx->tf_m, vol->n, ctx->bwd_layer_cap, rv)) {
       rv.off = ck_total;
       ck_total += (int64_t)rv.ngrp * npix;
-      ckj_total += (int64_t)rv.ngrp * npix;
     } else {
       rv.off = ck_total;
       ck_total += (int64_t)st->nseg * npix;
     }
   }
   const size_t ck_bytes = sizeof(float) * (size_t)std::max<int64_t>(ck_total, 1);
-  const size_t ckj_bytes = ckj_total > 0 ? sizeof(int32_t) * (size_t)ck_total : 0;
   const size_t nu_bytes = sizeof(int32_t) * ((size_t)nviews * npix + 64);
   // the buffers of the last destroyed state when they are large enough
   vr_ctx::StateBufs& sp = ctx->spare;
-  if (sp.ckpt && sp.ckpt_bytes >= ck_bytes && sp.nused_bytes >= nu_bytes && sp.ckpt_j_bytes >= ckj_bytes) {
+  if (sp.ckpt && sp.ckpt_bytes >= ck_bytes && sp.nused_bytes >= nu_bytes) {
     st->d_ckpt = sp.ckpt;
-    st->d_ckpt_j = sp.ckpt_j;
     st->d_nused = sp.nused;
     st->ckpt_bytes = sp.ckpt_bytes;
-    st->ckpt_j_bytes = sp.ckpt_j_bytes;
     st->nused_bytes = sp.nused_bytes;
     sp = vr_ctx::StateBufs();
   } else {
     st->ckpt_bytes = ck_bytes;
-    st->ckpt_j_bytes = ckj_bytes;
     st->nused_bytes = nu_bytes;
-    if (dev_malloc(&st->d_ckpt, ck_bytes) != hipSuccess || dev_malloc(&st->d_nused, nu_bytes) != hipSuccess ||
-        (ckj_bytes > 0 && dev_malloc(&st->d_ckpt_j, ckj_bytes) != hipSuccess)) {
+    if (dev_malloc(&st->d_ckpt, ck_bytes) != hipSuccess || dev_malloc(&st->d_nused, nu_bytes) != hipSuccess) {
       (void)hipGetLastError();
       vr_state_destroy(st);
       return fail(VR_ENOMEM, "hipMalloc for %zu bytes of checkpoints failed", ck_bytes);
@@ -260,7 +239,6 @@ int render_with_state(vr_ctx* ctx, vr_volume* vol, const vr_view* views, int32_t
     SaveArgs sa;
     std::memset(&sa, 0, sizeof sa);
     sa.ckpt = st->d_ckpt + rv.off;
-    sa.ckpt_j = rv.ring ? st->d_ckpt_j + rv.off : nullptr;
     sa.nused = st->d_nused + (int64_t)v * npix;
     sa.K = rv.ring ? rv.L : st->K;
     sa.npix = (int32_t)npix;
@@ -269,7 +247,7 @@ int render_with_state(vr_ctx* ctx, vr_volume* vol, const vr_view* views, int32_t
       // while the GPU marches view v - 1)
       const std::vector<double> cost = tile_costs(cams[v], base.hi, p->step, W, H);
       xcd_bands(cost, rv.fwd_wpb, sa.band);
-      xcd_bands(cost, rv.bwd_wpb, st->vs[v].band);
+      xcd_bands(cost, 1, st->vs[v].band);
     }
     if (!side) rc = stage_begin(ctx, VR_STAGE_MARCH, s);
     if (rc == VR_OK) {
@@ -310,15 +288,12 @@ int vr_state_destroy(vr_state* st) {
     // kept for the context's next forward with state (calls on a context are
     // ordered, so no work of this state can still be reading them then)
     sp.ckpt = st->d_ckpt;
-    sp.ckpt_j = st->d_ckpt_j;
     sp.nused = st->d_nused;
     sp.ckpt_bytes = st->ckpt_bytes;
-    sp.ckpt_j_bytes = st->ckpt_j_bytes;
     sp.nused_bytes = st->nused_bytes;
   } else {
     (void)hipDeviceSynchronize();
     if (st->d_ckpt) (void)hipFree(st->d_ckpt);
-    if (st->d_ckpt_j) (void)hipFree(st->d_ckpt_j);
     if (st->d_nused) (void)hipFree(st->d_nused);
   }
   delete st;
@@ -381,8 +356,10 @@ int vr_render_backward(vr_ctx* ctx, const vr_volume* vol, const vr_state* st, co
     BwdArgs bb;
     std::memset(&bb, 0, sizeof bb);
     std::memcpy(bb.band, rv.band, sizeof bb.band);
-    pbase[v + 1] = pbase[v] + (rv.ring ? bwd_ring_blocks(a0, bb, rv.bwd_wpb) : bwd_blocks(a0));
+    pbase[v + 1] = pbase[v] + (rv.ring ? bwd_ring_blocks(a0, bb) : bwd_blocks(a0));
   }
+  float max_alpha = 0.f;
+  for (int32_t i = 0; i < M; i++) max_alpha = std::max(max_alpha, ctx->h_tf[4 * (size_t)i + 3]);
   const bool side = ctx->bwd_side && st->nviews > 1;
   int64_t nslots = 1;
   for (int32_t v = 0; v < st->nviews; v++) nslots = std::max(nslots, pbase[v + 1] - pbase[v]);
@@ -405,7 +382,6 @@ int vr_render_backward(vr_ctx* ctx, const vr_volume* vol, const vr_state* st, co
     BwdArgs ba;
     std::memset(&ba, 0, sizeof ba);
     ba.ckpt = st->d_ckpt + rv.off;
-    ba.ckpt_j = rv.ring ? st->d_ckpt_j + rv.off : nullptr;
     ba.nused = st->d_nused + (int64_t)v * npix;
     ba.gout = reinterpret_cast<const float4*>(grad_out) + (int64_t)v * npix;
     ba.gvol = grad_vol;
@@ -415,12 +391,13 @@ int vr_render_backward(vr_ctx* ctx, const vr_volume* vol, const vr_state* st, co
     ba.K = rv.ring ? rv.L : st->K;
     ba.npix = (int32_t)npix;
     ba.smax = rv.smax;
+    ba.replay = max_alpha > kMaxDivAlpha ? 1 : 0;
     std::memcpy(ba.band, rv.band, sizeof ba.band);
     ba.flag = st->d_flag;
     if (rv.ring) {
       a.slab_axis = rv.axis;
       a.ring_slot = rv.slot;
-      VR_HIP(launch_bwd_ring(a, ba, rv.bwd_wpb, vs));
+      VR_HIP(launch_bwd_ring(a, ba, vs));
     } else {
       VR_HIP(launch_bwd(a, ba, vs));
     }

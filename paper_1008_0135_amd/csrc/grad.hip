@@ -246,22 +246,27 @@ __global__ __launch_bounds__(256) void k_bwd(MarchArgs a, BwdArgs ba) {
 // grad_tf[e] (+)= sum over blocks of the partials, accumulated in double, in
 // two passes with a fixed order (the same bits on every run): slice s sums
 // blocks s, s + kSlices, ...; then each entry sums its slices in order.
-constexpr int kSlices = 64;
+constexpr int kSlices = 256;
 
 __global__ __launch_bounds__(256) void k_tf_slices(const double* part, int nblocks, int n, double* sl) {
   const int e = blockIdx.x * 256 + threadIdx.x;
   if (e >= n) return;
   double acc = 0.0;
+#pragma unroll 4
   for (int b = (int)blockIdx.y; b < nblocks; b += kSlices) acc += part[(int64_t)b * n + e];
   sl[(int64_t)blockIdx.y * n + e] = acc;
 }
 
+// One wavefront per entry: lane l sums slices l, l + 64, ..., then the lanes
+// are added pairwise (a fixed order).
 __global__ __launch_bounds__(256) void k_tf_reduce(const double* sl, int n, float* grad_tf) {
-  const int e = blockIdx.x * 256 + threadIdx.x;
+  const int e = blockIdx.x * 4 + (threadIdx.x >> 6);
   if (e >= n) return;
   double acc = 0.0;
-  for (int s = 0; s < kSlices; s++) acc += sl[(int64_t)s * n + e];
-  grad_tf[e] = (float)((double)grad_tf[e] + acc);
+#pragma unroll
+  for (int s = threadIdx.x & 63; s < kSlices; s += 64) acc += sl[(int64_t)s * n + e];
+  for (int off = 32; off > 0; off >>= 1) acc += __shfl_xor(acc, off);
+  if ((threadIdx.x & 63) == 0) grad_tf[e] = (float)((double)grad_tf[e] + acc);
 }
 
 __global__ __launch_bounds__(256) void k_fill(float* p, int64_t n, float v) {
@@ -294,7 +299,7 @@ int tf_reduce_slices() { return kSlices; }
 
 hipError_t launch_tf_reduce(const double* part, int nblocks, int n, float* grad_tf, double* slices, hipStream_t s) {
   hipLaunchKernelGGL(k_tf_slices, dim3((n + 255) / 256, kSlices), dim3(256), 0, s, part, nblocks, n, slices);
-  hipLaunchKernelGGL(k_tf_reduce, dim3((n + 255) / 256), dim3(256), 0, s, slices, n, grad_tf);
+  hipLaunchKernelGGL(k_tf_reduce, dim3((n + 3) / 4), dim3(256), 0, s, slices, n, grad_tf);
   return hipGetLastError();
 }
 

@@ -1,32 +1,43 @@
 // grad_ring.hip -- the adjoint march on the ring-window layout (gfx950).
 //
-// The differentiable forward (k_march_ring<false, true>) walks every 8 x 8 ray
-// tile cell layer by cell layer along the slab axis b and stores, for every
-// group of L consecutive cell layers of the tile (in marching order), each
-// ray's transmittance and sample cursor at the group's start.  This kernel
-// walks the groups from the last to the first.  For a group it
+// The differentiable forward (k_march_ring<SAVE>) walks every 8 x 8 ray tile
+// cell layer by cell layer along the slab axis b and stores, for every group
+// of L consecutive cell layers of the tile (in marching order), each ray's
+// transmittance at the group's start, and after the last group at the ray's
+// end.  This kernel walks the groups from the last to the first.  A workgroup
+// of four wavefronts takes one tile: four neighbouring lanes share a ray and
+// hold four consecutive samples of it, so a ray's chain is a quarter as long
+// and the tile's windows serve four wavefronts.  For a group it
 //   1. copies the L + 1 voxel windows the group's samples read into LDS
-//      (the same windows as the forward: rows along axis 1, direct
-//      global->LDS loads) and clears L + 1 gradient windows of the same shape;
-//   2. replays each ray's samples of the group forward from the stored
-//      transmittance, keeping T before each sample in LDS;
-//   3. walks them backward with the division-free recursion
+//      (rows along axis 1, as in the forward) beside L + 1 gradient windows;
+//   2. takes the group's samples four per ray from the last to the first with
+//      the recursion
 //        dL/dc_k = g_rgb T_{k-1} a_k,
 //        dL/da_k = T_{k-1} (h_k - S_k),  h_k = g_rgb . c_k + g_A,
-//        S_{k-1} = a_k h_k + (1 - a_k) S_k,
+//        S_{k-1} = a_k h_k + (1 - a_k) S_k
 //      (S: the output gradient times what the ray gathers behind a sample, per
-//      unit of transmittance) carrying S from group to group; table gradients
+//      unit of transmittance), carrying S from block to block; table gradients
 //      go to double LDS accumulators (one set per workgroup, reduced by
 //      k_tf_reduce), voxel gradients to the gradient windows with LDS double
 //      atomics;
-//   4. adds the gradient windows to the gradient volume with one float atomic
-//      per non-zero window voxel, row after row (coalesced), instead of eight
-//      scattered atomics per sample.
+//   3. adds the finished gradient windows to the gradient volume with one float
+//      atomic per non-zero window voxel, row after row (coalesced), instead of
+//      eight scattered atomics per sample.
+// T before a block comes from the group's end by division by its samples'
+// 1 - a (every sample is evaluated once), or, for tables whose opacity exceeds
+// kMaxDivAlpha, from a replay of the group from its start (REPLAY): dividing by
+// 1 - a multiplies the error of a by a / (1 - a).
 // Samples are evaluated at double-precision positions (start + j step, one
 // rounding per axis; cell_d), with the trilinear value, the table lookup, the
-// recursion and the gradient algebra in double precision.  A tile whose window would not
-// fit reads its corners from global memory and adds its voxel gradients with
-// global atomics directly (same groups, same arithmetic).
+// recursion and the gradient algebra in double precision; which group a
+// sample belongs to follows the forward's single-precision position, so the
+// stored transmittances fit.  A tile whose window would not fit reads its
+// corners from global memory and adds its voxel gradients with global atomics
+// directly (same groups, same arithmetic).
+//
+// Bound by the LDS atomics (16 double adds per sample, 28 to 33 cycles per
+// wavefront instruction on one compute unit) and the double-precision vector
+// work.
 #include <algorithm>
 
 #include "ring_common.h"
@@ -45,6 +56,7 @@ struct Eval {
   double sraw;        // unclamped normalised value
   double wx, wy, wz;  // trilinear fractions
   int i;              // table interval
+  float4 t0, t1;      // its entries
 };
 
 // A sample in double precision: position start + j step (one rounding per
@@ -88,374 +100,398 @@ __device__ __forceinline__ Eval eval_d(const float (&v)[8], const CellD& c, doub
   const double u = s * (double)(M - 1);
   e.i = min((int)u, M - 2);
   e.w = u - (double)e.i;
-  const float4 t0 = s_tf[e.i], t1 = s_tf[e.i + 1];
-  e.r = fma(e.w, (double)t1.x - (double)t0.x, (double)t0.x);
-  e.g = fma(e.w, (double)t1.y - (double)t0.y, (double)t0.y);
-  e.b = fma(e.w, (double)t1.z - (double)t0.z, (double)t0.z);
-  e.a = fma(e.w, (double)t1.w - (double)t0.w, (double)t0.w);
+  e.t0 = s_tf[e.i];
+  e.t1 = s_tf[e.i + 1];
+  e.r = fma(e.w, (double)e.t1.x - (double)e.t0.x, (double)e.t0.x);
+  e.g = fma(e.w, (double)e.t1.y - (double)e.t0.y, (double)e.t0.y);
+  e.b = fma(e.w, (double)e.t1.z - (double)e.t0.z, (double)e.t0.z);
+  e.a = fma(e.w, (double)e.t1.w - (double)e.t0.w, (double)e.t0.w);
   return e;
 }
 
-// LDS of one wavefront in floats: L + 1 voxel windows (float), L + 1 gradient
-// windows (double), window offsets, T before each sample of the group.
-__host__ __device__ constexpr size_t per_wave_floats(int L, int slot, int smax) {
-  return (size_t)3 * (L + 1) * slot + 64 + (size_t)smax * 64;
+// LDS of one tile in floats: L + 1 voxel windows (float), L + 1 gradient
+// windows (double), window offsets, layer ranges, and, for the replay, T before
+// every block of four samples of the group.
+__host__ __device__ constexpr size_t tile_floats(int L, int slot, int smax, bool replay) {
+  return (size_t)3 * (L + 1) * slot + 64 + (replay ? (size_t)((smax + 3) / 4) * 128 : 0);
 }
 
-__global__ __launch_bounds__(256) void k_bwd_ring(MarchArgs a, BwdArgs ba) {
+// value of v in lane I of the four lanes that share a ray
+template <int I>
+__device__ __forceinline__ double quad_bcast(double v) {
+  const int lo = __builtin_amdgcn_update_dpp(0, __double2loint(v), 0x55 * I, 0xf, 0xf, true);
+  const int hi = __builtin_amdgcn_update_dpp(0, __double2hiint(v), 0x55 * I, 0xf, 0xf, true);
+  return __hiloint2double(hi, lo);
+}
+
+__device__ __forceinline__ double quad_pick(int dl, double v0, double v1, double v2, double v3) {
+  const double lo = dl & 1 ? v1 : v0, hi = dl & 1 ? v3 : v2;
+  return dl & 2 ? hi : lo;
+}
+
+constexpr int kAhead = 3;  // layers of windows kept ahead in registers
+
+template <bool REPLAY>
+__global__ __launch_bounds__(256) __attribute__((amdgpu_waves_per_eu(4))) void k_bwd_ring(MarchArgs a, BwdArgs ba) {
   extern __shared__ double dsm[];
   const int M = a.M, L = ba.K;
   // table gradients [4][M]: neighbouring entries in neighbouring banks (an
   // [M][4] layout makes entries 8 apart collide: 56 cycles per add against 33)
   double* s_gtf = dsm;
-  float4* s_tf = reinterpret_cast<float4*>(dsm + 4 * M);    // [M]
-  const int wpb = (int)(blockDim.x >> 6);
-  const int wave = uni((int)(threadIdx.x >> 6)), lane = threadIdx.x & 63;
+  float4* s_tf = reinterpret_cast<float4*>(dsm + 4 * M);  // [M]
   const int slot = a.ring_slot;
-  const int smax = ba.smax;  // samples of one ray in one group, at most
-  const size_t per_wave = per_wave_floats(L, slot, smax);
-  float* s_vox = reinterpret_cast<float*>(s_tf + M) + (size_t)wave * per_wave;
-  double* s_grad = reinterpret_cast<double*>(s_vox + (size_t)(L + 1) * slot);
-  int* s_boff = reinterpret_cast<int*>(s_grad + (size_t)(L + 1) * slot);
-  float* s_T = reinterpret_cast<float*>(s_boff + 64);
+  // The gradient windows hold doubles: on gfx950 one ds_add_f32 takes about
+  // 195 cycles of a compute unit's LDS whatever its addresses (it retires
+  // about a lane every three cycles), ds_add_f64 9 without conflicts and 28
+  // with a tile's.
+  double* s_grad = reinterpret_cast<double*>(s_tf + M);                          // [L + 1][slot]
+  float* s_vox = reinterpret_cast<float*>(s_grad + (size_t)(L + 1) * slot);     // [L + 1][slot]
+  int* s_boff = reinterpret_cast<int*>(s_vox + (size_t)(L + 1) * slot);         // [32] window offsets
+  int* s_range = s_boff + 32;                                                   // [8] layer ranges
+  double* s_T = reinterpret_cast<double*>(s_boff + 64);                         // REPLAY: [blocks][64]
   for (int i = threadIdx.x; i < M; i += blockDim.x) {
     s_tf[i] = a.tf[i];
     s_gtf[i] = s_gtf[M + i] = s_gtf[2 * M + i] = s_gtf[3 * M + i] = 0.0;
   }
-  __syncthreads();
+  for (int e = threadIdx.x; e < (L + 1) * slot; e += blockDim.x) s_grad[e] = 0.0;
 
   // same tile order as the forward
-  const int ngroups_b = (a.ntiles + wpb - 1) / wpb;
-  int grp;
+  int tile;
   if (ba.band[8] > 0) {
     const int x = (int)(blockIdx.x & 7), g = ba.band[x] + (int)(blockIdx.x >> 3);
-    grp = g < ba.band[x + 1] ? g : ngroups_b;
+    tile = g < ba.band[x + 1] ? g : a.ntiles;
   } else {
-    grp = (int)(blockIdx.x & 7) * ((ngroups_b + 7) >> 3) + (int)(blockIdx.x >> 3);
+    tile = (int)(blockIdx.x & 7) * ((a.ntiles + 7) >> 3) + (int)(blockIdx.x >> 3);
   }
-  const int tile = grp < ngroups_b ? grp * wpb + wave : a.ntiles;
-  const bool tile_on = tile < a.ntiles;
-  // every wavefront reaches the workgroup barrier at the end, so the work
-  // sits inside `if (tile_on)` rather than behind an early return
-  if (tile_on) {
-    const DevBrickView bvw = a.bv[0];
-    const DevBrick br = a.bricks[0];
-    const int tx = tile % bvw.tiles_x, ty = tile / bvw.tiles_x;
-    const int lx = tx * 8 + (lane & 7), ly = ty * 8 + (lane >> 3);
-    const bool valid = lx < bvw.w && ly < bvw.h;
-    const int u = bvw.x0 + min(lx, bvw.w - 1), v = bvw.y0 + min(ly, bvw.h - 1);
-    const int pix = ly * bvw.w + lx;
+  const int tid = threadIdx.x, wave = uni(tid >> 6), lane = tid & 63, dl = tid & 3;
+  // a wavefront's 16 rays are every other pixel of the tile both ways: rays
+  // next to each other would add to the same voxels (8 views 14.8 ms against
+  // 13.1)
+  const int ray = tid >> 2;
+  const DevBrickView bvw = a.bv[0];
+  const DevBrick br = a.bricks[0];
+  const int tx = tile % bvw.tiles_x, ty = tile / bvw.tiles_x;
+  const int lx = tx * 8 + ((ray & 3) << 1) + (wave & 1);
+  const int ly = ty * 8 + ((ray >> 2 & 3) << 1) + (wave >> 1);
+  const bool valid = tile < a.ntiles && lx < bvw.w && ly < bvw.h;
+  const int u = bvw.x0 + min(lx, bvw.w - 1), v = bvw.y0 + min(ly, bvw.h - 1);
+  const int pix = ly * bvw.w + lx;
 
-    // ---- ray setup, frame and layer range: as the forward ring march
-    const double* d = a.cam.e3;
-    double o[3];
-    pixel_origin(a.cam, u, v, o);
-    int cnt = 0;
-    float px = 0.f, py = 0.f, pz = 0.f;
-    double p0[3] = {0.0, 0.0, 0.0};
-    const double sv[3] = {a.step * d[0], a.step * d[1], a.step * d[2]};
-    double tin;
-    int64_t n;
-    if (valid && ray_lattice(o, d, a.hi, a.step, tin, n)) {
-      int64_t k0, k1;
-      brick_krange(o, d, tin, a.step, n, br.lo, br.hi, br.closed, k0, k1);
-      if (k1 > k0) {
-        const double t0 = tin + ((double)k0 + 0.5) * a.step;
-        for (int i = 0; i < 3; i++) p0[i] = o[i] + t0 * d[i] - (double)br.lo[i];
-        px = (float)p0[0];
-        py = (float)p0[1];
-        pz = (float)p0[2];
-        cnt = (int)(k1 - k0);
-      }
+  // ---- ray setup, frame and layer range: as the forward ring march
+  const double* d = a.cam.e3;
+  double o[3];
+  pixel_origin(a.cam, u, v, o);
+  int cnt = 0;
+  double p0[3] = {0.0, 0.0, 0.0};
+  const double sv[3] = {a.step * d[0], a.step * d[1], a.step * d[2]};
+  double tin;
+  int64_t n;
+  if (valid && ray_lattice(o, d, a.hi, a.step, tin, n)) {
+    int64_t k0, k1;
+    brick_krange(o, d, tin, a.step, n, br.lo, br.hi, br.closed, k0, k1);
+    if (k1 > k0) {
+      const double t0 = tin + ((double)k0 + 0.5) * a.step;
+      for (int i = 0; i < 3; i++) p0[i] = o[i] + t0 * d[i] - (double)br.lo[i];
+      cnt = (int)(k1 - k0);
     }
-    const float sx = (float)(a.step * d[0]), sy = (float)(a.step * d[1]), sz = (float)(a.step * d[2]);
-    const bool by = a.slab_axis == 1;
-    const float pb = by ? py : pz, sb = by ? sy : sz;
-    const int cloB = by ? br.clo[1] : br.clo[2], chiB = by ? br.chi[1] : br.chi[2];
-    const int cloG = by ? br.clo[2] : br.clo[1], chiG = by ? br.chi[2] : br.chi[1];
-    const int cloF = br.clo[0], chiF = br.chi[0];
-    const double db = by ? d[1] : d[2], dg = by ? d[2] : d[1];
-    const bool up = db > 0.0;
-    int c_first = up ? 0x7fffffff : -0x7fffffff, c_last = up ? -0x7fffffff : 0x7fffffff;
-    if (cnt > 0) {
-      c_first = (int)floorf(__builtin_amdgcn_fmed3f(pb, (float)cloB, (float)chiB));
-      c_last = (int)floorf(__builtin_amdgcn_fmed3f(fmaf((float)(cnt - 1), sb, pb), (float)cloB, (float)chiB));
+  }
+  const bool by = a.slab_axis == 1;
+  const float pb = (float)(by ? p0[1] : p0[2]), sb = (float)(a.step * (by ? d[1] : d[2]));
+  const int cloB = by ? br.clo[1] : br.clo[2], chiB = by ? br.chi[1] : br.chi[2];
+  const int cloG = by ? br.clo[2] : br.clo[1], chiG = by ? br.chi[2] : br.chi[1];
+  const int cloF = br.clo[0], chiF = br.chi[0];
+  const double db = by ? d[1] : d[2], dg = by ? d[2] : d[1];
+  const bool up = db > 0.0;
+  // cell layer of sample j, as the forward has it
+  auto layer_of = [&](int j) {
+    return (int)floorf(__builtin_amdgcn_fmed3f(fmaf((float)j, sb, pb), (float)cloB, (float)chiB));
+  };
+  int c_first = up ? 0x7fffffff : -0x7fffffff, c_last = up ? -0x7fffffff : 0x7fffffff;
+  if (cnt > 0) {
+    c_first = layer_of(0);
+    c_last = layer_of(cnt - 1);
+  }
+  c_first = up ? wave_imin(c_first) : wave_imax(c_first);
+  c_last = up ? wave_imax(c_last) : wave_imin(c_last);
+  if (lane == 0) {
+    s_range[wave] = c_first;
+    s_range[4 + wave] = c_last;
+  }
+  __syncthreads();
+  int Lbeg = s_range[0], Lend = s_range[4];
+  for (int w = 1; w < 4; ++w) {
+    Lbeg = up ? min(Lbeg, s_range[w]) : max(Lbeg, s_range[w]);
+    Lend = up ? max(Lend, s_range[4 + w]) : min(Lend, s_range[4 + w]);
+  }
+  Lbeg = uni(Lbeg);
+  Lend = uni(Lend);
+  if (up ? Lbeg <= Lend : Lbeg >= Lend) {  // the same for the whole workgroup
+    const int nlay = up ? Lend - Lbeg + 1 : Lbeg - Lend + 1;
+    const int vstep = up ? 1 : -1;
+    const int V0 = up ? Lbeg : Lbeg + 1;  // voxel layer V_k = V0 + k vstep
+    // window geometry from the tile's corner rays (lanes 0..3)
+    const double rfd = d[0] / db, rgd = dg / db;
+    const float rf = (float)rfd, rg = (float)rgd;
+    float Af, Ag;
+    {
+      const int cx = bvw.x0 + tx * 8, cy = bvw.y0 + ty * 8;
+      const int ex = min(cx + 7, bvw.x0 + bvw.w - 1), ey = min(cy + 7, bvw.y0 + bvw.h - 1);
+      const int cc = lane & 3;
+      double oc[3];
+      pixel_origin(a.cam, (cc & 1) ? ex : cx, (cc & 2) ? ey : cy, oc);
+      const double ob = (by ? oc[1] : oc[2]) - (double)(by ? br.lo[1] : br.lo[2]);
+      Af = (float)(oc[0] - (double)br.lo[0] - ob * rfd);
+      Ag = (float)((by ? oc[2] : oc[1]) - (double)(by ? br.lo[2] : br.lo[1]) - ob * rgd);
     }
-    int Lbeg, Lend;
-    if (up) {
-      Lbeg = uni(wave_imin(c_first));
-      Lend = uni(wave_imax(c_last));
-    } else {
-      Lbeg = uni(wave_imax(c_first));
-      Lend = uni(wave_imin(c_last));
-    }
-    if (!(up ? Lbeg > Lend : Lbeg < Lend)) {
-      const int nlay = up ? Lend - Lbeg + 1 : Lbeg - Lend + 1;
-      const int vstep = up ? 1 : -1;
-      const int V0 = up ? Lbeg : Lbeg + 1;  // voxel layer V_k = V0 + k vstep
-      // window geometry from the tile's corner rays (lanes 0..3)
-      const double rfd = d[0] / db, rgd = dg / db;
-      const float rf = (float)rfd, rg = (float)rgd;
-      float Af, Ag;
-      {
-        const int cx = bvw.x0 + tx * 8, cy = bvw.y0 + ty * 8;
-        const int ex = min(cx + 7, bvw.x0 + bvw.w - 1), ey = min(cy + 7, bvw.y0 + bvw.h - 1);
-        const int cc = lane & 3;
-        double oc[3];
-        pixel_origin(a.cam, (cc & 1) ? ex : cx, (cc & 2) ? ey : cy, oc);
-        const double ob = (by ? oc[1] : oc[2]) - (double)(by ? br.lo[1] : br.lo[2]);
-        Af = (float)(oc[0] - (double)br.lo[0] - ob * rfd);
-        Ag = (float)((by ? oc[2] : oc[1]) - (double)(by ? br.lo[2] : br.lo[1]) - ob * rgd);
-      }
-      const float Af_lo = unif(wmin4(Af)), Af_hi = unif(wmax4(Af));
-      const float Ag_lo = unif(wmin4(Ag)), Ag_hi = unif(wmax4(Ag));
-      const float arf = fabsf(rf), arg = fabsf(rg);
-      const int NF = uni((int)floorf(Af_hi - Af_lo + 2.f * arf + 0.2f) + 3);
-      const int pitch = (NF + 3) & ~3;
-      int NG = uni((int)floorf(Ag_hi - Ag_lo + 2.f * arg + 0.2f) + 3);
-      NG = min(NG, chiG + 2 - cloG);
-      const int ysl = br.sy, zsl = br.sz;
-      const int sB = by ? ysl : zsl, sG = by ? zsl : ysl;
-      gfloat* gbase = (gfloat*)br.base;
-      float* gvol = ba.gvol;  // whole volume: brick-local == global
-      const bool inl = !(pitch > chiF + 2 - cloF || pitch * NG > slot || pitch > 256 ||
-                         ((int64_t)(64 / (pitch >> 2)) * sG + pitch) * 4 >= ((int64_t)1 << 32));
-      auto window = [&](int V) {
-        Window w;
-        const float Pf = (float)V * rf, Pg = (float)V * rg;
-        const int flo = max((int)floorf(Af_lo + Pf - arf - 0.05f), cloF);
-        const int glo = max((int)floorf(Ag_lo + Pg - arg - 0.05f), cloG);
-        w.f0 = uni(max(cloF, min(flo, chiF + 2 - pitch)));
-        w.g0 = uni(max(cloG, min(glo, chiG + 2 - NG)));
-        return w;
-      };
-      const int nf4 = pitch >> 2;
-      const int R = uni(64 / max(nf4, 1));
-      const int rl = lane / max(nf4, 1), c4l = lane - rl * nf4;
-      const bool lane_on = rl < R;
-      const int nload = uni((NG + R - 1) / max(R, 1));
-      const unsigned voff = (unsigned)(rl * sG + 4 * c4l) * 4u;
-      const int64_t gstep = (int64_t)R * sG;
-      const unsigned lstep = (unsigned)(R * pitch) * 4u;
-      auto issue = [&](int V, const Window& w, float* sdst) {
-        gfloat* gb = gbase + ((int64_t)V * sB + (int64_t)w.g0 * sG + w.f0);
-        const unsigned l0 = uni(lds_addr(sdst));
-        for (int k = 0; k < nload; ++k)
-          if (lane_on && k * R + rl < NG) lds_dma16(unip(gb + k * gstep), voff, l0 + (unsigned)k * lstep);
-      };
+    const float Af_lo = unif(wmin4(Af)), Af_hi = unif(wmax4(Af));
+    const float Ag_lo = unif(wmin4(Ag)), Ag_hi = unif(wmax4(Ag));
+    const float arf = fabsf(rf), arg = fabsf(rg);
+    const int NF = uni((int)floorf(Af_hi - Af_lo + 2.f * arf + 0.2f) + 3);
+    const int pitch = (NF + 3) & ~3;
+    int NG = uni((int)floorf(Ag_hi - Ag_lo + 2.f * arg + 0.2f) + 3);
+    NG = min(NG, chiG + 2 - cloG);
+    const int ysl = br.sy, zsl = br.sz;
+    const int sB = by ? ysl : zsl, sG = by ? zsl : ysl;
+    gfloat* gbase = (gfloat*)br.base;
+    float* gvol = ba.gvol;  // whole volume: brick-local == global
+    const bool inl = !(pitch > chiF + 2 - cloF || pitch * NG > slot || pitch > 256);
+    auto window = [&](int V) {
+      Window w;
+      const float Pf = (float)V * rf, Pg = (float)V * rg;
+      const int flo = max((int)floorf(Af_lo + Pf - arf - 0.05f), cloF);
+      const int glo = max((int)floorf(Ag_lo + Pg - arg - 0.05f), cloG);
+      w.f0 = uni(max(cloF, min(flo, chiF + 2 - pitch)));
+      w.g0 = uni(max(cloG, min(glo, chiG + 2 - NG)));
+      return w;
+    };
+    // element e of a window: row e / pitch, column e % pitch
+    const float inv_pitch = 1.0f / (float)pitch;
+    const int nwin = NG * pitch;
 
-      // per-ray state of the backward walk
-      const int used = valid ? ba.nused[pix] : 0;
-      const float4 gf = valid ? ba.gout[pix] : make_float4(0.f, 0.f, 0.f, 0.f);
-      const double gx = gf.x, gy = gf.y, gz = gf.z, gw = gf.w;
-      const double dvs = (double)(M - 1) * ba.inv_range;  // du/dv inside the window
-      double S = 0.0;  // g . (what the ray gathers behind the sample, per unit of transmittance)
-      const int ngrp = (nlay + L - 1) / L;
-      const int npix = ba.npix;
-      // Consecutive samples of a ray mostly fall in the same table interval and
-      // often in the same cell: their table- and voxel-gradient terms are summed
-      // in registers and added to LDS once per run (far fewer atomics on the
-      // few table entries every lane of the tile hits)
-      int ti = -1;  // table interval of the pending sums
-      float run_tf[8];  // a run is a few samples: float sums lose nothing the tolerance sees
-      auto flush_tf = [&]() {
-        if (ti >= 0) {
-          double* e0 = s_gtf + ti;
-          for (int q = 0; q < 4; ++q) {
-            atomicAdd(e0 + q * M, (double)run_tf[q]);
-            atomicAdd(e0 + q * M + 1, (double)run_tf[4 + q]);
-          }
-          ti = -1;
+    // per-ray state of the backward walk
+    const int used = valid ? ba.nused[pix] : 0;
+    const float4 gf = valid ? ba.gout[pix] : make_float4(0.f, 0.f, 0.f, 0.f);
+    const double gx = gf.x, gy = gf.y, gz = gf.z, gw = gf.w;
+    const double dvs = (double)(M - 1) * ba.inv_range;  // du/dv inside the window
+    double S = 0.0;
+    const int ngrp = (nlay + L - 1) / L;
+    const int npix = ba.npix;
+    // first sample in cell layer k or a later one (marching order): the
+    // forward's layers are monotone along a ray
+    const float inv_sb = 1.f / sb;
+    auto first_at = [&](int k) {
+      const int c = up ? Lbeg + k : Lbeg - k;
+      const float est = ((float)(up ? c : c + 1) - pb) * inv_sb;
+      int j = min(max((int)ceilf(fminf(fmaxf(est, -1.f), 1e9f)), 0), cnt);
+      while (j > 0 && (up ? layer_of(j - 1) >= c : layer_of(j - 1) <= c)) --j;
+      while (j < cnt && !(up ? layer_of(j) >= c : layer_of(j) <= c)) ++j;
+      return j;
+    };
+    // Voxel layer V_m lives in slot m % (L + 1) for every group, so the layer
+    // two consecutive groups share (V_{k0} of a group, V_{k1} of the one
+    // before it, which is taken next) keeps its voxel window and its gradient
+    // window: it is neither reloaded nor cleared there, and flushed once,
+    // with both groups' terms, by the group taken later.
+    auto pslot = [&](int m) { return m % (L + 1); };
+    int jn = cnt;  // first sample of the group taken before (behind) this one
+    float Tn = valid ? ba.ckpt[(int64_t)ngrp * npix + pix] : 1.f;  // T behind the group
+    float Tg = valid ? ba.ckpt[(int64_t)(ngrp - 1) * npix + pix] : 1.f;  // T before the group
+    // chunk (16 bytes) of a window this lane copies: row pr, column pc
+    typedef float v4f __attribute__((ext_vector_type(4)));
+    typedef float v4u __attribute__((ext_vector_type(4), aligned(4)));
+    auto chunk = [&](int V, const Window& w, int e) {
+      const int r = (int)(((float)e + 0.5f) * inv_pitch), col = e - r * pitch;
+      return (v4f) * (const v4u __attribute__((address_space(1)))*)(gbase + ((int64_t)V * sB + (int64_t)(w.g0 + r) * sG +
+                                                                             w.f0 + col));
+    };
+    // windows of one chunk per lane: the next group's are loaded into registers
+    // while this group's samples are taken
+    const bool ahead = inl && nwin <= 1024 && L <= kAhead;
+    v4f pre[kAhead];
+    for (int g = ngrp - 1; g >= 0; --g) {
+      const int k0 = g * L, k1 = min(nlay, k0 + L);  // cell layers k0 .. k1 - 1
+      const int nv = k1 - k0 + 1;                     // voxel layers V_{k0} .. V_{k1}
+      if (inl) {
+        for (int i = 0; i < nv; ++i) {
+          const int V = V0 + (k0 + i) * vstep;
+          const Window w = window(V);
+          const int ps = pslot(k0 + i);
+          if (!(g + 1 < ngrp && i == nv - 1) && !(ahead && g + 1 < ngrp))  // (V_{k1} is kept from group g + 1)
+            for (int e = 4 * tid; e < nwin; e += 1024) *reinterpret_cast<v4f*>(s_vox + ps * slot + e) = chunk(V, w, e);
+          if (tid == 0) s_boff[i] = ps * slot - w.g0 * pitch - w.f0;
         }
-      };
-      // The gradient windows hold doubles: on gfx950 one ds_add_f32 takes about
-      // 195 cycles of a compute unit's LDS whatever its addresses (it retires
-      // about a lane every three cycles), ds_add_f64 9 without conflicts and 28
-      // with a tile's.  Float windows took 1.02e9 LDS cycles per 512^2 view of a
-      // 256 x 256 x 512 cube, these 3.5e8 (forward + backward of 8 views 25.3 ->
-      // 18.3 ms), and they round less.
-      int vl = -1, vu = -1;  // LDS offsets of the pending cell's lower and upper corner rows
-      float va[8];
-      auto flush_vox = [&]() {
-        if (vl >= 0) {
-          double* p = s_grad + vl;
-          double* q = s_grad + vu;
-          if (by) {  // dy selects the layer, dz the row
-            atomicAdd(p, (double)va[0]); atomicAdd(p + 1, (double)va[1]);
-            atomicAdd(q, (double)va[2]); atomicAdd(q + 1, (double)va[3]);
-            atomicAdd(p + pitch, (double)va[4]); atomicAdd(p + pitch + 1, (double)va[5]);
-            atomicAdd(q + pitch, (double)va[6]); atomicAdd(q + pitch + 1, (double)va[7]);
-          } else {   // dz selects the layer, dy the row
-            atomicAdd(p, (double)va[0]); atomicAdd(p + 1, (double)va[1]);
-            atomicAdd(p + pitch, (double)va[2]); atomicAdd(p + pitch + 1, (double)va[3]);
-            atomicAdd(q, (double)va[4]); atomicAdd(q + 1, (double)va[5]);
-            atomicAdd(q + pitch, (double)va[6]); atomicAdd(q + pitch + 1, (double)va[7]);
-          }
-          vl = -1;
-        }
-      };
-
-      // Voxel layer V_m lives in slot m % (L + 1) for every group, so the layer
-      // two consecutive groups share (V_{k0} of a group, V_{k1} of the one
-      // before it, which is taken next) keeps its voxel window and its gradient
-      // window: it is neither reloaded nor cleared there, and flushed once,
-      // with both groups' terms, by the group taken later.
-      auto pslot = [&](int m) { return m % (L + 1); };
-      for (int g = ngrp - 1; g >= 0; --g) {
-        const int k0 = g * L, k1 = min(nlay, k0 + L);  // cell layers k0 .. k1 - 1
-        const int nv = k1 - k0 + 1;                     // voxel layers V_{k0} .. V_{k1}
-        const bool shared_top = g + 1 < ngrp;           // V_{k1} kept from group g + 1
+        if (ahead && g + 1 < ngrp && 4 * tid < nwin)
+#pragma unroll
+          for (int i = 0; i < kAhead; ++i)
+            if (i < L) *reinterpret_cast<v4f*>(s_vox + pslot(k0 + i) * slot + 4 * tid) = pre[i];
+        __syncthreads();
+        if (ahead && g > 0 && 4 * tid < nwin)
+#pragma unroll
+          for (int i = 0; i < kAhead; ++i)
+            if (i < L) {
+              const int V = V0 + (k0 - L + i) * vstep;
+              pre[i] = chunk(V, window(V), 4 * tid);
+            }
+      }
+      const float Tp_next = valid && g > 0 ? ba.ckpt[(int64_t)(g - 1) * npix + pix] : 1.f;
+      const int js = first_at(k0), je = min(jn, used);
+      jn = js;
+      // cell of sample j and its eight corners, from the windows when both of
+      // its voxel layers are in the group's slots (always, up to rounding at
+      // a layer boundary), else from global memory; lofs/uofs: LDS offsets of
+      // the lower and upper corner rows, -1 for global
+      auto corners = [&](int j, CellD& c, float (&vv)[8], int& lofs, int& uofs) {
+        c = cell_d(j, p0, sv, br);
+        lofs = uofs = -1;
         if (inl) {
-          for (int i = 0; i < nv; ++i) {
-            const Window w = window(V0 + (k0 + i) * vstep);
-            const int ps = pslot(k0 + i);
-            if (!(shared_top && i == nv - 1)) {
-              issue(V0 + (k0 + i) * vstep, w, s_vox + ps * slot);
-              for (int e = lane; e < slot; e += 64) s_grad[ps * slot + e] = 0.0;
+          const int ib = by ? c.iy : c.iz, ig = by ? c.iz : c.iy;
+          const int kc = up ? ib - Lbeg : Lbeg - ib;  // cell layer index
+          const int sl = (up ? kc : kc + 1) - k0, su = (up ? kc + 1 : kc) - k0;
+          if (sl >= 0 && sl < nv && su >= 0 && su < nv) {
+            lofs = s_boff[sl] + __mul24(ig, pitch) + c.ix;
+            uofs = s_boff[su] + __mul24(ig, pitch) + c.ix;
+            const float* p = s_vox + lofs;
+            const float* q = s_vox + uofs;
+            if (by) {  // rows along z inside a window, layers along y
+              vv[0] = p[0]; vv[1] = p[1]; vv[2] = q[0]; vv[3] = q[1];
+              vv[4] = p[pitch]; vv[5] = p[pitch + 1]; vv[6] = q[pitch]; vv[7] = q[pitch + 1];
+            } else {   // rows along y, layers along z
+              vv[0] = p[0]; vv[1] = p[1]; vv[2] = p[pitch]; vv[3] = p[pitch + 1];
+              vv[4] = q[0]; vv[5] = q[1]; vv[6] = q[pitch]; vv[7] = q[pitch + 1];
             }
-            if (lane == 0) s_boff[i] = ps * slot - w.g0 * pitch - w.f0;
-          }
-          wait_loads();  // also orders the clears and offsets above
-        }
-        // this ray's samples in the group: [js, je), at most `used`
-        int js = 0, je = 0;
-        double T = 1.0;
-        if (valid) {
-          js = ba.ckpt_j[(int64_t)g * npix + pix];
-          je = g + 1 < ngrp ? ba.ckpt_j[(int64_t)(g + 1) * npix + pix] : cnt;
-          je = min(je, used);
-          T = (double)ba.ckpt[(int64_t)g * npix + pix];
-          // the plan bounds a ray's samples in one group by smax (L layers
-          // at one step each); a group beyond it is flagged, not clamped
-          if (je - js > smax) {
-            atomicOr(ba.flag, 1);
-            je = js + smax;
+            return;
           }
         }
-        // cell of sample j and its eight corners, from the windows when both of
-        // its voxel layers are in the group's slots (always, up to rounding at
-        // a layer boundary), else from global memory; lofs/uofs: LDS offsets of
-        // the lower and upper corner rows, -1 for global
-        auto corners = [&](int j, CellD& c, float (&vv)[8], int& lofs, int& uofs) {
-          c = cell_d(j, p0, sv, br);
-          lofs = uofs = -1;
-          if (inl) {
-            const int ib = by ? c.iy : c.iz, ig = by ? c.iz : c.iy;
-            const int kc = up ? ib - Lbeg : Lbeg - ib;  // cell layer index
-            const int sl = (up ? kc : kc + 1) - k0, su = (up ? kc + 1 : kc) - k0;
-            if (sl >= 0 && sl < nv && su >= 0 && su < nv) {
-              lofs = s_boff[sl] + __mul24(ig, pitch) + c.ix;
-              uofs = s_boff[su] + __mul24(ig, pitch) + c.ix;
-              const float* p = s_vox + lofs;
-              const float* q = s_vox + uofs;
-              if (by) {  // rows along z inside a window, layers along y
-                vv[0] = p[0]; vv[1] = p[1]; vv[2] = q[0]; vv[3] = q[1];
-                vv[4] = p[pitch]; vv[5] = p[pitch + 1]; vv[6] = q[pitch]; vv[7] = q[pitch + 1];
-              } else {   // rows along y, layers along z
-                vv[0] = p[0]; vv[1] = p[1]; vv[2] = p[pitch]; vv[3] = p[pitch + 1];
-                vv[4] = q[0]; vv[5] = q[1]; vv[6] = q[pitch]; vv[7] = q[pitch + 1];
-              }
-              return;
-            }
-          }
-          gfloat* p = gbase + (c.iz * zsl + c.iy * ysl + c.ix);
-          vv[0] = p[0]; vv[1] = p[1]; vv[2] = p[ysl]; vv[3] = p[ysl + 1];
-          vv[4] = p[zsl]; vv[5] = p[zsl + 1]; vv[6] = p[zsl + ysl]; vv[7] = p[zsl + ysl + 1];
-        };
-        // replay: T before each sample of the group
-        for (int j = js; j < je; ++j) {
+        gfloat* p = gbase + (c.iz * zsl + c.iy * ysl + c.ix);
+        vv[0] = p[0]; vv[1] = p[1]; vv[2] = p[ysl]; vv[3] = p[ysl + 1];
+        vv[4] = p[zsl]; vv[5] = p[zsl + 1]; vv[6] = p[zsl + ysl]; vv[7] = p[zsl + ysl + 1];
+      };
+      int nblk = (max(je - js, 0) + 3) >> 2;  // blocks of four samples from js on
+      if constexpr (REPLAY) {
+        // T before every block; the plan bounds a ray's samples in one group by
+        // smax (L layers at one step each): a group beyond it is flagged
+        if (nblk > (ba.smax + 3) / 4) {
+          atomicOr(ba.flag, 1);
+          nblk = (ba.smax + 3) / 4;
+        }
+        double T = (double)Tg;
+        for (int b = 0; b < nblk; ++b) {
+          if (dl == 0) s_T[b * 64 + ray] = T;
+          const int j = js + 4 * b + dl;
           CellD c;
           float vv[8];
           int lofs, uofs;
-          corners(j, c, vv, lofs, uofs);
+          corners(min(j, je - 1), c, vv, lofs, uofs);
           const Eval e = eval_d(vv, c, ba.vmin, ba.inv_range, M, s_tf);
-          s_T[(j - js) * 64 + lane] = (float)T;
-          T = fma(-T, e.a, T);
+          const double al = j < je ? e.a : 0.0;
+          T = fma(-T, quad_bcast<0>(al), T);
+          T = fma(-T, quad_bcast<1>(al), T);
+          T = fma(-T, quad_bcast<2>(al), T);
+          T = fma(-T, quad_bcast<3>(al), T);
         }
-        // backward walk
-        for (int j = je - 1; j >= js; --j) {
-          CellD c;
-          float vv[8];
-          int lofs, uofs;
-          corners(j, c, vv, lofs, uofs);
-          const Eval e = eval_d(vv, c, ba.vmin, ba.inv_range, M, s_tf);
-          const double Tp = (double)s_T[(j - js) * 64 + lane];
-          const double ta = Tp * e.a;
-          const double gr = gx * ta, gg = gy * ta, gb = gz * ta;
-          const double h = fma(gx, e.r, fma(gy, e.g, fma(gz, e.b, gw)));
-          const double ga = Tp * (h - S);
-          S = fma(e.a, h - S, S);
-          const double w1 = e.w, w0 = 1.0 - e.w;
-          if (e.i != ti) {
-            flush_tf();
-            ti = e.i;
-            for (int q = 0; q < 8; ++q) run_tf[q] = 0.f;
-          }
-          run_tf[0] += (float)(w0 * gr);
-          run_tf[1] += (float)(w0 * gg);
-          run_tf[2] += (float)(w0 * gb);
-          run_tf[3] += (float)(w0 * ga);
-          run_tf[4] += (float)(w1 * gr);
-          run_tf[5] += (float)(w1 * gg);
-          run_tf[6] += (float)(w1 * gb);
-          run_tf[7] += (float)(w1 * ga);
-          if (gvol && e.sraw > 0.0 && e.sraw < 1.0) {
-            const float4 t0f = s_tf[e.i], t1f = s_tf[e.i + 1];
-            const double du = gr * ((double)t1f.x - (double)t0f.x) + gg * ((double)t1f.y - (double)t0f.y) +
-                              gb * ((double)t1f.z - (double)t0f.z) + ga * ((double)t1f.w - (double)t0f.w);
-            const double gv = du * dvs;
-            if (gv != 0.0) {
-              const double x1 = e.wx, x0 = 1.0 - e.wx, y1 = e.wy, y0 = 1.0 - e.wy, z1 = e.wz, z0 = 1.0 - e.wz;
-              // corner weights in v[dz][dy][dx] order
-              const float cw[8] = {(float)(gv * x0 * y0 * z0), (float)(gv * x1 * y0 * z0), (float)(gv * x0 * y1 * z0),
-                                   (float)(gv * x1 * y1 * z0), (float)(gv * x0 * y0 * z1), (float)(gv * x1 * y0 * z1),
-                                   (float)(gv * x0 * y1 * z1), (float)(gv * x1 * y1 * z1)};
-              if (lofs >= 0) {
-                if (lofs != vl) {
-                  flush_vox();
-                  vl = lofs;
-                  vu = uofs;
-                  for (int q = 0; q < 8; ++q) va[q] = 0.f;
-                }
-                for (int q = 0; q < 8; ++q) va[q] += cw[q];
-              } else {
-                float* q = gvol + (c.iz * zsl + c.iy * ysl + c.ix);
-                unsafeAtomicAdd(q, cw[0]);
-                unsafeAtomicAdd(q + 1, cw[1]);
-                unsafeAtomicAdd(q + ysl, cw[2]);
-                unsafeAtomicAdd(q + ysl + 1, cw[3]);
-                unsafeAtomicAdd(q + zsl, cw[4]);
-                unsafeAtomicAdd(q + zsl + 1, cw[5]);
-                unsafeAtomicAdd(q + zsl + ysl, cw[6]);
-                unsafeAtomicAdd(q + zsl + ysl + 1, cw[7]);
-              }
-            }
-          }
-        }
-        flush_vox();
-        // add the group's gradient windows to the volume: rows contiguous along axis 1
-        if (inl && gvol) {
-          __builtin_amdgcn_wave_barrier();
-          __builtin_amdgcn_fence(__ATOMIC_ACQ_REL, "wavefront");
-          const float inv_pitch = 1.0f / (float)pitch;
-          for (int i = g > 0 ? 1 : 0; i < nv; ++i) {  // V_{k0} goes on into group g - 1
-            const Window w = window(V0 + (k0 + i) * vstep);
-            float* gl = gvol + ((int64_t)(V0 + (k0 + i) * vstep) * sB + (int64_t)w.g0 * sG + w.f0);
-            const double* sg = s_grad + pslot(k0 + i) * slot;
-            for (int e = lane; e < NG * pitch; e += 64) {
-              const float val = (float)sg[e];
-              if (val != 0.f) {
-                const int r = (int)(((float)e + 0.5f) * inv_pitch), col = e - r * pitch;
-                unsafeAtomicAdd(gl + ((int64_t)r * sG + col), val);
-              }
-            }
-          }
-        }
-        // the next group reuses the windows: every lane is done with them
-        __builtin_amdgcn_wave_barrier();
-        __builtin_amdgcn_fence(__ATOMIC_ACQ_REL, "wavefront");
       }
-      flush_tf();
+      double Tend = (double)Tn;
+      for (int b = nblk - 1; b >= 0; --b) {
+        const int j = js + 4 * b + dl;
+        const bool on = j < je;
+        CellD c;
+        float vv[8];
+        int lofs, uofs;
+        corners(min(j, je - 1), c, vv, lofs, uofs);
+        const Eval e = eval_d(vv, c, ba.vmin, ba.inv_range, M, s_tf);
+        const double h = fma(gx, e.r, fma(gy, e.g, fma(gz, e.b, gw)));
+        const double al = on ? e.a : 0.0;
+        const double a0 = quad_bcast<0>(al), a1 = quad_bcast<1>(al), a2 = quad_bcast<2>(al), a3 = quad_bcast<3>(al);
+        const double h0 = quad_bcast<0>(h), h1 = quad_bcast<1>(h), h2 = quad_bcast<2>(h), h3 = quad_bcast<3>(h);
+        // T before this lane's sample
+        const double e1 = 1.0 - a0, e2 = fma(-e1, a1, e1), e3 = fma(-e2, a2, e2);
+        double Ts;
+        if constexpr (REPLAY) {
+          Ts = s_T[b * 64 + ray];
+        } else {
+          const double e4 = fma(-e3, a3, e3);
+          // Tend / e4: the hardware's reciprocal and two Newton steps
+          double r = __builtin_amdgcn_rcp(e4);
+          r = fma(r, fma(-e4, r, 1.0), r);
+          r = fma(r, fma(-e4, r, 1.0), r);
+          Ts = Tend * r;
+          Tend = Ts;
+        }
+        const double Tp = Ts * quad_pick(dl, 1.0, e1, e2, e3);
+        // S behind this lane's sample
+        const double S2 = fma(a3, h3 - S, S), S1 = fma(a2, h2 - S2, S2), S0 = fma(a1, h1 - S1, S1);
+        const double Sk = quad_pick(dl, S0, S1, S2, S);
+        S = fma(a0, h0 - S0, S0);
+        if (!on) continue;
+        const double ta = Tp * e.a;
+        const double gr = gx * ta, gg = gy * ta, gb = gz * ta;
+        const double ga = Tp * (h - Sk);
+        const double w1 = e.w, w0 = 1.0 - e.w;
+        double* q = s_gtf + e.i;
+        atomicAdd(q, w0 * gr);
+        atomicAdd(q + 1, w1 * gr);
+        atomicAdd(q + M, w0 * gg);
+        atomicAdd(q + M + 1, w1 * gg);
+        atomicAdd(q + 2 * M, w0 * gb);
+        atomicAdd(q + 2 * M + 1, w1 * gb);
+        atomicAdd(q + 3 * M, w0 * ga);
+        atomicAdd(q + 3 * M + 1, w1 * ga);
+        if (gvol && e.sraw > 0.0 && e.sraw < 1.0) {
+          const double du = gr * ((double)e.t1.x - (double)e.t0.x) + gg * ((double)e.t1.y - (double)e.t0.y) +
+                            gb * ((double)e.t1.z - (double)e.t0.z) + ga * ((double)e.t1.w - (double)e.t0.w);
+          const double gv = du * dvs;
+          if (gv != 0.0) {
+            const double x1 = e.wx * gv, x0 = gv - x1, y1 = e.wy, y0 = 1.0 - e.wy, z1 = e.wz, z0 = 1.0 - e.wz;
+            const double yz00 = y0 * z0, yz10 = y1 * z0, yz01 = y0 * z1, yz11 = y1 * z1;
+            if (lofs >= 0) {
+              // rows of the lower and of the upper voxel layer: y selects the
+              // layer and z the row, or z the layer and y the row
+              double* lo = s_grad + lofs;
+              double* hi = s_grad + uofs;
+              const double l1 = by ? yz01 : yz10, u0 = by ? yz10 : yz01;
+              atomicAdd(lo, x0 * yz00);
+              atomicAdd(lo + 1, x1 * yz00);
+              atomicAdd(lo + pitch, x0 * l1);
+              atomicAdd(lo + pitch + 1, x1 * l1);
+              atomicAdd(hi, x0 * u0);
+              atomicAdd(hi + 1, x1 * u0);
+              atomicAdd(hi + pitch, x0 * yz11);
+              atomicAdd(hi + pitch + 1, x1 * yz11);
+            } else {
+              float* gq = gvol + (c.iz * zsl + c.iy * ysl + c.ix);
+              unsafeAtomicAdd(gq, (float)(x0 * yz00));
+              unsafeAtomicAdd(gq + 1, (float)(x1 * yz00));
+              unsafeAtomicAdd(gq + ysl, (float)(x0 * yz10));
+              unsafeAtomicAdd(gq + ysl + 1, (float)(x1 * yz10));
+              unsafeAtomicAdd(gq + zsl, (float)(x0 * yz01));
+              unsafeAtomicAdd(gq + zsl + 1, (float)(x1 * yz01));
+              unsafeAtomicAdd(gq + zsl + ysl, (float)(x0 * yz11));
+              unsafeAtomicAdd(gq + zsl + ysl + 1, (float)(x1 * yz11));
+            }
+          }
+        }
+      }
+      Tn = Tg;
+      Tg = Tp_next;
+      if (inl) {
+        __syncthreads();  // every sample of the group is in the windows
+        // add the finished gradient windows to the volume (rows contiguous
+        // along axis 1) and clear them; V_{k0} goes on into group g - 1
+        for (int i = g > 0 ? 1 : 0; i < nv && gvol; ++i) {
+          const int V = V0 + (k0 + i) * vstep;
+          const Window w = window(V);
+          float* gl = gvol + ((int64_t)V * sB + (int64_t)w.g0 * sG + w.f0);
+          double* sg = s_grad + pslot(k0 + i) * slot;
+          for (int e = tid; e < nwin; e += 256) {
+            const float val = (float)sg[e];
+            sg[e] = 0.0;
+            if (val != 0.f) {
+              const int r = (int)(((float)e + 0.5f) * inv_pitch), col = e - r * pitch;
+              unsafeAtomicAdd(gl + ((int64_t)r * sG + col), val);
+            }
+          }
+        }
+      }
     }
   }
   __syncthreads();
@@ -465,37 +501,37 @@ __global__ __launch_bounds__(256) void k_bwd_ring(MarchArgs a, BwdArgs ba) {
 
 }  // namespace
 
-size_t bwd_ring_lds_bytes(const MarchArgs& a, const BwdArgs& ba, int wpb) {
-  return sizeof(double) * 4 * (size_t)a.M + sizeof(float4) * (size_t)a.M +
-         sizeof(float) * wpb * per_wave_floats(ba.K, a.ring_slot, ba.smax);
+size_t bwd_ring_lds_bytes(int M, int L, int slot, int smax, bool replay) {
+  return sizeof(double) * 4 * (size_t)M + sizeof(float4) * (size_t)M + sizeof(float) * tile_floats(L, slot, smax, replay);
 }
 
-int bwd_ring_blocks(const MarchArgs& a, const BwdArgs& ba, int wpb) {
+int bwd_ring_blocks(const MarchArgs& a, const BwdArgs& ba) {
   if (a.ntiles <= 0) return 0;
   if (ba.band[8] > 0) {
     int widest = 0;
     for (int x = 0; x < 8; x++) widest = std::max(widest, ba.band[x + 1] - ba.band[x]);
     return 8 * widest;
   }
-  const int groups = (a.ntiles + wpb - 1) / wpb;
-  return ((groups + 7) / 8) * 8;
+  return ((a.ntiles + 7) / 8) * 8;
 }
 
-hipError_t launch_bwd_ring(const MarchArgs& a, const BwdArgs& ba, int wpb, hipStream_t s) {
+hipError_t launch_bwd_ring(const MarchArgs& a, const BwdArgs& ba, hipStream_t s) {
   if (a.ntiles <= 0) return hipSuccess;
-  if (a.tile_w != 8 || a.ring_slot <= 0 || (a.ring_slot & 3) != 0 || (wpb != 1 && wpb != 2 && wpb != 4) ||
-      a.cam.persp != 0 || ba.K < 1 || ba.smax < 1 || !ba.ckpt_j)
+  // (the offsets of L + 1 windows have 32 places)
+  if (a.tile_w != 8 || a.ring_slot <= 0 || (a.ring_slot & 3) != 0 || a.cam.persp != 0 || ba.K < 1 || ba.K > 31 ||
+      ba.smax < 1)
     return hipErrorInvalidValue;
-  const size_t lds = bwd_ring_lds_bytes(a, ba, wpb);
+  const size_t lds = bwd_ring_lds_bytes(a.M, ba.K, a.ring_slot, ba.smax, ba.replay != 0);
   if (lds > 160 * 1024) return hipErrorInvalidValue;
-  static bool attr_set = false;  // dynamic LDS beyond the default limit (up to 160 KB)
-  if (!attr_set) {
-    const hipError_t e = hipFuncSetAttribute(reinterpret_cast<const void*>(&k_bwd_ring),
-                                             hipFuncAttributeMaxDynamicSharedMemorySize, 160 * 1024);
+  const void* f = ba.replay ? reinterpret_cast<const void*>(&k_bwd_ring<true>)
+                            : reinterpret_cast<const void*>(&k_bwd_ring<false>);
+  if (lds > 64 * 1024) {  // dynamic LDS beyond the default limit
+    const hipError_t e = hipFuncSetAttribute(f, hipFuncAttributeMaxDynamicSharedMemorySize, 160 * 1024);
     if (e != hipSuccess) return e;
-    attr_set = true;
   }
-  hipLaunchKernelGGL(k_bwd_ring, dim3(bwd_ring_blocks(a, ba, wpb)), dim3(64 * wpb), lds, s, a, ba);
+  const dim3 g(bwd_ring_blocks(a, ba)), b(256);
+  if (ba.replay) hipLaunchKernelGGL(k_bwd_ring<true>, g, b, lds, s, a, ba);
+  else hipLaunchKernelGGL(k_bwd_ring<false>, g, b, lds, s, a, ba);
   return hipGetLastError();
 }
 

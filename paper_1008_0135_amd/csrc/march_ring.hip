@@ -323,11 +323,8 @@ __global__ __launch_bounds__(256) void k_march_ring(MarchArgs a, SaveArgs sa) {
   }
   const int nlay = up ? Lend - Lbeg + 1 : Lbeg - Lend + 1;  // cell layers
   // SAVE: state of the ray at the start of group g (cell layers gK .. gK + K - 1)
-  auto save_group = [&](int g, float Tg, int jg) {
-    if (valid) {
-      sa.ckpt[(int64_t)g * sa.npix + pix] = Tg;
-      sa.ckpt_j[(int64_t)g * sa.npix + pix] = jg;
-    }
+  auto save_group = [&](int g, float Tg) {
+    if (valid) sa.ckpt[(int64_t)g * sa.npix + pix] = Tg;
   };
   const int ngrp_tile = SAVE ? (nlay + sa.K - 1) / sa.K : 0;
 
@@ -408,7 +405,7 @@ __global__ __launch_bounds__(256) void k_march_ring(MarchArgs a, SaveArgs sa) {
       if (SAVE) {
         const int ib = by ? c.iy : c.iz;
         const int gi = (up ? ib - Lbeg : Lbeg - ib) / sa.K;
-        while (gnext <= gi) save_group(gnext++, T, j);
+        while (gnext <= gi) save_group(gnext++, T);
       }
       gfloat* p = gbase + (c.iz * zsl + c.iy * ysl + c.ix);
       const float val = trilerp(p[0], p[1], p[ysl], p[ysl + 1], p[zsl], p[zsl + 1], p[zsl + ysl], p[zsl + ysl + 1], c);
@@ -426,7 +423,7 @@ __global__ __launch_bounds__(256) void k_march_ring(MarchArgs a, SaveArgs sa) {
       }
     }
     if (SAVE) {
-      while (gnext < ngrp_tile) save_group(gnext++, T, j);
+      while (gnext <= ngrp_tile) save_group(gnext++, T);
       if (valid) sa.nused[pix] = j;
     }
     // carried state: only rays with samples here write (another brick of the
@@ -561,7 +558,7 @@ __global__ __launch_bounds__(256) void k_march_ring(MarchArgs a, SaveArgs sa) {
     issue(V0 + vstep, w1, s_ring + slot);
     int s0 = 0;  // slot of V_k
     for (int k = 0; k < nlay; ++k) {
-      if (SAVE && k % sa.K == 0) save_group(k / sa.K, T, j);
+      if (SAVE && k % sa.K == 0) save_group(k / sa.K, T);
       wait_loads();  // V_k and V_{k+1} are in LDS
       // start V_{k+2} into the slot V_{k-1} used (cell layer c_{k-1} is finished);
       // with two slots, into the slot of V_k once c_k is finished
@@ -608,7 +605,7 @@ __global__ __launch_bounds__(256) void k_march_ring(MarchArgs a, SaveArgs sa) {
       }
       if (__all(done)) {
         if (SAVE)
-          for (int g = k / sa.K + 1; g < ngrp_tile; ++g) save_group(g, T, j);
+          for (int g = k / sa.K + 1; g <= ngrp_tile; ++g) save_group(g, T);
         break;
       }
       if (TWO && k + 1 < nlay) issue(V0 + (k + 2) * vstep, w2, s_ring + s0 * slot);
@@ -885,7 +882,7 @@ static hipError_t launch_march_ring_main(const MarchArgs& a, int wpb, hipStream_
 hipError_t launch_march_ring_save(const MarchArgs& a, const SaveArgs& sa, int wpb, hipStream_t s) {
   if (a.ntiles <= 0) return hipSuccess;
   if (a.tile_w != 8 || a.ring_slot <= 0 || (a.ring_slot & 3) != 0 || (wpb != 1 && wpb != 2 && wpb != 4) ||
-      a.mc != 0 || a.mip != 0 || a.cam.persp != 0 || a.ring_nslots == 2 || sa.K < 1 || !sa.ckpt_j)
+      a.mc != 0 || a.mip != 0 || a.cam.persp != 0 || a.ring_nslots == 2 || sa.K < 1)
     return hipErrorInvalidValue;
   const int groups = (a.ntiles + wpb - 1) / wpb;
   int grid = ((groups + 7) / 8) * 8;

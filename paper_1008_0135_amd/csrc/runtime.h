@@ -65,13 +65,12 @@ struct vr_ctx {
   size_t small_bytes = 0;
   void* d_scratch = nullptr;
   size_t scratch_bytes = 0;
-  // device buffers of the last destroyed forward state (checkpoints, sample
-  // cursors, samples used + the adjoint's bound flag), kept for the next one
+  // device buffers of the last destroyed forward state (checkpoints,
+  // samples used + the adjoint's bound flag), kept for the next one
   struct StateBufs {
     float* ckpt = nullptr;
-    int32_t* ckpt_j = nullptr;
     int32_t* nused = nullptr;
-    size_t ckpt_bytes = 0, ckpt_j_bytes = 0, nused_bytes = 0;
+    size_t ckpt_bytes = 0, nused_bytes = 0;
   } spare;
   // footprint-cell marches: per side stream, a count and the work items of
   // cells with more than 64 pixels

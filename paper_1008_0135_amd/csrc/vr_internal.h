@@ -297,8 +297,7 @@ struct CompArgs {
 // Differentiable path (whole volume).  Checkpoints are stored [segment][pixel].
 struct SaveArgs {
   float* ckpt;        // sample segments: T before samples 0, K, 2K, ... [segment][pixel];
-                      // layer groups: T at the start of each group [group][pixel]
-  int32_t* ckpt_j;    // layer groups: sample cursor at the start of each group [group][pixel]
+                      // layer groups: T at the start of each group, then at the ray's end [group][pixel]
   int32_t* nused;     // samples applied per ray (early termination included)
   int32_t K;          // samples per segment, or cell layers per group
   int32_t npix;       // W * H
@@ -307,7 +306,6 @@ struct SaveArgs {
 
 struct BwdArgs {
   const float* ckpt;
-  const int32_t* ckpt_j;  // layer groups: sample cursor at each group start (null for sample segments)
   const int32_t* nused;
   const float4* gout; // dL/d(image) of this view, [H][W]
   float* gvol;        // dL/d(voxels), [n3][n2][n1], or null
@@ -316,8 +314,9 @@ struct BwdArgs {
   int32_t K;          // samples per segment, or cell layers per group
   int32_t npix;
   int32_t smax;       // layer groups: samples of one ray in one group, at most
-  // ring adjoint: tile groups of XCD x (workgroup b runs on XCD b % 8 and takes
-  // group band[x] + b / 8 while below band[x + 1]); contiguous bands of equal
+  int32_t replay;     // layer groups: T from a replay of the group (else by division from its end)
+  // ring adjoint: tiles of XCD x (workgroup b runs on XCD b % 8 and takes
+  // tile band[x] + b / 8 while below band[x + 1]); contiguous bands of equal
   // estimated work.  band[8] == 0: equal counts of groups
   int32_t band[9];
   int32_t* flag;      // set to 1 when a ray's group held more than smax samples
@@ -375,9 +374,13 @@ size_t block_lds_bytes(const MarchArgs& a);
 // per-group checkpoints of sa (layer groups of sa.K cell layers).
 hipError_t launch_march_ring_save(const MarchArgs& a, const SaveArgs& sa, int wpb, hipStream_t s);
 // Adjoint on the ring layout (grad_ring.hip): layer groups of ba.K cell layers.
-hipError_t launch_bwd_ring(const MarchArgs& a, const BwdArgs& ba, int wpb, hipStream_t s);
-size_t bwd_ring_lds_bytes(const MarchArgs& a, const BwdArgs& ba, int wpb);
-int bwd_ring_blocks(const MarchArgs& a, const BwdArgs& ba, int wpb);
+// T by division by 1 - a only for tables whose opacity stays at most this: the
+// error of a, about 1e-5 relative from the forward's single-precision
+// positions, enters T multiplied by a / (1 - a)
+constexpr float kMaxDivAlpha = 0.25f;
+hipError_t launch_bwd_ring(const MarchArgs& a, const BwdArgs& ba, hipStream_t s);
+size_t bwd_ring_lds_bytes(int M, int L, int slot, int smax, bool replay);
+int bwd_ring_blocks(const MarchArgs& a, const BwdArgs& ba);
 hipError_t launch_march_lds(const MarchArgs& a, hipStream_t s);
 hipError_t launch_composite(const CompArgs& a, hipStream_t s);
 // partials of x; dst non-null: also copies x there (both 16-byte aligned)
