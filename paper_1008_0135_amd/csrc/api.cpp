@@ -236,12 +236,31 @@ int volume_range(vr_volume* vol, hipStream_t s) {
   return VR_OK;
 }
 
+// The largest T with 1.f - T >= tau in single precision (the difference rounds
+// monotonically, so the test is T <= that): bisected over the floats of [0, 1],
+// tau = 2 (no test) over the two candidates next to -1.
+float stop_transmittance(float tau) {
+  if (tau > 1.0f) return 1.0f - std::nextafterf(-1.0f, 0.0f) >= tau ? std::nextafterf(-1.0f, 0.0f) : -1.0f;
+  if (0.0f >= tau) return 1.0f;
+  uint32_t lo = 0, hi = 0x3f800000u;  // bits of 0 (stops) and 1 (does not)
+  while (hi - lo > 1) {
+    const uint32_t mid = lo + (hi - lo) / 2;
+    float t;
+    std::memcpy(&t, &mid, 4);
+    (1.0f - t >= tau ? lo : hi) = mid;
+  }
+  float t;
+  std::memcpy(&t, &lo, 4);
+  return t;
+}
+
 void fill_march_common(MarchArgs& a, const vr_volume* vol, const vr_params* p, double vmin, double vmax,
                        const float4* tf, int32_t M) {
   for (int i = 0; i < 3; i++) a.hi[i] = (double)(vol->n[i] - 1);
   a.step = p->step;
   a.tau = p->tau >= 1.0 ? 2.0f : (float)p->tau;
   a.ert = p->tau < 1.0;
+  a.t_stop = stop_transmittance(a.tau);
   a.vmin = (float)vmin;
   a.inv_range = vmax > vmin ? (float)(1.0 / (vmax - vmin)) : 0.0f;
   a.M = M;

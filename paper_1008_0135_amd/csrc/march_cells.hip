@@ -16,13 +16,19 @@
 // trilinear margin, rows along f (the contiguous storage axis).  Cell layer c
 // is sampled from voxel layers c and c + 1.
 //
-// k_march_cells: two LDS slots per wavefront hold the two layers being
+// k_march_cells: bound by vector instructions (0.73 of their issue rate) and
+// LDS reads (0.65) where rays are 1 to 2 voxels apart, by window traffic where
+// they are 3 apart.  Two LDS slots per wavefront hold the two layers being
 // sampled; the window of the layer after next is loaded into registers while
 // a layer is sampled and written over the finished layer afterwards, so every
 // wavefront keeps a layer in flight without a third slot.  Window loads are
 // addressed from a uniform base (scalar registers) plus a per-lane offset
 // fixed for the cell, and the slab axis is a template parameter, so the
-// per-layer and per-sample bookkeeping stays small.
+// per-layer and per-sample bookkeeping stays small; so are window rows of 32
+// and 64 floats (a row is then part of a read's offset) and the opacity test is
+// one comparison (t_stop).  Two 1024^2 views of 512 x 512 x 1024 in eight
+// bricks: 2.42 -> 1.88 ms, of which 0.30 by numbering the cells along g, 0.07 by
+// spreading their rays over the LDS banks (spread_rays).
 //
 // k_march_block: the blk_f x blk_g wavefronts of a workgroup march the cells
 // of one block (a wavefront per cell) together, one cell layer at a time, with
@@ -30,6 +36,7 @@
 // share of rows through registers); per layer: sample; barrier; write V_{k+2}
 // over V_k and start V_{k+3}; barrier.
 #include <algorithm>
+#include <type_traits>
 
 #include "ring_common.h"
 #include "sample.h"
@@ -57,11 +64,9 @@ struct CellRay {
 
 template <bool PERSP>
 __device__ __forceinline__ CellRay cell_ray(const MarchArgs& a, const DevBrickView& bvw, const DevBrick& br,
-                                            const FootRuns& fr, int lane) {
+                                            int u, int v) {
   CellRay r;
-  int u, v;
-  foot_pixel(fr, lane, u, v);
-  r.valid = lane < fr.n;
+  r.valid = u >= 0;
   if (!r.valid) {
     u = 0;
     v = 0;
@@ -102,53 +107,96 @@ __device__ __forceinline__ CellRay cell_ray(const MarchArgs& a, const DevBrickVi
   return r;
 }
 
-// The samples of one lane that fall in cell layer c, read from the two LDS
-// windows whose origins are wl (voxel layer c) and wu (layer c + 1).
-template <bool MIP, bool BY>
-__device__ __forceinline__ void sample_layer(const MarchArgs& a, const DevBrick& br, const CellRay& r,
-                                             const float4* s_tf, const float* s_ring, int slot, int pitch, int c,
-                                             const Window& wl, const Window& wu, int sl, int su, float fclo,
-                                             float fchi, int& j, bool& done, float& Cr, float& Cg, float& Cb,
-                                             float& T, float& mx) {
-  const float* baseL = s_ring + (sl * slot - wl.g0 * pitch - wl.f0);
-  const int dU = (su * slot - wu.g0 * pitch - wu.f0) - (sl * slot - wl.g0 * pitch - wl.f0);
-  while (!done) {
-    const SamplePos q = sample_pos(j, r.px, r.py, r.pz, r.sx, r.sy, r.sz);
-    const int ib = (int)floorf(__builtin_amdgcn_fmed3f(BY ? q.y : q.z, fclo, fchi));
-    if (ib != c) break;
-    const Cell cl = cell_of(q, br);
-    const int ig = BY ? cl.iz : cl.iy;
-    const float* p = baseL + (__mul24(ig, pitch) + cl.ix);
-    const float* pu = p + dU;
-    // corners v[dz][dy][dx]: within a window rows run along g, layers along b
-    const float l00 = p[0], l01 = p[1], l10 = p[pitch], l11 = p[pitch + 1];
-    const float u00 = pu[0], u01 = pu[1], u10 = pu[pitch], u11 = pu[pitch + 1];
-    const float val = BY ? trilerp(l00, l01, u00, u01, l10, l11, u10, u11, cl)
-                         : trilerp(l00, l01, l10, l11, u00, u01, u10, u11, cl);
-    ++j;
-    if (MIP) {
-      const float sv = norm_value(val, a.vmin, a.inv_range);
-      mx = fmaxf(mx, sv);
-      if (j >= r.cnt || mx >= 1.f) done = true;
-    } else {
-      const Classified kk = classify(val, a.vmin, a.inv_range, a.M, s_tf);
-      accumulate(kk, Cr, Cg, Cb, T);
-      if (j >= r.cnt || 1.f - T >= a.tau) done = true;
-    }
+// Rays of a cell over the lanes of the wavefront.  LDS reads are served 32
+// lanes at a time, and two rays whose columns of the window lie in the same
+// bank wait for each other: the rays are ranked by their bank (bank: 0 <= bank
+// < 2^24, any scale) and the ranks dealt to the two halves in turn, so that the
+// rays of a half are spread evenly over the banks.  Parallel rays keep their
+// distances, and so the spread, from layer to layer (bank conflicts per sample
+// down by 15 % with rows of 64 floats, 52 % with rows of 32).  The pixel of
+// this lane is exchanged for the one it takes; scratch: 64 int2 of LDS of this
+// wavefront.
+__device__ __forceinline__ void spread_rays(int bank, int lane, int2* scratch, int& u, int& v) {
+  const int key = bank * 64 + lane;
+  int rank = 0;
+#pragma unroll 16
+  for (int i = 0; i < 64; ++i) rank += __builtin_amdgcn_readlane(key, i) < key ? 1 : 0;
+  scratch[(rank >> 1) + 32 * (rank & 1)] = make_int2(u, v);
+  __builtin_amdgcn_wave_barrier();
+  __builtin_amdgcn_fence(__ATOMIC_ACQ_REL, "wavefront");
+  const int2 p = scratch[lane];
+  u = p.x;
+  v = p.y;
+  __builtin_amdgcn_wave_barrier();
+  __builtin_amdgcn_fence(__ATOMIC_ACQ_REL, "wavefront");
+}
+
+// One sample of a lane at position q (q_b in the cell layer whose floor is fb):
+// corners from the two LDS windows at pl (lower voxel layer) and pu (upper),
+// each offset by the window's origin.
+template <bool MIP, bool BY, bool MASK>
+__device__ __forceinline__ void take_sample(const MarchArgs& a, const DevBrick& br, const float4* s_tf, const float* s_mask,
+                                            const float* pl,
+                                            const float* pu, int pitch, const SamplePos& q, float& Cr, float& Cg,
+                                            float& Cb, float& T, float& mx) {
+  const Cell cl = cell_of(q, br);
+  const int at = __mul24(BY ? cl.iz : cl.iy, pitch) + cl.ix;
+  pl += at;
+  pu += at;
+  [[maybe_unused]] float w = 1.f;
+  if constexpr (MASK) w = channel_weight(s_mask, a.mask_axis, br.lo[a.mask_axis], cl);
+  // corners v[dz][dy][dx]: within a window rows run along g, layers along b
+  const float l00 = pl[0], l01 = pl[1], l10 = pl[pitch], l11 = pl[pitch + 1];
+  const float u00 = pu[0], u01 = pu[1], u10 = pu[pitch], u11 = pu[pitch + 1];
+  const float val = BY ? trilerp(l00, l01, u00, u01, l10, l11, u10, u11, cl)
+                       : trilerp(l00, l01, l10, l11, u00, u01, u10, u11, cl);
+  if (MIP) {
+    float sv = norm_value(val, a.vmin, a.inv_range);
+    if constexpr (MASK) sv *= w;
+    mx = fmaxf(mx, sv);
+  } else {
+    Classified kk = classify(val, a.vmin, a.inv_range, a.M, s_tf);
+    if constexpr (MASK) kk.a *= w;
+    accumulate(kk, Cr, Cg, Cb, T);
   }
 }
 
-template <bool MIP, bool BY, bool PERSP>
+// The samples of one lane that fall in cell layer c, read from the two LDS
+// windows whose origins are wl (voxel layer c) and wu (layer c + 1).
+template <bool MIP, bool BY, bool MASK>
+__device__ __forceinline__ void sample_layer(const MarchArgs& a, const DevBrick& br, const CellRay& r,
+                                             const float4* s_tf, const float* s_mask, const float* s_ring, int slot, int pitch, int c,
+                                             const Window& wl, const Window& wu, int sl, int su, float fclo,
+                                             float fchi, float& j, bool& done, float& Cr, float& Cg, float& Cb,
+                                             float& T, float& mx) {
+  const float* baseL = s_ring + (sl * slot - wl.g0 * pitch - wl.f0);
+  const float* baseU = s_ring + (su * slot - wu.g0 * pitch - wu.f0);
+  const float fc = (float)c, fcnt = (float)r.cnt;
+  while (!done) {
+    const SamplePos q = sample_pos(j, r.px, r.py, r.pz, r.sx, r.sy, r.sz);
+    if (floorf(__builtin_amdgcn_fmed3f(BY ? q.y : q.z, fclo, fchi)) != fc) break;
+    take_sample<MIP, BY, MASK>(a, br, s_tf, s_mask, baseL, baseU, pitch, q, Cr, Cg, Cb, T, mx);
+    j += 1.f;  // exact: a brick's rays have fewer than 2^24 samples
+    done = j >= fcnt || (MIP ? mx >= 1.f : T <= a.t_stop);
+  }
+}
+
+template <bool MIP, bool BY, bool PERSP, bool MASK, int PITCH>
 __global__ __launch_bounds__(256) __attribute__((amdgpu_waves_per_eu(4))) void k_march_cells(MarchArgs a) {
   extern __shared__ float4 smem[];
   float4* s_tf = smem;
   for (int i = threadIdx.x; i < a.M; i += blockDim.x) s_tf[i] = a.tf[i];
+  // the channel weights behind the table: a load from memory per sample would
+  // wait for the layer in flight (loads return in order)
+  [[maybe_unused]] const float* s_mask = reinterpret_cast<float*>(smem + a.M);
+  if constexpr (MASK)
+    for (int i = threadIdx.x; i < a.mask_n; i += blockDim.x) reinterpret_cast<float*>(smem + a.M)[i] = a.mask[i];
   __syncthreads();
 
   const int wpb = (int)(blockDim.x >> 6);
   const int wave = uni((int)(threadIdx.x >> 6)), lane = threadIdx.x & 63;
   const int slot = a.ring_slot;  // floats per slot (one voxel layer's window)
-  float* s_ring = reinterpret_cast<float*>(smem + a.M) + (size_t)wave * 2 * slot;
+  float* s_ring = reinterpret_cast<float*>(smem + (MASK ? cells_table_rows(a) : a.M)) + (size_t)wave * 2 * slot;
 
   // XCD-aware order: workgroup b runs on XCD b % 8; each XCD takes one
   // contiguous range of cells (neighbouring cells share its L2)
@@ -165,11 +213,23 @@ __global__ __launch_bounds__(256) __attribute__((amdgpu_waves_per_eu(4))) void k
   const DevBrickView bvw = a.bv[find_bv(a, tile)];
   const DevBrick br = a.bricks[bvw.brick];
   int ci, cj;
-  foot_cell(bvw, tile - bvw.tile_begin, ci, cj);
+  foot_cell(a, bvw, tile - bvw.tile_begin, ci, cj);
   const FootRuns fr = PERSP ? foot_runs_persp(a, bvw, br, ci, cj, lane) : foot_runs(a, bvw, ci, cj, lane);
   // pixels past the 64th of a cell are marched by k_march_ring_ovf afterwards
   if (fr.n > 64 && lane == 0) a.ovf_tiles[atomicAdd(a.ovf_count, 1u)] = tile * 8;
-  const CellRay r = cell_ray<PERSP>(a, bvw, br, fr, lane);
+  int u, v;
+  foot_pixel(fr, lane, u, v);
+  if (lane >= fr.n) u = -1;  // no ray
+  if (!PERSP && a.cols) {
+    const int pitch = PITCH > 0 ? PITCH : (a.foot_nf + 3) & ~3;
+    const float f = (float)((bvw.fa0 + a.fa_u * u + a.fa_v * v - ci) * a.foot_Tf);
+    const float g = (float)((bvw.fb0 + a.fb_u * u + a.fb_v * v - cj) * a.foot_Tg);
+    const float bank = fmaxf(f, 0.f) + (float)(((int)fmaxf(g, 0.f) * pitch) & 63);
+    // the window's columns wrap after 64 banks; lanes without a ray come last
+    const int key = u < 0 ? 64 << 10 : (int)(1024.f * fminf(bank >= 64.f ? bank - 64.f : bank, 63.9f));
+    spread_rays(key, lane, reinterpret_cast<int2*>(s_ring), u, v);
+  }
+  const CellRay r = cell_ray<PERSP>(a, bvw, br, u, v);
 
   // ---- frame: b = slab axis (axis 2 if BY, else axis 3), g = the other, f = axis 1
   const float pb = BY ? r.py : r.pz, sb = BY ? r.sy : r.sz;
@@ -205,7 +265,7 @@ __global__ __launch_bounds__(256) __attribute__((amdgpu_waves_per_eu(4))) void k
   const float Ef = PERSP ? (float)(a.cam.eye[0] - (double)br.lo[0]) : 0.f;
   const float Eg = PERSP ? (float)(a.cam.eye[BY ? 2 : 1] - (double)br.lo[BY ? 2 : 1]) : 0.f;
   const float inv_Eb = PERSP ? (float)(1.0 / Eb) : 0.f;
-  const int pitch = PERSP ? bvw.ppitch : (a.foot_nf + 3) & ~3;
+  const int pitch = PITCH > 0 ? PITCH : PERSP ? bvw.ppitch : (a.foot_nf + 3) & ~3;
   const int NG = min(PERSP ? bvw.png : a.foot_ng, chiG + 2 - cloG);
   const int sB = BY ? br.sy : br.sz, sG = BY ? br.sz : br.sy;
   gfloat* gbase = (gfloat*)br.base;
@@ -287,7 +347,7 @@ __global__ __launch_bounds__(256) __attribute__((amdgpu_waves_per_eu(4))) void k
   const int V0 = up ? Lbeg : Lbeg + 1;
   const float fclo = (float)cloB, fchi = (float)chiB;
   float Cr = r.carried.x, Cg = r.carried.y, Cb = r.carried.z, T = r.carried.w, mx = 0.f;
-  int j = 0;
+  float j = 0.f;
   bool done = r.cnt == 0;
 
   Window w0 = window(V0), w1 = window(V0 + vstep), w2;
@@ -304,8 +364,8 @@ __global__ __launch_bounds__(256) __attribute__((amdgpu_waves_per_eu(4))) void k
     const int c = up ? Lbeg + k : Lbeg - k;
     const Window& wl = up ? w0 : w1;
     const Window& wu = up ? w1 : w0;
-    sample_layer<MIP, BY>(a, br, r, s_tf, s_ring, slot, pitch, c, wl, wu, up ? s0 : s0 ^ 1, up ? s0 ^ 1 : s0,
-                          fclo, fchi, j, done, Cr, Cg, Cb, T, mx);
+    sample_layer<MIP, BY, MASK>(a, br, r, s_tf, s_mask, s_ring, slot, pitch, c, wl, wu, up ? s0 : s0 ^ 1,
+                                up ? s0 ^ 1 : s0, fclo, fchi, j, done, Cr, Cg, Cb, T, mx);
     if (__all(done)) break;
     if (k + 1 < nlay) {
       rstore(s_ring + s0 * slot);  // V_{k+2} replaces V_k (same wavefront: LDS order holds)
@@ -348,7 +408,9 @@ __global__ __launch_bounds__(512) __attribute__((amdgpu_waves_per_eu(4))) void k
   block_cell(a, bvw, t, wave, ci, cj);
   const FootRuns fr = foot_runs(a, bvw, ci, cj, lane);
   if (fr.n > 64 && lane == 0) a.ovf_tiles[atomicAdd(a.ovf_count, 1u)] = tile * 8 + wave;
-  const CellRay r = cell_ray<false>(a, bvw, br, fr, lane);
+  int u, v;
+  foot_pixel(fr, lane, u, v);
+  const CellRay r = cell_ray<false>(a, bvw, br, lane < fr.n ? u : -1, v);
 
   const float pb = BY ? r.py : r.pz, sb = BY ? r.sy : r.sz;
   const int cloB = BY ? br.clo[1] : br.clo[2], chiB = BY ? br.chi[1] : br.chi[2];
@@ -425,7 +487,7 @@ __global__ __launch_bounds__(512) __attribute__((amdgpu_waves_per_eu(4))) void k
   const int V0 = up ? Lbeg : Lbeg + 1;
   const float fclo = (float)cloB, fchi = (float)chiB;
   float Cr = r.carried.x, Cg = r.carried.y, Cb = r.carried.z, T = r.carried.w, mx = 0.f;
-  int j = 0;
+  float j = 0.f;
   bool done = r.cnt == 0;
 
   Window w0 = window(V0), w1 = window(V0 + vstep), w2;
@@ -443,7 +505,7 @@ __global__ __launch_bounds__(512) __attribute__((amdgpu_waves_per_eu(4))) void k
     const int c = up ? Lbeg + k : Lbeg - k;
     const Window& wl = up ? w0 : w1;
     const Window& wu = up ? w1 : w0;
-    sample_layer<MIP, BY>(a, br, r, s_tf, s_ring, slot, pitch, c, wl, wu, up ? s0 : s0 ^ 1, up ? s0 ^ 1 : s0,
+    sample_layer<MIP, BY, false>(a, br, r, s_tf, nullptr, s_ring, slot, pitch, c, wl, wu, up ? s0 : s0 ^ 1, up ? s0 ^ 1 : s0,
                           fclo, fchi, j, done, Cr, Cg, Cb, T, mx);
     // vote of the block (slot k & 1 is cleared for the next layer's vote
     // between the two barriers)
@@ -474,14 +536,14 @@ size_t block_lds_bytes(const MarchArgs& a) {
 }
 
 size_t cells_lds_bytes(const MarchArgs& a, int wpb) {
-  return sizeof(float4) * (size_t)a.M + sizeof(float) * 2 * (size_t)wpb * (size_t)a.ring_slot;
+  return sizeof(float4) * (size_t)cells_table_rows(a) + sizeof(float) * 2 * (size_t)wpb * (size_t)a.ring_slot;
 }
 
 // checks shared by both launches: a window's rows and loads as the kernels
 // assume them
 static bool cells_args_ok(const MarchArgs& a, int waves_per_window) {
   const int64_t pitch = (a.foot_nf + 3) & ~3;
-  if (a.mc != 0 || a.mask || !a.foot || a.ring_slot <= 0 || (a.ring_slot & 3) != 0 ||
+  if (a.mc != 0 || !a.foot || a.ring_slot <= 0 || (a.ring_slot & 3) != 0 ||
       (a.slab_axis != 1 && a.slab_axis != 2))
     return false;
   // perspective: windows sized per brick, each checked against the slot and
@@ -496,7 +558,7 @@ static bool cells_args_ok(const MarchArgs& a, int waves_per_window) {
 hipError_t launch_march_block(const MarchArgs& a, hipStream_t s) {
   const int nw = a.blk_f * a.blk_g;
   if (a.ntiles <= 0) return hipSuccess;
-  if (a.blk_f < 1 || a.blk_g < 1 || nw > kBlkMaxWaves || !cells_args_ok(a, nw)) return hipErrorInvalidValue;
+  if (a.mask || a.blk_f < 1 || a.blk_g < 1 || nw > kBlkMaxWaves || !cells_args_ok(a, nw)) return hipErrorInvalidValue;
   const int grid = ((a.ntiles + 7) / 8) * 8;
   const dim3 g(grid), b(64 * nw);
   const size_t lds = block_lds_bytes(a);
@@ -517,17 +579,27 @@ hipError_t launch_march_cells(const MarchArgs& a, int wpb, hipStream_t s) {
   const dim3 g(grid), b(64 * wpb);
   const size_t lds = std::max(cells_lds_bytes(a, wpb), (size_t)std::max(0, a.lds_floor));
   const bool by = a.slab_axis == 1;
-  if (a.cam.persp) {
-    if (a.mip && by) hipLaunchKernelGGL((k_march_cells<true, true, true>), g, b, lds, s, a);
-    else if (a.mip) hipLaunchKernelGGL((k_march_cells<true, false, true>), g, b, lds, s, a);
-    else if (by) hipLaunchKernelGGL((k_march_cells<false, true, true>), g, b, lds, s, a);
-    else hipLaunchKernelGGL((k_march_cells<false, false, true>), g, b, lds, s, a);
-  } else {
-    if (a.mip && by) hipLaunchKernelGGL((k_march_cells<true, true, false>), g, b, lds, s, a);
-    else if (a.mip) hipLaunchKernelGGL((k_march_cells<true, false, false>), g, b, lds, s, a);
-    else if (by) hipLaunchKernelGGL((k_march_cells<false, true, false>), g, b, lds, s, a);
-    else hipLaunchKernelGGL((k_march_cells<false, false, false>), g, b, lds, s, a);
-  }
+  auto go = [&](auto kernel) { hipLaunchKernelGGL(kernel, g, b, lds, s, a); };
+  // window rows of 32 or 64 floats (parallel unmasked views) are known to the
+  // compiler, which then folds a row into the corner reads' offsets
+  auto pick = [&](auto persp, auto mask, auto pitch) {
+    constexpr bool P = decltype(persp)::value, K = decltype(mask)::value;
+    constexpr int N = decltype(pitch)::value;
+    if (a.mip && by) go(k_march_cells<true, true, P, K, N>);
+    else if (a.mip) go(k_march_cells<true, false, P, K, N>);
+    else if (by) go(k_march_cells<false, true, P, K, N>);
+    else go(k_march_cells<false, false, P, K, N>);
+  };
+  const std::true_type yes;
+  const std::false_type no;
+  const std::integral_constant<int, 0> any;
+  const int row = (a.foot_nf + 3) & ~3;
+  if (a.cam.persp && a.mask) pick(yes, yes, any);
+  else if (a.cam.persp) pick(yes, no, any);
+  else if (a.mask) pick(no, yes, any);
+  else if (row == 32) pick(no, no, std::integral_constant<int, 32>{});
+  else if (row == 64) pick(no, no, std::integral_constant<int, 64>{});
+  else pick(no, no, any);
   return hipGetLastError();
 }
 

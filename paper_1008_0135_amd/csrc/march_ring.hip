@@ -112,7 +112,7 @@ __global__ __launch_bounds__(256) void k_march_ring(MarchArgs a, SaveArgs sa) {
   FootRuns fr;
   int tx = 0, ty = 0;
   if (foot) {
-    foot_cell(bvw, t, ci, cj);
+    foot_cell(a, bvw, t, ci, cj);
     fr = foot_runs(a, bvw, ci, cj, lane);
     // cells of more than 64 pixels: the pixels past the 64th are marched by
     // k_march_ring_ovf after this launch
@@ -750,7 +750,7 @@ __global__ __launch_bounds__(256) void k_march_ring_ovf(MarchArgs a) {
     const DevBrick br = a.bricks[bvw.brick];
     int ci, cj;
     if (a.blk_f > 0) block_cell(a, bvw, tile - bvw.tile_begin, w, ci, cj);
-    else foot_cell(bvw, tile - bvw.tile_begin, ci, cj);
+    else foot_cell(a, bvw, tile - bvw.tile_begin, ci, cj);
     const FootRuns fr = a.cam.persp ? foot_runs_persp(a, bvw, br, ci, cj, lane) : foot_runs(a, bvw, ci, cj, lane);
     gfloat* gb = (gfloat*)br.base;
     const int ys = br.sy, zs = br.sz;

@@ -155,6 +155,8 @@ __global__ __launch_bounds__(256) void k_march_skip(MarchArgs a) {
                                    dir.z != 0.f ? 1.f / dir.z : 1e9f, 0.f);
     gfloat* base = (gfloat*)br.base;
     const int ys = br.sy, zs = br.sz;
+    [[maybe_unused]] gfloat* mask = nullptr;
+    if constexpr (MASK) mask = (gfloat*)(a.mask + br.lo[a.mask_axis]);
     for (int jc = 0; __any(jc < cnt); jc += 1024) {
       unsigned long long blocks = 0;
       const int jend = min(cnt, jc + 1024);
@@ -182,6 +184,7 @@ __global__ __launch_bounds__(256) void k_march_skip(MarchArgs a) {
         // the corners of the next block are loaded while one is composited
         Cell c;
         f2u a00, a01, a10, a11;
+        [[maybe_unused]] f2u mw;
         int j = 0;
         auto load = [&]() {
           j = jc + 16 * __builtin_ctzll(m) + dl;
@@ -192,13 +195,14 @@ __global__ __launch_bounds__(256) void k_march_skip(MarchArgs a) {
           a01 = ld_pair(p + ys);
           a10 = ld_pair(p + zs);
           a11 = ld_pair(p + zs + ys);
+          if constexpr (MASK) mw = ld_pair(mask + (a.mask_axis == 2 ? c.iz : c.iy));
         };
         bool more = m != 0;
         if (more) load();
         while (more) {
           const float val = trilerp(a00.x, a00.y, a01.x, a01.y, a10.x, a10.y, a11.x, a11.y, c);
           Classified k = classify(val, a.vmin, a.inv_range, a.M, s_tf);
-          if constexpr (MASK) k.a *= channel_weight(a.mask, a.mask_axis, br.lo[a.mask_axis], c);
+          if constexpr (MASK) k.a *= channel_weight(mw.x, mw.y, a.mask_axis, c);
           if (j >= rc) k.a = 0.f;  // past the ray's last sample: adds nothing
           more = m != 0;
           if (more) load();
@@ -299,10 +303,15 @@ __global__ __launch_bounds__(256) void k_march(MarchArgs a) {
       const int cnt = (int)(k1 - k0);
       gfloat* base = (gfloat*)br.base;
       const int ys = br.sy, zs = br.sz;
-      // the corners of the next samples are loaded while these are composited
+      [[maybe_unused]] gfloat* mask = nullptr;
+      if constexpr (MASK) mask = (gfloat*)(a.mask + br.lo[a.mask_axis]);
+      // the corners (and mask weights) of the next samples are loaded while
+      // these are composited; loads return in order, so a load of its own in
+      // the middle of a sample would wait for the next corners too
       int j;
       Cell c;
       f2u a00, a01, a10, a11;
+      [[maybe_unused]] f2u mw;
       auto load = [&](int jb) {
         j = jb + dl;
         c = cell_of(sample_pos(D == 1 ? j : min(j, cnt - 1), px, py, pz, sx, sy, sz), br);
@@ -311,12 +320,13 @@ __global__ __launch_bounds__(256) void k_march(MarchArgs a) {
         a01 = ld_pair(p + ys);
         a10 = ld_pair(p + zs);
         a11 = ld_pair(p + zs + ys);
+        if constexpr (MASK) mw = ld_pair(mask + (a.mask_axis == 2 ? c.iz : c.iy));
       };
       load(0);
       for (int jb = D;; jb += D) {
         const float val = trilerp(a00.x, a00.y, a01.x, a01.y, a10.x, a10.y, a11.x, a11.y, c);
         [[maybe_unused]] float w = 1.f;
-        if constexpr (MASK) w = channel_weight(a.mask, a.mask_axis, br.lo[a.mask_axis], c);
+        if constexpr (MASK) w = channel_weight(mw.x, mw.y, a.mask_axis, c);
         const bool past = D > 1 && j >= cnt;
         const bool more = jb < cnt;
         if (more) load(jb);

@@ -241,10 +241,12 @@ __device__ __forceinline__ void foot_pixel(const FootRuns& fr, int k, int& u, in
   v = fr.vrow0 + r;
 }
 
-// Footprint cell of work item t of a brick view.
-__device__ __forceinline__ void foot_cell(const DevBrickView& bvw, int t, int& ci, int& cj) {
-  ci = bvw.cf0 + t % bvw.tiles_x;
-  cj = bvw.cg0 + t / bvw.tiles_x;
+// Footprint cell of work item t of a brick view, numbered along f or (a.cols)
+// along g first (bvw.blocks_x: cells along g).
+__device__ __forceinline__ void foot_cell(const MarchArgs& a, const DevBrickView& bvw, int t, int& ci, int& cj) {
+  const int n = a.cols ? bvw.blocks_x : bvw.tiles_x, q = t / n, r = t - q * n;
+  ci = bvw.cf0 + (a.cols ? q : r);
+  cj = bvw.cg0 + (a.cols ? r : q);
 }
 
 // Footprint cell of wavefront w of work item t when work items are blocks of

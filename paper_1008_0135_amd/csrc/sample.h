@@ -14,9 +14,12 @@ struct SamplePos {
   float x, y, z;
 };
 
-__device__ __forceinline__ SamplePos sample_pos(int j, float px, float py, float pz, float sx, float sy, float sz) {
-  const float fj = (float)j;
+__device__ __forceinline__ SamplePos sample_pos(float fj, float px, float py, float pz, float sx, float sy, float sz) {
   return SamplePos{fmaf(fj, sx, px), fmaf(fj, sy, py), fmaf(fj, sz, pz)};
+}
+
+__device__ __forceinline__ SamplePos sample_pos(int j, float px, float py, float pz, float sx, float sy, float sz) {
+  return sample_pos((float)j, px, py, pz, sx, sy, sz);
 }
 
 // Base cell (clamped to the brick's stored range) and fractions.
@@ -95,6 +98,11 @@ __device__ __forceinline__ float channel_weight(const float* mask, int axis, int
   const float w = axis == 2 ? c.wz : c.wy;
   const float m0 = mask[i], m1 = mask[i + 1];
   return fmaf(w, m1 - m0, m0);
+}
+// The same from the two weights already loaded.
+__device__ __forceinline__ float channel_weight(float m0, float m1, int axis, const Cell& c) {
+#pragma clang fp contract(off)
+  return fmaf(axis == 2 ? c.wz : c.wy, m1 - m0, m0);
 }
 
 // One front-to-back emission-absorption step: C += T a rgb, T *= (1 - a).

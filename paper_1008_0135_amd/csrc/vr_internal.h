@@ -201,7 +201,7 @@ struct DevBrickView {
   int32_t cf0;         // footprint cells: index of the first cell along f
   int64_t img_off;     // offset (in pixels) of the brick image in the image arena
   int32_t cg0;         // footprint cells: index of the first cell along g
-  int32_t blocks_x;    // blocks of footprint cells: blocks along f
+  int32_t blocks_x;    // footprint cells: cells along g; in blocks: blocks along f
   double fa0, fb0;     // footprint cells: cell coordinates (f / Tf, g / Tg) of pixel (0, 0)'s ray on the
                        // brick-local plane b = 0
   // footprint cells of a perspective view (sized per brick: rays from the eye
@@ -224,6 +224,7 @@ struct MarchArgs {
   double step;
   float tau;             // ERT threshold (ert == 0: off)
   int32_t ert;
+  float t_stop;          // the largest T with 1.f - T >= tau (negative: none)
   float vmin, inv_range; // normalisation window (inv_range = 0 when vmax == vmin)
   int32_t M;             // table entries
   int32_t nbv;           // rendered bricks in this launch
@@ -257,6 +258,7 @@ struct MarchArgs {
                          // kRingRegLoads loads per lane per layer)
   int32_t mask_axis;     // axis of the channel mask (2, or 1 in the permuted copy)
   const float* mask;     // channel weights along mask_axis (global indices), or null
+  int32_t mask_n;        // their number
   int32_t tile_order;    // ring march: tiles of a brick numbered along rows (0), down columns (1),
                          // or in blocks of tile_bw x tile_bh tiles (2)
   int32_t tile_bw, tile_bh;
@@ -268,6 +270,7 @@ struct MarchArgs {
   // margin, foot_nf x foot_ng floats
   int32_t foot;
   int32_t foot_nf, foot_ng;
+  int32_t cols;          // cells numbered along g first, their rays spread over the LDS banks
   int32_t foot_pad;
   double foot_Tf, foot_Tg;
   double fa_u, fa_v, fb_u, fb_v;  // cell coordinates per pixel step along u and v
@@ -340,6 +343,11 @@ struct BatchReq {
 // descriptor table of at most kNoAllocMaxReq requests, then the work counter.
 // register-staged ring march: 16-byte loads per lane for one voxel layer's window
 constexpr int kRingRegLoads = 8;
+// channel weights the cells march keeps in LDS beside the table (longer masks
+// would cost wavefronts: three-slot ring march)
+constexpr int kCellsMaskMax = 4096;
+// LDS of a cells workgroup before its windows, in table rows of 16 bytes
+constexpr int cells_table_rows(const MarchArgs& a) { return a.M + (a.mask ? (a.mask_n + 3) / 4 : 0); }
 constexpr int kNoAllocMaxReq = 512;
 constexpr size_t kNoAllocBytes = sizeof(BatchReq) * kNoAllocMaxReq + 256;
 constexpr int kMaxDevices = 64;
