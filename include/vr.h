@@ -387,9 +387,8 @@ typedef struct {
 } vr_request;
 
 /*
- * Render n requests in one persistent launch: (request, pixel tile) work
- * items, ordered by estimated cost, are pulled from an atomic counter by a
- * grid sized to the device.  The launch sequence is captured once into a HIP
+ * Render n requests in one launch: (request, pixel tile) work items, ordered
+ * by estimated cost, longest first.  The launch sequence is captured once into a HIP
  * graph held in *cache (created when *cache is NULL) and replayed while the
  * request shapes (count, volumes, image sizes, table sizes) match; otherwise
  * it is rebuilt.  Table values, views, windows and output pointers may change
@@ -403,9 +402,8 @@ int vr_batch_destroy(vr_batch *b);
 /*
  * Allocation-free variant of vr_render_batch, for callers that cannot
  * allocate device memory (code under HIP graph capture, tight serving loops,
- * harnesses that forbid allocation).  The same persistent kernel and the same
- * images, launched directly (no graph); its descriptor table and work counter
- * live in a fixed device array of the library (at most 512 requests, about 160 KiB
+ * harnesses that forbid allocation).  The same kernel and the same images,
+ * launched directly (no graph); its descriptor table lives in a fixed device array of the library (at most 512 requests, about 160 KiB
  * per device, held by each device the library runs on until the process
  * ends); the descriptors travel through pinned staging made by vr_create.
  * The call allocates nothing.  Windows must be given, or the volume's range
@@ -422,7 +420,7 @@ int vr_render_batch_noalloc(vr_ctx *ctx, const vr_request *reqs, int32_t n, cons
 /* ------------------------------------------------------------------ autotuning */
 typedef struct {
   int32_t tile;          /* chosen wavefront tile edge (pixels) */
-  int32_t waves_per_cu;  /* chosen persistent-grid occupancy (batched path) */
+  int32_t waves_per_cu;  /* chosen occupancy (batched path) */
   double ms;             /* best measured time */
   double ms_default;     /* time with the defaults */
   int32_t lds_budget;    /* chosen LDS floats per slab box (LDS-staged march) */

@@ -1,6 +1,5 @@
 // batch.cpp -- vr_render_batch: descriptor table, longest-first work order,
-// HIP-graph capture of [descriptor copy -> counter reset -> persistent
-// kernel] on a private stream, and replay on the caller's stream.
+// HIP-graph capture of [descriptor copy -> kernel] on a private stream, and replay on the caller's stream.
 #include <hip/hip_runtime.h>
 
 #include <algorithm>
@@ -20,11 +19,10 @@ struct vr_batch {
   std::vector<int32_t> W, H, M;
   double step = 0.0;
   float tau = 0.f;
-  int32_t blocks = 0;
+  int32_t waves_per_cu = 0;
   // device and pinned host descriptor tables
   vr::BatchReq* d_reqs = nullptr;
   vr::BatchReq* h_reqs = nullptr;
-  unsigned int* d_counter = nullptr;
   int32_t total_items = 0, max_M = 0;
   hipStream_t cap = nullptr;
   hipGraph_t graph = nullptr;
@@ -41,27 +39,28 @@ static void batch_free(vr_batch* b) {
   if (b->graph) (void)hipGraphDestroy(b->graph);
   if (b->cap) (void)hipStreamDestroy(b->cap);
   if (b->d_reqs) (void)hipFree(b->d_reqs);
-  if (b->d_counter) (void)hipFree(b->d_counter);
   if (b->h_reqs) (void)hipHostFree(b->h_reqs);
   if (b->launched) (void)hipEventDestroy(b->launched);
   b->exec = nullptr;
   b->graph = nullptr;
   b->cap = nullptr;
   b->d_reqs = nullptr;
-  b->d_counter = nullptr;
   b->h_reqs = nullptr;
   b->launched = nullptr;
   b->pending = false;
 }
 
-int batch_blocks(vr_ctx* ctx) {
-  int cus = 256;
-  hipDeviceProp_t prop;
-  if (hipGetDeviceProperties(&prop, ctx->device) == hipSuccess && prop.multiProcessorCount > 0)
-    cus = prop.multiProcessorCount;
-  // 64 requests: 2.49 ms with 8 wavefronts per compute unit, 1.81 with 16, 1.89 with 24
-  const int wpc = ctx->tune_waves_per_cu > 0 ? ctx->tune_waves_per_cu : 16;
-  return std::max(1, cus * wpc / 4);  // 4 wavefronts per block
+// Lanes per ray of a request in a batch of `tiles` tiles, by its shape alone (a
+// view's own extent may change from replay to replay).  Four lanes touch fewer
+// lines per sample where rays are close, sixteen make a ray's chain of loads
+// shorter: 64 requests 1.33 ms with the line at 1.3 voxels between rays or
+// beyond, 1.40 at 1.0, 2.19 with sixteen lanes for all; 30 requests of 100^3 to
+// 256^3 on 60^2 to 120^2 pixels 320 us with four, 209 with sixteen; four
+// requests of 50 tiles each 39 and 35.
+static int32_t batch_lanes(const vr_volume* v, int32_t W, int64_t tiles) {
+  double diag = 0.0;
+  for (int i = 0; i < 3; i++) diag += (double)(v->n[i] - 1) * (double)(v->n[i] - 1);
+  return std::sqrt(diag) / W < 1.5 && tiles >= 512 ? 4 : 16;
 }
 
 // Estimated samples per pixel of a request: box volume / (pixel area x step), per pixel.
@@ -147,6 +146,11 @@ int plan_batch(vr_ctx* ctx, const vr_request* reqs, int32_t n, const vr_params* 
   std::vector<double> cost((size_t)n);
   for (int32_t i = 0; i < n; i++) cost[i] = 64.0 * pixel_cost(reqs[i].vol, reqs[i].view, p->step);
   std::stable_sort(order.begin(), order.end(), [&](int32_t x, int32_t y) { return cost[x] > cost[y]; });
+  int64_t ntiles = 0;
+  for (int32_t i = 0; i < n; i++) {
+    const int32_t th = 64 / tw[i];
+    ntiles += (int64_t)((reqs[i].view.W + tw[i] - 1) / tw[i]) * ((reqs[i].view.H + th - 1) / th);
+  }
   desc.assign((size_t)n, BatchReq());
   items = 0;
   maxM = 2;
@@ -170,21 +174,22 @@ int plan_batch(vr_ctx* ctx, const vr_request* reqs, int32_t n, const vr_params* 
     const int32_t th = 64 / tw[i];
     d.ntiles = d.tiles_x * ((r.view.H + th - 1) / th);
     d.item_begin = items;
-    items += d.ntiles;
+    d.lanes = batch_lanes(r.vol, r.view.W, ntiles);
+    items += d.lanes == 16 ? 4 * d.ntiles : d.ntiles;
     maxM = std::max(maxM, r.m);
   }
   return VR_OK;
 }
 
 int render_batch(vr_ctx* ctx, const vr_request* reqs, int32_t n, const vr_params* p, vr_batch** cache,
-                 hipStream_t s, int32_t force_blocks, const int32_t* tiles) {
+                 hipStream_t s, int32_t force_wpc, const int32_t* tiles) {
   VR_TRY(check_batch(ctx, reqs, n, p));
   vr_batch* b = *cache;
   if (b && b->ctx != ctx) return fail(VR_EINVAL, "batch cache belongs to another context");
-  const int32_t blocks = force_blocks > 0 ? force_blocks : batch_blocks(ctx);
+  const int32_t wpc = force_wpc > 0 ? force_wpc : ctx->tune_waves_per_cu;
   // shape key
   bool match = b && (int32_t)b->vols.size() == n && b->step == p->step && b->tau == (float)(p->tau >= 1.0 ? 2.0 : p->tau) &&
-               b->blocks == blocks;
+               b->waves_per_cu == wpc;
   for (int32_t i = 0; match && i < n; i++)
     match = b->vols[i] == reqs[i].vol && b->W[i] == reqs[i].view.W && b->H[i] == reqs[i].view.H && b->M[i] == reqs[i].m;
   std::vector<BatchReq> desc;
@@ -213,11 +218,11 @@ int render_batch(vr_ctx* ctx, const vr_request* reqs, int32_t n, const vr_params
     }
     b->step = p->step;
     b->tau = (float)(p->tau >= 1.0 ? 2.0 : p->tau);
-    b->blocks = blocks;
+    b->waves_per_cu = wpc;
     b->total_items = items;
     b->max_M = maxM;
     const size_t bytes = sizeof(BatchReq) * (size_t)std::max(n, 1);
-    if (dev_malloc(&b->d_reqs, bytes) != hipSuccess || dev_malloc(&b->d_counter, 256) != hipSuccess ||
+    if (dev_malloc(&b->d_reqs, bytes) != hipSuccess ||
         hipHostMalloc(&b->h_reqs, bytes, hipHostMallocDefault) != hipSuccess) {
       (void)hipGetLastError();
       batch_free(b);
@@ -229,15 +234,14 @@ int render_batch(vr_ctx* ctx, const vr_request* reqs, int32_t n, const vr_params
     BatchArgs a;
     std::memset(&a, 0, sizeof a);
     a.reqs = b->d_reqs;
-    a.counter = b->d_counter;
     a.nreq = n;
     a.total_items = items;
-    a.max_M = maxM;
+      a.max_M = maxM;
     a.step = p->step;
     a.tau = b->tau;
     VR_HIP(hipStreamBeginCapture(b->cap, hipStreamCaptureModeThreadLocal));
     hipError_t e1 = hipMemcpyAsync(b->d_reqs, b->h_reqs, sizeof(BatchReq) * (size_t)n, hipMemcpyHostToDevice, b->cap);
-    hipError_t e2 = e1 == hipSuccess ? launch_batch(a, blocks, b->cap) : e1;
+    hipError_t e2 = e1 == hipSuccess ? launch_batch(a, wpc, b->cap) : e1;
     hipError_t e3 = hipStreamEndCapture(b->cap, &b->graph);
     if (e1 != hipSuccess || e2 != hipSuccess || e3 != hipSuccess) {
       (void)hipGetLastError();
@@ -302,14 +306,12 @@ int vr_render_batch_noalloc(vr_ctx* ctx, const vr_request* reqs, int32_t n, cons
   BatchArgs a;
   std::memset(&a, 0, sizeof a);
   a.reqs = reinterpret_cast<const BatchReq*>(dev);
-  a.counter = reinterpret_cast<unsigned int*>(dev + sizeof(BatchReq) * (size_t)kNoAllocMaxReq);
   a.nreq = n;
   a.total_items = items;
   a.max_M = maxM;
   a.step = p->step;
   a.tau = (float)(p->tau >= 1.0 ? 2.0 : p->tau);
-  // the work counter is cleared by a kernel of the launch sequence (no memset)
-  VR_HIP(launch_batch(a, batch_blocks(ctx), s));
+  VR_HIP(launch_batch(a, ctx->tune_waves_per_cu, s));
   return ctx_end(ctx, s);
 }
 

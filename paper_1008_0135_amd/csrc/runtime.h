@@ -138,7 +138,7 @@ struct vr_ctx {
     double ms;
   };
   std::vector<TuneEntry> tune;
-  int32_t tune_waves_per_cu = 0;  // persistent-grid occupancy of the batched path (0 = default 8)
+  int32_t tune_waves_per_cu = 0;  // batched path: wavefronts per compute unit at most (0 = as many as fit)
   // allocation-free batched path: pinned staging for its descriptor table
   // (made at creation) and the event of the last copy out of it
   void* na_host = nullptr;
@@ -227,13 +227,12 @@ void tuned_shape(const vr_ctx* ctx, const vr_volume* vol, int32_t W, int32_t H, 
 std::string tune_key(const vr_volume* vol, int32_t W, int32_t H, int32_t mode);
 void tune_load(vr_ctx* ctx);
 int render_batch(vr_ctx* ctx, const vr_request* reqs, int32_t n, const vr_params* p, vr_batch** cache, hipStream_t s,
-                 int32_t force_blocks, const int32_t* tiles);
+                 int32_t force_wpc, const int32_t* tiles);
 int check_batch(vr_ctx* ctx, const vr_request* reqs, int32_t n, const vr_params* p);
 int plan_batch(vr_ctx* ctx, const vr_request* reqs, int32_t n, const vr_params* p, const int32_t* tiles,
                bool may_reduce, hipStream_t s, std::vector<BatchReq>& desc, int32_t& items, int32_t& maxM);
 std::string batch_key(const vr_volume* v, int32_t W, int32_t H);
 int32_t batch_tile(const vr_ctx* ctx, const vr_volume* v, int32_t W, int32_t H);
-int batch_blocks(vr_ctx* ctx);
 // Allocation-free batched path: look up the device's scratch address once
 // (device current; called by vr_create), and return it (null before init).
 int noalloc_init(int device);

@@ -177,10 +177,6 @@ int vr_autotune_batch(vr_ctx* ctx, const vr_request* reqs, int32_t n, const vr_p
   VR_TRY(check_batch(ctx, reqs, n, p));
   DeviceGuard g(ctx->device);
   hipStream_t s = (hipStream_t)stream;
-  int cus = 256;
-  hipDeviceProp_t prop;
-  if (hipGetDeviceProperties(&prop, ctx->device) == hipSuccess && prop.multiProcessorCount > 0)
-    cus = prop.multiProcessorCount;
   // 1. tile shape per size class: the requests of one class rendered as a
   //    batch of their own with each candidate tile (same grid as the default)
   std::vector<std::string> keys((size_t)n);
@@ -223,7 +219,7 @@ int vr_autotune_batch(vr_ctx* ctx, const vr_request* reqs, int32_t n, const vr_p
     ctx->tune.push_back(vr_ctx::TuneEntry{key, pick, 0, 1, best});
     ntile_wins[pick == 4 ? 0 : pick == 8 ? 1 : pick == 16 ? 2 : 3]++;
   }
-  // 2. persistent-grid occupancy for the whole batch with the tuned tiles
+  // 2. occupancy for the whole batch with the tuned tiles
   const int32_t cands[] = {8, 2, 4, 16, 32};
   double best = INFINITY, dflt = INFINITY;
   int32_t pick = 8;
@@ -231,7 +227,7 @@ int vr_autotune_batch(vr_ctx* ctx, const vr_request* reqs, int32_t n, const vr_p
     double ms = 0.0;
     VR_TRY(time_ms(s, 3, [&]() {
       VR_TRY(ctx_begin(ctx, s));
-      VR_TRY(render_batch(ctx, reqs, n, p, cache, s, std::max(1, cus * wpc / 4), nullptr));
+      VR_TRY(render_batch(ctx, reqs, n, p, cache, s, wpc, nullptr));
       return ctx_end(ctx, s);
     }, ms));
     if (wpc == 8) dflt = ms;

@@ -336,11 +336,12 @@ struct BatchReq {
   float4* out;
   int32_t M, tiles_x, ntiles, item_begin;
   int32_t tile_shift;    // tile width 2^tile_shift pixels (4, 8, 16 or 32), height 64 / width
-  int32_t pad_[3];
+  int32_t lanes;         // lanes per ray: 4 (an item is a tile) or 16 (a quarter of one)
+  int32_t pad_[2];
 };
 
 // Allocation-free batched entry point: its device scratch holds the
-// descriptor table of at most kNoAllocMaxReq requests, then the work counter.
+// descriptor table of at most kNoAllocMaxReq requests.
 // register-staged ring march: 16-byte loads per lane for one voxel layer's window
 constexpr int kRingRegLoads = 8;
 // channel weights the cells march keeps in LDS beside the table (longer masks
@@ -349,12 +350,11 @@ constexpr int kCellsMaskMax = 4096;
 // LDS of a cells workgroup before its windows, in table rows of 16 bytes
 constexpr int cells_table_rows(const MarchArgs& a) { return a.M + (a.mask ? (a.mask_n + 3) / 4 : 0); }
 constexpr int kNoAllocMaxReq = 512;
-constexpr size_t kNoAllocBytes = sizeof(BatchReq) * kNoAllocMaxReq + 256;
+constexpr size_t kNoAllocBytes = sizeof(BatchReq) * kNoAllocMaxReq;
 constexpr int kMaxDevices = 64;
 
 struct BatchArgs {
   const BatchReq* reqs;
-  unsigned int* counter;  // next work item
   int32_t nreq, total_items, max_M, pad;
   double step;
   float tau;
@@ -407,7 +407,7 @@ int bwd_blocks(const MarchArgs& a);
 int tf_reduce_slices();
 hipError_t launch_tf_reduce(const double* part, int nblocks, int n, float* grad_tf, double* slices, hipStream_t s);
 hipError_t launch_fill(float* p, int64_t n, float v, hipStream_t s);
-hipError_t launch_batch(const BatchArgs& a, int blocks, hipStream_t s);
+hipError_t launch_batch(const BatchArgs& a, int waves_per_cu, hipStream_t s);
 hipError_t launch_copy_box(const float* src, const int64_t sn[3], const int64_t so[3], float* dst,
                            const int64_t dn[3], hipStream_t s);
 // dst[x][z][y] = src[z][y][x] for a volume of dims n (dst holds n[0] n[1] n[2] floats)
