@@ -32,9 +32,13 @@ constexpr int32_t kLdsPerCu = 160 * 1024;
 // perspective views with rays closer than this many voxels (on the plane
 // through the box centre): cells hold 20 rays on average there (their sizes
 // follow the brick's densest point) and gathers are as fast (two views of
-// 1024 x 1024 x 768 at 1.6 voxels: 8.4 ms against 8.8); at 3.2 voxels the
-// cells take 11.9 ms per view of the 24 GiB cube, gathers 14.7
+// 1024 x 1024 x 768 at 1.6 voxels: 8.0 ms against 8.8)
 constexpr double kPerspCellPitch = 1.8;
+// further apart: samples per second of the cells, and the chains of cells a
+// compute unit's wavefronts take one after another (near bricks' wide windows
+// leave room for few).  The 24 GiB cube at 3.2 voxels: 11.7 ms per view, 14.7 by
+// gathers; 1000^3 at 1.9 and 3.5 voxels: 5.1 and 3.0 ms, 4.0 and 2.0 by gathers
+constexpr double kPerspCellRate = 106e9, kPerspChains = 5.0;
 // whole-ray termination, views whose gathers are estimated below this: every
 // ray through all its bricks in one launch (0.3 ms per 200^2 view of 64 bricks
 // against 1.6 ms in 10 launches); above, launches per front of bricks, in
@@ -44,17 +48,26 @@ constexpr double kThruBelow = 0.4e-3;
 }  // namespace
 
 // Estimated times of a view (seconds) by the cell march with the shape fs
-// (infinite when null) and by gathers, for boxes marched side by side.
-//   gathers: 182 G samples/s with rays 1.2 voxels apart or closer (the cache
-//     lookups of four row pairs per sample bind), falling as 1 / pitch (60 at
-//     4.2 voxels, 86 measured on the 24 GiB cube at 3.2);
-//   cells: the larger of 300 G samples/s (vector instructions), 2.3 times the
-//     boxes' bytes at 7.2 TB/s (window traffic), and the chain of one wavefront
-//     (1.3 us a layer, more with the wide windows of sparse rays), which no
-//     number of wavefronts shortens.  Rays less than 0.75 voxels apart, where
-//     the narrowest cells hold more than 64 of them, are left to the gathers
-//     (300^3 at 1024^2, 0.5 voxels: 6.0 ms by cells, 2.1 by gathers).
-MarchTimes march_times(const Camera& cam, const std::vector<Box>& boxes, double step, const FootShape* fs) {
+// (infinite when null) and by gathers, for boxes marched side by side (and
+// `views` views on streams of their own).
+//   gathers: 230 G samples/s with rays less than 1.1 voxels apart (4 lanes
+//     per ray), else 182 falling with the distance (cache lookups of four row pairs
+//     per sample, then lines used by fewer and fewer rays): 140 to 165 measured
+//     at 1.7 voxels, 110 to 150 at 2.4, 75 to 150 at 2.9, 65 to 95 at 4.6;
+//   cells: the larger of 300 G samples/s (vector instructions and LDS), 2.3
+//     times the boxes' bytes at 7.2 TB/s (window traffic), and the chain of one
+//     wavefront (1.0 us a layer with rays a voxel apart, 1.3 at three, more with
+//     the wide windows beyond), which no number of wavefronts shortens; slower where windows leave room
+//     for fewer than 12 wavefronts on a compute unit (an 800^3 view at 4.6
+//     voxels: 2 wavefronts 2.3 ms, 10 0.8, gathers 0.5 to 0.8).  Rays less than
+//     0.75 voxels apart, where the narrowest cells hold more than 64 of them,
+//     are left to the gathers (300^3 at 800^2, 0.65 voxels: 1.1 ms by cells,
+//     0.49 by gathers).
+int32_t gather_lanes(const Camera& cam) {
+  return cam.S / (double)cam.W < 1.1 && (int64_t)cam.W * cam.H >= ((int64_t)1 << 16) ? 4 : 16;
+}
+
+MarchTimes march_times(const Camera& cam, const std::vector<Box>& boxes, double step, const FootShape* fs, int views) {
   MarchTimes t;
   t.pitch = cam.S / (double)cam.W;
   double samples = 0.0, bytes = 0.0;
@@ -69,15 +82,17 @@ MarchTimes march_times(const Camera& cam, const std::vector<Box>& boxes, double 
     bytes += 4.0 * vol;
     if (fs) layers = std::max(layers, b.hi[fs->axis] - b.lo[fs->axis]);
   }
-  t.gather = 20e-6 + samples * std::max(1.0, t.pitch / 1.2) / 182e9;
+  t.samples = samples;
+  t.gather = 20e-6 + samples * std::pow(std::max(1.0, t.pitch / 1.2), 0.75) / (gather_lanes(cam) == 4 ? 230e9 : 182e9);
   if (!fs || t.pitch < 0.75) return t;
-  const double chain = (double)layers * 1.3e-6 * (1.0 + std::max(0.0, t.pitch - 4.0) / 4.0);
-  t.cells = std::max(std::max(samples / 300e9, 2.3 * bytes / 7.2e12), chain);
+  t.chain = (double)layers * (0.9e-6 + 0.13e-6 * t.pitch) * (1.0 + std::max(0.0, t.pitch - 4.0) / 4.0);
+  t.cells = std::max(std::max(samples / 300e9, 2.3 * bytes / 7.2e12), t.chain / (double)std::max(1, views));
+  if (fs->waves > 0) t.cells *= std::max(1.0, 12.0 / (double)fs->waves);
   return t;
 }
 
 bool pick_foot(const Camera& cam, const int64_t n[3], int32_t M, bool plain, bool reg_on, int32_t nslots,
-               double rays, int32_t pad, int32_t kmax, FootShape& fs, int32_t max_px) {
+               double rays, int32_t pad, int32_t kmax, FootShape& fs, int32_t max_px, int32_t axis) {
   // register-staged cells: a lane's offset inside a window's rows (at most
   // kRingRegLoads instructions of up to 16 rows) must stay below 4 GiB
   const int64_t row_stride = std::max(n[0], n[0] * n[1]);
@@ -85,7 +100,52 @@ bool pick_foot(const Camera& cam, const int64_t n[3], int32_t M, bool plain, boo
   const bool two = rays > 64.0;  // two pixels per lane: half the wavefronts, twice the window loads
   const int32_t rw = two ? kRingRegWaves / 2 : kRingRegWaves;
   return choose_foot(cam, kRingCap, M, kRingMaxWaves, reg ? rw : kRingWantWaves, rays, plain ? nslots : 3, fs, pad,
-                     kmax, reg ? rw : 0, two ? 2 * kRingRegLoads : kRingRegLoads, max_px);
+                     kmax, reg ? rw : 0, two ? 2 * kRingRegLoads : kRingRegLoads, max_px, axis);
+}
+
+void foot_args(const vr_ctx* ctx, const FootShape& fs, MarchArgs& a, int& wpb) {
+  a.foot = 1;
+  a.slab_axis = fs.axis;
+  a.ring_slot = fs.slot;
+  a.ring_nslots = fs.nslots;
+  a.ring_reg = fs.reg;
+  wpb = fs.reg && ctx->cells_wpb > 0 ? ctx->cells_wpb : fs.wpb;
+  // The wavefronts of a workgroup hold its LDS until the last is done, and
+  // cells side by side along g (a few rows wide) cross a brick in about the
+  // same number of layers, along f (28 or 60 voxels) they do not: numbered
+  // along g, marches bound by their own work are 5 to 20 % faster (two
+  // views of eight 512^3 bricks 2.19 -> 1.90 ms, six bricks 1.47 -> 1.38).
+  // Along f neighbours share a line of every window row, which counts where
+  // traffic binds: cells of many rows, most of them no neighbour's (rays 3
+  // voxels apart: 2 to 9 % faster along f).
+  a.cols = fs.reg && fs.blk_f == 0 && fs.Tg < 16.0 && fs.ng >= 1.4 * fs.Tg;
+  if (fs.reg && ctx->cells_waves > 0) {
+    // at most cells_waves wavefronts per compute unit: reserve LDS so that
+    // one workgroup more would not fit (more wavefronts ran slower: their
+    // windows crowd each other out of the caches)
+    const int32_t nwg = std::max(1, ctx->cells_waves / wpb);
+    a.lds_floor = kLdsPerCu / (nwg + 1) + 1024;
+  }
+  a.foot_nf = fs.nf;
+  a.foot_ng = fs.ng;
+  a.foot_Tf = fs.Tf;
+  a.foot_Tg = fs.Tg;
+  a.fa_u = fs.fa_u;
+  a.fa_v = fs.fa_v;
+  a.fb_u = fs.fb_u;
+  a.fb_v = fs.fb_v;
+}
+
+int32_t foot_brick(const Camera& cam, const FootShape& fs, const Box& box, DevBrickView& b) {
+  int32_t ncf, ncg;
+  foot_cells(cam, fs, box, b.cf0, b.cg0, ncf, ncg, b.fa0, b.fb0);
+  b.tiles_x = ncf;
+  if (fs.blk_f > 0) {
+    b.blocks_x = (ncf + fs.blk_f - 1) / fs.blk_f;
+    return b.blocks_x * ((ncg + fs.blk_g - 1) / fs.blk_g);
+  }
+  b.blocks_x = ncg;  // cells along g
+  return ncf * ncg;
 }
 
 // Plan one view of a bricked volume: rectangles, culling (empty rectangle or
@@ -216,13 +276,14 @@ int render_forward(vr_ctx* ctx, vr_volume* vol, const vr_view* views, int32_t nv
   }
   // work items of a view marched by gathers: 64 / D pixels each (8 x 8 with
   // macrocell skipping)
-  auto gather_tiles = [](ViewPlan& vp, int32_t first, int32_t last, int32_t w, int32_t h) {
+  // tiles of e x e pixels, numbered by blocks of 2 x 2
+  auto gather_tiles = [](ViewPlan& vp, int32_t first, int32_t last, int32_t e) {
     int32_t t = 0;
     for (int32_t i = first; i < last; i++) {
       DevBrickView& b = vp.bv[i];
-      b.tiles_x = (b.w + w - 1) / w;
+      b.tiles_x = (b.w + 2 * e - 1) / (2 * e);
       b.tile_begin = t;
-      t += b.tiles_x * ((b.h + h - 1) / h);
+      t += 4 * b.tiles_x * ((b.h + 2 * e - 1) / (2 * e));
     }
     return t;
   };
@@ -231,9 +292,9 @@ int render_forward(vr_ctx* ctx, vr_volume* vol, const vr_view* views, int32_t nv
     const int32_t e = vp.skip ? 8 : depth == 16 ? 2 : 4;
     if (global && !vp.thru)
       for (size_t w = 0; w + 1 < vp.wave_begin.size(); w++)
-        vp.wave_tiles[w] = gather_tiles(vp, vp.wave_begin[w], vp.wave_begin[w + 1], e, e);
-    else if (vp.thru) vp.ntiles = ((W + e - 1) / e) * ((H + e - 1) / e);
-    else vp.ntiles = gather_tiles(vp, 0, (int32_t)vp.bv.size(), e, e);
+        vp.wave_tiles[w] = gather_tiles(vp, vp.wave_begin[w], vp.wave_begin[w + 1], e);
+    else if (vp.thru) vp.ntiles = 4 * ((W + 2 * e - 1) / (2 * e)) * ((H + 2 * e - 1) / (2 * e));
+    else vp.ntiles = gather_tiles(vp, 0, (int32_t)vp.bv.size(), e);
   };
   // every ray through all its bricks in one launch: bricks front to back
   auto thru_order = [&](int32_t v) {
@@ -284,11 +345,17 @@ int render_forward(vr_ctx* ctx, vr_volume* vol, const vr_view* views, int32_t nv
   // axis along which the eye lies outside its slab; the bricks neither axis
   // suits, and views with rays less than kPerspCellPitch voxels apart, by
   // gathers
+  auto persp_faster = [&](const Camera& cam, const ViewPlan& vp) {
+    FootShape any;
+    any.axis = std::fabs(cam.e3[1]) >= std::fabs(cam.e3[2]) ? 1 : 2;
+    const MarchTimes t = march_times(cam, view_boxes(vp), p->step, &any);
+    return t.samples / kPerspCellRate + kPerspChains * t.chain <= t.gather;
+  };
   for (int32_t v = 0; v < nviews; v++) {
     ViewPlan& vp = plans[v];
     if (!pick || !cams[v].persp || vp.bv.empty() || vp.deep || global) continue;
     const bool cells = bricked && ctx->persp_cells && (!base.mask || base.mask_n <= kCellsMaskMax) && ctx->ring_reg > 0 && ctx->ring_nslots != 3 &&
-                       cams[v].S / W >= kPerspCellPitch;
+                       cams[v].S / W >= kPerspCellPitch && persp_faster(cams[v], vp);
     const int first_axis = std::fabs(cams[v].e3[1]) >= std::fabs(cams[v].e3[2]) ? 1 : 2;
     std::vector<int32_t> axis(vp.bv.size(), 0);
     bool any = false;
@@ -318,7 +385,7 @@ int render_forward(vr_ctx* ctx, vr_volume* vol, const vr_view* views, int32_t nv
       }
     }
     if (!any) {
-      gather_view(vp, 16);
+      gather_view(vp, gather_lanes(cams[v]));
       continue;
     }
     std::vector<DevBrickView> grouped;
@@ -344,7 +411,7 @@ int render_forward(vr_ctx* ctx, vr_volume* vol, const vr_view* views, int32_t nv
     vp.bv.swap(grouped);
     if (vp.class_axis.back() == 0)
       vp.class_tiles.back() =
-          gather_tiles(vp, vp.class_begin[vp.class_begin.size() - 2], (int32_t)vp.bv.size(), 2, 2);
+          gather_tiles(vp, vp.class_begin[vp.class_begin.size() - 2], (int32_t)vp.bv.size(), 2);
   }
   // parallel rays on the ring march: footprint cells instead of 8 x 8 pixel
   // tiles (the cell counts replace the tile counts of the plan)
@@ -366,7 +433,7 @@ int render_forward(vr_ctx* ctx, vr_volume* vol, const vr_view* views, int32_t nv
         sure = sure && t.gather < t.cells;
       }
       if (sure) {
-        gather_view(vp, 16);
+        gather_view(vp, gather_lanes(cams[v]));
         continue;
       }
     }
@@ -382,7 +449,7 @@ int render_forward(vr_ctx* ctx, vr_volume* vol, const vr_view* views, int32_t nv
       if (ctx->debug_plan)
         std::fprintf(stderr, "[vr] view %d: estimated cells %.0f us, gathers %.0f us\n", v, t.cells * 1e6, t.gather * 1e6);
       if (t.gather < t.cells) {
-        gather_view(vp, 16);
+        gather_view(vp, gather_lanes(cams[v]));
         continue;
       }
     }
@@ -424,17 +491,8 @@ int render_forward(vr_ctx* ctx, vr_volume* vol, const vr_view* views, int32_t nv
         while (w + 1 < vp.wave_begin.size() && (int32_t)i >= vp.wave_begin[w + 1]) w++;
         if ((int32_t)i == vp.wave_begin[w]) tiles = 0;
       }
-      int32_t ncf, ncg;
-      foot_cells(cams[v], fs, bricked ? vol->part.boxes[b.brick] : whole, b.cf0, b.cg0, ncf, ncg, b.fa0, b.fb0);
-      b.tiles_x = ncf;
       b.tile_begin = tiles;
-      if (fs.blk_f > 0) {
-        b.blocks_x = (ncf + fs.blk_f - 1) / fs.blk_f;
-        tiles += b.blocks_x * ((ncg + fs.blk_g - 1) / fs.blk_g);
-      } else {
-        b.blocks_x = ncg;  // cells along g
-        tiles += ncf * ncg;
-      }
+      tiles += foot_brick(cams[v], fs, bricked ? vol->part.boxes[b.brick] : whole, b);
       if (global) vp.wave_tiles[w] = tiles;
     }
     if (!global) vp.ntiles = tiles;
@@ -520,32 +578,7 @@ int render_forward(vr_ctx* ctx, vr_volume* vol, const vr_view* views, int32_t nv
     if (vp.foot) {
       const FootShape& fs = vp.fs;
       ring = true;
-      a.foot = 1;
-      a.slab_axis = fs.axis;
-      a.ring_slot = fs.slot;
-      a.ring_nslots = fs.nslots;
-      a.ring_reg = fs.reg;
-      ring_wpb = fs.reg && ctx->cells_wpb > 0 ? ctx->cells_wpb : fs.wpb;
-      // The wavefronts of a workgroup hold its LDS until the last is done, and
-      // cells side by side along g (a few rows wide) cross a brick in about the
-      // same number of layers, along f (28 or 60 voxels) they do not: numbered
-      // along g, marches bound by their own work are 5 to 20 % faster (two
-      // views of eight 512^3 bricks 2.19 -> 1.90 ms, six bricks 1.47 -> 1.38).
-      // Along f neighbours share a line of every window row, which counts where
-      // traffic binds: cells of many rows, most of them no neighbour's (rays 3
-      // voxels apart: 2 to 9 % faster along f).
-      a.cols = fs.reg && fs.blk_f == 0 && fs.Tg < 16.0 && fs.ng >= 1.4 * fs.Tg;
-      if (fs.reg && ctx->cells_waves > 0) {
-        // at most cells_waves wavefronts per compute unit: reserve LDS so that
-        // one workgroup more would not fit (more wavefronts ran slower: their
-        // windows crowd each other out of the caches)
-        const int32_t nwg = std::max(1, ctx->cells_waves / ring_wpb);
-        a.lds_floor = kLdsPerCu / (nwg + 1) + 1024;
-      }
-      a.foot_nf = fs.nf;
-      a.foot_ng = fs.ng;
-      a.foot_Tf = fs.Tf;
-      a.foot_Tg = fs.Tg;
+      foot_args(ctx, fs, a, ring_wpb);
       if (fs.blk_f > 0) {
         // one window per block: its rows and slot replace the cell's
         a.blk_f = fs.blk_f;
@@ -555,10 +588,6 @@ int render_forward(vr_ctx* ctx, vr_volume* vol, const vr_view* views, int32_t nv
         a.ring_slot = fs.blk_slot;
         a.ring_nslots = 2;
       }
-      a.fa_u = fs.fa_u;
-      a.fa_v = fs.fa_v;
-      a.fb_u = fs.fb_u;
-      a.fb_v = fs.fb_v;
       unsigned char* ovf = reinterpret_cast<unsigned char*>(ctx->d_ovf) + (global ? (size_t)(v % vr_ctx::kAux) * ovf_stride : 0);
       a.ovf_count = reinterpret_cast<unsigned int*>(ovf);
       a.ovf_tiles = reinterpret_cast<int32_t*>(ovf + 256);

@@ -44,17 +44,33 @@ struct ForwardExtras {
 
 struct MarchTimes {
   double cells = 1e30, gather = 0.0;  // seconds
+  double samples = 0.0, chain = 0.0;  // samples, and the part of cells that is a wavefront's chain
   double pitch = 0.0;                 // voxels between rays
 };
-MarchTimes march_times(const Camera& cam, const std::vector<Box>& boxes, double step, const FootShape* fs);
+// Lanes per ray of a view's gathers: 4 x 4 rays of four consecutive samples
+// touch fewer lines than 2 x 2 rays of sixteen where rays are less than 1.1
+// voxels apart, sixteen lanes shorten the chain of a ray where there are few (two
+// views of 201 x 187 x 333 at 0.8 voxels 405 us with 16, 330 with 4; 400^3 at
+// 0.7 1.23 ms and 1.00, at 1.35 414 us and 484; 256^2 rays through 128^3 59
+// and 59, fewer rays up to twice as slow with 4).
+int32_t gather_lanes(const Camera& cam);
+MarchTimes march_times(const Camera& cam, const std::vector<Box>& boxes, double step, const FootShape* fs,
+                       int views = 1);
 
 // Footprint-cell shape of one parallel view of a volume of size n, as the
 // forward picks it: plain = the plain march (no macrocell skipping, no mask),
 // reg_on = register staging allowed, nslots = the ring-slot rule (0, 2 or 3),
 // cells of about `rays` pixels with window rows of at most kmax 128-byte
-// lines (+ pad floats).  False when the view has no suitable slab axis.
+// lines (+ pad floats), along slab axis `axis` (0: either).  False when the view has no suitable slab axis.
 bool pick_foot(const Camera& cam, const int64_t n[3], int32_t M, bool plain, bool reg_on, int32_t nslots,
-               double rays, int32_t pad, int32_t kmax, FootShape& fs, int32_t max_px = 0);
+               double rays, int32_t pad, int32_t kmax, FootShape& fs, int32_t max_px = 0,
+               int32_t axis = 0);
+
+// Launch arguments of the cell march with shape fs (wpb: wavefronts per
+// workgroup), and the shape and place of a box's cells in its view entry;
+// returns the number of cells.
+void foot_args(const vr_ctx* ctx, const FootShape& fs, MarchArgs& a, int& wpb);
+int32_t foot_brick(const Camera& cam, const FootShape& fs, const Box& box, DevBrickView& b);
 
 void plan_bricked_view(const vr_volume* vol, const Camera& cam, const vr_params* p, int32_t tile_w,
                        const float* tf, int32_t M, double vmin, double vmax, ViewPlan& vp, bool waves = false);

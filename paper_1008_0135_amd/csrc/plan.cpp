@@ -467,7 +467,7 @@ int32_t window_loads(int32_t pitch, int32_t ng) {
 
 bool choose_foot(const Camera& cam, int32_t cap, int32_t M, int32_t max_waves, int32_t want_waves, double rays,
                  int32_t nslots_rule, FootShape& out, int32_t pad, int32_t kmax, int32_t reg_waves,
-                 int32_t reg_loads, int32_t max_px_in) {
+                 int32_t reg_loads, int32_t max_px_in, int32_t only_axis) {
   if (cam.persp) return false;
   const double p = cam.S / (double)cam.W;
   const double* e1 = cam.e1;
@@ -478,6 +478,7 @@ bool choose_foot(const Camera& cam, int32_t cap, int32_t M, int32_t max_waves, i
   double best = INFINITY;
   bool found = false;
   for (int b = 1; b <= 2; b++) {
+    if (only_axis != 0 && b != only_axis) continue;
     const int g = 3 - b;
     if (std::fabs(d[b]) < 0.05) continue;  // windows grow as 1 / |d_b|
     const double rf = d[0] / d[b], rg = d[g] / d[b];

@@ -147,7 +147,7 @@ struct FootShape {
 // suits.
 bool choose_foot(const Camera& cam, int32_t cap, int32_t M, int32_t max_waves, int32_t want_waves, double rays,
                  int32_t nslots_rule, FootShape& out, int32_t pad = 0, int32_t kmax = 4, int32_t reg_waves = 0,
-                 int32_t reg_loads = 0, int32_t max_px = 0);
+                 int32_t reg_loads = 0, int32_t max_px = 0, int32_t only_axis = 0);
 // Blocks of footprint cells for the chosen cell shape: blk_f x blk_g cells
 // (at most 8) marched by one workgroup with one window per voxel layer, the
 // choice with the fewest 128-byte lines per ray and layer, counting the cells

@@ -43,8 +43,19 @@ __device__ __forceinline__ f2u ld_pair(gfloat* p) {
 // over 64 bricks 4.4 -> 2.5 ms).
 constexpr int kXcdRun = 8;
 __device__ __forceinline__ int xcd_block() {
-  const int r = (int)blockIdx.x % (8 * kXcdRun);
-  return (int)blockIdx.x - r + (r & 7) * kXcdRun + (r >> 3);
+  // which XCD takes which run of a round of eight moves on by three from round
+  // to round: image rows of 8 or 16 runs would else give an XCD the same column
+  // of the image in every row
+  const int b = (int)blockIdx.x, n = b / (8 * kXcdRun), r = b - n * (8 * kXcdRun);
+  return b - r + ((r + 3 * (n >> 2)) & 7) * kXcdRun + (r >> 3);
+}
+
+// Tile t of a grid of tiles numbered by blocks of 2 x 2 (blocks_x blocks a row):
+// the four wavefronts of a workgroup share more lines than four tiles in a row.
+__device__ __forceinline__ void block_tile(int t, int blocks_x, int& tx, int& ty) {
+  const int q = t >> 2, by = q / blocks_x;
+  tx = (q - by * blocks_x) * 2 + (t & 1);
+  ty = by * 2 + (t >> 1 & 1);
 }
 
 // Run of samples of a ray from sample j on whose cells lie in the macrocell
@@ -104,8 +115,8 @@ __global__ __launch_bounds__(256) void k_march_skip(MarchArgs a) {
   const int rx = THRU ? 0 : a.bv[lo].x0, ry = THRU ? 0 : a.bv[lo].y0;
   const int rw = THRU ? a.cam.W : a.bv[lo].w, rh = THRU ? a.cam.H : a.bv[lo].h;
   const int t = THRU ? tile : tile - a.bv[lo].tile_begin;
-  const int tiles_x = THRU ? (rw + 7) / 8 : a.bv[lo].tiles_x;
-  const int tx = t % tiles_x, ty = t / tiles_x;
+  int tx, ty;
+  block_tile(t, THRU ? (rw + 15) / 16 : a.bv[lo].tiles_x, tx, ty);
   // ray `lane` belongs to rod lane >> 2 (2 x 2 pixels, 4 x 4 rods)
   const int lx = tx * 8 + ((lane >> 2) & 3) * 2 + (lane & 1), ly = ty * 8 + (lane >> 4) * 2 + ((lane >> 1) & 1);
   const bool valid = lx < rw && ly < rh;
@@ -259,8 +270,14 @@ __global__ __launch_bounds__(256) void k_march(MarchArgs a) {
   const int rx = THRU ? 0 : a.bv[lo].x0, ry = THRU ? 0 : a.bv[lo].y0;
   const int rw = THRU ? a.cam.W : a.bv[lo].w, rh = THRU ? a.cam.H : a.bv[lo].h;
   const int t = THRU ? tile : tile - a.bv[lo].tile_begin;
-  const int tiles_x = THRU ? (rw + TW - 1) / TW : a.bv[lo].tiles_x;
-  const int tx = t % tiles_x, ty = t / tiles_x;
+  const int tiles_x = THRU ? (rw + 2 * TW - 1) / (2 * TW) : a.bv[lo].tiles_x;
+  int tx, ty;
+  if constexpr (D > 1) {
+    block_tile(t, tiles_x, tx, ty);
+  } else {
+    tx = t % tiles_x;
+    ty = t / tiles_x;
+  }
   const int ray = (threadIdx.x & 63) / D, dl = threadIdx.x & (D - 1);
   const int lx = tx * TW + (ray % TW), ly = ty * TH + (ray / TW);
   if (lx >= rw || ly >= rh) return;
