@@ -21,16 +21,19 @@ struct vr_state {
   double vmin = 0.0, vmax = 0.0;
   int32_t W = 0, H = 0, nviews = 0, K = 32, nseg = 0;
   // per view: checkpoint layout.  Ring views keep, per group of L cell layers
-  // of each 8 x 8 tile, T at the group's start, and at the ray's end; the
+  // along the slab axis, T at a ray's start of the group, and at its end; the
   // others keep T before every K-th sample.
   struct View {
     bool ring = false;
-    int32_t axis = 0, slot = 0, fwd_wpb = 4, L = 0, smax = 0, ngrp = 0;
+    int32_t axis = 0, slot = 0, L = 0, smax = 0, ngrp = 0;
     int64_t off = 0;  // offset of this view's checkpoints in d_ckpt
+    int32_t parts = 1, part_groups = 0;  // workgroups per tile and the groups each takes
+    int64_t sums = 0;                    // offset of this view's sums in d_sums
     int32_t band[9] = {};  // ring adjoint: tiles per XCD (all zero: equal counts)
   };
   std::vector<View> vs;
   float* d_ckpt = nullptr;     // checkpoints, all views
+  double4* d_sums = nullptr;   // behind the checkpoints: views in parts
   int32_t* d_nused = nullptr;  // [view][pixel], then the adjoint's bound flag
   size_t ckpt_bytes = 0, nused_bytes = 0;  // allocated sizes
   int32_t* d_flag = nullptr;   // set by the adjoint when a group held more samples than its bound
@@ -39,6 +42,8 @@ struct vr_state {
 namespace vr {
 
 namespace {
+
+constexpr int32_t kPartBlocks = 4096, kMaxParts = 16;
 
 // Device tables of one view of a whole-volume render: [DevBrick][DevBrickView].
 struct WholeTables {
@@ -111,8 +116,8 @@ void xcd_bands(const std::vector<double>& cost, int wpb, int32_t band[9]) {
   band[8] = ng;
 }
 
-// Ring layout for the differentiable pair of one view: slab axis, window slot,
-// forward launch shape and cell layers per checkpoint group (about K samples,
+// Ring layout for the differentiable pair of one view: slab axis, window slot
+// and cell layers per checkpoint group (about K samples,
 // the adjoint's windows of one tile within 160 KB of LDS).  False when the view
 // needs the sample-segment kernels.
 bool plan_ring_view(const Camera& cam, const vr_params* p, int32_t M, const int64_t n[3], int layer_cap,
@@ -131,7 +136,6 @@ bool plan_ring_view(const Camera& cam, const vr_params* p, int32_t M, const int6
     rv.ring = true;
     rv.axis = axis;
     rv.slot = slot;
-    rv.fwd_wpb = wpb;
     rv.L = L;
     rv.smax = smax;
     rv.ngrp = (int32_t)((n[axis] - 1 + L - 1) / L) + 1;
@@ -174,19 +178,53 @@ int render_with_state(vr_ctx* ctx, vr_volume* vol, const vr_view* views, int32_t
   // per-view layout and checkpoint offsets
   std::vector<Camera> cams((size_t)nviews);
   st->vs.assign((size_t)nviews, vr_state::View());
-  int64_t ck_total = 0;
+  int64_t ck_total = 0, sums_total = 0;
+  Box whole;
+  for (int i = 0; i < 3; i++) {
+    whole.lo[i] = 0;
+    whole.hi[i] = vol->n[i] - 1;
+    whole.closed[i] = 1;
+  }
+  std::vector<FootShape> shapes((size_t)nviews);  // (axis 0: no cells)
+  std::vector<int32_t> cells((size_t)nviews, 0);
   for (int32_t v = 0; v < nviews; v++) {
     make_camera(views[v], vol->n, cams[v]);
     vr_state::View& rv = st->vs[v];
-    if (ctx->march_mode != 1 && plan_ring_view(cams[v], p, ctx->tf_m, vol->n, ctx->bwd_layer_cap, rv)) {
-      rv.off = ck_total;
-      ck_total += (int64_t)rv.ngrp * npix;
-    } else {
-      rv.off = ck_total;
+    rv.off = ck_total;
+    if (ctx->march_mode == 1 || !plan_ring_view(cams[v], p, ctx->tf_m, vol->n, ctx->bwd_layer_cap, rv)) {
       ck_total += (int64_t)st->nseg * npix;
+      continue;
+    }
+    ck_total += (int64_t)rv.ngrp * npix;
+    // the forward's march: footprint cells along the slab axis of the groups
+    // where they are estimated faster, else gathers (three of the side streams
+    // run at a time)
+    FootShape fs;
+    fs.axis = rv.axis;
+    const MarchTimes t = march_times(cams[v], {whole}, p->step, &fs, ctx->bwd_side ? std::min(nviews, 3) : 1);
+    if (ctx->foot && t.cells <= t.gather &&
+        pick_foot(cams[v], vol->n, ctx->tf_m, true, ctx->ring_reg > 0, ctx->ring_nslots, ctx->foot_rays,
+                  ctx->foot_pad, ctx->foot_kmax, fs, ctx->foot_maxpx, rv.axis) &&
+        fs.reg) {
+      shapes[v] = fs;
+      continue;
+    }
+    // Few tiles leave most compute units without a workgroup of the adjoint, and
+    // its time is one tile's chain of groups: parts of the groups side by side
+    // until there are kPartBlocks workgroups (two views of 100 x 92 rays through
+    // 61 x 83 x 72 voxels: 202 -> 95 us per view, the step 720 -> 585; one view of
+    // 256^2 rays through 128^3: 690 -> 600; 16384 gains nothing more)
+    const int32_t tiles = ntiles_of(W, H, 8, 8) * nviews, groups = rv.ngrp - 1;
+    const int32_t want = std::max(1, std::min({kPartBlocks / std::max(1, tiles), kMaxParts, groups / 2}));
+    rv.part_groups = (groups + want - 1) / want;
+    rv.parts = (groups + rv.part_groups - 1) / rv.part_groups;
+    if (rv.parts > 1) {
+      rv.sums = sums_total;
+      sums_total += (int64_t)rv.parts * npix;
     }
   }
-  const size_t ck_bytes = sizeof(float) * (size_t)std::max<int64_t>(ck_total, 1);
+  const size_t sums_at = (sizeof(float) * (size_t)std::max<int64_t>(ck_total, 1) + 31) & ~(size_t)31;
+  const size_t ck_bytes = sums_at + sizeof(double4) * (size_t)sums_total;
   const size_t nu_bytes = sizeof(int32_t) * ((size_t)nviews * npix + 64);
   // the buffers of the last destroyed state when they are large enough
   vr_ctx::StateBufs& sp = ctx->spare;
@@ -205,6 +243,7 @@ int render_with_state(vr_ctx* ctx, vr_volume* vol, const vr_view* views, int32_t
       return fail(VR_ENOMEM, "hipMalloc for %zu bytes of checkpoints failed", ck_bytes);
     }
   }
+  st->d_sums = reinterpret_cast<double4*>(reinterpret_cast<unsigned char*>(st->d_ckpt) + sums_at);
   st->d_flag = st->d_nused + (size_t)nviews * npix;
   {
     const hipError_t e = launch_fill(reinterpret_cast<float*>(st->d_flag), 1, 0.f, s);
@@ -219,6 +258,23 @@ int render_with_state(vr_ctx* ctx, vr_volume* vol, const vr_view* views, int32_t
   std::vector<unsigned char> host;
   std::vector<size_t> off_bv;
   pack_whole(vol, W, H, base.tile_w, base.tile_h, nviews, host, off_bv);
+  int32_t most = 0;
+  for (int32_t v = 0; v < nviews; v++) {
+    if (shapes[v].axis == 0) continue;
+    DevBrickView b;
+    std::memcpy(&b, host.data() + off_bv[v], sizeof b);
+    cells[v] = foot_brick(cams[v], shapes[v], whole, b);
+    std::memcpy(host.data() + off_bv[v], &b, sizeof b);
+    most = std::max(most, cells[v]);
+  }
+  const size_t ovf_stride = (256 + 4 * (size_t)most + 15) & ~(size_t)15;
+  if (most > 0) {
+    const int oc = ensure_device(&ctx->d_ovf, &ctx->ovf_bytes, ovf_stride * vr_ctx::kAux);
+    if (oc != VR_OK) {
+      vr_state_destroy(st);
+      return oc;
+    }
+  }
   void* dtab = nullptr;
   int rc = upload_tables(ctx, s, host.data(), host.size(), &dtab);
   // views write disjoint frames and checkpoints: side by side on the side
@@ -242,20 +298,30 @@ int render_with_state(vr_ctx* ctx, vr_volume* vol, const vr_view* views, int32_t
     sa.nused = st->d_nused + (int64_t)v * npix;
     sa.K = rv.ring ? rv.L : st->K;
     sa.npix = (int32_t)npix;
-    if (rv.ring && ctx->bwd_bands) {
-      // XCD bands of this view's forward and adjoint (the host plans view v
-      // while the GPU marches view v - 1)
-      const std::vector<double> cost = tile_costs(cams[v], base.hi, p->step, W, H);
-      xcd_bands(cost, rv.fwd_wpb, sa.band);
-      xcd_bands(cost, 1, st->vs[v].band);
-    }
+    sa.parts = rv.parts;
+    sa.part_groups = rv.part_groups;
+    sa.sums = st->d_sums + rv.sums;
+    if (rv.ring && ctx->bwd_bands)  // XCD bands of the adjoint
+      xcd_bands(tile_costs(cams[v], base.hi, p->step, W, H), 1, st->vs[v].band);
     if (!side) rc = stage_begin(ctx, VR_STAGE_MARCH, s);
     if (rc == VR_OK) {
       hipError_t e;
-      if (rv.ring) {
-        a.slab_axis = rv.axis;
-        a.ring_slot = rv.slot;
-        e = launch_march_ring_save(a, sa, rv.fwd_wpb, vs);
+      a.slab_axis = rv.axis;
+      if (rv.ring && shapes[v].axis != 0) {
+        int wpb = 4;
+        foot_args(ctx, shapes[v], a, wpb);
+        a.xcd_chunk = 16;
+        a.ntiles = cells[v];
+        unsigned char* ovf = reinterpret_cast<unsigned char*>(ctx->d_ovf) + (size_t)(v % vr_ctx::kAux) * ovf_stride;
+        a.ovf_count = reinterpret_cast<unsigned int*>(ovf);
+        a.ovf_tiles = reinterpret_cast<int32_t*>(ovf + 256);
+        // pixels without samples are not written by the cells
+        e = launch_zero(a.img + (int64_t)v * npix, npix, vs);
+        if (e == hipSuccess) e = launch_fill(reinterpret_cast<float*>(sa.nused), npix, 0.f, vs);
+        if (e == hipSuccess) e = launch_march_ring(a, wpb, vs, &sa);
+      } else if (rv.ring) {
+        a.ntiles = 4 * ((W + 3) / 4) * ((H + 3) / 4);  // blocks of 2 x 2 tiles of 2 x 2 pixels
+        e = launch_march_save(a, sa, vs);
       } else {
         e = launch_fwd_save(a, sa, vs);
       }
@@ -356,10 +422,12 @@ int vr_render_backward(vr_ctx* ctx, const vr_volume* vol, const vr_state* st, co
     BwdArgs bb;
     std::memset(&bb, 0, sizeof bb);
     std::memcpy(bb.band, rv.band, sizeof bb.band);
+    bb.parts = rv.parts;
     pbase[v + 1] = pbase[v] + (rv.ring ? bwd_ring_blocks(a0, bb) : bwd_blocks(a0));
   }
   float max_alpha = 0.f;
   for (int32_t i = 0; i < M; i++) max_alpha = std::max(max_alpha, ctx->h_tf[4 * (size_t)i + 3]);
+  const bool replay = max_alpha > kMaxDivAlpha;
   const bool side = ctx->bwd_side && st->nviews > 1;
   int64_t nslots = 1;
   for (int32_t v = 0; v < st->nviews; v++) nslots = std::max(nslots, pbase[v + 1] - pbase[v]);
@@ -391,9 +459,12 @@ int vr_render_backward(vr_ctx* ctx, const vr_volume* vol, const vr_state* st, co
     ba.K = rv.ring ? rv.L : st->K;
     ba.npix = (int32_t)npix;
     ba.smax = rv.smax;
-    ba.replay = max_alpha > kMaxDivAlpha ? 1 : 0;
+    ba.replay = replay ? 1 : 0;
     std::memcpy(ba.band, rv.band, sizeof ba.band);
     ba.flag = st->d_flag;
+    ba.parts = rv.parts;
+    ba.part_groups = rv.part_groups;
+    ba.sums = st->d_sums + rv.sums;
     if (rv.ring) {
       a.slab_axis = rv.axis;
       a.ring_slot = rv.slot;
@@ -409,8 +480,10 @@ int vr_render_backward(vr_ctx* ctx, const vr_volume* vol, const vr_state* st, co
   }
   VR_TRY(stage_end(ctx, s));
   VR_TRY(ctx_end(ctx, s));
-  // the ring adjoint's bound on the samples of one ray in one checkpoint group
-  // holds by construction; a group that exceeded it is reported, not clamped
+  // the replay's bound on the samples of one ray in one checkpoint group holds
+  // by construction; a group that exceeded it is reported, not clamped (only
+  // the replay can: without it the call returns while the GPU works)
+  if (!replay) return VR_OK;
   int32_t flag = 0;
   VR_HIP(hipMemcpyAsync(&flag, st->d_flag, sizeof flag, hipMemcpyDeviceToHost, s));
   VR_HIP(hipStreamSynchronize(s));

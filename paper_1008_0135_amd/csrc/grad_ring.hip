@@ -1,10 +1,10 @@
 // grad_ring.hip -- the adjoint march on the ring-window layout (gfx950).
 //
-// The differentiable forward (k_march_ring<SAVE>) walks every 8 x 8 ray tile
-// cell layer by cell layer along the slab axis b and stores, for every group
-// of L consecutive cell layers of the tile (in marching order), each ray's
-// transmittance at the group's start, and after the last group at the ray's
-// end.  This kernel walks the groups from the last to the first.  A workgroup
+// The differentiable forward (k_march_cells, k_march_ring_ovf, k_march_save)
+// stores, for every group of L consecutive cell layers along the slab axis b
+// (counted in marching order from the box's first) that a ray has samples in,
+// its transmittance at the group's start, and after the last one at its end.
+// This kernel walks the groups of an 8 x 8 ray tile from the last to the first.  A workgroup
 // of four wavefronts takes one tile: four neighbouring lanes share a ray and
 // hold four consecutive samples of it, so a ray's chain is a quarter as long
 // and the tile's windows serve four wavefronts.  For a group it
@@ -23,6 +23,9 @@
 //   3. adds the finished gradient windows to the gradient volume with one float
 //      atomic per non-zero window voxel, row after row (coalesced), instead of
 //      eight scattered atomics per sample.
+// In small views several workgroups share a tile, each a part of its groups:
+// what a ray gathers behind a part is known from the forward (BwdArgs::sums, in
+// double precision), so S can start there.
 // T before a block comes from the group's end by division by its samples'
 // 1 - a (every sample is evaluated once), or, for tables whose opacity exceeds
 // kMaxDivAlpha, from a replay of the group from its start (REPLAY): dividing by
@@ -131,7 +134,7 @@ __device__ __forceinline__ double quad_pick(int dl, double v0, double v1, double
 
 constexpr int kAhead = 3;  // layers of windows kept ahead in registers
 
-template <bool REPLAY>
+template <bool REPLAY, bool by>
 __global__ __launch_bounds__(256) __attribute__((amdgpu_waves_per_eu(4))) void k_bwd_ring(MarchArgs a, BwdArgs ba) {
   extern __shared__ double dsm[];
   const int M = a.M, L = ba.K;
@@ -195,7 +198,6 @@ __global__ __launch_bounds__(256) __attribute__((amdgpu_waves_per_eu(4))) void k
       cnt = (int)(k1 - k0);
     }
   }
-  const bool by = a.slab_axis == 1;
   const float pb = (float)(by ? p0[1] : p0[2]), sb = (float)(a.step * (by ? d[1] : d[2]));
   const int cloB = by ? br.clo[1] : br.clo[2], chiB = by ? br.chi[1] : br.chi[2];
   const int cloG = by ? br.clo[2] : br.clo[1], chiG = by ? br.chi[2] : br.chi[1];
@@ -226,6 +228,10 @@ __global__ __launch_bounds__(256) __attribute__((amdgpu_waves_per_eu(4))) void k
   Lbeg = uni(Lbeg);
   Lend = uni(Lend);
   if (up ? Lbeg <= Lend : Lbeg >= Lend) {  // the same for the whole workgroup
+    // groups are counted from the box's first layer in marching order: the
+    // tile's start where the group of its first layer starts
+    const int g0 = uni((up ? Lbeg - cloB : chiB - Lbeg) / L);
+    Lbeg = up ? cloB + g0 * L : chiB - g0 * L;
     const int nlay = up ? Lend - Lbeg + 1 : Lbeg - Lend + 1;
     const int vstep = up ? 1 : -1;
     const int V0 = up ? Lbeg : Lbeg + 1;  // voxel layer V_k = V0 + k vstep
@@ -270,8 +276,7 @@ __global__ __launch_bounds__(256) __attribute__((amdgpu_waves_per_eu(4))) void k
 
     // per-ray state of the backward walk
     const int used = valid ? ba.nused[pix] : 0;
-    const float4 gf = valid ? ba.gout[pix] : make_float4(0.f, 0.f, 0.f, 0.f);
-    const double gx = gf.x, gy = gf.y, gz = gf.z, gw = gf.w;
+    float4 gf = valid ? ba.gout[pix] : make_float4(0.f, 0.f, 0.f, 0.f);
     const double dvs = (double)(M - 1) * ba.inv_range;  // du/dv inside the window
     double S = 0.0;
     const int ngrp = (nlay + L - 1) / L;
@@ -293,9 +298,26 @@ __global__ __launch_bounds__(256) __attribute__((amdgpu_waves_per_eu(4))) void k
     // window: it is neither reloaded nor cleared there, and flushed once,
     // with both groups' terms, by the group taken later.
     auto pslot = [&](int m) { return m % (L + 1); };
+    // groups of this workgroup (relative to the tile's first): all, or those of
+    // one part of the layers
+    int gb = 0, ge = ngrp;
+    if (ba.parts > 1) {
+      const int q = ba.part_groups, k = (int)blockIdx.y;
+      gb = max(0, k * q - g0);
+      ge = min(ngrp, (k + 1) * q - g0);
+    }
     int jn = cnt;  // first sample of the group taken before (behind) this one
-    float Tn = valid ? ba.ckpt[(int64_t)ngrp * npix + pix] : 1.f;  // T behind the group
-    float Tg = valid ? ba.ckpt[(int64_t)(ngrp - 1) * npix + pix] : 1.f;  // T before the group
+    float Tn = valid && ge > gb ? ba.ckpt[(int64_t)(g0 + ge) * npix + pix] : 1.f;  // T behind the group
+    float Tg = valid && ge > gb ? ba.ckpt[(int64_t)(g0 + ge - 1) * npix + pix] : 1.f;  // T before the group
+    if (gb < ge && ge < ngrp) {
+      // what the ray gathers behind the part, per unit of transmittance there
+      jn = first_at(ge * L);
+      if (jn > 0 && jn < used) {
+        const double4 all = ba.sums[pix], f = ba.sums[(int64_t)((int)blockIdx.y + 1) * npix + pix];
+        S = ((double)gf.x * (all.x - f.x) + (double)gf.y * (all.y - f.y) + (double)gf.z * (all.z - f.z) +
+             (double)gf.w * (all.w - f.w)) / (double)Tn;
+      }
+    }
     // chunk (16 bytes) of a window this lane copies: row pr, column pc
     typedef float v4f __attribute__((ext_vector_type(4)));
     typedef float v4u __attribute__((ext_vector_type(4), aligned(4)));
@@ -306,9 +328,12 @@ __global__ __launch_bounds__(256) __attribute__((amdgpu_waves_per_eu(4))) void k
     };
     // windows of one chunk per lane: the next group's are loaded into registers
     // while this group's samples are taken
-    const bool ahead = inl && nwin <= 1024 && L <= kAhead;
+    const bool ahead = inl && nwin <= 1024 && L <= kAhead && ((int64_t)NG * sG + pitch) * 4 < ((int64_t)1 << 31);
+    // byte offset of this lane's chunk from the window's first voxel
+    const int pre_row = (int)(((float)(4 * tid) + 0.5f) * inv_pitch);
+    unsigned pre_off = ahead ? (unsigned)(pre_row * sG + 4 * tid - pre_row * pitch) * 4u : 0u;
     v4f pre[kAhead];
-    for (int g = ngrp - 1; g >= 0; --g) {
+    for (int g = ge - 1; g >= gb; --g) {
       const int k0 = g * L, k1 = min(nlay, k0 + L);  // cell layers k0 .. k1 - 1
       const int nv = k1 - k0 + 1;                     // voxel layers V_{k0} .. V_{k1}
       if (inl) {
@@ -316,24 +341,27 @@ __global__ __launch_bounds__(256) __attribute__((amdgpu_waves_per_eu(4))) void k
           const int V = V0 + (k0 + i) * vstep;
           const Window w = window(V);
           const int ps = pslot(k0 + i);
-          if (!(g + 1 < ngrp && i == nv - 1) && !(ahead && g + 1 < ngrp))  // (V_{k1} is kept from group g + 1)
+          if (!(g + 1 < ge && i == nv - 1) && !(ahead && g + 1 < ge))  // (V_{k1} is kept from group g + 1)
             for (int e = 4 * tid; e < nwin; e += 1024) *reinterpret_cast<v4f*>(s_vox + ps * slot + e) = chunk(V, w, e);
           if (tid == 0) s_boff[i] = ps * slot - w.g0 * pitch - w.f0;
         }
-        if (ahead && g + 1 < ngrp && 4 * tid < nwin)
+        if (ahead && g + 1 < ge && 4 * tid < nwin)
 #pragma unroll
           for (int i = 0; i < kAhead; ++i)
             if (i < L) *reinterpret_cast<v4f*>(s_vox + pslot(k0 + i) * slot + 4 * tid) = pre[i];
         __syncthreads();
-        if (ahead && g > 0 && 4 * tid < nwin)
+        if (ahead && g > gb && 4 * tid < nwin)
 #pragma unroll
           for (int i = 0; i < kAhead; ++i)
             if (i < L) {
               const int V = V0 + (k0 - L + i) * vstep;
-              pre[i] = chunk(V, window(V), 4 * tid);
+              const Window w = window(V);
+              asm volatile("" : "+v"(pre_off));  // (not hoisted as a 64-bit address per window)
+              const char* wb = (const char*)unip(gbase + ((int64_t)V * sB + (int64_t)w.g0 * sG + w.f0));
+              pre[i] = (v4f) * (const v4u __attribute__((address_space(1)))*)(wb + pre_off);
             }
       }
-      const float Tp_next = valid && g > 0 ? ba.ckpt[(int64_t)(g - 1) * npix + pix] : 1.f;
+      float Tp_next = valid && g > gb ? ba.ckpt[(int64_t)(g0 + g - 1) * npix + pix] : 1.f;
       const int js = first_at(k0), je = min(jn, used);
       jn = js;
       // cell of sample j and its eight corners, from the windows when both of
@@ -399,7 +427,9 @@ __global__ __launch_bounds__(256) __attribute__((amdgpu_waves_per_eu(4))) void k
         int lofs, uofs;
         corners(min(j, je - 1), c, vv, lofs, uofs);
         const Eval e = eval_d(vv, c, ba.vmin, ba.inv_range, M, s_tf);
-        const double h = fma(gx, e.r, fma(gy, e.g, fma(gz, e.b, gw)));
+        asm volatile("" : "+v"(gf.x), "+v"(gf.y), "+v"(gf.z), "+v"(gf.w));  // (kept in single precision)
+        const double gx = gf.x, gy = gf.y, gz = gf.z;
+        const double h = fma(gx, e.r, fma(gy, e.g, fma(gz, e.b, (double)gf.w)));
         const double al = on ? e.a : 0.0;
         const double a0 = quad_bcast<0>(al), a1 = quad_bcast<1>(al), a2 = quad_bcast<2>(al), a3 = quad_bcast<3>(al);
         const double h0 = quad_bcast<0>(h), h1 = quad_bcast<1>(h), h2 = quad_bcast<2>(h), h3 = quad_bcast<3>(h);
@@ -471,13 +501,19 @@ __global__ __launch_bounds__(256) __attribute__((amdgpu_waves_per_eu(4))) void k
           }
         }
       }
+      // what the next group needs has arrived by now: taken here, no wait for
+      // it comes after the atomics below (memory operations return in order,
+      // and a wait for a load would wait for every atomic issued before it)
+#pragma unroll
+      for (int i = 0; i < kAhead; ++i) asm volatile("" : "+v"(pre[i]));
+      asm volatile("" : "+v"(Tp_next));
       Tn = Tg;
       Tg = Tp_next;
       if (inl) {
         __syncthreads();  // every sample of the group is in the windows
         // add the finished gradient windows to the volume (rows contiguous
         // along axis 1) and clear them; V_{k0} goes on into group g - 1
-        for (int i = g > 0 ? 1 : 0; i < nv && gvol; ++i) {
+        for (int i = g > gb ? 1 : 0; i < nv && gvol; ++i) {
           const int V = V0 + (k0 + i) * vstep;
           const Window w = window(V);
           float* gl = gvol + ((int64_t)V * sB + (int64_t)w.g0 * sG + w.f0);
@@ -495,7 +531,7 @@ __global__ __launch_bounds__(256) __attribute__((amdgpu_waves_per_eu(4))) void k
     }
   }
   __syncthreads();
-  double* part = ba.tf_part + (int64_t)blockIdx.x * M * 4;
+  double* part = ba.tf_part + ((int64_t)blockIdx.y * gridDim.x + blockIdx.x) * M * 4;
   for (int i = threadIdx.x; i < M * 4; i += blockDim.x) part[i] = s_gtf[(i & 3) * M + (i >> 2)];
 }
 
@@ -507,12 +543,13 @@ size_t bwd_ring_lds_bytes(int M, int L, int slot, int smax, bool replay) {
 
 int bwd_ring_blocks(const MarchArgs& a, const BwdArgs& ba) {
   if (a.ntiles <= 0) return 0;
+  const int parts = std::max(1, ba.parts);
   if (ba.band[8] > 0) {
     int widest = 0;
     for (int x = 0; x < 8; x++) widest = std::max(widest, ba.band[x + 1] - ba.band[x]);
-    return 8 * widest;
+    return 8 * widest * parts;
   }
-  return ((a.ntiles + 7) / 8) * 8;
+  return ((a.ntiles + 7) / 8) * 8 * parts;
 }
 
 hipError_t launch_bwd_ring(const MarchArgs& a, const BwdArgs& ba, hipStream_t s) {
@@ -523,15 +560,17 @@ hipError_t launch_bwd_ring(const MarchArgs& a, const BwdArgs& ba, hipStream_t s)
     return hipErrorInvalidValue;
   const size_t lds = bwd_ring_lds_bytes(a.M, ba.K, a.ring_slot, ba.smax, ba.replay != 0);
   if (lds > 160 * 1024) return hipErrorInvalidValue;
-  const void* f = ba.replay ? reinterpret_cast<const void*>(&k_bwd_ring<true>)
-                            : reinterpret_cast<const void*>(&k_bwd_ring<false>);
+  const bool by = a.slab_axis == 1;
+  const auto f = ba.replay ? (by ? &k_bwd_ring<true, true> : &k_bwd_ring<true, false>)
+                           : (by ? &k_bwd_ring<false, true> : &k_bwd_ring<false, false>);
   if (lds > 64 * 1024) {  // dynamic LDS beyond the default limit
-    const hipError_t e = hipFuncSetAttribute(f, hipFuncAttributeMaxDynamicSharedMemorySize, 160 * 1024);
+    const hipError_t e = hipFuncSetAttribute(reinterpret_cast<const void*>(f), hipFuncAttributeMaxDynamicSharedMemorySize, 160 * 1024);
     if (e != hipSuccess) return e;
   }
-  const dim3 g(bwd_ring_blocks(a, ba)), b(256);
-  if (ba.replay) hipLaunchKernelGGL(k_bwd_ring<true>, g, b, lds, s, a, ba);
-  else hipLaunchKernelGGL(k_bwd_ring<false>, g, b, lds, s, a, ba);
+  if (ba.parts > 1 && (!ba.sums || ba.part_groups < 1)) return hipErrorInvalidValue;
+  const int parts = std::max(1, ba.parts);
+  const dim3 g(bwd_ring_blocks(a, ba) / parts, parts), b(256);
+  hipLaunchKernelGGL(f, g, b, lds, s, a, ba);
   return hipGetLastError();
 }
 

@@ -36,6 +36,7 @@
 // share of rows through registers); per layer: sample; barrier; write V_{k+2}
 // over V_k and start V_{k+3}; barrier.
 #include <algorithm>
+#include <cstring>
 #include <type_traits>
 
 #include "ring_common.h"
@@ -59,6 +60,7 @@ struct CellRay {
   float4* dst;
   float4 carried;
   int cnt;
+  int pix;  // place in the frame
   float px, py, pz, sx, sy, sz;
 };
 
@@ -84,6 +86,7 @@ __device__ __forceinline__ CellRay cell_ray(const MarchArgs& a, const DevBrickVi
   r.cnt = 0;
   r.px = r.py = r.pz = 0.f;
   r.dst = a.carry ? a.img + (int64_t)v * a.cam.W + u : a.img + bvw.img_off + (int64_t)ly * bvw.w + lx;
+  r.pix = v * a.cam.W + u;
   r.wr_ok = a.carry || inrect;  // dst is this pixel's place
   r.carried = make_float4(0.f, 0.f, 0.f, 1.f);
   if (a.carry && r.valid) r.carried = *r.dst;
@@ -181,8 +184,9 @@ __device__ __forceinline__ void sample_layer(const MarchArgs& a, const DevBrick&
   }
 }
 
-template <bool MIP, bool BY, bool PERSP, bool MASK, int PITCH>
-__global__ __launch_bounds__(256) __attribute__((amdgpu_waves_per_eu(4))) void k_march_cells(MarchArgs a) {
+template <bool MIP, bool BY, bool PERSP, bool MASK, int PITCH, bool SAVE = false>
+__global__ __launch_bounds__(256) __attribute__((amdgpu_waves_per_eu(4))) void k_march_cells(MarchArgs a,
+                                                                                               SaveArgs sa) {
   extern __shared__ float4 smem[];
   float4* s_tf = smem;
   for (int i = threadIdx.x; i < a.M; i += blockDim.x) s_tf[i] = a.tf[i];
@@ -360,8 +364,18 @@ __global__ __launch_bounds__(256) __attribute__((amdgpu_waves_per_eu(4))) void k
     rload(V0 + 2 * vstep, w2);
   }
   int s0 = 0;  // slot of V_k (V_{k+1} is in the other)
+  [[maybe_unused]] int grp_end = 0;
   for (int k = 0; k < nlay; ++k) {
     const int c = up ? Lbeg + k : Lbeg - k;
+    if constexpr (SAVE) {
+      // T where a group of layers begins (stopped rays: their last T, which is
+      // also what the group after their last one is to hold)
+      const int m = up ? c - cloB : chiB - c, gi = uni(m / sa.K);
+      if (k == 0 || gi == grp_end) {
+        if (r.cnt > 0) sa.ckpt[(int64_t)gi * sa.npix + r.pix] = T;
+        grp_end = gi + 1;
+      }
+    }
     const Window& wl = up ? w0 : w1;
     const Window& wu = up ? w1 : w0;
     sample_layer<MIP, BY, MASK>(a, br, r, s_tf, s_mask, s_ring, slot, pitch, c, wl, wu, up ? s0 : s0 ^ 1,
@@ -377,6 +391,12 @@ __global__ __launch_bounds__(256) __attribute__((amdgpu_waves_per_eu(4))) void k
       }
     }
     s0 ^= 1;
+  }
+  if constexpr (SAVE) {
+    if (r.cnt > 0) {
+      sa.ckpt[(int64_t)grp_end * sa.npix + r.pix] = T;
+      sa.nused[r.pix] = (int)j;
+    }
   }
   if (r.valid && r.wr_ok && r.cnt > 0)
     *r.dst = MIP ? make_float4(mx, mx, mx, mx) : make_float4(Cr, Cg, Cb, a.carry ? T : 1.f - T);
@@ -570,7 +590,7 @@ hipError_t launch_march_block(const MarchArgs& a, hipStream_t s) {
   return hipGetLastError();
 }
 
-hipError_t launch_march_cells(const MarchArgs& a, int wpb, hipStream_t s) {
+hipError_t launch_march_cells(const MarchArgs& a, int wpb, hipStream_t s, const SaveArgs* sa) {
   if (a.ntiles <= 0) return hipSuccess;
   if ((wpb != 1 && wpb != 2 && wpb != 4) || !cells_args_ok(a, 1)) return hipErrorInvalidValue;
   const int groups = (a.ntiles + wpb - 1) / wpb;
@@ -579,12 +599,25 @@ hipError_t launch_march_cells(const MarchArgs& a, int wpb, hipStream_t s) {
   const dim3 g(grid), b(64 * wpb);
   const size_t lds = std::max(cells_lds_bytes(a, wpb), (size_t)std::max(0, a.lds_floor));
   const bool by = a.slab_axis == 1;
-  auto go = [&](auto kernel) { hipLaunchKernelGGL(kernel, g, b, lds, s, a); };
+  SaveArgs save;
+  std::memset(&save, 0, sizeof save);
+  if (sa) {
+    if (sa->K < 1 || a.mip || a.mask || a.cam.persp || a.carry) return hipErrorInvalidValue;
+    save = *sa;
+  }
+  auto go = [&](auto kernel) { hipLaunchKernelGGL(kernel, g, b, lds, s, a, save); };
   // window rows of 32 or 64 floats (parallel unmasked views) are known to the
   // compiler, which then folds a row into the corner reads' offsets
   auto pick = [&](auto persp, auto mask, auto pitch) {
     constexpr bool P = decltype(persp)::value, K = decltype(mask)::value;
     constexpr int N = decltype(pitch)::value;
+    if constexpr (!P && !K) {
+      if (sa) {
+        if (by) go(k_march_cells<false, true, P, K, N, true>);
+        else go(k_march_cells<false, false, P, K, N, true>);
+        return;
+      }
+    }
     if (a.mip && by) go(k_march_cells<true, true, P, K, N>);
     else if (a.mip) go(k_march_cells<true, false, P, K, N>);
     else if (by) go(k_march_cells<false, true, P, K, N>);

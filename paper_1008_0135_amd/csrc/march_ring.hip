@@ -53,20 +53,16 @@ using namespace ring;
 
 constexpr int kSlotsMax = 3;
 
-// SAVE (differentiable forward, whole volume): also store, for every group of
-// sa.K cell layers of the tile (in marching order), each ray's transmittance
-// and sample cursor at the group's start, and the samples applied per ray.
-// MIP: maximum intensity projection (no table, no skipping, no saving).
+// MIP: maximum intensity projection (no table, no skipping).
 // REG (two slots, perspective views): the window of the layer after next is
 // loaded into registers while the current cell layer is sampled and written
 // over the finished layer afterwards, for tiles whose window takes at most
 // kRingRegLoads loads per lane (the others load straight into LDS), so every
 // wavefront keeps a layer in flight without a third slot.
-template <bool ESS, bool SAVE, bool MIP, bool PERSP, bool TWO = false, bool MASK = false, bool REG = false>
-__global__ __launch_bounds__(256) void k_march_ring(MarchArgs a, SaveArgs sa) {
-  static_assert(!(PERSP && SAVE), "the checkpointing forward is orthographic");
-  static_assert(!TWO || !(ESS || SAVE), "two slots: the plain march");
-  static_assert(!(MASK && (SAVE || TWO)), "the channel mask: three-slot forward marches");
+template <bool ESS, bool MIP, bool PERSP, bool TWO = false, bool MASK = false, bool REG = false>
+__global__ __launch_bounds__(256) void k_march_ring(MarchArgs a) {
+  static_assert(!TWO || !ESS, "two slots: the plain march");
+  static_assert(!(MASK && TWO), "the channel mask: three-slot forward marches");
   static_assert(!REG || TWO, "registers stage the third layer of a two-slot ring");
   constexpr int kSlots = TWO ? 2 : 3;
   extern __shared__ float4 smem[];
@@ -84,11 +80,6 @@ __global__ __launch_bounds__(256) void k_march_ring(MarchArgs a, SaveArgs sa) {
   const int ngroups = (a.ntiles + wpb - 1) / wpb;
   const int per = (ngroups + 7) >> 3;
   int grp = (int)(blockIdx.x & 7) * per + (int)(blockIdx.x >> 3);
-  if (SAVE && sa.band[8] > 0) {
-    // the checkpointing forward: bands of equal estimated work per XCD
-    const int x = (int)(blockIdx.x & 7), g = sa.band[x] + (int)(blockIdx.x >> 3);
-    grp = g < sa.band[x + 1] ? g : ngroups;
-  }
   const int tile = grp * wpb + wave;
   if (tile >= a.ntiles) return;
 
@@ -107,7 +98,7 @@ __global__ __launch_bounds__(256) void k_march_ring(MarchArgs a, SaveArgs sa) {
   // coordinate is monotone along a row); lane r measures the run of row
   // vrow0 + r, and a wave scan numbers the cell's pixels row by row.  The
   // wavefront marches the cell's first 64 pixels.
-  const bool foot = !PERSP && !SAVE && a.foot != 0;
+  const bool foot = !PERSP && a.foot != 0;
   int ci = 0, cj = 0;
   FootRuns fr;
   int tx = 0, ty = 0;
@@ -315,18 +306,11 @@ __global__ __launch_bounds__(256) void k_march_ring(MarchArgs a, SaveArgs sa) {
     Lbeg = uni(wave_imax(c_first));
     Lend = uni(wave_imin(c_last));
   }
-  const int pix = ly * bvw.w + lx;  // SAVE: pixel of the whole-volume image
   if (!force_gather && (up ? Lbeg > Lend : Lbeg < Lend)) {
     if (valid && !a.carry && !foot) *dst = make_float4(0.f, 0.f, 0.f, 0.f);
-    if (SAVE && valid) sa.nused[pix] = 0;
     continue;
   }
   const int nlay = up ? Lend - Lbeg + 1 : Lbeg - Lend + 1;  // cell layers
-  // SAVE: state of the ray at the start of group g (cell layers gK .. gK + K - 1)
-  auto save_group = [&](int g, float Tg) {
-    if (valid) sa.ckpt[(int64_t)g * sa.npix + pix] = Tg;
-  };
-  const int ngrp_tile = SAVE ? (nlay + sa.K - 1) / sa.K : 0;
 
   // ---- window geometry from the tile's corner rays (lanes 0..3)
   // A corner ray meets the plane b = P at f = Af + P rf, g = Ag + P rg.
@@ -399,14 +383,8 @@ __global__ __launch_bounds__(256) void k_march_ring(MarchArgs a, SaveArgs sa) {
   if (force_gather || pitch > chiF + 2 - cloF || pitch * NG > slot || pitch > 256 ||
       ((int64_t)(64 / (pitch >> 2)) * sG + pitch) * 4 >= ((int64_t)1 << 32)) {
     // the window does not fit: read the corners from global memory
-    int gnext = 0;  // SAVE: next group whose start state is to be stored
     while (!done) {
       const Cell c = cell_of(sample_pos(j, px, py, pz, sx, sy, sz), br);
-      if (SAVE) {
-        const int ib = by ? c.iy : c.iz;
-        const int gi = (up ? ib - Lbeg : Lbeg - ib) / sa.K;
-        while (gnext <= gi) save_group(gnext++, T);
-      }
       gfloat* p = gbase + (c.iz * zsl + c.iy * ysl + c.ix);
       const float val = trilerp(p[0], p[1], p[ysl], p[ysl + 1], p[zsl], p[zsl + 1], p[zsl + ysl], p[zsl + ysl + 1], c);
       ++j;
@@ -421,10 +399,6 @@ __global__ __launch_bounds__(256) void k_march_ring(MarchArgs a, SaveArgs sa) {
         accumulate(k, Cr, Cg, Cb, T);
         if (j >= cnt || 1.f - T >= a.tau) done = true;
       }
-    }
-    if (SAVE) {
-      while (gnext <= ngrp_tile) save_group(gnext++, T);
-      if (valid) sa.nused[pix] = j;
     }
     // carried state: only rays with samples here write (another brick of the
     // wave whose rectangle holds the pixel may update it)
@@ -558,7 +532,6 @@ __global__ __launch_bounds__(256) void k_march_ring(MarchArgs a, SaveArgs sa) {
     issue(V0 + vstep, w1, s_ring + slot);
     int s0 = 0;  // slot of V_k
     for (int k = 0; k < nlay; ++k) {
-      if (SAVE && k % sa.K == 0) save_group(k / sa.K, T);
       wait_loads();  // V_k and V_{k+1} are in LDS
       // start V_{k+2} into the slot V_{k-1} used (cell layer c_{k-1} is finished);
       // with two slots, into the slot of V_k once c_k is finished
@@ -603,11 +576,7 @@ __global__ __launch_bounds__(256) void k_march_ring(MarchArgs a, SaveArgs sa) {
           if (j >= cnt || 1.f - T >= a.tau) done = true;
         }
       }
-      if (__all(done)) {
-        if (SAVE)
-          for (int g = k / sa.K + 1; g <= ngrp_tile; ++g) save_group(g, T);
-        break;
-      }
+      if (__all(done)) break;
       if (TWO && k + 1 < nlay) issue(V0 + (k + 2) * vstep, w2, s_ring + s0 * slot);
       s0 = s1;
       w0 = w1;
@@ -724,7 +693,6 @@ __global__ __launch_bounds__(256) void k_march_ring(MarchArgs a, SaveArgs sa) {
     }
   }
   wait_loads();  // no load may still target LDS when the wavefront ends (or the next batch starts)
-  if (SAVE && valid) sa.nused[pix] = j;
   if (valid && wr_ok && (cnt > 0 || (!a.carry && !foot)))
     *dst = MIP ? make_float4(mx, mx, mx, mx) : make_float4(Cr, Cg, Cb, a.carry ? T : 1.f - T);
   } while (false);
@@ -735,8 +703,8 @@ __global__ __launch_bounds__(256) void k_march_ring(MarchArgs a, SaveArgs sa) {
 // lane, its corners read from global memory; the same samples, arithmetic and
 // order as every march.  Wavefronts take listed cells in turn until the list
 // is done.
-template <bool MIP, bool MASK>
-__global__ __launch_bounds__(256) void k_march_ring_ovf(MarchArgs a) {
+template <bool MIP, bool MASK, bool SAVE = false>
+__global__ __launch_bounds__(256) void k_march_ring_ovf(MarchArgs a, SaveArgs sa) {
   extern __shared__ float4 smem[];
   float4* s_tf = smem;
   for (int i = threadIdx.x; i < a.M; i += blockDim.x) s_tf[i] = a.tf[i];
@@ -779,8 +747,16 @@ __global__ __launch_bounds__(256) void k_march_ring_ovf(MarchArgs a) {
       const float sx = (float)(a.step * d[0]), sy = (float)(a.step * d[1]), sz = (float)(a.step * d[2]);
       const int cnt = (int)(k1b - k0b);
       float Cr = c0.x, Cg = c0.y, Cb = c0.z, T = c0.w, mx = 0.f;
-      for (int j = 0; j < cnt;) {
+      [[maybe_unused]] int grp = -1;
+      int j = 0;
+      while (j < cnt) {
         const Cell c = cell_of(sample_pos(j, px, py, pz, sx, sy, sz), br);
+        if constexpr (SAVE) {
+          const int b = a.slab_axis, ib = b == 1 ? c.iy : c.iz;
+          const int gi = (a.cam.e3[b] > 0.0 ? ib - br.clo[b] : br.chi[b] - ib) / sa.K;
+          if (gi != grp) sa.ckpt[(int64_t)gi * sa.npix + vv * a.cam.W + uu] = T;
+          grp = gi;
+        }
         gfloat* p = gb + (c.iz * zs + c.iy * ys + c.ix);
         const float val = trilerp(p[0], p[1], p[ys], p[ys + 1], p[zs], p[zs + 1], p[zs + ys], p[zs + ys + 1], c);
         ++j;
@@ -795,6 +771,10 @@ __global__ __launch_bounds__(256) void k_march_ring_ovf(MarchArgs a) {
           accumulate(k, Cr, Cg, Cb, T);
           if (1.f - T >= a.tau) break;
         }
+      }
+      if constexpr (SAVE) {
+        sa.ckpt[(int64_t)(grp + 1) * sa.npix + vv * a.cam.W + uu] = T;
+        sa.nused[vv * a.cam.W + uu] = j;
       }
       if (a.carry || inr)
         *dst = MIP ? make_float4(mx, mx, mx, mx) : make_float4(Cr, Cg, Cb, a.carry ? T : 1.f - T);
@@ -813,8 +793,9 @@ size_t ring_lds_bytes(const MarchArgs& a, int wpb) {
 
 static hipError_t launch_march_ring_main(const MarchArgs& a, int wpb, hipStream_t s);
 
-hipError_t launch_march_ring(const MarchArgs& a, int wpb, hipStream_t s) {
+hipError_t launch_march_ring(const MarchArgs& a, int wpb, hipStream_t s, const SaveArgs* sa) {
   if (a.ntiles <= 0) return hipSuccess;
+  if (sa && (!a.foot || !a.ring_reg || a.blk_f > 0)) return hipErrorInvalidValue;  // (saved by the cells march)
   if (!a.foot) return launch_march_ring_main(a, wpb, s);
   // footprint cells: clear the overflow list, march, then the listed cells' pixels past the 64th
   // (perspective views: the register-staged cell march only)
@@ -823,14 +804,19 @@ hipError_t launch_march_ring(const MarchArgs& a, int wpb, hipStream_t s) {
   hipError_t e = hipGetLastError();
   if (e != hipSuccess) return e;
   e = a.blk_f > 0 ? launch_march_block(a, s)
-                   : (a.ring_reg ? launch_march_cells(a, wpb, s) : launch_march_ring_main(a, wpb, s));
+                   : (a.ring_reg ? launch_march_cells(a, wpb, s, sa) : launch_march_ring_main(a, wpb, s));
   if (e != hipSuccess) return e;
   const dim3 g(256), b(256);
   const size_t lds = sizeof(float4) * (size_t)a.M;
-  if (a.mip && a.mask) hipLaunchKernelGGL((k_march_ring_ovf<true, true>), g, b, lds, s, a);
-  else if (a.mip) hipLaunchKernelGGL((k_march_ring_ovf<true, false>), g, b, lds, s, a);
-  else if (a.mask) hipLaunchKernelGGL((k_march_ring_ovf<false, true>), g, b, lds, s, a);
-  else hipLaunchKernelGGL((k_march_ring_ovf<false, false>), g, b, lds, s, a);
+  SaveArgs save;
+  std::memset(&save, 0, sizeof save);
+  if (sa) save = *sa;
+  auto go = [&](auto kernel) { hipLaunchKernelGGL(kernel, g, b, lds, s, a, save); };
+  if (sa) go(k_march_ring_ovf<false, false, true>);
+  else if (a.mip && a.mask) go(k_march_ring_ovf<true, true>);
+  else if (a.mip) go(k_march_ring_ovf<true, false>);
+  else if (a.mask) go(k_march_ring_ovf<false, true>);
+  else go(k_march_ring_ovf<false, false>);
   return hipGetLastError();
 }
 
@@ -841,8 +827,6 @@ static hipError_t launch_march_ring_main(const MarchArgs& a, int wpb, hipStream_
   const int grid = ((groups + 7) / 8) * 8;
   // macrocell skipping lives in its own instantiation: its bookkeeping costs
   // registers the plain march does not need
-  SaveArgs none;
-  std::memset(&none, 0, sizeof none);
   const dim3 g(grid), b(64 * wpb);
   const size_t lds = ring_lds_bytes(a, wpb);
   if (a.mip && a.mc > 0) return hipErrorInvalidValue;
@@ -851,47 +835,31 @@ static hipError_t launch_march_ring_main(const MarchArgs& a, int wpb, hipStream_
     // the channel mask lives in instantiations of its own (three slots)
     if (a.ring_nslots == 2) return hipErrorInvalidValue;
     if (a.cam.persp) {
-      if (a.mip) hipLaunchKernelGGL((k_march_ring<false, false, true, true, false, true>), g, b, lds, s, a, none);
-      else if (a.mc > 0) hipLaunchKernelGGL((k_march_ring<true, false, false, true, false, true>), g, b, lds, s, a, none);
-      else hipLaunchKernelGGL((k_march_ring<false, false, false, true, false, true>), g, b, lds, s, a, none);
+      if (a.mip) hipLaunchKernelGGL((k_march_ring<false, true, true, false, true>), g, b, lds, s, a);
+      else if (a.mc > 0) hipLaunchKernelGGL((k_march_ring<true, false, true, false, true>), g, b, lds, s, a);
+      else hipLaunchKernelGGL((k_march_ring<false, false, true, false, true>), g, b, lds, s, a);
     } else {
-      if (a.mip) hipLaunchKernelGGL((k_march_ring<false, false, true, false, false, true>), g, b, lds, s, a, none);
-      else if (a.mc > 0) hipLaunchKernelGGL((k_march_ring<true, false, false, false, false, true>), g, b, lds, s, a, none);
-      else hipLaunchKernelGGL((k_march_ring<false, false, false, false, false, true>), g, b, lds, s, a, none);
+      if (a.mip) hipLaunchKernelGGL((k_march_ring<false, true, false, false, true>), g, b, lds, s, a);
+      else if (a.mc > 0) hipLaunchKernelGGL((k_march_ring<true, false, false, false, true>), g, b, lds, s, a);
+      else hipLaunchKernelGGL((k_march_ring<false, false, false, false, true>), g, b, lds, s, a);
     }
     return hipGetLastError();
   }
   if (a.cam.persp) {
     if (!a.mip && a.mc == 0 && a.ring_nslots == 2 && a.ring_reg)
-      hipLaunchKernelGGL((k_march_ring<false, false, false, true, true, false, true>), g, b, lds, s, a, none);
-    else if (a.mip && a.ring_nslots == 2) hipLaunchKernelGGL((k_march_ring<false, false, true, true, true>), g, b, lds, s, a, none);
-    else if (a.mip) hipLaunchKernelGGL((k_march_ring<false, false, true, true>), g, b, lds, s, a, none);
-    else if (a.mc > 0) hipLaunchKernelGGL((k_march_ring<true, false, false, true>), g, b, lds, s, a, none);
-    else if (a.ring_nslots == 2) hipLaunchKernelGGL((k_march_ring<false, false, false, true, true>), g, b, lds, s, a, none);
-    else hipLaunchKernelGGL((k_march_ring<false, false, false, true>), g, b, lds, s, a, none);
+      hipLaunchKernelGGL((k_march_ring<false, false, true, true, false, true>), g, b, lds, s, a);
+    else if (a.mip && a.ring_nslots == 2) hipLaunchKernelGGL((k_march_ring<false, true, true, true>), g, b, lds, s, a);
+    else if (a.mip) hipLaunchKernelGGL((k_march_ring<false, true, true>), g, b, lds, s, a);
+    else if (a.mc > 0) hipLaunchKernelGGL((k_march_ring<true, false, true>), g, b, lds, s, a);
+    else if (a.ring_nslots == 2) hipLaunchKernelGGL((k_march_ring<false, false, true, true>), g, b, lds, s, a);
+    else hipLaunchKernelGGL((k_march_ring<false, false, true>), g, b, lds, s, a);
   } else {
-    if (a.mip && a.ring_nslots == 2) hipLaunchKernelGGL((k_march_ring<false, false, true, false, true>), g, b, lds, s, a, none);
-    else if (a.mip) hipLaunchKernelGGL((k_march_ring<false, false, true, false>), g, b, lds, s, a, none);
-    else if (a.mc > 0) hipLaunchKernelGGL((k_march_ring<true, false, false, false>), g, b, lds, s, a, none);
-    else if (a.ring_nslots == 2) hipLaunchKernelGGL((k_march_ring<false, false, false, false, true>), g, b, lds, s, a, none);
-    else hipLaunchKernelGGL((k_march_ring<false, false, false, false>), g, b, lds, s, a, none);
+    if (a.mip && a.ring_nslots == 2) hipLaunchKernelGGL((k_march_ring<false, true, false, true>), g, b, lds, s, a);
+    else if (a.mip) hipLaunchKernelGGL((k_march_ring<false, true, false>), g, b, lds, s, a);
+    else if (a.mc > 0) hipLaunchKernelGGL((k_march_ring<true, false, false>), g, b, lds, s, a);
+    else if (a.ring_nslots == 2) hipLaunchKernelGGL((k_march_ring<false, false, false, true>), g, b, lds, s, a);
+    else hipLaunchKernelGGL((k_march_ring<false, false, false>), g, b, lds, s, a);
   }
-  return hipGetLastError();
-}
-
-hipError_t launch_march_ring_save(const MarchArgs& a, const SaveArgs& sa, int wpb, hipStream_t s) {
-  if (a.ntiles <= 0) return hipSuccess;
-  if (a.tile_w != 8 || a.ring_slot <= 0 || (a.ring_slot & 3) != 0 || (wpb != 1 && wpb != 2 && wpb != 4) ||
-      a.mc != 0 || a.mip != 0 || a.cam.persp != 0 || a.ring_nslots == 2 || sa.K < 1)
-    return hipErrorInvalidValue;
-  const int groups = (a.ntiles + wpb - 1) / wpb;
-  int grid = ((groups + 7) / 8) * 8;
-  if (sa.band[8] > 0) {
-    int widest = 0;
-    for (int x = 0; x < 8; x++) widest = std::max(widest, sa.band[x + 1] - sa.band[x]);
-    grid = 8 * widest;
-  }
-  hipLaunchKernelGGL((k_march_ring<false, true, false, false>), dim3(grid), dim3(64 * wpb), ring_lds_bytes(a, wpb), s, a, sa);
   return hipGetLastError();
 }
 

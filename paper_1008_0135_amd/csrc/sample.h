@@ -154,9 +154,15 @@ __device__ __forceinline__ void accumulate_lanes(const Classified& k, float& Cr,
 #undef VR_ROW
 #undef VR_LANE_OPERANDS
 
+// The same with `other` for lanes whose source lies outside the row.
+template <int CTRL>
+__device__ __forceinline__ float dpp_or(float v, float other) {
+  return __int_as_float(__builtin_amdgcn_update_dpp(__float_as_int(other), __float_as_int(v), CTRL, 0xf, 0xf, false));
+}
+
 template <int D, int I>
-__device__ __forceinline__ void accumulate_until(const Classified& k, float tau, bool& done, float& Cr, float& Cg,
-                                                 float& Cb, float& T) {
+__device__ __forceinline__ void accumulate_until(const Classified& k, float tau, bool& done, int& taken, float& Cr,
+                                                 float& Cg, float& Cb, float& T) {
   if constexpr (I < D) {
     constexpr int ctrl = D == 4 ? 0x55 * I : 0x150 + I;
     Classified q;
@@ -167,17 +173,18 @@ __device__ __forceinline__ void accumulate_until(const Classified& k, float tau,
     if (!done) {
       accumulate(q, Cr, Cg, Cb, T);
       done = 1.f - T >= tau;
+      ++taken;
     }
-    accumulate_until<D, I + 1>(k, tau, done, Cr, Cg, Cb, T);
+    accumulate_until<D, I + 1>(k, tau, done, taken, Cr, Cg, Cb, T);
   }
 }
 
 // The group's steps with early termination; true once the ray has stopped.
 // T only falls, so a stop shows after the group, which is then taken again one
-// sample at a time from its start.
+// sample at a time from its start (taken: samples up to the stop, then).
 template <int D>
 __device__ __forceinline__ bool accumulate_group(const Classified& k, float tau, float& Cr, float& Cg, float& Cb,
-                                                 float& T) {
+                                                 float& T, int* taken = nullptr) {
   const float Cr0 = Cr, Cg0 = Cg, Cb0 = Cb, T0 = T;
   accumulate_lanes<D>(k, Cr, Cg, Cb, T);
   if (!(1.f - T >= tau)) return false;
@@ -186,7 +193,9 @@ __device__ __forceinline__ bool accumulate_group(const Classified& k, float tau,
   Cb = Cb0;
   T = T0;
   bool done = false;
-  accumulate_until<D, 0>(k, tau, done, Cr, Cg, Cb, T);
+  int n = 0;
+  accumulate_until<D, 0>(k, tau, done, n, Cr, Cg, Cb, T);
+  if (taken) *taken = n;
   return true;
 }
 

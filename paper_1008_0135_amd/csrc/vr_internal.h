@@ -299,12 +299,18 @@ struct CompArgs {
 
 // Differentiable path (whole volume).  Checkpoints are stored [segment][pixel].
 struct SaveArgs {
-  float* ckpt;        // sample segments: T before samples 0, K, 2K, ... [segment][pixel];
-                      // layer groups: T at the start of each group, then at the ray's end [group][pixel]
+  float* ckpt;        // sample segments: T before samples 0, K, 2K, ... [segment][pixel]; layer groups
+                      // (K cell layers along the slab axis, counted in marching order from the box's
+                      // first): T at the ray's start of each group it has samples in, then at its
+                      // end [group][pixel]
   int32_t* nused;     // samples applied per ray (early termination included)
   int32_t K;          // samples per segment, or cell layers per group
   int32_t npix;       // W * H
-  int32_t band[9];    // ring march: tile groups per XCD, as BwdArgs::band (band[8] == 0: equal counts)
+  // layer groups taken by `parts` workgroups per tile, part_groups each: in
+  // sums[part][pixel] what a ray has gathered in front of the part (r, g, b, a;
+  // unnormalised), in sums[0] all it gathers
+  int32_t parts, part_groups;
+  double4* sums;
 };
 
 struct BwdArgs {
@@ -323,6 +329,8 @@ struct BwdArgs {
   // estimated work.  band[8] == 0: equal counts of groups
   int32_t band[9];
   int32_t* flag;      // set to 1 when a ray's group held more than smax samples
+  int32_t parts, part_groups;  // as SaveArgs
+  const double4* sums;
 };
 
 // Batched rendering: one descriptor per request (whole volume, own view,
@@ -369,18 +377,17 @@ hipError_t launch_carry(float4* img, int64_t n, bool final, hipStream_t s);
 hipError_t launch_zero(float4* img, int64_t n, hipStream_t s);
 // Ring march (march_ring.hip): 8 x 8 tiles, a.ring_slot floats per window slot,
 // `wpb` wavefronts per workgroup (1, 2 or 4).
-hipError_t launch_march_ring(const MarchArgs& a, int wpb, hipStream_t s);
+hipError_t launch_march_ring(const MarchArgs& a, int wpb, hipStream_t s, const SaveArgs* sa = nullptr);
 size_t ring_lds_bytes(const MarchArgs& a, int wpb);
 // footprint cells: a wavefront per cell, windows staged through registers
 // (the host keeps a lane's offset inside a window's rows below 4 GiB), or
 // blocks of a.blk_f x a.blk_g cells per workgroup
-hipError_t launch_march_cells(const MarchArgs& a, int wpb, hipStream_t s);
+hipError_t launch_march_cells(const MarchArgs& a, int wpb, hipStream_t s, const SaveArgs* sa = nullptr);
 size_t cells_lds_bytes(const MarchArgs& a, int wpb);
 hipError_t launch_march_block(const MarchArgs& a, hipStream_t s);
 size_t block_lds_bytes(const MarchArgs& a);
 // Differentiable forward on the ring layout (whole volume): also stores the
 // per-group checkpoints of sa (layer groups of sa.K cell layers).
-hipError_t launch_march_ring_save(const MarchArgs& a, const SaveArgs& sa, int wpb, hipStream_t s);
 // Adjoint on the ring layout (grad_ring.hip): layer groups of ba.K cell layers.
 // T by division by 1 - a only for tables whose opacity stays at most this: the
 // error of a, about 1e-5 relative from the forward's single-precision
@@ -400,6 +407,9 @@ constexpr int kBrickRangePlanes = 2;  // z-planes of one workgroup of the brick 
 // zgroups groups of zper planes; scratch holds nb*zgroups float2 partials.
 hipError_t launch_brick_minmax_parts(const float* vol, const int64_t n[3], const int64_t* boxes, int32_t nb,
                                      int zgroups, int zper, float* scratch, float* out2, hipStream_t s);
+// checkpointing forwards: layer groups along a.slab_axis (16 lanes per ray, tiles of 2 x 2 pixels; cells by
+// launch_march_ring) and sample segments
+hipError_t launch_march_save(const MarchArgs& a, const SaveArgs& sa, hipStream_t s);
 hipError_t launch_fwd_save(const MarchArgs& a, const SaveArgs& sa, hipStream_t s);
 hipError_t launch_bwd(const MarchArgs& a, const BwdArgs& ba, hipStream_t s);
 int bwd_blocks(const MarchArgs& a);
