@@ -860,7 +860,7 @@ static int make_twin(vr_volume* vol, int32_t macrocell, hipStream_t s) {
   VR_TRY(make_whole_brick(t));
   Partition P;
   std::vector<int32_t> src_brick;
-  permute_partition(vol->part, t->n, P, src_brick);
+  permute_partition(vol->part, t->n, P, &src_brick);
   VR_TRY(brick_volume(t, P, false, macrocell, vol, src_brick, s));
   t->version++;
   return VR_OK;
@@ -1150,8 +1150,7 @@ int vr_plan_cells(const int64_t dims[3], const vr_brick_spec* spec, const vr_vie
     n[1] = dims[2];
     n[2] = dims[0];
     Partition Q;
-    std::vector<int32_t> src;
-    permute_partition(P, n, Q, src);
+    permute_partition(P, n, Q);
     P = Q;
   }
   Camera cam;

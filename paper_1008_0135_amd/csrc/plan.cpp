@@ -107,25 +107,25 @@ bool make_kd(const int64_t n[3], int32_t nparts, Partition& out, std::string& er
 }
 
 // src[b]: the brick of p that brick b of the copy is.
-void permute_partition(const Partition& p, const int64_t n_twin[3], Partition& out, std::vector<int32_t>& src) {
+void permute_partition(const Partition& p, const int64_t n_twin[3], Partition& out, std::vector<int32_t>* src) {
   // axis a of the volume is axis t[a] of the copy
   static const int t[3] = {2, 0, 1};
-  src.resize(p.boxes.size());
+  if (src) src->resize(p.boxes.size());
   if (p.mode == VR_BRICK_GRID) {
     int64_t size[3];
     for (int a = 0; a < 3; a++) size[t[a]] = p.gsize[a];
     std::string err;
     make_grid(n_twin, size, out, err);  // cannot fail: the same counts as p
-    for (size_t b = 0; b < src.size(); b++) {
+    for (size_t b = 0; src && b < src->size(); b++) {
       int32_t k[3];  // indices of the copy's brick along its axes
       k[0] = (int32_t)b % out.gcount[0];
       k[1] = (int32_t)b / out.gcount[0] % out.gcount[1];
       k[2] = (int32_t)b / out.gcount[0] / out.gcount[1];
-      src[b] = (k[t[2]] * p.gcount[1] + k[t[1]]) * p.gcount[0] + k[t[0]];
+      (*src)[b] = (k[t[2]] * p.gcount[1] + k[t[1]]) * p.gcount[0] + k[t[0]];
     }
     return;
   }
-  for (size_t b = 0; b < src.size(); b++) src[b] = (int32_t)b;
+  for (size_t b = 0; src && b < src->size(); b++) (*src)[b] = (int32_t)b;
   out = Partition();
   out.mode = p.mode;
   out.boxes.resize(p.boxes.size());
