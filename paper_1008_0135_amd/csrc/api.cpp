@@ -406,7 +406,6 @@ int vr_create(int device, vr_ctx** out) {
   }
   if (const char* m = std::getenv("VR_FOOT_PAD")) ctx->foot_pad = std::max(0, std::min(32, std::atoi(m)));
   if (const char* m = std::getenv("VR_FOOT_KMAX")) ctx->foot_kmax = std::max(1, std::min(4, std::atoi(m)));
-  if (const char* m = std::getenv("VR_PERSP_CLASSES")) ctx->persp_classes = std::max(1, std::min(4, std::atoi(m)));
   if (const char* m = std::getenv("VR_PERSP_CELLS")) ctx->persp_cells = std::atoi(m) != 0 ? 1 : 0;
   if (const char* m = std::getenv("VR_PERSP_KMAX")) ctx->persp_kmax = std::max(1, std::min(4, std::atoi(m)));
   if (const char* m = std::getenv("VR_CELLS_WPB")) {
@@ -414,10 +413,6 @@ int vr_create(int device, vr_ctx** out) {
     ctx->cells_wpb = (k == 1 || k == 2 || k == 4) ? k : 0;
   }
   if (const char* m = std::getenv("VR_DEBUG_PLAN")) ctx->debug_plan = std::atoi(m) != 0;
-  if (const char* m = std::getenv("VR_PERSP_FIT")) {
-    const double f = std::atof(m);
-    if (f >= 0.3 && f <= 1.0) ctx->persp_fit = f;
-  }
   if (const char* m = std::getenv("VR_FOOT_MAXPX")) ctx->foot_maxpx = std::max(16, std::min(4096, std::atoi(m)));
   if (const char* m = std::getenv("VR_FOOT_RAYS")) {
     const double r = std::atof(m);

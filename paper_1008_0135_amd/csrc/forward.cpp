@@ -217,7 +217,7 @@ void plan_bricked_view(const vr_volume* vol, const Camera& cam, const vr_params*
 }
 
 int render_forward(vr_ctx* ctx, vr_volume* vol, const vr_view* views, int32_t nviews, const vr_params* p,
-                   float* out, hipStream_t s, ForwardExtras* extras) {
+                   float* out, hipStream_t s) {
   const bool bricked = vol->bricked;
   const int32_t W = views[0].W, H = views[0].H;
   double vmin, vmax;
@@ -236,13 +236,13 @@ int render_forward(vr_ctx* ctx, vr_volume* vol, const vr_view* views, int32_t nv
     base.mask = ctx->d_mask;
     base.mask_n = ctx->mask_n;
   }
-  if (!extras) VR_TRY(prepare_macrocells(ctx, vol, p, vmin, vmax, base, s));
+  VR_TRY(prepare_macrocells(ctx, vol, p, vmin, vmax, base, s));
   const int32_t tw = base.tile_w, th = base.tile_h;
   // opacity tested over the whole ray: bricks marched in front-to-back waves
   // straight into the frame, each ray carrying its state from brick to brick
-  const bool global = bricked && out && !extras && !base.mip && p->ert_scope == VR_ERT_GLOBAL;
+  const bool global = bricked && out && !base.mip && p->ert_scope == VR_ERT_GLOBAL;
   // the march is chosen per view (the default shapes and no forced march)
-  const bool pick = !extras && (mode == 0 || mode == 3) && tw == 8;
+  const bool pick = (mode == 0 || mode == 3) && tw == 8;
   if (pick && base.mc > 0) {
     // few clear macrocells: what the walk from macrocell to macrocell and the
     // 16-sample blocks around the others cost outweighs the samples saved (a
@@ -354,8 +354,8 @@ int render_forward(vr_ctx* ctx, vr_volume* vol, const vr_view* views, int32_t nv
   for (int32_t v = 0; v < nviews; v++) {
     ViewPlan& vp = plans[v];
     if (!pick || !cams[v].persp || vp.bv.empty() || vp.deep || global) continue;
-    const bool cells = bricked && ctx->persp_cells && (!base.mask || base.mask_n <= kCellsMaskMax) && ctx->ring_reg > 0 && ctx->ring_nslots != 3 &&
-                       cams[v].S / W >= kPerspCellPitch && persp_faster(cams[v], vp);
+    const bool cells = bricked && ctx->persp_cells && (!base.mask || base.mask_n <= kCellsMaskMax) &&
+                       ctx->ring_reg > 0 && ctx->ring_nslots != 3 && cams[v].S / W >= kPerspCellPitch && persp_faster(cams[v], vp);
     const int first_axis = std::fabs(cams[v].e3[1]) >= std::fabs(cams[v].e3[2]) ? 1 : 2;
     std::vector<int32_t> axis(vp.bv.size(), 0);
     bool any = false;
@@ -438,8 +438,8 @@ int render_forward(vr_ctx* ctx, vr_volume* vol, const vr_view* views, int32_t nv
       }
     }
     auto shape = [&](bool plain) {
-      return ctx->foot && pick_foot(cams[v], vol->n, plain ? table_rows : base.M, plain, ctx->ring_reg > 0, ctx->ring_nslots,
-                                    ctx->foot_rays, ctx->foot_pad, ctx->foot_kmax, fs, ctx->foot_maxpx);
+      return ctx->foot && pick_foot(cams[v], vol->n, plain ? table_rows : base.M, plain, ctx->ring_reg > 0,
+                                    ctx->ring_nslots, ctx->foot_rays, ctx->foot_pad, ctx->foot_kmax, fs, ctx->foot_maxpx);
     };
     bool cells = shape(base.mc == 0 && (!base.mask || base.mask_n <= kCellsMaskMax));
     // a channel mask: register-staged cells or three slots
@@ -563,7 +563,6 @@ int render_forward(vr_ctx* ctx, vr_volume* vol, const vr_view* views, int32_t nv
       a.bricks = reinterpret_cast<const DevBrick*>(dt);
       a.img = reinterpret_cast<float4*>(out);
     }
-    if (extras) extras->prepare(a, v);
     bool lds = false, ring = false;
     int ring_wpb = 4;
     a.lds_budget = budget;
@@ -597,7 +596,7 @@ int render_forward(vr_ctx* ctx, vr_volume* vol, const vr_view* views, int32_t nv
         VR_HIP(launch_zero(bricked ? arena : reinterpret_cast<float4*>(out) + (int64_t)v * W * H,
                            bricked ? vp.pixels : (int64_t)W * H, s));
       }
-    } else if (!extras && (mode == 0 || mode == 3) && a.tile_w == 8) {
+    } else if ((mode == 0 || mode == 3) && a.tile_w == 8) {
       if (!cams[v].persp && !vp.deep) {
         int32_t waves3 = 0;
         ring = choose_ring(cams[v], kRingCap, a.M, kRingMaxWaves, kRingWantWaves, kRingMinWaves, a.slab_axis,
@@ -610,8 +609,7 @@ int render_forward(vr_ctx* ctx, vr_volume* vol, const vr_view* views, int32_t nv
         // lookahead: 12 -> 16 wavefronts took one view from 12.1 to 9.3 ms, a
         // fourth slot at fewer wavefronts cost 35 %), or when forced; plain
         // march and maximum intensity projection only
-        const bool plain = a.mc == 0 && !a.mask;
-        if (ring && plain && ctx->ring_nslots != 3) {
+        if (ring && !a.mask && ctx->ring_nslots != 3) {
           int32_t ax2 = 0, slot2 = 0, wpb2 = 4, waves2 = 0;
           if (choose_ring(cams[v], kRingCap, a.M, kRingMaxWaves, kRingWantWaves, kRingMinWaves, ax2, slot2, wpb2, 2,
                           &waves2) &&
@@ -632,7 +630,8 @@ int render_forward(vr_ctx* ctx, vr_volume* vol, const vr_view* views, int32_t nv
       a.tile_bw = ctx->tile_bw;
       a.tile_bh = ctx->tile_bh;
     }
-    if (!ring && !extras && mode != 1 && !a.mip && !a.mask && !vp.deep && vp.class_begin.empty()) {  // (the slab march has no MIP and no mask)
+    // (the slab march has no MIP and no mask)
+    if (!ring && mode != 1 && !a.mip && !a.mask && !vp.deep && vp.class_begin.empty()) {
       lds = choose_slab(cams[v], a.tile_w, a.tile_h, budget, a.slab_axis, a.slab_T);
       // rays nearly parallel to axis 1 need a wider slab box: retry with twice the budget
       if (!lds && budget < 8192 && choose_slab(cams[v], a.tile_w, a.tile_h, 8192, a.slab_axis, a.slab_T)) {
@@ -710,8 +709,7 @@ int render_forward(vr_ctx* ctx, vr_volume* vol, const vr_view* views, int32_t nv
         VR_HIP(launch_march_ring(ac, cwpb, s));
       }
     } else {
-      VR_HIP(extras ? extras->launch(a, s)
-                    : (ring ? launch_march_ring(a, ring_wpb, s) : (lds ? launch_march_lds(a, s) : launch_march(a, s))));
+      VR_HIP(ring ? launch_march_ring(a, ring_wpb, s) : (lds ? launch_march_lds(a, s) : launch_march(a, s)));
     }
     VR_TRY(stage_end(ctx, s));
     if (bricked && out) {
@@ -730,10 +728,6 @@ int render_forward(vr_ctx* ctx, vr_volume* vol, const vr_view* views, int32_t nv
   }
   if (side) VR_TRY(aux_join(ctx, s));
   if (global) VR_TRY(stage_end(ctx, s));
-  if (extras) {
-    extras->vmin = vmin;
-    extras->vmax = vmax;
-  }
   return VR_OK;
 }
 
@@ -770,7 +764,7 @@ int vr_render(vr_ctx* ctx, const vr_volume* cvol, const vr_view* views, int32_t 
   if (save) return render_with_state(ctx, vol, views, nviews, p, out, s, save);
   VR_TRY(ctx_begin(ctx, s));
   if (!vol->twin || !vol->bricked) {
-    VR_TRY(render_forward(ctx, vol, views, nviews, p, out, s, nullptr));
+    VR_TRY(render_forward(ctx, vol, views, nviews, p, out, s));
     return ctx_end(ctx, s);
   }
   // views looking mostly along axis 1 (the contiguous one) are rendered from
@@ -793,9 +787,9 @@ int vr_render(vr_ctx* ctx, const vr_volume* cvol, const vr_view* views, int32_t 
           q.R[3 * r + 1] = z;
           q.R[3 * r + 2] = x;
         }
-      VR_TRY(render_forward(ctx, vol->twin, pv.data(), v1 - v0, p, out + v0 * frame, s, nullptr));
+      VR_TRY(render_forward(ctx, vol->twin, pv.data(), v1 - v0, p, out + v0 * frame, s));
     } else {
-      VR_TRY(render_forward(ctx, vol, views + v0, v1 - v0, p, out + v0 * frame, s, nullptr));
+      VR_TRY(render_forward(ctx, vol, views + v0, v1 - v0, p, out + v0 * frame, s));
     }
     v0 = v1;
   }
@@ -826,7 +820,7 @@ int vr_render_bricks(vr_ctx* ctx, const vr_volume* cvol, const vr_view* view, co
   plan_bricked_view(vol, cam, p, tw, ctx->h_tf.data(), ctx->tf_m, vmin, vmax, vp);
   if ((int32_t)vp.bv.size() > *nimg)
     return fail(VR_EINVAL, "capacity %d below the %d rendered bricks", *nimg, (int)vp.bv.size());
-  VR_TRY(render_forward(ctx, vol, view, 1, p, nullptr, s, nullptr));
+  VR_TRY(render_forward(ctx, vol, view, 1, p, nullptr, s));
   float4* arena = reinterpret_cast<float4*>(ctx->d_arena);
   for (size_t i = 0; i < vp.bv.size(); i++) {
     const DevBrickView& b = vp.bv[i];

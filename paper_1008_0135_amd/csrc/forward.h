@@ -33,15 +33,6 @@ struct ViewPlan {
   FootShape fs;
 };
 
-// Hook that replaces the march launch (the differentiable forward saves
-// per-ray state from its own kernel variant).
-struct ForwardExtras {
-  virtual ~ForwardExtras() {}
-  virtual void prepare(MarchArgs& a, int32_t view) = 0;
-  virtual hipError_t launch(const MarchArgs& a, hipStream_t s) = 0;
-  double vmin = 0.0, vmax = 0.0;
-};
-
 struct MarchTimes {
   double cells = 1e30, gather = 0.0;  // seconds
   double samples = 0.0, chain = 0.0;  // samples, and the part of cells that is a wavefront's chain
@@ -75,7 +66,7 @@ int32_t foot_brick(const Camera& cam, const FootShape& fs, const Box& box, DevBr
 void plan_bricked_view(const vr_volume* vol, const Camera& cam, const vr_params* p, int32_t tile_w,
                        const float* tf, int32_t M, double vmin, double vmax, ViewPlan& vp, bool waves = false);
 int render_forward(vr_ctx* ctx, vr_volume* vol, const vr_view* views, int32_t nviews, const vr_params* p, float* out,
-                   hipStream_t s, ForwardExtras* extras);
+                   hipStream_t s);
 int validate_render(vr_ctx* ctx, const vr_volume* vol, const vr_view* views, int32_t nviews, const vr_params* p);
 int render_with_state(vr_ctx* ctx, vr_volume* vol, const vr_view* views, int32_t nviews, const vr_params* p,
                       float* out, hipStream_t s, vr_state** save);

@@ -30,15 +30,6 @@
 // output frame holding each ray's (C, T) from the bricks in front of this
 // one; a ray starts from it (and not at all once 1 - T >= tau) and leaves its
 // new state there.
-//
-// Perspective views (PERSP): the tile's rays leave one eye, so their
-// directions are positive combinations of the four corner directions; when
-// the corner rays all move the same way along b, every ray of the tile meets
-// a plane b = P inside the range the corner rays span there, and the window
-// of layer V is the box of the four corner lines over [V - 1, V + 1] (its size
-// grows with depth: the bound is taken at the tile's first and last layer,
-// where the convex width is largest).  A tile whose corner rays disagree on
-// the direction along b samples from global memory.
 #include <cstring>
 
 #include "ring_common.h"
@@ -53,17 +44,10 @@ using namespace ring;
 
 constexpr int kSlotsMax = 3;
 
-// MIP: maximum intensity projection (no table, no skipping).
-// REG (two slots, perspective views): the window of the layer after next is
-// loaded into registers while the current cell layer is sampled and written
-// over the finished layer afterwards, for tiles whose window takes at most
-// kRingRegLoads loads per lane (the others load straight into LDS), so every
-// wavefront keeps a layer in flight without a third slot.
-template <bool ESS, bool MIP, bool PERSP, bool TWO = false, bool MASK = false, bool REG = false>
+// MIP: maximum intensity projection (no table).
+template <bool MIP, bool TWO, bool MASK>
 __global__ __launch_bounds__(256) void k_march_ring(MarchArgs a) {
-  static_assert(!TWO || !ESS, "two slots: the plain march");
   static_assert(!(MASK && TWO), "the channel mask: three-slot forward marches");
-  static_assert(!REG || TWO, "registers stage the third layer of a two-slot ring");
   constexpr int kSlots = TWO ? 2 : 3;
   extern __shared__ float4 smem[];
   float4* s_tf = smem;
@@ -98,7 +82,7 @@ __global__ __launch_bounds__(256) void k_march_ring(MarchArgs a) {
   // coordinate is monotone along a row); lane r measures the run of row
   // vrow0 + r, and a wave scan numbers the cell's pixels row by row.  The
   // wavefront marches the cell's first 64 pixels.
-  const bool foot = !PERSP && a.foot != 0;
+  const bool foot = a.foot != 0;
   int ci = 0, cj = 0;
   FootRuns fr;
   int tx = 0, ty = 0;
@@ -174,15 +158,9 @@ __global__ __launch_bounds__(256) void k_march_ring(MarchArgs a) {
   const bool inrect = lx >= 0 && lx < bvw.w && ly >= 0 && ly < bvw.h;
 
   // ---- per-lane ray setup (double precision, shared with every march)
-  double o[3], dl[3];
-  const double* d;
-  if constexpr (PERSP) {
-    pixel_ray(a.cam, u, v, o, dl);
-    d = dl;
-  } else {
-    d = a.cam.e3;
-    pixel_origin(a.cam, u, v, o);
-  }
+  double o[3];
+  const double* d = a.cam.e3;
+  pixel_origin(a.cam, u, v, o);
   int cnt = 0;
   float px = 0.f, py = 0.f, pz = 0.f;
   float4* const dst =
@@ -206,91 +184,14 @@ __global__ __launch_bounds__(256) void k_march_ring(MarchArgs a) {
   }
   const float sx = (float)(a.step * d[0]), sy = (float)(a.step * d[1]), sz = (float)(a.step * d[2]);
 
-  // range of four lines x = A[c] + P r[c] over the planes [P0, P1] (P0 <= P1)
-  auto crange = [](const float* A, const float* r, float P0, float P1, float& lo, float& hi) {
-    lo = INFINITY;
-    hi = -INFINITY;
-    for (int c = 0; c < 4; ++c) {
-      const float x0 = fmaf(P0, r[c], A[c]), x1 = fmaf(P1, r[c], A[c]);
-      lo = fminf(lo, fminf(x0, x1));
-      hi = fmaxf(hi, fmaxf(x0, x1));
-    }
-  };
-
   // ---- frame: b = slab axis (axis 2 or 3), g = the other of axes 2/3, f = axis 1
-  // PERSP: the corner rays of the tile (lane l holds corner l & 3) pick the
-  // axis per tile: of the axes along which all four move the same way, the one
-  // whose window over the brick's layers is smaller (rays from an eye turn
-  // across the image, so no one axis suits every tile)
-  bool by = a.slab_axis == 1;
-  bool force_gather = false;
-  double oc[3] = {0.0, 0.0, 0.0}, dc[3] = {0.0, 0.0, 1.0};
-  if constexpr (PERSP) {
-    const int cx = bvw.x0 + tx * 8, cy = bvw.y0 + ty * 8;
-    const int ex = min(cx + 7, bvw.x0 + bvw.w - 1), ey = min(cy + 7, bvw.y0 + bvw.h - 1);
-    const int cc = lane & 3;
-    pixel_ray(a.cam, (cc & 1) ? ex : cx, (cc & 2) ? ey : cy, oc, dc);
-    int pick = 0;
-    int best = 0x7fffffff;
-    for (int bb = 1; bb <= 2; ++bb) {
-      const double dcb = dc[bb];
-      const bool upb = uni(dcb > 0.0 ? 1 : 0) != 0;
-      if (wany(!(fabs(dcb) > 1e-6) || (dcb > 0.0) != upb)) continue;
-      const int gg = 3 - bb;
-      const double rfd = dc[0] / dcb, rgd = dc[gg] / dcb;
-      const double ob = oc[bb] - (double)br.lo[bb];
-      const float A_f = (float)(oc[0] - (double)br.lo[0] - ob * rfd);
-      const float A_g = (float)(oc[gg] - (double)br.lo[gg] - ob * rgd);
-      float qA[4], qr[4], qB[4], qs[4];
-      for (int c = 0; c < 4; ++c) {
-        qA[c] = lanef(A_f, c);
-        qr[c] = lanef((float)rfd, c);
-        qB[c] = lanef(A_g, c);
-        qs[c] = lanef((float)rgd, c);
-      }
-      const float Va = (float)br.clo[bb], Vb = (float)(br.chi[bb] + 1);
-      float l0, h0, l1, h1;
-      crange(qA, qr, Va - 1.f, Va + 1.f, l0, h0);
-      crange(qA, qr, Vb - 1.f, Vb + 1.f, l1, h1);
-      const float wf = fmaxf(h0 - l0, h1 - l1);
-      crange(qB, qs, Va - 1.f, Va + 1.f, l0, h0);
-      crange(qB, qs, Vb - 1.f, Vb + 1.f, l1, h1);
-      const float wg = fmaxf(h0 - l0, h1 - l1);
-      if (!(wf < 4096.f && wg < 4096.f)) continue;
-      const int nf = (((int)floorf(wf + 0.2f) + 3) + 3) & ~3;
-      const int ng = min((int)floorf(wg + 0.2f) + 3, br.chi[gg] + 2 - br.clo[gg]);
-      const int size = uni(nf * ng);
-      if (size < best) {
-        best = size;
-        pick = bb;
-      }
-    }
-    if (pick == 0) force_gather = true;
-    else by = uni(pick) == 1;
-  }
+  const bool by = a.slab_axis == 1;
   const float pb = by ? py : pz, sb = by ? sy : sz;
   const int cloB = by ? br.clo[1] : br.clo[2], chiB = by ? br.chi[1] : br.chi[2];
   const int cloG = by ? br.clo[2] : br.clo[1], chiG = by ? br.chi[2] : br.chi[1];
   const int cloF = br.clo[0], chiF = br.chi[0];
   const double db = by ? d[1] : d[2], dg = by ? d[2] : d[1];
-  // PERSP: the corner lines f = Afc + P rfc, g = Agc + P rgc on the planes
-  // b = P bound the bundle
-  float Afc = 0.f, Agc = 0.f, rfc = 0.f, rgc = 0.f;
-  bool up;
-  if constexpr (PERSP) {
-    const double dcb = by ? dc[1] : dc[2], dcg = by ? dc[2] : dc[1];
-    up = uni(dcb > 0.0 ? 1 : 0) != 0;
-    if (!force_gather) {
-      const double rfd = dc[0] / dcb, rgd = dcg / dcb;
-      const double ob = (by ? oc[1] : oc[2]) - (double)(by ? br.lo[1] : br.lo[2]);
-      Afc = (float)(oc[0] - (double)br.lo[0] - ob * rfd);
-      Agc = (float)((by ? oc[2] : oc[1]) - (double)(by ? br.lo[2] : br.lo[1]) - ob * rgd);
-      rfc = (float)rfd;
-      rgc = (float)rgd;
-    }
-  } else {
-    up = db > 0.0;
-  }
+  const bool up = db > 0.0;
 
   // cell layers (along b) of the lane's first and last samples
   int c_first = up ? 0x7fffffff : -0x7fffffff, c_last = up ? -0x7fffffff : 0x7fffffff;
@@ -306,7 +207,7 @@ __global__ __launch_bounds__(256) void k_march_ring(MarchArgs a) {
     Lbeg = uni(wave_imax(c_first));
     Lend = uni(wave_imin(c_last));
   }
-  if (!force_gather && (up ? Lbeg > Lend : Lbeg < Lend)) {
+  if (up ? Lbeg > Lend : Lbeg < Lend) {
     if (valid && !a.carry && !foot) *dst = make_float4(0.f, 0.f, 0.f, 0.f);
     continue;
   }
@@ -314,10 +215,10 @@ __global__ __launch_bounds__(256) void k_march_ring(MarchArgs a) {
 
   // ---- window geometry from the tile's corner rays (lanes 0..3)
   // A corner ray meets the plane b = P at f = Af + P rf, g = Ag + P rg.
-  const double rfd = PERSP ? 0.0 : d[0] / db, rgd = PERSP ? 0.0 : dg / db;
+  const double rfd = d[0] / db, rgd = dg / db;
   const float rf = (float)rfd, rg = (float)rgd;
   float Af = 0.f, Ag = 0.f;
-  if (!PERSP && !foot) {
+  if (!foot) {
     const int cx = bvw.x0 + tx * 8, cy = bvw.y0 + ty * 8;
     const int ex = min(cx + 7, bvw.x0 + bvw.w - 1), ey = min(cy + 7, bvw.y0 + bvw.h - 1);
     const int cc = lane & 3;
@@ -336,34 +237,9 @@ __global__ __launch_bounds__(256) void k_march_ring(MarchArgs a) {
     Ag_hi = (float)((double)(cj + 1) * a.foot_Tg);
   }
   const float arf = fabsf(rf), arg = fabsf(rg);
-  // PERSP: the four corner lines as uniform values
-  float cAf[4], crf[4], cAg[4], crg[4];
-  if constexpr (PERSP)
-    for (int c = 0; c < 4; ++c) {
-      cAf[c] = lanef(Afc, c);
-      crf[c] = lanef(rfc, c);
-      cAg[c] = lanef(Agc, c);
-      crg[c] = lanef(rgc, c);
-    }
   // window extents: f_hi - f_lo + 1 <= floor(span + 0.1) + 3 for the 0.05 margins
   int NF, NG;
-  if constexpr (PERSP) {
-    if (force_gather) {
-      NF = 1 << 20;
-      NG = 1;
-    } else {
-      // the span over [V - 1, V + 1] is convex in V: largest at the first or
-      // last voxel layer the tile loads
-      const float Va = (float)(up ? Lbeg : Lbeg + 1), Vb = (float)(up ? Lend + 1 : Lend);
-      float l0, h0, l1, h1;
-      crange(cAf, crf, Va - 1.f, Va + 1.f, l0, h0);
-      crange(cAf, crf, Vb - 1.f, Vb + 1.f, l1, h1);
-      NF = uni((int)floorf(fmaxf(h0 - l0, h1 - l1) + 0.2f) + 3);
-      crange(cAg, crg, Va - 1.f, Va + 1.f, l0, h0);
-      crange(cAg, crg, Vb - 1.f, Vb + 1.f, l1, h1);
-      NG = uni((int)floorf(fmaxf(h0 - l0, h1 - l1) + 0.2f) + 3);
-    }
-  } else if (foot) {
+  if (foot) {
     NF = a.foot_nf;
     NG = a.foot_ng;
   } else {
@@ -380,7 +256,7 @@ __global__ __launch_bounds__(256) void k_march_ring(MarchArgs a) {
   int j = 0;
   bool done = cnt == 0;
 
-  if (force_gather || pitch > chiF + 2 - cloF || pitch * NG > slot || pitch > 256 ||
+  if (pitch > chiF + 2 - cloF || pitch * NG > slot || pitch > 256 ||
       ((int64_t)(64 / (pitch >> 2)) * sG + pitch) * 4 >= ((int64_t)1 << 32)) {
     // the window does not fit: read the corners from global memory
     while (!done) {
@@ -412,18 +288,9 @@ __global__ __launch_bounds__(256) void k_march_ring(MarchArgs a) {
   // window of voxel layer V (brick-local): rows [g0, g0 + NG), columns [f0, f0 + pitch)
   auto window = [&](int V) {
     Window w;
-    int flo, glo;
-    if constexpr (PERSP) {
-      float lf, hf, lg, hg;
-      crange(cAf, crf, (float)(V - 1), (float)(V + 1), lf, hf);
-      crange(cAg, crg, (float)(V - 1), (float)(V + 1), lg, hg);
-      flo = max((int)floorf(lf - 0.05f), cloF);
-      glo = max((int)floorf(lg - 0.05f), cloG);
-    } else {
-      const float Pf = (float)V * rf, Pg = (float)V * rg;
-      flo = max((int)floorf(Af_lo + Pf - arf - 0.05f), cloF);
-      glo = max((int)floorf(Ag_lo + Pg - arg - 0.05f), cloG);
-    }
+    const float Pf = (float)V * rf, Pg = (float)V * rg;
+    const int flo = max((int)floorf(Af_lo + Pf - arf - 0.05f), cloF);
+    const int glo = max((int)floorf(Ag_lo + Pg - arg - 0.05f), cloG);
     w.f0 = uni(max(cloF, min(flo, chiF + 2 - pitch)));
     w.g0 = uni(max(cloG, min(glo, chiG + 2 - NG)));
     return w;
@@ -451,246 +318,61 @@ __global__ __launch_bounds__(256) void k_march_ring(MarchArgs a) {
   // cell layer c_k = Lbeg +- k reads V_k and V_{k+1}
   const int vstep = up ? 1 : -1;
   const int V0 = up ? Lbeg : Lbeg + 1;
-  if (REG && nload <= kRingRegLoads) {
-    // two LDS slots; V_{k+2} waits in registers while c_k is sampled
-    const float fclo = (float)cloB, fchi = (float)chiB;
-    // every lane of a load instruction reads a row of the window (lanes past
-    // the instruction's rows, and rows past the window, re-read its last row)
-    // and only lanes holding a row of the window write it to LDS
-    typedef float v4f __attribute__((ext_vector_type(4)));
-    v4f rr[kRingRegLoads];
-    const int rl_c = min(rl, R - 1), c4_c = lane_on ? c4l : 0;
-    auto rload = [&](int V, const Window& w) {
-      gfloat* gb = gbase + ((int64_t)V * sB + (int64_t)w.g0 * sG + w.f0) + 4 * c4_c;
-#pragma unroll
-      for (int i = 0; i < kRingRegLoads; ++i)
-        if (i < nload)
-          rr[i] = *(const v4f __attribute__((address_space(1)))*)(gb + (int64_t)min(i * R + rl_c, NG - 1) * sG);
-    };
-    auto rstore = [&](float* sdst) {
-      v4f* l = (v4f*)(sdst + 4 * lane);
-#pragma unroll
-      for (int i = 0; i < kRingRegLoads; ++i)
-        if (i < nload && lane_on && i * R + rl < NG) l[i * R * (pitch >> 2)] = rr[i];
-    };
-    Window w0 = window(V0), w1 = window(V0 + vstep), w2;
-    rload(V0, w0);
-    rstore(s_ring);
-    rload(V0 + vstep, w1);
-    rstore(s_ring + slot);
-    if (nlay > 1) {
-      w2 = window(V0 + 2 * vstep);
-      rload(V0 + 2 * vstep, w2);
+  const float fclo = (float)cloB, fchi = (float)chiB;
+  Window w0 = window(V0), w1 = window(V0 + vstep);
+  issue(V0, w0, s_ring);
+  issue(V0 + vstep, w1, s_ring + slot);
+  int s0 = 0;  // slot of V_k
+  for (int k = 0; k < nlay; ++k) {
+    wait_loads();  // V_k and V_{k+1} are in LDS
+    // start V_{k+2} into the slot V_{k-1} used (cell layer c_{k-1} is finished);
+    // with two slots, into the slot of V_k once c_k is finished
+    const int s1 = s0 == kSlots - 1 ? 0 : s0 + 1;
+    const int s2 = s1 == kSlots - 1 ? 0 : s1 + 1;
+    Window w2;
+    if (k + 1 < nlay) {
+      const int V2 = V0 + (k + 2) * vstep;
+      w2 = window(V2);
+      if (!TWO) issue(V2, w2, s_ring + s2 * slot);
     }
-    int s0 = 0;  // slot of V_k (V_{k+1} is in the other)
-    for (int k = 0; k < nlay; ++k) {
-      const int c = up ? Lbeg + k : Lbeg - k;
-      const Window& wl = up ? w0 : w1;
-      const Window& wu = up ? w1 : w0;
-      const int sl = up ? s0 : s0 ^ 1, su = up ? s0 ^ 1 : s0;
-      const float* baseL = s_ring + (sl * slot - wl.g0 * pitch - wl.f0);
-      const int dU = (su * slot - wu.g0 * pitch - wu.f0) - (sl * slot - wl.g0 * pitch - wl.f0);
-      while (!done) {
-        const SamplePos q = sample_pos(j, px, py, pz, sx, sy, sz);
-        const int ib = (int)floorf(__builtin_amdgcn_fmed3f(by ? q.y : q.z, fclo, fchi));
-        if (ib != c) break;
-        const Cell cl = cell_of(q, br);
-        const int ig = by ? cl.iz : cl.iy;
-        const float* p = baseL + (__mul24(ig, pitch) + cl.ix);
-        const float* pu = p + dU;
-        const float l00 = p[0], l01 = p[1], l10 = p[pitch], l11 = p[pitch + 1];
-        const float u00 = pu[0], u01 = pu[1], u10 = pu[pitch], u11 = pu[pitch + 1];
-        const float val = by ? trilerp(l00, l01, u00, u01, l10, l11, u10, u11, cl)
-                             : trilerp(l00, l01, l10, l11, u00, u01, u10, u11, cl);
-        ++j;
-        if (MIP) {
-          const float s = norm_value(val, a.vmin, a.inv_range);
-          mx = fmaxf(mx, s);
-          if (j >= cnt || mx >= 1.f) done = true;
-        } else {
-          const Classified kk = classify(val, a.vmin, a.inv_range, a.M, s_tf);
-          accumulate(kk, Cr, Cg, Cb, T);
-          if (j >= cnt || 1.f - T >= a.tau) done = true;
-        }
-      }
-      if (__all(done)) break;
-      if (k + 1 < nlay) {
-        rstore(s_ring + s0 * slot);  // V_{k+2} replaces V_k (same wavefront: LDS order holds)
-        w0 = w1;
-        w1 = w2;
-        if (k + 2 < nlay) {
-          w2 = window(V0 + (k + 3) * vstep);
-          rload(V0 + (k + 3) * vstep, w2);
-        }
-      }
-      s0 ^= 1;
-    }
-  } else if constexpr (!ESS) {
-    const float fclo = (float)cloB, fchi = (float)chiB;
-    Window w0 = window(V0), w1 = window(V0 + vstep);
-    issue(V0, w0, s_ring);
-    issue(V0 + vstep, w1, s_ring + slot);
-    int s0 = 0;  // slot of V_k
-    for (int k = 0; k < nlay; ++k) {
-      wait_loads();  // V_k and V_{k+1} are in LDS
-      // start V_{k+2} into the slot V_{k-1} used (cell layer c_{k-1} is finished);
-      // with two slots, into the slot of V_k once c_k is finished
-      const int s1 = s0 == kSlots - 1 ? 0 : s0 + 1;
-      const int s2 = s1 == kSlots - 1 ? 0 : s1 + 1;
-      Window w2;
-      if (k + 1 < nlay) {
-        const int V2 = V0 + (k + 2) * vstep;
-        w2 = window(V2);
-        if (!TWO) issue(V2, w2, s_ring + s2 * slot);
-      }
-      // lower and upper voxel layer of cell layer c_k
-      const int c = up ? Lbeg + k : Lbeg - k;
-      const Window& wl = up ? w0 : w1;
-      const Window& wu = up ? w1 : w0;
-      const int sl = up ? s0 : s1, su = up ? s1 : s0;
-      const float* baseL = s_ring + (sl * slot - wl.g0 * pitch - wl.f0);
-      const int dU = (su * slot - wu.g0 * pitch - wu.f0) - (sl * slot - wl.g0 * pitch - wl.f0);
-      while (!done) {
-        const SamplePos q = sample_pos(j, px, py, pz, sx, sy, sz);
-        const int ib = (int)floorf(__builtin_amdgcn_fmed3f(by ? q.y : q.z, fclo, fchi));
-        if (ib != c) break;
-        const Cell cl = cell_of(q, br);
-        const int ig = by ? cl.iz : cl.iy;
-        const float* p = baseL + (__mul24(ig, pitch) + cl.ix);
-        const float* pu = p + dU;
-        // corners v[dz][dy][dx]: within a window rows run along g, layers along b
-        const float l00 = p[0], l01 = p[1], l10 = p[pitch], l11 = p[pitch + 1];
-        const float u00 = pu[0], u01 = pu[1], u10 = pu[pitch], u11 = pu[pitch + 1];
-        const float val = by ? trilerp(l00, l01, u00, u01, l10, l11, u10, u11, cl)
-                             : trilerp(l00, l01, l10, l11, u00, u01, u10, u11, cl);
-        ++j;
-        if (MIP) {
-          float s = norm_value(val, a.vmin, a.inv_range);
-          if constexpr (MASK) s *= channel_weight(a.mask, a.mask_axis, br.lo[a.mask_axis], cl);
-          mx = fmaxf(mx, s);
-          if (j >= cnt || mx >= 1.f) done = true;
-        } else {
-          Classified k = classify(val, a.vmin, a.inv_range, a.M, s_tf);
-          if constexpr (MASK) k.a *= channel_weight(a.mask, a.mask_axis, br.lo[a.mask_axis], cl);
-          accumulate(k, Cr, Cg, Cb, T);
-          if (j >= cnt || 1.f - T >= a.tau) done = true;
-        }
-      }
-      if (__all(done)) break;
-      if (TWO && k + 1 < nlay) issue(V0 + (k + 2) * vstep, w2, s_ring + s0 * slot);
-      s0 = s1;
-      w0 = w1;
-      w1 = w2;
-    }
-  } else {
-    const float fclo = (float)cloB, fchi = (float)chiB;
-    const int loB = by ? br.lo[1] : br.lo[2], loG = by ? br.lo[2] : br.lo[1];
-    // Empty-space skipping: cell layers are taken in steps that end at macrocell
-    // boundaries along b; a step whose cells all lie in macrocells with zero
-    // opacity over their range is neither loaded nor sampled (its samples would
-    // add nothing and leave T as it is), the lanes only move their cursors.
-    auto step_clear = [&](int c, int c_end) {
-      const int P0 = min(c, c_end), P1 = max(c, c_end) + 1;  // planes bounding the step
-      int f0, f1, g0, g1;
-      if constexpr (PERSP) {
-        float lf, hf, lg, hg;
-        crange(cAf, crf, (float)P0, (float)P1, lf, hf);
-        crange(cAg, crg, (float)P0, (float)P1, lg, hg);
-        f0 = max((int)floorf(lf - 0.05f), cloF);
-        f1 = min((int)floorf(hf + 0.05f), chiF);
-        g0 = max((int)floorf(lg - 0.05f), cloG);
-        g1 = min((int)floorf(hg + 0.05f), chiG);
+    // lower and upper voxel layer of cell layer c_k
+    const int c = up ? Lbeg + k : Lbeg - k;
+    const Window& wl = up ? w0 : w1;
+    const Window& wu = up ? w1 : w0;
+    const int sl = up ? s0 : s1, su = up ? s1 : s0;
+    const float* baseL = s_ring + (sl * slot - wl.g0 * pitch - wl.f0);
+    const int dU = (su * slot - wu.g0 * pitch - wu.f0) - (sl * slot - wl.g0 * pitch - wl.f0);
+    while (!done) {
+      const SamplePos q = sample_pos(j, px, py, pz, sx, sy, sz);
+      const int ib = (int)floorf(__builtin_amdgcn_fmed3f(by ? q.y : q.z, fclo, fchi));
+      if (ib != c) break;
+      const Cell cl = cell_of(q, br);
+      const int ig = by ? cl.iz : cl.iy;
+      const float* p = baseL + (__mul24(ig, pitch) + cl.ix);
+      const float* pu = p + dU;
+      // corners v[dz][dy][dx]: within a window rows run along g, layers along b
+      const float l00 = p[0], l01 = p[1], l10 = p[pitch], l11 = p[pitch + 1];
+      const float u00 = pu[0], u01 = pu[1], u10 = pu[pitch], u11 = pu[pitch + 1];
+      const float val = by ? trilerp(l00, l01, u00, u01, l10, l11, u10, u11, cl)
+                           : trilerp(l00, l01, l10, l11, u00, u01, u10, u11, cl);
+      ++j;
+      if (MIP) {
+        float s = norm_value(val, a.vmin, a.inv_range);
+        if constexpr (MASK) s *= channel_weight(a.mask, a.mask_axis, br.lo[a.mask_axis], cl);
+        mx = fmaxf(mx, s);
+        if (j >= cnt || mx >= 1.f) done = true;
       } else {
-        const float lo_f = fminf((float)P0 * rf, (float)P1 * rf), hi_f = fmaxf((float)P0 * rf, (float)P1 * rf);
-        const float lo_g = fminf((float)P0 * rg, (float)P1 * rg), hi_g = fmaxf((float)P0 * rg, (float)P1 * rg);
-        f0 = max((int)floorf(Af_lo + lo_f - 0.05f), cloF);
-        f1 = min((int)floorf(Af_hi + hi_f + 0.05f), chiF);
-        g0 = max((int)floorf(Ag_lo + lo_g - 0.05f), cloG);
-        g1 = min((int)floorf(Ag_hi + hi_g + 0.05f), chiG);
-      }
-      const int mc = a.mc;
-      const int mf0 = (f0 + br.lo[0]) / mc, mf1 = (max(f1, f0) + br.lo[0]) / mc;
-      const int mg0 = (g0 + loG) / mc, mg1 = (max(g1, g0) + loG) / mc;
-      const int mb = (c + loB) / mc;
-      const int nmf = mf1 - mf0 + 1, tot = nmf * (mg1 - mg0 + 1);
-      bool opaque = false;
-#pragma nounroll
-      for (int i = lane; i < tot; i += 64) {
-        const int mf = mf0 + i % nmf, mg = mg0 + i / nmf;
-        const int my = by ? mb : mg, mz = by ? mg : mb;
-        opaque |= a.mc_clear[((int64_t)mz * a.mcn[1] + my) * a.mcn[0] + mf] == 0;
-      }
-      return !__any(opaque);
-    };
-
-    // voxel layer V_i lives in slot i % 3; `issued` counts the layers started
-    auto start = [&](int i) {
-      const int V = V0 + i * vstep;
-      issue(V, window(V), s_ring + (i % kSlots) * slot);
-    };
-    int issued = 0;
-    int next_check = 0;  // first layer of the next skipping step
-    int k = 0;
-    while (k < nlay) {
-      const int c = up ? Lbeg + k : Lbeg - k;
-      if (ESS && k >= next_check) {
-        const int mb = (c + loB) / a.mc;
-        const int c_end = up ? min(Lend, (mb + 1) * a.mc - 1 - loB) : max(Lend, mb * a.mc - loB);
-        const int k_end = up ? c_end - Lbeg : Lbeg - c_end;
-        if (step_clear(c, c_end)) {
-#pragma nounroll
-          while (!done) {
-            const int ib = (int)floorf(__builtin_amdgcn_fmed3f(fmaf((float)j, sb, pb), fclo, fchi));
-            if (up ? ib > c_end : ib < c_end) break;
-            ++j;
-            if (j >= cnt) done = true;
-          }
-          k = k_end + 1;
-          next_check = k;
-          if (__all(done)) break;
-          continue;
-        }
-        next_check = k_end + 1;
-        if (issued < k) {  // after a skipped step: restart the ring at V_k
-          wait_loads();    // loads started before the step may still be landing
-          issued = k;
-        }
-      }
-#pragma nounroll
-      while (issued <= k + 1) start(issued++);
-      wait_loads();  // V_k and V_{k+1} are in LDS
-      // start V_{k+2} into the slot V_{k-1} used (cell layer c_{k-1} is finished)
-      if (k + 2 <= nlay) start(issued++);
-      // lower and upper voxel layer of cell layer c_k
-      const Window w0 = window(V0 + k * vstep), w1 = window(V0 + (k + 1) * vstep);
-      const int s0 = k % kSlots, s1 = (k + 1) % kSlots;
-      const Window& wl = up ? w0 : w1;
-      const Window& wu = up ? w1 : w0;
-      const int sl = up ? s0 : s1, su = up ? s1 : s0;
-      const float* baseL = s_ring + (sl * slot - wl.g0 * pitch - wl.f0);
-      const int dU = (su * slot - wu.g0 * pitch - wu.f0) - (sl * slot - wl.g0 * pitch - wl.f0);
-      while (!done) {
-        const SamplePos q = sample_pos(j, px, py, pz, sx, sy, sz);
-        const int ib = (int)floorf(__builtin_amdgcn_fmed3f(by ? q.y : q.z, fclo, fchi));
-        if (ib != c) break;
-        const Cell cl = cell_of(q, br);
-        const int ig = by ? cl.iz : cl.iy;
-        const float* p = baseL + (__mul24(ig, pitch) + cl.ix);
-        const float* pu = p + dU;
-        // corners v[dz][dy][dx]: within a window rows run along g, layers along b
-        const float l00 = p[0], l01 = p[1], l10 = p[pitch], l11 = p[pitch + 1];
-        const float u00 = pu[0], u01 = pu[1], u10 = pu[pitch], u11 = pu[pitch + 1];
-        const float val = by ? trilerp(l00, l01, u00, u01, l10, l11, u10, u11, cl)
-                             : trilerp(l00, l01, l10, l11, u00, u01, u10, u11, cl);
         Classified k = classify(val, a.vmin, a.inv_range, a.M, s_tf);
         if constexpr (MASK) k.a *= channel_weight(a.mask, a.mask_axis, br.lo[a.mask_axis], cl);
         accumulate(k, Cr, Cg, Cb, T);
-        ++j;
         if (j >= cnt || 1.f - T >= a.tau) done = true;
       }
-      if (__all(done)) break;
-      ++k;
     }
+    if (__all(done)) break;
+    if (TWO && k + 1 < nlay) issue(V0 + (k + 2) * vstep, w2, s_ring + s0 * slot);
+    s0 = s1;
+    w0 = w1;
+    w1 = w2;
   }
   wait_loads();  // no load may still target LDS when the wavefront ends (or the next batch starts)
   if (valid && wr_ok && (cnt > 0 || (!a.carry && !foot)))
@@ -825,40 +507,21 @@ static hipError_t launch_march_ring_main(const MarchArgs& a, int wpb, hipStream_
     return hipErrorInvalidValue;
   const int groups = (a.ntiles + wpb - 1) / wpb;
   const int grid = ((groups + 7) / 8) * 8;
-  // macrocell skipping lives in its own instantiation: its bookkeeping costs
-  // registers the plain march does not need
   const dim3 g(grid), b(64 * wpb);
   const size_t lds = ring_lds_bytes(a, wpb);
-  if (a.mip && a.mc > 0) return hipErrorInvalidValue;
-  if (a.ring_nslots == 2 && a.mc > 0) return hipErrorInvalidValue;
+  if (a.mc > 0 || a.cam.persp) return hipErrorInvalidValue;  // (gather marches, perspective cells)
+  auto go = [&](auto kernel) { hipLaunchKernelGGL(kernel, g, b, lds, s, a); };
   if (a.mask) {
     // the channel mask lives in instantiations of its own (three slots)
     if (a.ring_nslots == 2) return hipErrorInvalidValue;
-    if (a.cam.persp) {
-      if (a.mip) hipLaunchKernelGGL((k_march_ring<false, true, true, false, true>), g, b, lds, s, a);
-      else if (a.mc > 0) hipLaunchKernelGGL((k_march_ring<true, false, true, false, true>), g, b, lds, s, a);
-      else hipLaunchKernelGGL((k_march_ring<false, false, true, false, true>), g, b, lds, s, a);
-    } else {
-      if (a.mip) hipLaunchKernelGGL((k_march_ring<false, true, false, false, true>), g, b, lds, s, a);
-      else if (a.mc > 0) hipLaunchKernelGGL((k_march_ring<true, false, false, false, true>), g, b, lds, s, a);
-      else hipLaunchKernelGGL((k_march_ring<false, false, false, false, true>), g, b, lds, s, a);
-    }
-    return hipGetLastError();
-  }
-  if (a.cam.persp) {
-    if (!a.mip && a.mc == 0 && a.ring_nslots == 2 && a.ring_reg)
-      hipLaunchKernelGGL((k_march_ring<false, false, true, true, false, true>), g, b, lds, s, a);
-    else if (a.mip && a.ring_nslots == 2) hipLaunchKernelGGL((k_march_ring<false, true, true, true>), g, b, lds, s, a);
-    else if (a.mip) hipLaunchKernelGGL((k_march_ring<false, true, true>), g, b, lds, s, a);
-    else if (a.mc > 0) hipLaunchKernelGGL((k_march_ring<true, false, true>), g, b, lds, s, a);
-    else if (a.ring_nslots == 2) hipLaunchKernelGGL((k_march_ring<false, false, true, true>), g, b, lds, s, a);
-    else hipLaunchKernelGGL((k_march_ring<false, false, true>), g, b, lds, s, a);
+    if (a.mip) go(k_march_ring<true, false, true>);
+    else go(k_march_ring<false, false, true>);
+  } else if (a.ring_nslots == 2) {
+    if (a.mip) go(k_march_ring<true, true, false>);
+    else go(k_march_ring<false, true, false>);
   } else {
-    if (a.mip && a.ring_nslots == 2) hipLaunchKernelGGL((k_march_ring<false, true, false, true>), g, b, lds, s, a);
-    else if (a.mip) hipLaunchKernelGGL((k_march_ring<false, true, false>), g, b, lds, s, a);
-    else if (a.mc > 0) hipLaunchKernelGGL((k_march_ring<true, false, false>), g, b, lds, s, a);
-    else if (a.ring_nslots == 2) hipLaunchKernelGGL((k_march_ring<false, false, false, true>), g, b, lds, s, a);
-    else hipLaunchKernelGGL((k_march_ring<false, false, false>), g, b, lds, s, a);
+    if (a.mip) go(k_march_ring<true, false, false>);
+    else go(k_march_ring<false, false, false>);
   }
   return hipGetLastError();
 }

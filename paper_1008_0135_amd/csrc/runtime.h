@@ -127,8 +127,6 @@ struct vr_ctx {
   int32_t foot_block = 0;     // blocks of cells per workgroup: -1 = by cost, 0 = off, 1 = foot_block_f x _g
   int32_t foot_block_f = 0, foot_block_g = 0;
   bool debug_plan = false;    // print each view's march shape to stderr
-  double persp_fit = 0.95;    // perspective ring march: fraction of tiles whose windows the slot holds
-  int32_t persp_classes = 3;  // perspective ring march: launches per view, bricks grouped by window size
   int32_t persp_cells = 1;    // perspective views: footprint cells sized per brick (0: 8 x 8 pixel tiles)
   int32_t persp_kmax = 1;     // perspective footprint cells: window rows of at most this many 128-byte lines
   // autotune cache: render shapes -> (tile edge, LDS budget, march mode)

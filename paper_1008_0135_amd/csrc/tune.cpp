@@ -143,7 +143,7 @@ int vr_autotune(vr_ctx* ctx, const vr_volume* cvol, const vr_view* view, const v
     double ms = 0.0;
     rc = time_ms(s, 3, [&]() {
       VR_TRY(ctx_begin(ctx, s));
-      VR_TRY(render_forward(ctx, vol, view, 1, &q, img, s, nullptr));
+      VR_TRY(render_forward(ctx, vol, view, 1, &q, img, s));
       return ctx_end(ctx, s);
     }, ms);
     ctx->march_mode = saved_mode;
