@@ -39,10 +39,13 @@ constexpr double kPerspCellPitch = 1.8;
 // leave room for few).  The 24 GiB cube at 3.2 voxels: 11.7 ms per view, 14.7 by
 // gathers; 1000^3 at 1.9 and 3.5 voxels: 5.1 and 3.0 ms, 4.0 and 2.0 by gathers
 constexpr double kPerspCellRate = 106e9, kPerspChains = 5.0;
-// whole-ray termination, views whose gathers are estimated below this: every
-// ray through all its bricks in one launch (0.3 ms per 200^2 view of 64 bricks
-// against 1.6 ms in 10 launches); above, launches per front of bricks, in
-// which a launch works on a compact part of the volume
+// whole-ray termination: every ray through all its bricks in one launch for a
+// view on its own (512^3 in 64 bricks at 768^2 1.53 -> 1.24 ms, 700^3 2.28 ->
+// 1.88), for rays less than a voxel apart (two views of 300^3 at 768^2 1.15 ->
+// 1.03) and for views whose gathers are estimated below this (0.3 ms per 200^2
+// view of 64 bricks against 1.6 in 10 launches).  Otherwise launches per front
+// of bricks, each working on a compact part of the volume, the views' side by
+// side (two views of 1024 x 1024 x 512 6.2 ms against 6.9)
 constexpr double kThruBelow = 0.4e-3;
 
 }  // namespace
@@ -332,9 +335,9 @@ int render_forward(vr_ctx* ctx, vr_volume* vol, const vr_view* views, int32_t nv
       gather_view(vp, 16);
     } else if (global) {
       const MarchTimes t = march_times(cams[v], view_boxes(vp), p->step, nullptr);
-      if (t.gather < kThruBelow) {
+      if (nviews == 1 || t.pitch < 1.0 || t.gather < kThruBelow) {
         thru_order(v);
-        gather_view(vp, 16);
+        gather_view(vp, gather_lanes(cams[v]));
       } else if (base.mask || vp.wave_begin.size() > 8) {
         gather_view(vp, t.pitch < 2.0 ? 4 : 16);
       }

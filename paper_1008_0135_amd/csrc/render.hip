@@ -579,8 +579,11 @@ hipError_t launch_march(const MarchArgs& a, hipStream_t s) {
     else if (mask) go(k_march_skip<true, false>);
     else go(k_march_skip<false, false>);
   } else if (a.thru) {
-    if (mip || a.depth != 16) return hipErrorInvalidValue;
-    if (mask) go(k_march<16, 2, false, true, true>);
+    if (mip || (a.depth != 16 && a.depth != 4)) return hipErrorInvalidValue;
+    // (4 lanes or 16)
+    if (a.depth == 4 && mask) go(k_march<4, 4, false, true, true>);
+    else if (a.depth == 4) go(k_march<4, 4, false, false, true>);
+    else if (mask) go(k_march<16, 2, false, true, true>);
     else go(k_march<16, 2, false, false, true>);
   } else {
     auto shape = [&](auto d, auto tw) {
