@@ -117,15 +117,25 @@ void xcd_bands(const std::vector<double>& cost, int wpb, int32_t band[9]) {
 }
 
 // Ring layout for the differentiable pair of one view: slab axis, window slot
-// and cell layers per checkpoint group (about K samples,
-// the adjoint's windows of one tile within 160 KB of LDS).  False when the view
-// needs the sample-segment kernels.
+// and cell layers per checkpoint group (about K samples, the adjoint's windows of
+// one tile within 160 KB of LDS).  False when the view needs the sample-segment
+// kernels (perspective; rays along axis 1).
 bool plan_ring_view(const Camera& cam, const vr_params* p, int32_t M, const int64_t n[3], int layer_cap,
                     vr_state::View& rv) {
   if (p->tile != 0 && p->tile != 8) return false;
   if (cam.persp) return false;  // the ring adjoint assumes parallel rays
   int32_t axis = 0, slot = 0, wpb = 4;
-  if (!choose_ring(cam, 4096, M, 24, 12, 2, axis, slot, wpb)) return false;
+  if (!choose_ring(cam, 4096, M, 24, 12, 2, axis, slot, wpb)) {
+    // rays so far apart that no tile's windows fit: the same adjoint without
+    // windows (corners from memory, voxel gradients by global atomics, which
+    // hardly meet there), 4 lanes per ray and in parts, against one lane walking
+    // segments: four views of 51 x 83 rays through 55 x 82 x 438 voxels 1.37 ->
+    // 0.66 ms, of 64^2 through 256^3 5.6 -> 1.6
+    axis = std::fabs(cam.e3[1]) >= std::fabs(cam.e3[2]) ? 1 : 2;
+    if (std::fabs(cam.e3[axis]) < 0.05) return false;
+    slot = 4;
+    layer_cap = std::max(layer_cap, 8);
+  }
   const double db = std::fabs(cam.e3[axis]);
   // layers per group: about K samples, at most `layer_cap` (LDS per wavefront
   // grows with the group and occupancy falls)

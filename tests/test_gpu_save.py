@@ -45,9 +45,11 @@ def _step(dims, image, nviews, tau, mode=None):
     return plain, out, gtf, gvol, ring
 
 
-# gathers with several workgroups per tile, with one, and footprint cells
+# gathers with several workgroups per tile, with one, footprint cells, and rays
+# too far apart for windows
 @pytest.mark.parametrize("dims,image,nviews", [((61, 83, 72), (100, 92), 2), ((5, 9, 40), (17, 12), 1),
-                                               ((60, 64, 50), (420, 400), 2), ((300, 200, 260), (384, 380), 3)])
+                                               ((60, 64, 50), (420, 400), 2), ((300, 200, 260), (384, 380), 3),
+                                               ((80, 82, 238), (21, 23), 3)])
 @pytest.mark.parametrize("tau", [2.0, 0.9])
 def test_save(dims, image, nviews, tau):
     import torch
