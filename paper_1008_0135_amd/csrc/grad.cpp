@@ -44,6 +44,15 @@ namespace vr {
 namespace {
 
 constexpr int32_t kPartBlocks = 4096, kMaxParts = 16;
+// tables with (nearly) opaque entries: no parts.  Behind a sample of opacity 1
+// the forward's sums hold nothing, but its own gradient needs what lies there.
+constexpr float kPartAlpha = 0.99f;
+
+float table_max_alpha(const vr_ctx* ctx) {
+  float m = 0.f;
+  for (int32_t i = 0; i < ctx->tf_m; i++) m = std::max(m, ctx->h_tf[4 * (size_t)i + 3]);
+  return m;
+}
 
 // Device tables of one view of a whole-volume render: [DevBrick][DevBrickView].
 struct WholeTables {
@@ -189,6 +198,7 @@ int render_with_state(vr_ctx* ctx, vr_volume* vol, const vr_view* views, int32_t
   std::vector<Camera> cams((size_t)nviews);
   st->vs.assign((size_t)nviews, vr_state::View());
   int64_t ck_total = 0, sums_total = 0;
+  const float max_alpha = table_max_alpha(ctx);
   Box whole;
   for (int i = 0; i < 3; i++) {
     whole.lo[i] = 0;
@@ -225,7 +235,8 @@ int render_with_state(vr_ctx* ctx, vr_volume* vol, const vr_view* views, int32_t
     // 61 x 83 x 72 voxels: 202 -> 95 us per view, the step 720 -> 585; one view of
     // 256^2 rays through 128^3: 690 -> 600; 16384 gains nothing more)
     const int32_t tiles = ntiles_of(W, H, 8, 8) * nviews, groups = rv.ngrp - 1;
-    const int32_t want = std::max(1, std::min({kPartBlocks / std::max(1, tiles), kMaxParts, groups / 2}));
+    const int32_t want =
+        max_alpha > kPartAlpha ? 1 : std::max(1, std::min({kPartBlocks / std::max(1, tiles), kMaxParts, groups / 2}));
     rv.part_groups = (groups + want - 1) / want;
     rv.parts = (groups + rv.part_groups - 1) / rv.part_groups;
     if (rv.parts > 1) {
@@ -435,9 +446,7 @@ int vr_render_backward(vr_ctx* ctx, const vr_volume* vol, const vr_state* st, co
     bb.parts = rv.parts;
     pbase[v + 1] = pbase[v] + (rv.ring ? bwd_ring_blocks(a0, bb) : bwd_blocks(a0));
   }
-  float max_alpha = 0.f;
-  for (int32_t i = 0; i < M; i++) max_alpha = std::max(max_alpha, ctx->h_tf[4 * (size_t)i + 3]);
-  const bool replay = max_alpha > kMaxDivAlpha;
+  const bool replay = table_max_alpha(ctx) > kMaxDivAlpha;
   const bool side = ctx->bwd_side && st->nviews > 1;
   int64_t nslots = 1;
   for (int32_t v = 0; v < st->nviews; v++) nslots = std::max(nslots, pbase[v + 1] - pbase[v]);

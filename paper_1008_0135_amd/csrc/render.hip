@@ -376,6 +376,14 @@ __global__ __launch_bounds__(256) void k_march(MarchArgs a) {
   if (dl == 0) *dst = MIP ? make_float4(mx, mx, mx, mx) : make_float4(Cr, Cg, Cb, !THRU && a.carry ? T : 1.f - T);
 }
 
+// v of the lane N before in the row of 16; 1 where there is none.
+template <int N>
+__device__ __forceinline__ double row_shr(double v) {
+  const int lo = __builtin_amdgcn_update_dpp(0, __double2loint(v), 0x110 + N, 0xf, 0xf, false);
+  const int hi = __builtin_amdgcn_update_dpp(0x3ff00000, __double2hiint(v), 0x110 + N, 0xf, 0xf, false);
+  return __hiloint2double(hi, lo);
+}
+
 // Sum of v over the 16 lanes of a row, and over its lanes before lane dl.
 __device__ __forceinline__ double row_sum(double v) {
 #pragma unroll
@@ -452,6 +460,9 @@ __global__ __launch_bounds__(256) void k_march_save(MarchArgs a, SaveArgs sa) {
     // what this lane's samples add to the ray (parts: summed over the 16 lanes
     // where a part begins and at the end)
     double4 own = make_double4(0.0, 0.0, 0.0, 0.0);
+    // T by double products: what the adjoint starts from keeps only the errors of
+    // the opacities, not those of a chain of single-precision roundings
+    double Td = 1.0;
     for (int jb = D;; jb += D) {
       const float val = trilerp(a00.x, a00.y, a01.x, a01.y, a10.x, a10.y, a11.x, a11.y, c);
       const int jc = j, gi = group(BY ? c.iy : c.iz);
@@ -459,21 +470,23 @@ __global__ __launch_bounds__(256) void k_march_save(MarchArgs a, SaveArgs sa) {
       if (more) load(jb);
       Classified k = classify(val, a.vmin, a.inv_range, a.M, s_tf);
       if (jc >= cnt) k.a = 0.f;  // past the ray's last sample: adds nothing
-      // T before this lane's sample: the product of the lanes before
-      float q = 1.f - k.a;
-      q *= dpp_or<0x111>(q, 1.f);
-      q *= dpp_or<0x112>(q, 1.f);
-      q *= dpp_or<0x114>(q, 1.f);
-      q *= dpp_or<0x118>(q, 1.f);
-      const float Tb = T * dpp_or<0x111>(q, 1.f);
       const int gp = __shfl_up(gi, 1, D);
       int taken = 0;
       const bool stopped = accumulate_group<D>(k, a.tau, Cr, Cg, Cb, T, &taken);
       used = stopped ? jb - D + taken : min(jb, cnt);
+      // T before this lane's sample: the product over the lanes before
+      const double e = jc < used ? 1.0 - (double)k.a : 1.0;
+      double q = e;
+      q *= row_shr<1>(q);
+      q *= row_shr<2>(q);
+      q *= row_shr<4>(q);
+      q *= row_shr<8>(q);
+      const double Tb = Td * row_shr<1>(q);
+      Td *= __shfl(q, D - 1, D);
       const bool begins = jc < used && gi != (dl == 0 ? last : gp);
-      if (begins) sa.ckpt[(int64_t)gi * sa.npix + pix] = Tb;
+      if (begins) sa.ckpt[(int64_t)gi * sa.npix + pix] = (float)Tb;
       if constexpr (PARTS) {
-        const double w = jc < used ? (double)Tb * (double)k.a : 0.0;
+        const double w = jc < used ? Tb * (double)k.a : 0.0;
         const double4 add = make_double4(w * (double)k.r, w * (double)k.g, w * (double)k.b, w);
         const bool part = begins && gi % sa.part_groups == 0;
         if (__any(part)) {
@@ -490,7 +503,7 @@ __global__ __launch_bounds__(256) void k_march_save(MarchArgs a, SaveArgs sa) {
       last = __shfl(gi, D - 1, D);
       if (stopped || !more) break;
     }
-    if (dl == 0) sa.ckpt[(int64_t)(group_at(used - 1) + 1) * sa.npix + pix] = T;
+    if (dl == 0) sa.ckpt[(int64_t)(group_at(used - 1) + 1) * sa.npix + pix] = (float)Td;
     if constexpr (PARTS) {
       const double4 all = make_double4(row_sum(own.x), row_sum(own.y), row_sum(own.z), row_sum(own.w));
       if (dl == 0) sa.sums[pix] = all;

@@ -154,12 +154,6 @@ __device__ __forceinline__ void accumulate_lanes(const Classified& k, float& Cr,
 #undef VR_ROW
 #undef VR_LANE_OPERANDS
 
-// The same with `other` for lanes whose source lies outside the row.
-template <int CTRL>
-__device__ __forceinline__ float dpp_or(float v, float other) {
-  return __int_as_float(__builtin_amdgcn_update_dpp(__float_as_int(other), __float_as_int(v), CTRL, 0xf, 0xf, false));
-}
-
 template <int D, int I>
 __device__ __forceinline__ void accumulate_until(const Classified& k, float tau, bool& done, int& taken, float& Cr,
                                                  float& Cg, float& Cb, float& T) {
