@@ -184,7 +184,7 @@ def bench_c2(ctx, stream):
 
 
 def bench_batched(ctx, stream):
-    """64 uneven requests: one persistent graph-replayed launch vs 64 plain renders."""
+    """64 uneven requests: one graph-replayed launch vs 64 plain renders."""
     import torch
     t0 = time.time()
     descs = synth.batch_requests(seed=synth.CONFIGS["C4"]["seed"], nreq=synth.CONFIGS["C4"]["nreq"])
@@ -253,7 +253,7 @@ def bench_batched(ctx, stream):
         f"64 plain launches {ms_p:.3f} ms (same shapes: {ms_s:.3f} ms), grid {tune.waves_per_cu} waves/CU, "
         f"tiles {dict((t, tiles.count(t)) for t in sorted(set(tiles)))}")
     return {"workload": "64 requests, volumes U[32,256]^3 (non-cubic), images U[64,512]^2, random views and "
-                        "8-point tables, one persistent hipGraph launch; tile shape per size class and grid "
+                        "8-point tables, one hipGraph launch; tile shape per size class and grid "
                         "from the autotuner", "ms_per_batch": round(ms_b, 4),
             "gsamples_per_s": round(nominal / ms_b / 1e6, 3), "ms_64_plain_launches": round(ms_p, 4),
             "speedup_vs_plain": round(ms_p / ms_b, 3),
