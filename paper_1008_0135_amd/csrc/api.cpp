@@ -739,7 +739,40 @@ static int brick_volume(vr_volume* vol, Partition& P, bool materialize, int32_t 
   // per-brick (min, max) over stored voxels; the permuted copy's bricks hold
   // the same voxels as the source's
   std::vector<float> mm(2 * (size_t)nb);
-  if (src) {
+  // large bricks: their ranges from the macrocells' and the planes of voxels around
+  // those, so that the cube is read once, not twice; volumes held here only (all of
+  // their voxels are finite), and not where the macrocells find no memory
+  bool cells_built = false;
+  RangePieces rp;
+  if (!src && vol->owned && macrocell > 0 && range_pieces(sboxes, n, macrocell, rp)) {
+    cells_built = build_macrocells(vol, macrocell, nullptr, s) == VR_OK;
+    if (!cells_built) clear_error();
+  }
+  if (cells_built) {
+    const size_t nc = rp.cell_brick.size(), np = nc + rp.voxel_brick.size();
+    VR_TRY(ensure_device(&ctx->d_scratch, &ctx->scratch_bytes, np * 56 + 1024));
+    int64_t* d_boxes = reinterpret_cast<int64_t*>(ctx->d_scratch);
+    float* d_part = reinterpret_cast<float*>(d_boxes + 6 * np);
+    const int64_t cn[3] = {2 * vol->mcn[0], vol->mcn[1], vol->mcn[2]};
+    rp.cells.insert(rp.cells.end(), rp.voxels.begin(), rp.voxels.end());
+    VR_HIP(hipMemcpyAsync(d_boxes, rp.cells.data(), np * 48, hipMemcpyHostToDevice, s));
+    VR_HIP(launch_brick_minmax_parts(vol->d_mc_mm, cn, d_boxes, (int32_t)nc, 1, 1 << 30, d_part, nullptr, s));
+    if (np > nc)
+      VR_HIP(launch_brick_minmax_parts(vol->data, n, d_boxes + 6 * nc, (int32_t)(np - nc), 1, 1 << 30, d_part + 2 * nc,
+                                       nullptr, s));
+    std::vector<float> part(2 * np);
+    VR_HIP(hipMemcpyAsync(part.data(), d_part, np * 8, hipMemcpyDeviceToHost, s));
+    VR_HIP(hipStreamSynchronize(s));
+    for (int32_t b = 0; b < nb; b++) {
+      mm[2 * b] = INFINITY;
+      mm[2 * b + 1] = -INFINITY;
+    }
+    for (size_t i = 0; i < np; i++) {
+      const int32_t b = i < nc ? rp.cell_brick[i] : rp.voxel_brick[i - nc];
+      mm[2 * b] = std::min(mm[2 * b], part[2 * i]);
+      mm[2 * b + 1] = std::max(mm[2 * b + 1], part[2 * i + 1]);
+    }
+  } else if (src) {
     for (int32_t b = 0; b < nb; b++) {
       mm[2 * b] = src->bdesc[src_brick[b]].vmin;
       mm[2 * b + 1] = src->bdesc[src_brick[b]].vmax;
@@ -817,7 +850,7 @@ static int brick_volume(vr_volume* vol, Partition& P, bool materialize, int32_t 
   vol->bricked = true;
   vol->materialized = mat;
   vol->version++;
-  return build_macrocells(vol, macrocell, src, s);
+  return cells_built ? VR_OK : build_macrocells(vol, macrocell, src, s);
 }
 
 static void destroy_twin(vr_volume* vol) {

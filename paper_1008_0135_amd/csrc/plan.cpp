@@ -147,6 +147,76 @@ void stored_box(const Box& b, const int64_t n[3], int64_t slo[3], int64_t shi[3]
   }
 }
 
+// box cut into pieces of at most kRangePiece floats (whole rows where they fit)
+static void cut_box(const int64_t lo[3], const int64_t hi[3], int32_t brick, std::vector<int64_t>& boxes,
+                    std::vector<int32_t>& owner) {
+  const int64_t w = std::min(hi[0] - lo[0] + 1, kRangePiece);
+  const int64_t h = std::min(hi[1] - lo[1] + 1, std::max<int64_t>(1, kRangePiece / w));
+  const int64_t d = std::max<int64_t>(1, kRangePiece / (w * h));
+  for (int64_t z = lo[2]; z <= hi[2]; z += d)
+    for (int64_t y = lo[1]; y <= hi[1]; y += h)
+      for (int64_t x = lo[0]; x <= hi[0]; x += w) {
+        boxes.insert(boxes.end(), {x, y, z, std::min(hi[0], x + w - 1), std::min(hi[1], y + h - 1), std::min(hi[2], z + d - 1)});
+        owner.push_back(brick);
+      }
+}
+
+bool range_pieces(const std::vector<int64_t>& sboxes, const int64_t n[3], int32_t mc, RangePieces& out) {
+  const size_t nb = sboxes.size() / 6;
+  // the macrocells c0..c1 inside a box and the voxels v0..v1 they cover, or none
+  auto inside = [&](const int64_t* bx, int64_t c0[3], int64_t c1[3], int64_t v0[3], int64_t v1[3]) {
+    bool any = true;
+    for (int i = 0; i < 3; i++) {
+      c0[i] = (bx[i] + mc - 1) / mc;
+      c1[i] = bx[3 + i] == n[i] - 1 ? (n[i] - 1 + mc - 1) / mc - 1 : bx[3 + i] / mc - 1;
+      v0[i] = c0[i] * mc;
+      v1[i] = std::min(n[i] - 1, (c1[i] + 1) * mc);
+      any = any && c0[i] <= c1[i];
+    }
+    return any;
+  };
+  // planes across axis 1 are read by 128-byte lines
+  auto line = [](int64_t w) { return w > 0 ? (w + 31) / 32 * 32 : 0; };
+  int64_t c0[3], c1[3], v0[3], v1[3], cost = 0, all = 0;
+  for (size_t b = 0; b < nb; b++) {
+    const int64_t* bx = &sboxes[6 * b];
+    const int64_t box = (bx[3] - bx[0] + 1) * (bx[4] - bx[1] + 1) * (bx[5] - bx[2] + 1);
+    all += box;
+    if (!inside(bx, c0, c1, v0, v1)) {
+      cost += box;
+      continue;
+    }
+    cost += 2 * (c1[0] - c0[0] + 1) * (c1[1] - c0[1] + 1) * (c1[2] - c0[2] + 1);
+    const int64_t wy = v1[1] - v0[1] + 1, wz = v1[2] - v0[2] + 1;
+    cost += box - (bx[3] - bx[0] + 1) * wy * wz + (line(v0[0] - bx[0]) + line(bx[3] - v1[0])) * wy * wz;
+  }
+  if (5 * cost > 3 * all) return false;
+  for (size_t b = 0; b < nb; b++) {
+    int64_t lo[3], hi[3];
+    for (int i = 0; i < 3; i++) {
+      lo[i] = sboxes[6 * b + i];
+      hi[i] = sboxes[6 * b + 3 + i];
+    }
+    if (inside(&sboxes[6 * b], c0, c1, v0, v1)) {
+      const int64_t a[3] = {2 * c0[0], c0[1], c0[2]}, e[3] = {2 * c1[0] + 1, c1[1], c1[2]};
+      cut_box(a, e, (int32_t)b, out.cells, out.cell_brick);
+      for (int i = 2; i >= 0; i--) {  // below and above the cells along axis 3, then 2, then 1
+        const int64_t end = hi[i];
+        hi[i] = v0[i] - 1;
+        if (lo[i] <= hi[i]) cut_box(lo, hi, (int32_t)b, out.voxels, out.voxel_brick);
+        lo[i] = v1[i] + 1;
+        hi[i] = end;
+        if (lo[i] <= hi[i]) cut_box(lo, hi, (int32_t)b, out.voxels, out.voxel_brick);
+        lo[i] = v0[i];
+        hi[i] = v1[i];
+      }
+    } else {
+      cut_box(lo, hi, (int32_t)b, out.voxels, out.voxel_brick);
+    }
+  }
+  return true;
+}
+
 Rect brick_rect(const Camera& cam, const Box& b) {
   double umin = INFINITY, umax = -INFINITY, vmin = INFINITY, vmax = -INFINITY;
   const double k = (double)cam.W / cam.S;  // pixels per voxel

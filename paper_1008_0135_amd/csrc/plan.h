@@ -48,6 +48,21 @@ bool make_kd(const int64_t n[3], int32_t nparts, Partition& out, std::string& er
 // clipped to the volume.
 void stored_box(const Box& b, const int64_t n[3], int64_t slo[3], int64_t shi[3]);
 
+// Pieces that together hold every voxel of the bricks' stored boxes: runs of
+// whole macrocells, and the planes of voxels no macrocell inside the box covers.
+// cells, voxels: six numbers a piece (first, last along axes 1, 2, 3; a cell is
+// two floats along axis 1, its minimum and maximum), at most kRangePiece floats
+// each; *_brick: the piece's brick.  False where they would cost more than 0.6
+// of reading the boxes: 512 x 512 x 1024, macrocells of 16, brick ranges and
+// macrocells in 0.37 ms with bricks of 256^3 (0.56 from the boxes) and 0.46 with
+// 128^3 (0.56, cost 0.5); with 96^3 0.55 against 0.58, with 64^3 0.76 against 0.64.
+struct RangePieces {
+  std::vector<int64_t> cells, voxels;
+  std::vector<int32_t> cell_brick, voxel_brick;
+};
+constexpr int64_t kRangePiece = 4096;
+bool range_pieces(const std::vector<int64_t>& sboxes, const int64_t n[3], int32_t mc, RangePieces& out);
+
 // Conservative pixel rectangle of the box's projection (corner bounding box
 // padded by one pixel, clipped to the image).
 Rect brick_rect(const Camera& cam, const Box& b);

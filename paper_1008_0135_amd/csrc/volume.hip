@@ -288,7 +288,7 @@ hipError_t launch_brick_minmax_parts(const float* vol, const int64_t n[3], const
   hipLaunchKernelGGL(k_brick_minmax, dim3(nb * zgroups), dim3(256), 0, s, vol, n[0], n[1], boxes, zgroups, zper,
                      reinterpret_cast<float2*>(scratch));
   hipError_t e = hipGetLastError();
-  if (e != hipSuccess) return e;
+  if (e != hipSuccess || !out2) return e;
   hipLaunchKernelGGL(k_brick_minmax_final, dim3(nb), dim3(64), 0, s, reinterpret_cast<const float2*>(scratch),
                      zgroups, out2);
   return hipGetLastError();

@@ -404,7 +404,7 @@ hipError_t launch_minmax_final(const float* partial, int32_t nblocks, float* out
 constexpr int kBrickRangePlanes = 2;  // z-planes of one workgroup of the brick ranges
 // Per-brick (min, max) over stored voxel boxes: boxes is a device array of
 // nb x (slo1, slo2, slo3, shi1, shi2, shi3); each brick's z range is split into
-// zgroups groups of zper planes; scratch holds nb*zgroups float2 partials.
+// zgroups groups of zper planes; scratch holds nb*zgroups float2 partials (out2 null: only these).
 hipError_t launch_brick_minmax_parts(const float* vol, const int64_t n[3], const int64_t* boxes, int32_t nb,
                                      int zgroups, int zper, float* scratch, float* out2, hipStream_t s);
 // checkpointing forwards: layer groups along a.slab_axis (16 lanes per ray, tiles of 2 x 2 pixels; cells by
