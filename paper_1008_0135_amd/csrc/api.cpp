@@ -272,6 +272,30 @@ void fill_march_common(MarchArgs& a, const vr_volume* vol, const vr_params* p, d
   a.tile_h = 64 / a.tile_w;
 }
 
+// The voxels' pass of the macrocells has one workgroup per run of cells, few of them
+// where cells are large: edges of 24 and more are halved while even, and the small
+// cells joined (ranges and macrocells of 512^3 in 256^3 bricks, edges 24 / 32 / 64
+// / 128: 0.31 / 0.24 / 0.24 / 0.24 ms, in one pass 0.38 / 0.41 / 1.18 / 4.2; cells
+// of 9 read a ninth more: 512 x 512 x 1024, edge 18, 0.46 against 0.43).  One pass
+// where the small cells find no scratch.
+static int cells_of_voxels(vr_volume* vol, int32_t mc, const int64_t c[3], hipStream_t s) {
+  vr_ctx* ctx = vol->ctx;
+  int32_t fine = mc;
+  while (fine >= 24 && fine % 2 == 0) fine /= 2;
+  int64_t f[3];
+  for (int i = 0; i < 3; i++) f[i] = (vol->n[i] - 1 + fine - 1) / fine;
+  const size_t need = (size_t)(f[0] * f[1] * f[2]) * 8;
+  if (fine < mc && ensure_device(&ctx->d_scratch, &ctx->scratch_bytes, need) == VR_OK) {
+    float* d_fine = reinterpret_cast<float*>(ctx->d_scratch);
+    VR_HIP(launch_mc_minmax(vol->data, vol->n, fine, f, d_fine, s));
+    VR_HIP(launch_mc_join(d_fine, f, mc / fine, c, vol->d_mc_mm, s));
+    return VR_OK;
+  }
+  clear_error();
+  VR_HIP(launch_mc_minmax(vol->data, vol->n, mc, c, vol->d_mc_mm, s));
+  return VR_OK;
+}
+
 // (Re)build the macrocell grid of edge mc over the whole volume (mc = 0: drop it).
 // src: the volume this one is the permuted copy of, whose macrocells are the
 // same cells in permuted order (read 4 B x voxels less); null: from the voxels.
@@ -305,7 +329,7 @@ int build_macrocells(vr_volume* vol, int32_t mc, const vr_volume* src, hipStream
   }
   vol->d_mc_count = reinterpret_cast<unsigned int*>(vol->d_mc_clear + cbytes);
   if (src && src->mc == mc) VR_HIP(launch_mc_permute(src->d_mc_mm, src->mcn, vol->d_mc_mm, s));
-  else VR_HIP(launch_mc_minmax(vol->data, vol->n, mc, c, vol->d_mc_mm, s));
+  else VR_TRY(cells_of_voxels(vol, mc, c, s));
   VR_HIP(hipStreamSynchronize(s));
   vol->mc = mc;
   for (int i = 0; i < 3; i++) vol->mcn[i] = c[i];

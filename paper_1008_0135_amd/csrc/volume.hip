@@ -239,6 +239,29 @@ __global__ __launch_bounds__(256) void k_mc_minmax(const float* __restrict__ vol
   }
 }
 
+// Macrocells of edge k times that of fine ones, counts c and f: a wavefront per cell
+// joins up to k x k x k of them (those share their faces' voxels as cells do).
+__global__ __launch_bounds__(64) void k_mc_join(const float2* __restrict__ fine, int64_t f1, int64_t f2, int64_t f3,
+                                                int k, int64_t c1, int64_t c2, float2* __restrict__ out) {
+  const int64_t i = blockIdx.x;
+  const int64_t a1 = i % c1 * k, a2 = i / c1 % c2 * k, a3 = i / (c1 * c2) * k;
+  const int k1 = (int)min((int64_t)k, f1 - a1), k2 = (int)min((int64_t)k, f2 - a2), k3 = (int)min((int64_t)k, f3 - a3);
+  float mn = INFINITY, mx = -INFINITY;
+  int bad = 0;
+  for (int j = threadIdx.x; j < k1 * k2 * k3; j += 64) {
+    const float2 r = fine[((a3 + j / (k1 * k2)) * f2 + a2 + j / k1 % k2) * f1 + a1 + j % k1];
+    bad |= isnan(r.x);
+    mn = fminf(mn, r.x);
+    mx = fmaxf(mx, r.y);
+  }
+  for (int off = 32; off > 0; off >>= 1) {
+    mn = fminf(mn, __shfl_xor(mn, off));
+    mx = fmaxf(mx, __shfl_xor(mx, off));
+    bad |= __shfl_xor(bad, off);
+  }
+  if (threadIdx.x == 0) out[i] = make_float2(bad ? NAN : mn, mx);
+}
+
 // Same rule as the host's brick test: entries floor(u(min)) - 1 .. ceil(u(max)) + 1
 // (clamped to the table) must all have opacity 0; the one-entry margin covers
 // the rounding of a single-precision trilinear value and table coordinate.
@@ -358,6 +381,13 @@ hipError_t launch_copy_box(const float* src, const int64_t sn[3], const int64_t 
   const int grid = (int)(rows < 65536 ? rows : 65536);
   hipLaunchKernelGGL(k_copy_box, dim3(grid), dim3(256), 0, s, src, sn[0], sn[1], so[0], so[1], so[2], dst, dn[0],
                      dn[1], dn[2]);
+  return hipGetLastError();
+}
+
+hipError_t launch_mc_join(const float* fine2, const int64_t f[3], int k, const int64_t c[3], float* out2, hipStream_t s) {
+  hipLaunchKernelGGL(k_mc_join, dim3((uint32_t)(c[0] * c[1] * c[2])), dim3(64), 0, s,
+                     reinterpret_cast<const float2*>(fine2), f[0], f[1], f[2], k, c[0], c[1],
+                     reinterpret_cast<float2*>(out2));
   return hipGetLastError();
 }
 

@@ -425,6 +425,8 @@ hipError_t launch_twin(const float* src, const int64_t n[3], float* dst, hipStre
 // Macrocell (min, max) pairs [c3][c2][c1] of edge `mc` over the volume (mc in [2, 1024]).
 hipError_t launch_mc_minmax(const float* vol, const int64_t n[3], int mc, const int64_t c[3], float* out2,
                             hipStream_t s);
+// Macrocells (counts c) from those of an edge k times smaller (counts f), fine2.
+hipError_t launch_mc_join(const float* fine2, const int64_t f[3], int k, const int64_t c[3], float* out2, hipStream_t s);
 // The permuted copy's macrocells from the source's ([c3][c2][c1] pairs, counts c): [c1][c3][c2].
 hipError_t launch_mc_permute(const float* mm2, const int64_t c[3], float* out2, hipStream_t s);
 // clear[i] = 1 when the table's opacity is 0 over every entry macrocell i can reach

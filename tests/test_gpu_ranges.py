@@ -35,3 +35,31 @@ def test_ranges_of_stored_boxes(dims, size, edge, opt):
             assert (b.vmin, b.vmax) == (part.min(), part.max())
     vr.vr_volume_destroy(h)
     vr.vr_destroy(ctx)
+
+
+# even edges of 24 and more are joined from cells of 12 to 23 voxels: no, one and
+# more halvings, a volume smaller than a cell, last cells cut short in the middle of
+# a small one; a voxel that is not a number marks every cell that touches it
+@pytest.mark.parametrize("dims,edge", [((70, 41, 37), 18), ((200, 66, 65), 32), ((140, 70, 36), 34),
+                                       ((97, 100, 33), 40), ((20, 31, 130), 128), ((51, 17, 20), 17)])
+@pytest.mark.parametrize("wrapped", [False, True])
+def test_large_macrocells(dims, edge, wrapped):
+    import torch
+    import paper_1008_0135_amd as vr
+    a = np.random.default_rng(edge).standard_normal(dims[::-1], dtype=np.float32)
+    if wrapped:
+        a[tuple(n // 2 for n in a.shape)] = np.nan
+    src = torch.from_numpy(a).cuda()
+    ctx = vr.vr_create(0)
+    h = vr.vr_volume_wrap(ctx, src, dims) if wrapped else vr.vr_volume_create(ctx, src, dims)
+    vr.vr_volume_brick(h, vr.grid_spec(dims, macrocell=edge))
+    e, cnt, mm = vr.vr_volume_macrocell_info(h)
+    assert e == edge and tuple(cnt) == tuple(-(-(n - 1) // edge) for n in dims)
+    for m in np.ndindex(cnt[2], cnt[1], cnt[0]):
+        part = a[tuple(slice(k * e, min((k + 1) * e, n - 1) + 1) for k, n in zip(m, a.shape))]
+        if np.isnan(part).any():
+            assert np.isnan(mm[m][0])
+        else:
+            assert tuple(mm[m]) == (part.min(), part.max())
+    vr.vr_volume_destroy(h)
+    vr.vr_destroy(ctx)
