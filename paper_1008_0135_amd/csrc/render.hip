@@ -42,12 +42,13 @@ __device__ __forceinline__ f2u ld_pair(gfloat* p) {
 // 201 x 187 x 333 volume 535 -> 395 us for two views; whole-ray termination
 // over 64 bricks 4.4 -> 2.5 ms).
 constexpr int kXcdRun = 8;
+template <int RUN = kXcdRun>
 __device__ __forceinline__ int xcd_block() {
   // which XCD takes which run of a round of eight moves on by three from round
   // to round: image rows of 8 or 16 runs would else give an XCD the same column
   // of the image in every row
-  const int b = (int)blockIdx.x, n = b / (8 * kXcdRun), r = b - n * (8 * kXcdRun);
-  return b - r + ((r + 3 * (n >> 2)) & 7) * kXcdRun + (r >> 3);
+  const int b = (int)blockIdx.x, n = b / (8 * RUN), r = b - n * (8 * RUN);
+  return b - r + ((r + 3 * (n >> 2)) & 7) * RUN + (r >> 3);
 }
 
 // Tile t of a grid of tiles numbered by blocks of 2 x 2 (blocks_x blocks a row):
@@ -63,7 +64,7 @@ __device__ __forceinline__ void block_tile(int t, int blocks_x, int& tx, int& ty
 // planes against the rounding of sample positions) and whether that macrocell
 // is clear, i.e. whether each of them would add exactly nothing.
 __device__ __forceinline__ int macrocell_run(const MarchArgs& a, const DevBrick& br, int j, const float4& pos,
-                                             const float4& dir, const float4& inv, float inv_mc, bool& clear) {
+                                             const float4& dir, const float4& inv, float inv_mc, uint8_t& clear) {
   const SamplePos q = sample_pos(j, pos.x, pos.y, pos.z, dir.x, dir.y, dir.z);
   const Cell c = cell_of(q, br);
   // macrocell of a cell index i >= 0 (below 2^22): floor((i + 1/2) / mc)
@@ -71,7 +72,7 @@ __device__ __forceinline__ int macrocell_run(const MarchArgs& a, const DevBrick&
   const float mx = floorf(((float)(c.ix + br.lo[0]) + 0.5f) * inv_mc);
   const float my = floorf(((float)(c.iy + br.lo[1]) + 0.5f) * inv_mc);
   const float mz = floorf(((float)(c.iz + br.lo[2]) + 0.5f) * inv_mc);
-  clear = a.mc_clear[((int64_t)(int)mz * a.mcn[1] + (int)my) * a.mcn[0] + (int)mx] != 0;
+  clear = a.mc_clear[((int64_t)(int)mz * a.mcn[1] + (int)my) * a.mcn[0] + (int)mx];
   // steps to the far plane (brick-local); inv = 1 / dir, 1e9 for a component of 0
   auto steps = [&](float q1, float is, float m1, int lo) {
     const float edge = fmaf(m1, fmc, is > 0.f ? fmc - 1e-3f : 1e-3f) - (float)lo;
@@ -89,23 +90,32 @@ __device__ __forceinline__ int macrocell_run(const MarchArgs& a, const DevBrick&
 // of a ray, 4 rays (2 x 2 pixels) side by side, as k_march<16> does.  Passed
 // samples would add nothing and leave T as it is, so the images are those of
 // the other marches.
-// Bound by the longest wavefronts' chains of blocks; what a view costs follows
-// its rays and marked samples, not the voxels of its bricks (two 1024^2 views
-// of 1024 x 1024 x 768 with 95 % of the macrocells clear: 1.13 ms, 3.48 by a
-// march that skips whole steps of a brick's layers).
-template <bool MASK, bool THRU>
-__global__ __launch_bounds__(256) void k_march_skip(MarchArgs a) {
+// What a view costs follows its rays and marked samples, not the voxels of its
+// bricks (two 1024^2 views of 1024 x 1024 x 768 with 95 % of the macrocells clear:
+// 0.88 ms, 3.48 by a march that skips whole steps of a brick's layers).  Few
+// wavefronts have many blocks, and one alone issues as fast as its SIMD does for
+// one: a compute unit held 7.5 wavefronts on average while workgroups of four kept
+// their LDS for the longest of theirs (VALU issue 41 %).  So a workgroup is one
+// wavefront, up to tables of kSkipTable entries (its own copy of the table then
+// leaves room for few: 256 entries 0.88 against 1.03 ms, 1024 0.99 and 1.00, 2048
+// 1.52 and 1.07).  Two rods in step and blocks that add nothing to any of four
+// rays left out: 1.13 -> 1.04 ms, four flags in flight 1 to 3 % more.
+constexpr int kSkipTable = 1024;
+template <int WAVES, bool MASK, bool THRU>
+__global__ __launch_bounds__(64 * WAVES) void k_march_skip(MarchArgs a) {
   extern __shared__ float4 s_tf[];
-  __shared__ float4 s_pos[4][64], s_dir[4][64], s_acc[4][64];
-  __shared__ unsigned long long s_blocks[4][64];
-  for (int i = threadIdx.x; i < a.M; i += 256) s_tf[i] = a.tf[i];
-  __syncthreads();
+  __shared__ float4 s_pos[WAVES][64], s_dir[WAVES][64], s_acc[WAVES][64];
+  __shared__ unsigned long long s_blocks[WAVES][64];
+  [[maybe_unused]] bool table = WAVES > 1;  // in LDS: one wavefront reads it when it finds its first block
+  if constexpr (WAVES > 1) {
+    for (int i = threadIdx.x; i < a.M; i += 64 * WAVES) s_tf[i] = a.tf[i];
+    __syncthreads();
+  }
 
-  const int nblk = (a.ntiles + 3) >> 2;
-  const int lb = xcd_block();
-  const int wave = __builtin_amdgcn_readfirstlane((int)(threadIdx.x >> 6)), lane = threadIdx.x & 63;
-  const int tile = lb * 4 + wave;
-  if (lb >= nblk || tile >= a.ntiles) return;  // this wavefront only: no barrier follows
+  const int lb = xcd_block<kXcdRun * 4 / WAVES>();
+  const int wave = WAVES > 1 ? __builtin_amdgcn_readfirstlane((int)(threadIdx.x >> 6)) : 0, lane = threadIdx.x & 63;
+  const int tile = lb * WAVES + wave;
+  if (tile >= a.ntiles) return;  // this wavefront only: no barrier follows
   int lo = 0, hi = THRU ? 0 : a.nbv - 1;
   while (lo < hi) {
     int mid = (lo + hi + 1) >> 1;
@@ -171,55 +181,94 @@ __global__ __launch_bounds__(256) void k_march_skip(MarchArgs a) {
     for (int jc = 0; __any(jc < cnt); jc += 1024) {
       unsigned long long blocks = 0;
       const int jend = min(cnt, jc + 1024);
+      // where a run ends does not depend on its flag: four flags in flight
+      // (past the last sample positions stay in the brick's last cells)
       for (int j = jc; j < jend;) {
-        bool clear;
-        const int run = macrocell_run(a, br, j, pos, dir, inv, inv_mc, clear);
-        if (!clear) {
-          const int b0 = (j - jc) >> 4, b1 = (min(j + run, jend) - 1 - jc) >> 4;
-          blocks |= (~0ull << b0) & (~0ull >> (63 - b1));
+        int at[5];
+        uint8_t clear[4];
+        at[0] = j;
+#pragma unroll
+        for (int i = 0; i < 4; ++i) {
+          const int run = macrocell_run(a, br, at[i], pos, dir, inv, inv_mc, clear[i]);
+          at[i + 1] = min(at[i] + run, jend);
         }
-        j += run;
+#pragma unroll
+        for (int i = 0; i < 4; ++i) {
+          if (at[i] < jend && !clear[i]) {
+            const int b0 = (at[i] - jc) >> 4, b1 = (at[i + 1] - 1 - jc) >> 4;
+            blocks |= (~0ull << b0) & (~0ull >> (63 - b1));
+          }
+        }
+        j = at[4];
       }
       if (!__any(blocks != 0)) continue;
+      if (!table) {
+        for (int i = lane; i < a.M; i += 64) s_tf[i] = a.tf[i];
+        table = true;
+      }
       s_blocks[wave][lane] = blocks;
       __builtin_amdgcn_wave_barrier();
       __builtin_amdgcn_fence(__ATOMIC_ACQ_REL, "wavefront");
-      for (int q = 0; q < 16; ++q) {
-        const int ray = 4 * q + (lane >> 4);
-        unsigned long long m = s_blocks[wave][ray];
-        if (!__any(m != 0)) continue;
-        const float4 rp = s_pos[wave][ray], rd = s_dir[wave][ray];
-        float4 c0 = s_acc[wave][ray];
-        const int rc = __float_as_int(rp.w);
-        if (1.f - c0.w >= a.tau) m = 0;
+      for (int q = 0; q < 16; q += 2) {
+        // two rods in step: their loads and compositing chains overlap
+        unsigned long long m[2];
+        float4 rp[2], rd[2], c0[2];
+        int rc[2], j[2];
+        bool more[2];
+        Cell c[2];
+        f2u a00[2] = {}, a01[2] = {}, a10[2] = {}, a11[2] = {};
+        [[maybe_unused]] f2u mw[2] = {};
+#pragma unroll
+        for (int i = 0; i < 2; ++i) m[i] = s_blocks[wave][4 * (q + i) + (lane >> 4)];
+        if (!__any((m[0] | m[1]) != 0)) continue;
         // the corners of the next block are loaded while one is composited
-        Cell c;
-        f2u a00, a01, a10, a11;
-        [[maybe_unused]] f2u mw;
-        int j = 0;
-        auto load = [&]() {
-          j = jc + 16 * __builtin_ctzll(m) + dl;
-          m &= m - 1;
-          c = cell_of(sample_pos(min(j, rc - 1), rp.x, rp.y, rp.z, rd.x, rd.y, rd.z), br);
-          gfloat* p = base + (c.iz * zs + c.iy * ys + c.ix);
-          a00 = ld_pair(p);
-          a01 = ld_pair(p + ys);
-          a10 = ld_pair(p + zs);
-          a11 = ld_pair(p + zs + ys);
-          if constexpr (MASK) mw = ld_pair(mask + (a.mask_axis == 2 ? c.iz : c.iy));
+        auto load = [&](int i) {
+          j[i] = jc + 16 * __builtin_ctzll(m[i]) + dl;
+          m[i] &= m[i] - 1;
+          c[i] = cell_of(sample_pos(min(j[i], rc[i] - 1), rp[i].x, rp[i].y, rp[i].z, rd[i].x, rd[i].y, rd[i].z), br);
+          gfloat* p = base + (c[i].iz * zs + c[i].iy * ys + c[i].ix);
+          a00[i] = ld_pair(p);
+          a01[i] = ld_pair(p + ys);
+          a10[i] = ld_pair(p + zs);
+          a11[i] = ld_pair(p + zs + ys);
+          if constexpr (MASK) mw[i] = ld_pair(mask + (a.mask_axis == 2 ? c[i].iz : c[i].iy));
         };
-        bool more = m != 0;
-        if (more) load();
-        while (more) {
-          const float val = trilerp(a00.x, a00.y, a01.x, a01.y, a10.x, a10.y, a11.x, a11.y, c);
-          Classified k = classify(val, a.vmin, a.inv_range, a.M, s_tf);
-          if constexpr (MASK) k.a *= channel_weight(mw.x, mw.y, a.mask_axis, c);
-          if (j >= rc) k.a = 0.f;  // past the ray's last sample: adds nothing
-          more = m != 0;
-          if (more) load();
-          if (accumulate_group<16>(k, a.tau, c0.x, c0.y, c0.z, c0.w)) break;
+#pragma unroll
+        for (int i = 0; i < 2; ++i) {
+          const int ray = 4 * (q + i) + (lane >> 4);
+          rp[i] = s_pos[wave][ray];
+          rd[i] = s_dir[wave][ray];
+          c0[i] = s_acc[wave][ray];
+          rc[i] = __float_as_int(rp[i].w);
+          j[i] = 0;
+          c[i] = Cell{};
+          more[i] = m[i] != 0 && !(1.f - c0[i].w >= a.tau);
+          if (more[i]) load(i);
         }
-        if (dl == 0) s_acc[wave][ray] = c0;
+        while (__any(more[0] || more[1])) {
+          Classified k[2];
+#pragma unroll
+          for (int i = 0; i < 2; ++i) {
+            const float val =
+                trilerp(a00[i].x, a00[i].y, a01[i].x, a01[i].y, a10[i].x, a10[i].y, a11[i].x, a11[i].y, c[i]);
+            k[i] = classify(val, a.vmin, a.inv_range, a.M, s_tf);
+            if constexpr (MASK) k[i].a *= channel_weight(mw[i].x, mw[i].y, a.mask_axis, c[i]);
+            // no block left, or past the ray's last sample: adds nothing
+            if (!more[i] || j[i] >= rc[i]) k[i].a = 0.f;
+          }
+#pragma unroll
+          for (int i = 0; i < 2; ++i) {
+            more[i] = more[i] && m[i] != 0;
+            if (more[i]) load(i);
+          }
+#pragma unroll
+          for (int i = 0; i < 2; ++i)
+            if (__any(k[i].a != 0.f) && accumulate_group<16>(k[i], a.tau, c0[i].x, c0[i].y, c0[i].z, c0[i].w))
+              more[i] = false;
+        }
+#pragma unroll
+        for (int i = 0; i < 2; ++i)
+          if (dl == 0) s_acc[wave][4 * (q + i) + (lane >> 4)] = c0[i];
       }
       __builtin_amdgcn_wave_barrier();
       __builtin_amdgcn_fence(__ATOMIC_ACQ_REL, "wavefront");
@@ -587,10 +636,17 @@ hipError_t launch_march(const MarchArgs& a, hipStream_t s) {
   const bool mask = a.mask != nullptr, mip = a.mip != 0;
   if (a.skip) {
     if (mip || a.mc < 2) return hipErrorInvalidValue;
-    if (a.thru && mask) go(k_march_skip<true, true>);
-    else if (a.thru) go(k_march_skip<false, true>);
-    else if (mask) go(k_march_skip<true, false>);
-    else go(k_march_skip<false, false>);
+    auto skip = [&](auto waves) {
+      constexpr int N = decltype(waves)::value;
+      const int round = 8 * kXcdRun * 4;
+      const dim3 blocks((a.ntiles + round - 1) / round * round / N), threads(64 * N);
+      if (a.thru && mask) hipLaunchKernelGGL((k_march_skip<N, true, true>), blocks, threads, lds, s, a);
+      else if (a.thru) hipLaunchKernelGGL((k_march_skip<N, false, true>), blocks, threads, lds, s, a);
+      else if (mask) hipLaunchKernelGGL((k_march_skip<N, true, false>), blocks, threads, lds, s, a);
+      else hipLaunchKernelGGL((k_march_skip<N, false, false>), blocks, threads, lds, s, a);
+    };
+    if (a.M <= kSkipTable) skip(std::integral_constant<int, 1>{});
+    else skip(std::integral_constant<int, 4>{});
   } else if (a.thru) {
     if (mip || (a.depth != 16 && a.depth != 4)) return hipErrorInvalidValue;
     // (4 lanes or 16)
