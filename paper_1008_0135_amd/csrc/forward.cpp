@@ -106,6 +106,23 @@ bool pick_foot(const Camera& cam, const int64_t n[3], int32_t M, bool plain, boo
                      kmax, reg ? rw : 0, two ? 2 * kRingRegLoads : kRingRegLoads, max_px, axis);
 }
 
+bool brick_rows_readable(const vr_volume* vol, int32_t brick, int32_t pitch) {
+  const int64_t tail = vol->owned || (vol->bricked && vol->materialized) ? 64 : 0;
+  int64_t lo[3] = {0, 0, 0}, hi[3], n[3];
+  for (int i = 0; i < 3; i++) {
+    n[i] = vol->n[i];
+    hi[i] = n[i] - 1;
+    if (!vol->bricked) continue;
+    lo[i] = vol->bdesc[brick].slo[i];
+    hi[i] = vol->bdesc[brick].shi[i];
+    if (!vol->materialized) continue;
+    hi[i] -= lo[i];  // storage of its own
+    lo[i] = 0;
+    n[i] = hi[i] + 1;
+  }
+  return rows_readable(lo, hi, n, pitch, tail);
+}
+
 void foot_args(const vr_ctx* ctx, const FootShape& fs, MarchArgs& a, int& wpb) {
   a.foot = 1;
   a.slab_axis = fs.axis;
@@ -372,7 +389,8 @@ int render_forward(vr_ctx* ctx, vr_volume* vol, const vr_view* views, int32_t nv
       for (int tryax : {first_axis, 3 - first_axis}) {
         PerspCells pc;
         if (!persp_cells(cams[v], tryax, vol->part.boxes[b.brick], rc, ctx->foot_rays, ctx->persp_kmax, kRingCap,
-                         kRingRegLoads, pc, ctx->foot_maxpx))
+                         kRingRegLoads, pc, ctx->foot_maxpx) ||
+            !brick_rows_readable(vol, b.brick, pc.pitch))
           continue;
         axis[i] = tryax;
         any = true;
@@ -447,6 +465,9 @@ int render_forward(vr_ctx* ctx, vr_volume* vol, const vr_view* views, int32_t nv
     bool cells = shape(base.mc == 0 && (!base.mask || base.mask_n <= kCellsMaskMax));
     // a channel mask: register-staged cells or three slots
     if (base.mask && (!cells || !fs.reg)) cells = shape(false);
+    // staged windows read whole rows, past a narrow volume's end too
+    if (cells && fs.reg)
+      for (const DevBrickView& b : vp.bv) cells = cells && brick_rows_readable(vol, b.brick, (fs.nf + 3) & ~3);
     if (!global && ctx->foot && !vp.bv.empty()) {
       const MarchTimes t = march_times(cams[v], view_boxes(vp), p->step, cells ? &fs : nullptr);
       if (ctx->debug_plan)
@@ -572,6 +593,8 @@ int render_forward(vr_ctx* ctx, vr_volume* vol, const vr_view* views, int32_t nv
     a.depth = vp.deep;
     a.skip = vp.skip ? 1 : 0;
     a.thru = vp.thru ? 1 : 0;
+    if (vp.deep && ctx->debug_plan)
+      std::fprintf(stderr, "[vr] view %d: gathers lanes %d skip %d thru %d\n", v, vp.deep, a.skip, a.thru);
     // fewer bricks than XCDs: the cells of one brick spread over all of them
     // in runs (a whole volume 604 -> 553 us for two views, six bricks 1.70 ->
     // 1.59 ms); from 8 bricks on each XCD keeps bricks of its own (2.39 ms for
@@ -679,6 +702,7 @@ int render_forward(vr_ctx* ctx, vr_volume* vol, const vr_view* views, int32_t nv
         ac.ntiles = vp.class_tiles[c];
         if (vp.class_axis[c] == 0) {
           ac.depth = 16;
+          if (ctx->debug_plan) std::fprintf(stderr, "[vr] view %d gathers class %zu: bricks %d lanes 16\n", v, c, count);
           VR_HIP(launch_march(ac, s));
           continue;
         }

@@ -57,6 +57,11 @@ bool pick_foot(const Camera& cam, const int64_t n[3], int32_t M, bool plain, boo
                double rays, int32_t pad, int32_t kmax, FootShape& fs, int32_t max_px = 0,
                int32_t axis = 0);
 
+// Whether the rows of a brick (of the whole volume when it is not bricked) can be
+// read `pitch` floats at a time: library storage has 64 floats of slack, a
+// wrapped array none.
+bool brick_rows_readable(const vr_volume* vol, int32_t brick, int32_t pitch);
+
 // Launch arguments of the cell march with shape fs (wpb: wavefronts per
 // workgroup), and the shape and place of a box's cells in its view entry;
 // returns the number of cells.

@@ -4,6 +4,7 @@
 
 #include <algorithm>
 #include <cmath>
+#include <cstdio>
 #include <cstring>
 #include <vector>
 
@@ -225,8 +226,9 @@ int render_with_state(vr_ctx* ctx, vr_volume* vol, const vr_view* views, int32_t
     if (ctx->foot && t.cells <= t.gather &&
         pick_foot(cams[v], vol->n, ctx->tf_m, true, ctx->ring_reg > 0, ctx->ring_nslots, ctx->foot_rays,
                   ctx->foot_pad, ctx->foot_kmax, fs, ctx->foot_maxpx, rv.axis) &&
-        fs.reg) {
+        fs.reg && brick_rows_readable(vol, 0, (fs.nf + 3) & ~3)) {
       shapes[v] = fs;
+      if (ctx->debug_plan) std::fprintf(stderr, "[vr] view %d: saved by cells of %.1f x %.1f\n", v, fs.Tf, fs.Tg);
       continue;
     }
     // Few tiles leave most compute units without a workgroup of the adjoint, and
@@ -239,6 +241,7 @@ int render_with_state(vr_ctx* ctx, vr_volume* vol, const vr_view* views, int32_t
         max_alpha > kPartAlpha ? 1 : std::max(1, std::min({kPartBlocks / std::max(1, tiles), kMaxParts, groups / 2}));
     rv.part_groups = (groups + want - 1) / want;
     rv.parts = (groups + rv.part_groups - 1) / rv.part_groups;
+    if (ctx->debug_plan) std::fprintf(stderr, "[vr] view %d: saved by gathers, %d parts\n", v, rv.parts);
     if (rv.parts > 1) {
       rv.sums = sums_total;
       sums_total += (int64_t)rv.parts * npix;

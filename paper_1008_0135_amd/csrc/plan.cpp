@@ -675,6 +675,11 @@ bool choose_foot_block(const Camera& cam, FootShape& fs, const int64_t ext[3], i
   return found;
 }
 
+bool rows_readable(const int64_t slo[3], const int64_t shi[3], const int64_t n[3], int32_t pitch, int64_t tail) {
+  if (pitch <= shi[0] - slo[0] + 1) return true;
+  return (shi[2] * n[1] + shi[1]) * n[0] + slo[0] + pitch <= n[0] * n[1] * n[2] + tail;
+}
+
 void foot_cells(const Camera& cam, const FootShape& fs, const Box& box, int32_t& cf0, int32_t& cg0, int32_t& ncf,
                 int32_t& ncg, double& fa0, double& fb0) {
   const int b = fs.axis, g = 3 - b;

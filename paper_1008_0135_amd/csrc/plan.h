@@ -201,6 +201,12 @@ struct PerspCells {
 bool persp_cells(const Camera& cam, int b, const Box& box, const Rect& rect, double rays, int32_t kmax,
                  int32_t cap, int32_t reg_loads, PerspCells& out, int32_t max_px = 64);
 
+// Whether windows read `pitch` floats a row, wherever a march places them over the
+// stored box slo..shi (inclusive) of an [n[2]][n[1]][n[0]] array, stay inside the
+// array and the `tail` readable floats behind it.  A box at least that wide holds
+// every row; the last row of a narrower one runs over its end.
+bool rows_readable(const int64_t slo[3], const int64_t shi[3], const int64_t n[3], int32_t pitch, int64_t tail);
+
 // Bytes the window loads of the footprint-cell march request over one brick
 // (a model from the plan: every cell marches every layer its rays cross
 // inside the brick's ownership box, windows placed and clamped as the kernel
