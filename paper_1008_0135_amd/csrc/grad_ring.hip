@@ -310,13 +310,18 @@ __global__ __launch_bounds__(256) __attribute__((amdgpu_waves_per_eu(4))) void k
     float Tn = valid && ge > gb ? ba.ckpt[(int64_t)(g0 + ge) * npix + pix] : 1.f;  // T behind the group
     float Tg = valid && ge > gb ? ba.ckpt[(int64_t)(g0 + ge - 1) * npix + pix] : 1.f;  // T before the group
     if (gb < ge && ge < ngrp) {
-      // what the ray gathers behind the part, per unit of transmittance there
-      // (1 minus the opacity gathered in front of it)
+      // what the ray gathers behind the part, per unit of transmittance there: 1
+      // minus the opacity gathered in front of it, or, where that difference has
+      // lost its digits (opaque rays: it can be 0), the T stored there.  The sums'
+      // own rounding, about 1e-16, is then divided by T here and multiplied by it
+      // in every gradient; no transmittance left, nothing behind counts.
       jn = first_at(ge * L);
       if (jn > 0 && jn < used) {
         const double4 all = ba.sums[pix], f = ba.sums[(int64_t)((int)blockIdx.y + 1) * npix + pix];
-        S = ((double)gf.x * (all.x - f.x) + (double)gf.y * (all.y - f.y) + (double)gf.z * (all.z - f.z) +
-             (double)gf.w * (all.w - f.w)) / (1.0 - f.w);
+        const double left = 1.0 - f.w, behind = left > 1e-8 ? left : (double)Tn;
+        if (behind > 0.0)
+          S = ((double)gf.x * (all.x - f.x) + (double)gf.y * (all.y - f.y) + (double)gf.z * (all.z - f.z) +
+               (double)gf.w * (all.w - f.w)) / behind;
       }
     }
     // chunk (16 bytes) of a window this lane copies: row pr, column pc
