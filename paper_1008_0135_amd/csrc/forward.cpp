@@ -261,14 +261,15 @@ int render_forward(vr_ctx* ctx, vr_volume* vol, const vr_view* views, int32_t nv
   // opacity tested over the whole ray: bricks marched in front-to-back waves
   // straight into the frame, each ray carrying its state from brick to brick
   const bool global = bricked && out && !base.mip && p->ert_scope == VR_ERT_GLOBAL;
-  // the march is chosen per view (the default shapes and no forced march)
-  const bool pick = (mode == 0 || mode == 3) && tw == 8;
+  // the march is chosen per view (the default shapes, no other march forced);
+  // forced: windows in LDS wherever they fit, whatever the estimates say
+  const bool pick = (mode == 0 || mode == 3) && tw == 8, forced = mode == 3;
   if (pick && base.mc > 0) {
     // few clear macrocells: what the walk from macrocell to macrocell and the
     // 16-sample blocks around the others cost outweighs the samples saved (a
     // block-gathered sample costs about twice a sample of the cell march)
     const int64_t cells = vol->mcn[0] * vol->mcn[1] * vol->mcn[2];
-    if (2 * vol->mc_nclear < cells) base.mc = 0;
+    if (forced || 2 * vol->mc_nclear < cells) base.mc = 0;
   }
 
   std::vector<ViewPlan> plans((size_t)nviews);
@@ -350,7 +351,7 @@ int render_forward(vr_ctx* ctx, vr_volume* vol, const vr_view* views, int32_t nv
       if (global) thru_order(v);
       vp.skip = true;
       gather_view(vp, 16);
-    } else if (global) {
+    } else if (global && !forced) {
       const MarchTimes t = march_times(cams[v], view_boxes(vp), p->step, nullptr);
       if (nviews == 1 || t.pitch < 1.0 || t.gather < kThruBelow) {
         thru_order(v);
@@ -375,7 +376,8 @@ int render_forward(vr_ctx* ctx, vr_volume* vol, const vr_view* views, int32_t nv
     ViewPlan& vp = plans[v];
     if (!pick || !cams[v].persp || vp.bv.empty() || vp.deep || global) continue;
     const bool cells = bricked && ctx->persp_cells && (!base.mask || base.mask_n <= kCellsMaskMax) &&
-                       ctx->ring_reg > 0 && ctx->ring_nslots != 3 && cams[v].S / W >= kPerspCellPitch && persp_faster(cams[v], vp);
+                       ctx->ring_reg > 0 && ctx->ring_nslots != 3 &&
+                       (forced || (cams[v].S / W >= kPerspCellPitch && persp_faster(cams[v], vp)));
     const int first_axis = std::fabs(cams[v].e3[1]) >= std::fabs(cams[v].e3[2]) ? 1 : 2;
     std::vector<int32_t> axis(vp.bv.size(), 0);
     bool any = false;
@@ -444,7 +446,7 @@ int render_forward(vr_ctx* ctx, vr_volume* vol, const vr_view* views, int32_t nv
     FootShape fs;
     // gathers for certain: their estimate is below the cells' best (the slab
     // axis with fewer layers), without sizing the cells on the host (80 us)
-    if (!global && ctx->foot && !vp.bv.empty()) {
+    if (!forced && !global && ctx->foot && !vp.bv.empty()) {
       const std::vector<Box> boxes = view_boxes(vp);
       bool sure = true;
       for (int axis : {1, 2}) {
@@ -468,7 +470,7 @@ int render_forward(vr_ctx* ctx, vr_volume* vol, const vr_view* views, int32_t nv
     // staged windows read whole rows, past a narrow volume's end too
     if (cells && fs.reg)
       for (const DevBrickView& b : vp.bv) cells = cells && brick_rows_readable(vol, b.brick, (fs.nf + 3) & ~3);
-    if (!global && ctx->foot && !vp.bv.empty()) {
+    if (!forced && !global && ctx->foot && !vp.bv.empty()) {
       const MarchTimes t = march_times(cams[v], view_boxes(vp), p->step, cells ? &fs : nullptr);
       if (ctx->debug_plan)
         std::fprintf(stderr, "[vr] view %d: estimated cells %.0f us, gathers %.0f us\n", v, t.cells * 1e6, t.gather * 1e6);
