@@ -436,7 +436,8 @@ __global__ __launch_bounds__(256) void k_march_ring_ovf(MarchArgs a, SaveArgs sa
         if constexpr (SAVE) {
           const int b = a.slab_axis, ib = b == 1 ? c.iy : c.iz;
           const int gi = (a.cam.e3[b] > 0.0 ? ib - br.clo[b] : br.chi[b] - ib) / sa.K;
-          if (gi != grp) sa.ckpt[(int64_t)gi * sa.npix + vv * a.cam.W + uu] = T;
+          // (the groups without a sample in front of it too, as k_march_save)
+          for (int g = grp < 0 ? gi : grp + 1; g <= gi; ++g) sa.ckpt[(int64_t)g * sa.npix + vv * a.cam.W + uu] = T;
           grp = gi;
         }
         gfloat* p = gb + (c.iz * zs + c.iy * ys + c.ix);

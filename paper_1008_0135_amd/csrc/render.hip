@@ -532,17 +532,27 @@ __global__ __launch_bounds__(256) void k_march_save(MarchArgs a, SaveArgs sa) {
       q *= row_shr<8>(q);
       const double Tb = Td * row_shr<1>(q);
       Td *= __shfl(q, D - 1, D);
-      const bool begins = jc < used && gi != (dl == 0 ? last : gp);
-      if (begins) sa.ckpt[(int64_t)gi * sa.npix + pix] = (float)Tb;
+      // groups this sample is the ray's first in or behind: its own, and those
+      // since the last sample's (steps longer than a group leave some without a
+      // sample; the group in front of such a one ends with the T stored there)
+      const int before = dl == 0 ? last : gp;
+      const bool begins = jc < used && gi != before;
+      const int from = before < 0 ? gi : before + 1;
+      if (begins)
+        for (int g = from; g <= gi; ++g) sa.ckpt[(int64_t)g * sa.npix + pix] = (float)Tb;
       if constexpr (PARTS) {
         const double w = jc < used ? Tb * (double)k.a : 0.0;
         const double4 add = make_double4(w * (double)k.r, w * (double)k.g, w * (double)k.b, w);
-        const bool part = begins && gi % sa.part_groups == 0;
+        // the part that begins at one of these groups (the last, if several do)
+        const int pg = gi - gi % sa.part_groups;
+        const bool part = begins && pg >= from;
         if (__any(part)) {
           // all blocks before this one, and this block's lanes before this one
           const double4 f = make_double4(row_sum(own.x) + row_before(add.x, dl), row_sum(own.y) + row_before(add.y, dl),
                                          row_sum(own.z) + row_before(add.z, dl), row_sum(own.w) + row_before(add.w, dl));
-          if (part && gi > 0) sa.sums[(int64_t)(gi / sa.part_groups) * sa.npix + pix] = f;
+          if (part)
+            for (int g = pg; g >= from && g > 0; g -= sa.part_groups)
+              sa.sums[(int64_t)(g / sa.part_groups) * sa.npix + pix] = f;
         }
         own.x += add.x;
         own.y += add.y;
