@@ -504,8 +504,11 @@ int vr_render_backward(vr_ctx* ctx, const vr_volume* vol, const vr_state* st, co
   VR_TRY(ctx_end(ctx, s));
   // the replay's bound on the samples of one ray in one checkpoint group holds
   // by construction; a group that exceeded it is reported, not clamped (only
-  // the replay can: without it the call returns while the GPU works)
-  if (!replay) return VR_OK;
+  // the replay can).  Either way the call ends with its stream idle.
+  if (!replay) {
+    VR_HIP(hipStreamSynchronize(s));
+    return VR_OK;
+  }
   int32_t flag = 0;
   VR_HIP(hipMemcpyAsync(&flag, st->d_flag, sizeof flag, hipMemcpyDeviceToHost, s));
   VR_HIP(hipStreamSynchronize(s));
