@@ -392,7 +392,7 @@ int render_forward(vr_ctx* ctx, vr_volume* vol, const vr_view* views, int32_t nv
         PerspCells pc;
         if (!persp_cells(cams[v], tryax, vol->part.boxes[b.brick], rc, ctx->foot_rays, ctx->persp_kmax, kRingCap,
                          kRingRegLoads, pc, ctx->foot_maxpx) ||
-            !brick_rows_readable(vol, b.brick, pc.pitch))
+            !brick_rows_readable(vol, b.brick, pc.pitch) || !samples_countable(cams[v], vol->part.boxes[b.brick], p->step))
           continue;
         axis[i] = tryax;
         any = true;
@@ -470,6 +470,8 @@ int render_forward(vr_ctx* ctx, vr_volume* vol, const vr_view* views, int32_t nv
     // staged windows read whole rows, past a narrow volume's end too
     if (cells && fs.reg)
       for (const DevBrickView& b : vp.bv) cells = cells && brick_rows_readable(vol, b.brick, (fs.nf + 3) & ~3);
+    if (cells)
+      for (const Box& b : view_boxes(vp)) cells = cells && samples_countable(cams[v], b, p->step);
     if (!forced && !global && ctx->foot && !vp.bv.empty()) {
       const MarchTimes t = march_times(cams[v], view_boxes(vp), p->step, cells ? &fs : nullptr);
       if (ctx->debug_plan)

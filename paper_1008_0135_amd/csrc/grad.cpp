@@ -226,7 +226,7 @@ int render_with_state(vr_ctx* ctx, vr_volume* vol, const vr_view* views, int32_t
     if (ctx->foot && (ctx->march_mode == 3 || t.cells <= t.gather) &&
         pick_foot(cams[v], vol->n, ctx->tf_m, true, ctx->ring_reg > 0, ctx->ring_nslots, ctx->foot_rays,
                   ctx->foot_pad, ctx->foot_kmax, fs, ctx->foot_maxpx, rv.axis) &&
-        fs.reg && brick_rows_readable(vol, 0, (fs.nf + 3) & ~3)) {
+        fs.reg && brick_rows_readable(vol, 0, (fs.nf + 3) & ~3) && samples_countable(cams[v], whole, p->step)) {
       shapes[v] = fs;
       if (ctx->debug_plan) std::fprintf(stderr, "[vr] view %d: saved by cells of %.1f x %.1f\n", v, fs.Tf, fs.Tg);
       continue;

@@ -179,7 +179,7 @@ __device__ __forceinline__ void sample_layer(const MarchArgs& a, const DevBrick&
     const SamplePos q = sample_pos(j, r.px, r.py, r.pz, r.sx, r.sy, r.sz);
     if (floorf(__builtin_amdgcn_fmed3f(BY ? q.y : q.z, fclo, fchi)) != fc) break;
     take_sample<MIP, BY, MASK>(a, br, s_tf, s_mask, baseL, baseU, pitch, q, Cr, Cg, Cb, T, mx);
-    j += 1.f;  // exact: a brick's rays have fewer than 2^24 samples
+    j += 1.f;  // exact: the host leaves boxes whose rays could have 2^24 samples to other marches
     done = j >= fcnt || (MIP ? mx >= 1.f : T <= a.t_stop);
   }
 }

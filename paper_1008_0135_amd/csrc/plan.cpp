@@ -680,6 +680,17 @@ bool rows_readable(const int64_t slo[3], const int64_t shi[3], const int64_t n[3
   return (shi[2] * n[1] + shi[1]) * n[0] + slo[0] + pitch <= n[0] * n[1] * n[2] + tail;
 }
 
+bool samples_countable(const Camera& cam, const Box& b, double step) {
+  double diag = 0.0, dir = 0.0;
+  for (int i = 0; i < 3; i++) {
+    diag += (double)(b.hi[i] - b.lo[i]) * (double)(b.hi[i] - b.lo[i]);
+    dir += cam.e3[i] * cam.e3[i];
+  }
+  // voxels between samples: parallel rays take the view's direction as it is given
+  const double apart = step * (cam.persp ? 1.0 : std::sqrt(dir));
+  return std::sqrt(diag) / apart + 2.0 < 16777216.0;
+}
+
 void foot_cells(const Camera& cam, const FootShape& fs, const Box& box, int32_t& cf0, int32_t& cg0, int32_t& ncf,
                 int32_t& ncg, double& fa0, double& fb0) {
   const int b = fs.axis, g = 3 - b;

@@ -207,6 +207,11 @@ bool persp_cells(const Camera& cam, int b, const Box& box, const Rect& rect, dou
 // every row; the last row of a narrower one runs over its end.
 bool rows_readable(const int64_t slo[3], const int64_t shi[3], const int64_t n[3], int32_t pitch, int64_t tail);
 
+// Whether the cell march may count a ray's samples in the box in single precision:
+// the longest ray of the view holds fewer than 2^24 (a float counter stops growing
+// there, and a ray that neither ends nor becomes opaque would be marched for ever).
+bool samples_countable(const Camera& cam, const Box& b, double step);
+
 // Bytes the window loads of the footprint-cell march request over one brick
 // (a model from the plan: every cell marches every layer its rays cross
 // inside the brick's ownership box, windows placed and clamped as the kernel

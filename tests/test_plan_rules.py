@@ -44,3 +44,22 @@ def test_rows_readable(ask):
         want.append(bool(last < n[0] * n[1] * n[2] + tail))
     assert ask(lines) == want
     assert 50 < sum(want) < 380
+
+
+def test_samples_countable(ask):
+    """A float counter that is incremented by one reaches every count the rule lets pass."""
+    assert np.float32(2 ** 24) + np.float32(1) == np.float32(2 ** 24)
+    rng = np.random.default_rng(5)
+    lines, counts = [], []
+    for _ in range(300):
+        lo = rng.integers(0, 5000, 3)
+        ext = rng.integers(1, 4000, 3)
+        step = float(2.0 ** rng.uniform(-18, 1))
+        length = float(rng.choice([1.0, 0.25, 3.0]))  # parallel rays step by it
+        lines.append(["count", *lo, *(lo + ext), repr(step), length])
+        # most samples a ray along the diagonal can have in the box
+        counts.append(int(np.sqrt(float((ext.astype(float) ** 2).sum())) / (step * length)) + 1)
+    ok = ask(lines)
+    assert all(c < 2 ** 24 for c, k in zip(counts, ok) if k)
+    assert all(k for c, k in zip(counts, ok) if c < 0.999 * 2 ** 24)
+    assert 30 < sum(ok) < 290
