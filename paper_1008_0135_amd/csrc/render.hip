@@ -60,8 +60,8 @@ __device__ __forceinline__ void block_tile(int t, int blocks_x, int& tx, int& ty
 }
 
 // Run of samples of a ray from sample j on whose cells lie in the macrocell
-// holding sample j's: its length (at least 1; 0.001 voxel of margin at the far
-// planes against the rounding of sample positions) and whether that macrocell
+// holding sample j's: its length (1 to 1024, a chunk of the walk; 0.001 voxel of
+// margin at the far planes against the rounding of sample positions) and whether that macrocell
 // is clear, i.e. whether each of them would add exactly nothing.
 __device__ __forceinline__ int macrocell_run(const MarchArgs& a, const DevBrick& br, int j, const float4& pos,
                                              const float4& dir, const float4& inv, float inv_mc, uint8_t& clear) {
@@ -80,7 +80,7 @@ __device__ __forceinline__ int macrocell_run(const MarchArgs& a, const DevBrick&
   };
   const float n = fminf(fminf(steps(q.x, inv.x, mx, br.lo[0]), steps(q.y, inv.y, my, br.lo[1])),
                         steps(q.z, inv.z, mz, br.lo[2]));
-  return 1 + (int)fmaxf(0.f, floorf(n));
+  return 1 + (int)__builtin_amdgcn_fmed3f(floorf(n), 0.f, 1023.f);
 }
 
 // Empty-space skipping ray by ray (emission-absorption).  8 x 8 rays per
