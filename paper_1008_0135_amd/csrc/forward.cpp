@@ -269,7 +269,8 @@ int render_forward(vr_ctx* ctx, vr_volume* vol, const vr_view* views, int32_t nv
     // 16-sample blocks around the others cost outweighs the samples saved (a
     // block-gathered sample costs about twice a sample of the cell march)
     const int64_t cells = vol->mcn[0] * vol->mcn[1] * vol->mcn[2];
-    if (forced || 2 * vol->mc_nclear < cells) base.mc = 0;
+    const bool indexed = std::max({vol->n[0], vol->n[1], vol->n[2]}) <= kSkipIndex;
+    if (forced || !indexed || 2 * vol->mc_nclear < cells) base.mc = 0;
   }
 
   std::vector<ViewPlan> plans((size_t)nviews);

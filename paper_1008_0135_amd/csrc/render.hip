@@ -67,15 +67,17 @@ __device__ __forceinline__ int macrocell_run(const MarchArgs& a, const DevBrick&
                                              const float4& dir, const float4& inv, float inv_mc, uint8_t& clear) {
   const SamplePos q = sample_pos(j, pos.x, pos.y, pos.z, dir.x, dir.y, dir.z);
   const Cell c = cell_of(q, br);
-  // macrocell of a cell index i >= 0 (below 2^22): floor((i + 1/2) / mc)
+  // macrocell of a cell index i >= 0 (below kSkipIndex): floor((i + 1/2) / mc)
   const float fmc = (float)a.mc;
   const float mx = floorf(((float)(c.ix + br.lo[0]) + 0.5f) * inv_mc);
   const float my = floorf(((float)(c.iy + br.lo[1]) + 0.5f) * inv_mc);
   const float mz = floorf(((float)(c.iz + br.lo[2]) + 0.5f) * inv_mc);
   clear = a.mc_clear[((int64_t)(int)mz * a.mcn[1] + (int)my) * a.mcn[0] + (int)mx];
-  // steps to the far plane (brick-local); inv = 1 / dir, 1e9 for a component of 0
+  // steps to the far plane; inv = 1 / dir, 1e9 for a component of 0.  The plane
+  // is made brick-local first (whole numbers, exact): its margin would be lost in
+  // the rounding of a coordinate of the whole axis, from 2^14 on
   auto steps = [&](float q1, float is, float m1, int lo) {
-    const float edge = fmaf(m1, fmc, is > 0.f ? fmc - 1e-3f : 1e-3f) - (float)lo;
+    const float edge = fmaf(m1, fmc, -(float)lo) + (is > 0.f ? fmc - 1e-3f : 1e-3f);
     return (edge - q1) * is;
   };
   const float n = fminf(fminf(steps(q.x, inv.x, mx, br.lo[0]), steps(q.y, inv.y, my, br.lo[1])),

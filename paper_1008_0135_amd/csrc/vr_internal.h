@@ -350,6 +350,9 @@ struct BatchReq {
 
 // Allocation-free batched entry point: its device scratch holds the
 // descriptor table of at most kNoAllocMaxReq requests.
+// cell indices whose macrocell the skipping march finds in single precision: i + 1/2
+// over the edge, two roundings of 2^-24 against the 1/2
+constexpr int64_t kSkipIndex = (int64_t)1 << 22;
 // register-staged ring march: 16-byte loads per lane for one voxel layer's window
 constexpr int kRingRegLoads = 8;
 // channel weights the cells march keeps in LDS beside the table (longer masks

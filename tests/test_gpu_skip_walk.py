@@ -42,3 +42,52 @@ def test_more_samples_than_an_int(capfd):
     assert (alpha[hit][:, (x > 1030) & (x < 1499)] == 0.9375).all()  # four samples of opacity 1/2
     vr.vr_volume_destroy(h)
     vr.vr_destroy(ctx)
+
+
+@pytest.mark.parametrize("long_axis", [0, 2])
+@pytest.mark.parametrize("length,edge", [(200001, 16), (2 ** 22 + 60000, 6)])
+def test_far_along_an_axis(long_axis, length, edge, capfd):
+    import torch
+    torch.cuda.init()
+    import paper_1008_0135_amd as vr
+    os.environ["VR_DEBUG_PLAN"] = "1"
+    try:
+        ctx = vr.vr_create(0)
+    finally:
+        del os.environ["VR_DEBUG_PLAN"]
+    n = [12, 12, 12]
+    n[long_axis] = length
+    M = 4096
+    rng = np.random.default_rng(7)
+    # three macrocells of four hold values a step below the opaque half of the table,
+    # the fourth the largest value inside its faces
+    i = np.arange(length)
+    line = np.where(((i // edge) % 4 == 3) & (i % edge > 0), 1.0, 2045.9 / (M - 1)).astype(np.float32)
+    a = torch.from_numpy(line).cuda().expand(12, 12, length) if long_axis == 0 else \
+        torch.from_numpy(line).cuda()[:, None, None].expand(length, 12, 12)
+    a = a.contiguous()
+    a[0, 0, 0] = 0.0
+    tf = rng.uniform(0.2, 1.0, (M, 4)).astype(np.float32)
+    tf[:, 3] = np.where(np.arange(M) < M // 2, 0.0, 0.3)
+    size = [12, 12, 12]
+    size[long_axis] = 16000 if length < 2 ** 22 else 60000
+    h = vr.vr_volume_create(ctx, a, n)
+    vr.vr_volume_brick(h, vr.grid_spec(size, macrocell=edge))
+    vr.vr_tf_set(ctx, tf, 0.0, 1.0)
+    # rays along the long axis, both ways
+    e3 = [[1.0, 0.0, 0.0], None, [0.0, 0.0, 1.0]][long_axis]
+    e1, e2 = ([0.0, 1.0, 0.0], [0.0, 0.0, 1.0]) if long_axis == 0 else ([1.0, 0.0, 0.0], [0.0, 1.0, 0.0])
+    back = [-x for x in e3]
+    views = [vr.make_view([e1, e2, e3], 8, 8, extent=9.0), vr.make_view([e2, e1, back], 8, 8, extent=9.7)]
+    on, off = (torch.full((2, 8, 8, 4), -7.0, device="cuda") for _ in range(2))
+    for step in (0.5, 0.37):
+        capfd.readouterr()
+        vr.vr_render(ctx, h, views, vr.make_params(tau=2.0, ess=1, step=step), on)
+        torch.cuda.synchronize()
+        assert ("skip 1" in capfd.readouterr().err) == (length < 2 ** 22)
+        vr.vr_render(ctx, h, views, vr.make_params(tau=2.0, ess=0, step=step), off)
+        torch.cuda.synchronize()
+        assert float(off.abs().max()) > 0
+        assert torch.equal(on, off)
+    vr.vr_volume_destroy(h)
+    vr.vr_destroy(ctx)
