@@ -47,7 +47,7 @@ __device__ __forceinline__ int xcd_block() {
   // which XCD takes which run of a round of eight moves on by three from round
   // to round: image rows of 8 or 16 runs would else give an XCD the same column
   // of the image in every row
-  const int b = (int)blockIdx.x, n = b / (8 * RUN), r = b - n * (8 * RUN);
+  const int b = grid_block(), n = b / (8 * RUN), r = b - n * (8 * RUN);
   return b - r + ((r + 3 * (n >> 2)) & 7) * RUN + (r >> 3);
 }
 
@@ -644,14 +644,14 @@ hipError_t launch_march(const MarchArgs& a, hipStream_t s) {
   const int nblk = (a.ntiles + 3) / 4;
   const int grid = (nblk + 8 * kXcdRun - 1) / (8 * kXcdRun) * (8 * kXcdRun);
   const size_t lds = sizeof(float4) * (size_t)a.M;
-  auto go = [&](auto kernel) { hipLaunchKernelGGL(kernel, dim3(grid), dim3(256), lds, s, a); };
+  auto go = [&](auto kernel) { hipLaunchKernelGGL(kernel, grid_rows(grid), dim3(256), lds, s, a); };
   const bool mask = a.mask != nullptr, mip = a.mip != 0;
   if (a.skip) {
     if (mip || a.mc < 2) return hipErrorInvalidValue;
     auto skip = [&](auto waves) {
       constexpr int N = decltype(waves)::value;
       const int round = 8 * kXcdRun * 4;
-      const dim3 blocks((a.ntiles + round - 1) / round * round / N), threads(64 * N);
+      const dim3 blocks = grid_rows(((int64_t)a.ntiles + round - 1) / round * round / N), threads(64 * N);
       if (a.thru && mask) hipLaunchKernelGGL((k_march_skip<N, true, true>), blocks, threads, lds, s, a);
       else if (a.thru) hipLaunchKernelGGL((k_march_skip<N, false, true>), blocks, threads, lds, s, a);
       else if (mask) hipLaunchKernelGGL((k_march_skip<N, true, false>), blocks, threads, lds, s, a);
@@ -695,7 +695,7 @@ hipError_t launch_march_save(const MarchArgs& a, const SaveArgs& sa, hipStream_t
   const bool by = a.slab_axis == 1;
   const auto f = sa.parts > 1 ? (by ? &k_march_save<true, true> : &k_march_save<false, true>)
                               : (by ? &k_march_save<true, false> : &k_march_save<false, false>);
-  hipLaunchKernelGGL(f, dim3(grid), dim3(256), lds, s, a, sa);
+  hipLaunchKernelGGL(f, grid_rows(grid), dim3(256), lds, s, a, sa);
   return hipGetLastError();
 }
 

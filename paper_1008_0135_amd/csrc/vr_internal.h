@@ -360,6 +360,13 @@ constexpr int kRingRegLoads = 8;
 constexpr int kCellsMaskMax = 4096;
 // LDS of a cells workgroup before its windows, in table rows of 16 bytes
 constexpr int cells_table_rows(const MarchArgs& a) { return a.M + (a.mask ? (a.mask_n + 3) / 4 : 0); }
+// Workgroups along x of a launch at most (256 lanes each): the runtime counts a
+// dimension's lanes in 32 bits.  Larger grids take rows of as many along y.
+constexpr int kGridRow = 1 << 22;
+inline dim3 grid_rows(int64_t blocks) {
+  return blocks <= kGridRow ? dim3((unsigned)blocks) : dim3(kGridRow, (unsigned)((blocks + kGridRow - 1) / kGridRow));
+}
+__device__ __forceinline__ int grid_block() { return (int)(blockIdx.x + blockIdx.y * kGridRow); }
 constexpr int kNoAllocMaxReq = 512;
 constexpr size_t kNoAllocBytes = sizeof(BatchReq) * kNoAllocMaxReq;
 constexpr int kMaxDevices = 64;

@@ -1,0 +1,45 @@
+"""Calls whose launches pass 2^32 lanes along one dimension of the grid (several
+lanes share a ray, one workgroup takes an item, one workgroup two planes of a
+brick): they are rendered, batched and bricked like any other."""
+import os
+
+import numpy as np
+import pytest
+
+import synth
+
+pytestmark = pytest.mark.gpu
+
+
+def _march(vr, mode):
+    os.environ["VR_MARCH"] = mode
+    try:
+        return vr.vr_create(0)
+    finally:
+        del os.environ["VR_MARCH"]
+
+
+@pytest.mark.parametrize("save", [False, True])
+def test_march(save):
+    # 16 lanes per ray of the largest image, rays 1.2 voxels apart
+    import torch
+    torch.cuda.init()
+    import paper_1008_0135_amd as vr
+    W = H = 16384
+    dims = (40, 30, 50)
+    a = torch.from_numpy(synth.cube(*dims, seed=5, n_sources=4)).cuda()
+    outs = []
+    for ctx in (vr.vr_create(0), _march(vr, "gather")):
+        h = vr.vr_volume_create(ctx, a, dims)
+        vr.vr_tf_set(ctx, synth.tf_ramp(64))
+        out = torch.full((1, H, W, 4), 7.0, device="cuda")
+        st = vr.vr_render(ctx, h, [vr.make_view(synth.rot_axis(2, 30.0), W, H, extent=20000.0)],
+                          vr.make_params(ckpt_K=64), out, save=save and not outs)
+        torch.cuda.synchronize()
+        if st:
+            vr.vr_state_destroy(st)
+        outs.append(out)
+        vr.vr_volume_destroy(h)
+        vr.vr_destroy(ctx)
+    assert float(outs[0].abs().max()) > 0
+    assert torch.equal(*outs)
