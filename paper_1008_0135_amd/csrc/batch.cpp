@@ -56,11 +56,12 @@ static void batch_free(vr_batch* b) {
 // shorter: 64 requests 1.33 ms with the line at 1.3 voxels between rays or
 // beyond, 1.40 at 1.0, 2.19 with sixteen lanes for all; 30 requests of 100^3 to
 // 256^3 on 60^2 to 120^2 pixels 320 us with four, 209 with sixteen; four
-// requests of 50 tiles each 39 and 35.
+// requests of 50 tiles each 39 and 35.  (Items are counted in an int, four a tile
+// with sixteen lanes.)
 static int32_t batch_lanes(const vr_volume* v, int32_t W, int64_t tiles) {
   double diag = 0.0;
   for (int i = 0; i < 3; i++) diag += (double)(v->n[i] - 1) * (double)(v->n[i] - 1);
-  return std::sqrt(diag) / W < 1.5 && tiles >= 512 ? 4 : 16;
+  return (std::sqrt(diag) / W < 1.5 && tiles >= 512) || tiles >= (1 << 29) ? 4 : 16;
 }
 
 // Estimated samples per pixel of a request: box volume / (pixel area x step), per pixel.

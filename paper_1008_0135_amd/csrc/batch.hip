@@ -143,7 +143,7 @@ __device__ __forceinline__ void batch_rays(const BatchArgs& ba, const BatchReq& 
 __global__ __launch_bounds__(256) void k_batch(BatchArgs ba) {
   extern __shared__ float4 s_tf[];
   const int wave = __builtin_amdgcn_readfirstlane((int)(threadIdx.x >> 6)), lane = threadIdx.x & 63;
-  const int b = (int)blockIdx.x, round = b / (8 * kRun), r = b - round * (8 * kRun);
+  const int b = grid_block(), round = b / (8 * kRun), r = b - round * (8 * kRun);
   const int item = b - r + ((r + 3 * (round >> 2)) & 7) * kRun + (r >> 3);
   if (item >= ba.total_items) return;  // the whole workgroup
   // request owning the item: last with item_begin <= item
@@ -169,7 +169,7 @@ __global__ __launch_bounds__(256) void k_batch(BatchArgs ba) {
 
 hipError_t launch_batch(const BatchArgs& a, int waves_per_cu, hipStream_t s) {
   if (a.total_items <= 0) return hipSuccess;
-  const int grid = (a.total_items + 8 * kRun - 1) / (8 * kRun) * (8 * kRun);
+  const int64_t grid = ((int64_t)a.total_items + 8 * kRun - 1) / (8 * kRun) * (8 * kRun);
   // at most waves_per_cu wavefronts per compute unit: LDS for one workgroup
   // more than that would not fit
   size_t lds = sizeof(float4) * (size_t)a.max_M;
@@ -179,7 +179,7 @@ hipError_t launch_batch(const BatchArgs& a, int waves_per_cu, hipStream_t s) {
         hipFuncSetAttribute(reinterpret_cast<const void*>(&k_batch), hipFuncAttributeMaxDynamicSharedMemorySize, (int)lds);
     if (e != hipSuccess) return e;
   }
-  hipLaunchKernelGGL(k_batch, dim3(grid), dim3(256), lds, s, a);
+  hipLaunchKernelGGL(k_batch, grid_rows(grid), dim3(256), lds, s, a);
   return hipGetLastError();
 }
 

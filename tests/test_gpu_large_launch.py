@@ -43,3 +43,34 @@ def test_march(save):
         vr.vr_destroy(ctx)
     assert float(outs[0].abs().max()) > 0
     assert torch.equal(*outs)
+
+
+def test_batch():
+    # a request of the largest image, 16 lanes per ray: four items a tile
+    import torch
+    torch.cuda.init()
+    import paper_1008_0135_amd as vr
+    W = H = 16384
+    dims = (26000, 3, 4)
+    ctx = vr.vr_create(0)
+    a = torch.rand(dims[::-1], generator=torch.Generator("cuda").manual_seed(2), device="cuda")
+    h = vr.vr_volume_create(ctx, a, dims)
+    tf = synth.tf_ramp(64)
+    vr.vr_tf_set(ctx, tf)
+    t = torch.from_numpy(tf).cuda()
+    R = synth.rot_axis(1, 20.0)
+    batch = torch.full((H, W, 4), 7.0, device="cuda")
+    plain = torch.full((1, H, W, 4), 7.0, device="cuda")
+    cache = vr.vr_render_batch(ctx, [vr.make_request(h, R, W, H, t, 0.0, 0.0, batch)], vr.make_params())
+    torch.cuda.synchronize()
+    vr.vr_batch_destroy(cache)
+    g = _march(vr, "gather")
+    h2 = vr.vr_volume_create(g, a, dims)
+    vr.vr_tf_set(g, tf)
+    vr.vr_render(g, h2, [vr.make_view(R, W, H)], vr.make_params(), plain)
+    torch.cuda.synchronize()
+    assert float(batch.abs().max()) > 0
+    assert torch.equal(batch, plain[0])
+    for c, v in ((ctx, h), (g, h2)):
+        vr.vr_volume_destroy(v)
+        vr.vr_destroy(c)
