@@ -802,9 +802,10 @@ static int brick_volume(vr_volume* vol, Partition& P, bool materialize, int32_t 
       mm[2 * b + 1] = src->bdesc[src_brick[b]].vmax;
     }
   } else {
-    const int zper = kBrickRangePlanes;
     int zmax = 1;
     for (int32_t b = 0; b < nb; b++) zmax = std::max<int>(zmax, (int)(sboxes[6 * b + 5] - sboxes[6 * b + 2] + 1));
+    int zper = kBrickRangePlanes;  // (more where the workgroups would pass an int)
+    while ((int64_t)nb * ((zmax + zper - 1) / zper) >= (int64_t)1 << 30) zper *= 2;
     const int zgroups = (zmax + zper - 1) / zper;
     const size_t need = (size_t)nb * 48 + (size_t)nb * zgroups * 8 + (size_t)nb * 8 + 1024;
     VR_TRY(ensure_device(&ctx->d_scratch, &ctx->scratch_bytes, need));

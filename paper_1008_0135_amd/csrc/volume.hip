@@ -118,9 +118,10 @@ __global__ __launch_bounds__(256) void k_minmax_final(const MinMaxPart* part, in
 // single floats, 256 bytes per wavefront).  Bound by HBM: 1 GiB in 16 bricks
 // 0.66 ms with one load in flight and idle lanes at row ends, 0.29 so.
 __global__ __launch_bounds__(256) void k_brick_minmax(const float* __restrict__ vol, int64_t n1, int64_t n2,
-                                                      const int64_t* __restrict__ boxes, int zgroups,
+                                                      const int64_t* __restrict__ boxes, int nb, int zgroups,
                                                       int zper, float2* part) {
-  const int b = blockIdx.x / zgroups, g = blockIdx.x % zgroups;
+  const int b = grid_block() / zgroups, g = grid_block() - b * zgroups;
+  if (b >= nb) return;  // (the last row of a large grid)
   const int64_t* bx = boxes + 6 * b;
   const int64_t x0 = bx[0], y0 = bx[1], z0 = bx[2], x1 = bx[3], y1 = bx[4], z1 = bx[5];
   const int64_t za = z0 + (int64_t)g * zper;
@@ -152,7 +153,7 @@ __global__ __launch_bounds__(256) void k_brick_minmax(const float* __restrict__ 
     }
   }
   block_reduce(mn, mx, bad);
-  if (threadIdx.x == 0) part[blockIdx.x] = make_float2(mn, mx);
+  if (threadIdx.x == 0) part[grid_block()] = make_float2(mn, mx);
 }
 
 // One wavefront per brick.
@@ -308,8 +309,8 @@ hipError_t launch_minmax_final(const float* partial, int32_t nblocks, float* out
 // partial buffer is allocated by the caller as `scratch` of nb*zgroups float2.
 hipError_t launch_brick_minmax_parts(const float* vol, const int64_t n[3], const int64_t* boxes, int32_t nb,
                                      int zgroups, int zper, float* scratch, float* out2, hipStream_t s) {
-  hipLaunchKernelGGL(k_brick_minmax, dim3(nb * zgroups), dim3(256), 0, s, vol, n[0], n[1], boxes, zgroups, zper,
-                     reinterpret_cast<float2*>(scratch));
+  hipLaunchKernelGGL(k_brick_minmax, grid_rows((int64_t)nb * zgroups), dim3(256), 0, s, vol, n[0], n[1], boxes, nb, zgroups,
+                     zper, reinterpret_cast<float2*>(scratch));
   hipError_t e = hipGetLastError();
   if (e != hipSuccess || !out2) return e;
   hipLaunchKernelGGL(k_brick_minmax_final, dim3(nb), dim3(64), 0, s, reinterpret_cast<const float2*>(scratch),
