@@ -446,8 +446,9 @@ int vr_autotune(vr_ctx *ctx, const vr_volume *vol, const vr_view *view, const vr
  * grouped by volume size class (floor(log2 voxels) / 3) and image class
  * (floor(log2 pixels) / 2); the requests of each class are rendered as a
  * batch of their own with 8 x 8, 16 x 4, 4 x 16 and 32 x 2 pixel tiles, and
- * the fastest is kept per class.  Then the occupancy: at most 2, 4, 8, 16 and
- * 32 wavefronts per compute unit over the whole batch with the tuned tiles.
+ * the fastest is kept per class.  Then the occupancy: as many wavefronts per
+ * compute unit as fit (the default, reported as 32), or at most 2, 4, 8 or 16,
+ * over the whole batch with the tuned tiles.
  * Both choices apply to later batched calls on this context (and are written
  * to VR_TUNE_CACHE); *cache is left holding the graph of the chosen shapes.
  * out->tile is the tile chosen for most classes.  Synchronises.

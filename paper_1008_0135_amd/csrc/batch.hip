@@ -170,10 +170,10 @@ __global__ __launch_bounds__(256) void k_batch(BatchArgs ba) {
 hipError_t launch_batch(const BatchArgs& a, int waves_per_cu, hipStream_t s) {
   if (a.total_items <= 0) return hipSuccess;
   const int64_t grid = ((int64_t)a.total_items + 8 * kRun - 1) / (8 * kRun) * (8 * kRun);
-  // at most waves_per_cu wavefronts per compute unit: LDS for one workgroup
-  // more than that would not fit
+  // at most waves_per_cu wavefronts per compute unit (0, kBatchWaves: as many as
+  // fit): LDS for one workgroup more than that would not fit
   size_t lds = sizeof(float4) * (size_t)a.max_M;
-  if (waves_per_cu > 0) lds = std::max(lds, 160 * 1024 / (size_t)(std::max(1, waves_per_cu / 4) + 1) + 1024);
+  if (waves_per_cu > 0 && waves_per_cu < kBatchWaves) lds = std::max(lds, 160 * 1024 / (size_t)(std::max(1, waves_per_cu / 4) + 1) + 1024);
   if (lds > 64 * 1024) {  // dynamic LDS beyond the default limit
     const hipError_t e =
         hipFuncSetAttribute(reinterpret_cast<const void*>(&k_batch), hipFuncAttributeMaxDynamicSharedMemorySize, (int)lds);

@@ -55,10 +55,12 @@ void tune_load(vr_ctx* ctx) {
   int tile, budget, mode;
   double ms;
   while (std::fscanf(f, "%255s %d %d %d %lf", key, &tile, &budget, &mode, &ms) == 5) {
-    if (std::strcmp(key, "batch/waves_per_cu") == 0) {
-      ctx->tune_waves_per_cu = tile;
+    if (std::strcmp(key, "batch/waves_at_most") == 0) {
+      ctx->tune_waves_per_cu = tile > 0 ? tile : 0;
       continue;
     }
+    // sized a grid of resident workgroups, which is no more
+    if (std::strcmp(key, "batch/waves_per_cu") == 0) continue;
     if (std::strncmp(key, "batch/", 6) == 0) {
       if (tile == 4 || tile == 8 || tile == 16 || tile == 32) ctx->tune.push_back(vr_ctx::TuneEntry{key, tile, 0, 1, ms});
       continue;
@@ -75,7 +77,7 @@ static void tune_save(const vr_ctx* ctx) {
   FILE* f = std::fopen(path, "w");
   if (!f) return;
   for (const auto& e : ctx->tune) std::fprintf(f, "%s %d %d %d %.6f\n", e.key.c_str(), e.tile, e.lds_budget, e.march_mode, e.ms);
-  if (ctx->tune_waves_per_cu > 0) std::fprintf(f, "batch/waves_per_cu %d 0 0 0\n", ctx->tune_waves_per_cu);
+  if (ctx->tune_waves_per_cu > 0) std::fprintf(f, "batch/waves_at_most %d 0 0 0\n", ctx->tune_waves_per_cu);
   std::fclose(f);
 }
 
@@ -219,10 +221,11 @@ int vr_autotune_batch(vr_ctx* ctx, const vr_request* reqs, int32_t n, const vr_p
     ctx->tune.push_back(vr_ctx::TuneEntry{key, pick, 0, 1, best});
     ntile_wins[pick == 4 ? 0 : pick == 8 ? 1 : pick == 16 ? 2 : 3]++;
   }
-  // 2. occupancy for the whole batch with the tuned tiles
-  const int32_t cands[] = {8, 2, 4, 16, 32};
+  // 2. occupancy for the whole batch with the tuned tiles; kBatchWaves, the
+  //    default, is no limit
+  const int32_t cands[] = {kBatchWaves, 2, 4, 8, 16};
   double best = INFINITY, dflt = INFINITY;
-  int32_t pick = 8;
+  int32_t pick = kBatchWaves;
   for (int32_t wpc : cands) {
     double ms = 0.0;
     VR_TRY(time_ms(s, 3, [&]() {
@@ -230,7 +233,7 @@ int vr_autotune_batch(vr_ctx* ctx, const vr_request* reqs, int32_t n, const vr_p
       VR_TRY(render_batch(ctx, reqs, n, p, cache, s, wpc, nullptr));
       return ctx_end(ctx, s);
     }, ms));
-    if (wpc == 8) dflt = ms;
+    if (wpc == kBatchWaves) dflt = ms;
     if (ms < best) {
       best = ms;
       pick = wpc;

@@ -427,6 +427,7 @@ int bwd_blocks(const MarchArgs& a);
 int tf_reduce_slices();
 hipError_t launch_tf_reduce(const double* part, int nblocks, int n, float* grad_tf, double* slices, hipStream_t s);
 hipError_t launch_fill(float* p, int64_t n, float v, hipStream_t s);
+constexpr int kBatchWaves = 32;  // wavefronts a compute unit holds
 hipError_t launch_batch(const BatchArgs& a, int waves_per_cu, hipStream_t s);
 hipError_t launch_copy_box(const float* src, const int64_t sn[3], const int64_t so[3], float* dst,
                            const int64_t dn[3], hipStream_t s);
