@@ -173,10 +173,17 @@ int vr_volume_wrap(vr_ctx *ctx, float *dev_ptr, int64_t n1, int64_t n2, int64_t 
 /*
  * Frees the volume (waits for the device first).  Its device memory is kept
  * for volumes created later, up to 1/32 of the device's memory in all, until
- * the last context of the device is destroyed or an allocation of the library
- * would fail without it.
+ * the last context of the device is destroyed, an allocation of the library
+ * would fail without it, or vr_trim gives it back.
  */
 int vr_volume_destroy(vr_volume *vol);
+
+/*
+ * Gives back the device memory that destroyed volumes of ctx's device left with
+ * the library, for a caller whose own allocations need it.  No live object is
+ * touched; later volumes allocate anew.  Errors: VR_EINVAL (NULL).
+ */
+int vr_trim(vr_ctx *ctx);
 
 /* Global (min, max) over all voxels (paper Sec. 2.2).  Synchronises. */
 int vr_volume_minmax(vr_volume *vol, float *vmin, float *vmax);

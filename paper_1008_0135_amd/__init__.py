@@ -107,6 +107,7 @@ _SIGS = {
     "vr_volume_create": (_I, [_P, _P, _I, _I64, _I64, _I64, _P, _P, _U, _P]),
     "vr_volume_wrap": (_I, [_P, _P, _I64, _I64, _I64, _U, _P]),
     "vr_volume_destroy": (_I, [_P]),
+    "vr_trim": (_I, [_P]),
     "vr_volume_minmax": (_I, [_P, _P, _P]),
     "vr_volume_dims": (_I, [_P, _P]),
     "vr_volume_brick": (_I, [_P, _P, _U]),
@@ -292,6 +293,11 @@ def vr_volume_dims(vol):
 
 def vr_volume_brick(vol, spec, stream=None):
     _check(lib().vr_volume_brick(vol, C.byref(spec), _stream(stream)), "vr_volume_brick")
+
+
+def vr_trim(ctx):
+    """Give back the device memory that destroyed volumes left with the library."""
+    _check(lib().vr_trim(ctx), "vr_trim")
 
 
 def vr_volume_brick_info(vol):

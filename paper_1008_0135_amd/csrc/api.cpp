@@ -689,6 +689,14 @@ int vr_volume_destroy(vr_volume* vol) {
   return VR_OK;
 }
 
+int vr_trim(vr_ctx* ctx) {
+  clear_error();
+  if (!ctx) return fail(VR_EINVAL, "ctx is NULL");
+  DeviceGuard g(ctx->device);
+  pool_trim(ctx->device);
+  return VR_OK;
+}
+
 int vr_volume_minmax(vr_volume* vol, float* vmin, float* vmax) {
   clear_error();
   if (!vol || !vmin || !vmax) return fail(VR_EINVAL, "vol, vmin and vmax must be non-NULL");

@@ -5,8 +5,9 @@
 // clearing in hipMalloc: 56 of the 60 ms of opening and closing a 1 GiB cube
 // with its permuted copy in a steady loop.  Blocks of destroyed volumes are
 // therefore kept, at most a 1/32 of the device's memory, oldest given back
-// first; all are given back when the device's last context is destroyed and
-// whenever an allocation of the library fails (it is then tried again).
+// first; all are given back when the device's last context is destroyed,
+// whenever an allocation of the library fails (it is then tried again), and by
+// vr_trim, for other allocators of the process.
 //
 // A block enters the pool only after the device was synchronised (no stream
 // still uses it), so it can be handed out to work on any stream.  One lock
@@ -130,6 +131,12 @@ void pool_enter(int device) {
   if (device < 0 || device >= kMaxDevices) return;
   std::lock_guard<std::mutex> lk(g_mu);
   g_pool[device].contexts++;
+}
+
+void pool_trim(int device) {
+  if (device < 0 || device >= kMaxDevices) return;
+  std::lock_guard<std::mutex> lk(g_mu);
+  flush_locked(g_pool[device]);
 }
 
 void pool_leave(int device) {

@@ -203,6 +203,8 @@ inline hipError_t dev_take(T** p, size_t bytes, size_t* got) {
   return dev_take(reinterpret_cast<void**>(p), bytes, got);
 }
 void dev_give(void* p, size_t bytes);
+// all that the pool holds for a device, back to the driver
+void pool_trim(int device);
 // contexts of a device: the last one to leave frees the device's pool
 void pool_enter(int device);
 void pool_leave(int device);
