@@ -59,6 +59,24 @@ __device__ __forceinline__ void block_tile(int t, int blocks_x, int& tx, int& ty
   ty = by * 2 + (t >> 1 & 1);
 }
 
+// Rays through all bricks (a.bv front to back): the bricks whose rectangles meet a
+// tile of w x h pixels at (x0, y0), 64 tested at a time, a lane each (the whole
+// wavefront takes part); f(view) for each in order while more() holds.  One test
+// after another had every wavefront wait for every brick: 32768 bricks, one 768^2
+// view, 76 ms.
+template <class More, class F>
+__device__ __forceinline__ void bricks_of_tile(const MarchArgs& a, int x0, int y0, int w, int h, More more, F f) {
+  const int lane = threadIdx.x & 63;
+  for (int b0 = 0; b0 < a.nbv && more(); b0 += 64) {
+    bool hit = false;
+    if (b0 + lane < a.nbv) {
+      const DevBrickView& v = a.bv[b0 + lane];
+      hit = x0 < v.x0 + v.w && x0 + w > v.x0 && y0 < v.y0 + v.h && y0 + h > v.y0;
+    }
+    for (unsigned long long m = __ballot(hit); m != 0 && more(); m &= m - 1) f(a.bv[b0 + __builtin_ctzll(m)]);
+  }
+}
+
 // Run of samples of a ray from sample j on whose cells lie in the macrocell
 // holding sample j's: its length (1 to 1024, a chunk of the walk; 0.001 voxel of
 // margin at the far planes against the rounding of sample positions) and whether that macrocell
@@ -148,12 +166,7 @@ __global__ __launch_bounds__(64 * WAVES) void k_march_skip(MarchArgs a) {
   const float inv_mc = 1.f / (float)a.mc;
   const int dl = lane & 15;
   bool touched = false;
-  for (int b = lo; b < (THRU ? a.nbv : lo + 1); ++b) {
-    const DevBrickView& bvw = a.bv[b];
-    if constexpr (THRU) {
-      // the tile lies outside the brick's rectangle
-      if (tx * 8 >= bvw.x0 + bvw.w || tx * 8 + 8 <= bvw.x0 || ty * 8 >= bvw.y0 + bvw.h || ty * 8 + 8 <= bvw.y0) continue;
-    }
+  auto march = [&](const DevBrickView& bvw) {
     const DevBrick br = a.bricks[bvw.brick];
     float4 pos = make_float4(0.f, 0.f, 0.f, 0.f), dir = pos;
     int cnt = 0;
@@ -170,7 +183,7 @@ __global__ __launch_bounds__(64 * WAVES) void k_march_skip(MarchArgs a) {
         touched = true;
       }
     }
-    if (!__any(cnt > 0)) continue;
+    if (!__any(cnt > 0)) return;
     pos.w = __int_as_float(cnt);
     s_pos[wave][lane] = pos;
     s_dir[wave][lane] = dir;
@@ -279,8 +292,9 @@ __global__ __launch_bounds__(64 * WAVES) void k_march_skip(MarchArgs a) {
         cnt = 0;
       }
     }
-    if (!__any(live)) break;
-  }
+  };
+  if constexpr (THRU) bricks_of_tile(a, tx * 8, ty * 8, 8, 8, [&] { return __any(live) != 0; }, march);
+  else march(a.bv[lo]);
   acc = s_acc[wave][lane];
   // carried state: only a ray with samples here owns its pixel in this wave
   if (!valid || (!THRU && a.carry && !touched)) return;
@@ -331,7 +345,8 @@ __global__ __launch_bounds__(256) void k_march(MarchArgs a) {
   }
   const int ray = (threadIdx.x & 63) / D, dl = threadIdx.x & (D - 1);
   const int lx = tx * TW + (ray % TW), ly = ty * TH + (ray / TW);
-  if (lx >= rw || ly >= rh) return;
+  const bool inside = lx < rw && ly < rh;
+  if (!THRU && !inside) return;  // (THRU: every lane tests bricks)
   const int u = rx + lx, v = ry + ly;
 
   double o[3], d[3];
@@ -350,19 +365,14 @@ __global__ __launch_bounds__(256) void k_march(MarchArgs a) {
   int64_t n;
   bool touched = false;  // the ray has samples in this brick
   bool stopped = false;
-  if (ray_lattice(o, d, a.hi, a.step, tin, n)) {
+  const bool meets = inside && ray_lattice(o, d, a.hi, a.step, tin, n);
+  {
     const float sx = (float)(a.step * d[0]), sy = (float)(a.step * d[1]), sz = (float)(a.step * d[2]);
-    for (int b = lo; b < (THRU ? a.nbv : lo + 1); ++b) {
-      const DevBrickView& bvw = a.bv[b];
-      if constexpr (THRU) {
-        // the tile lies outside the brick's rectangle (the same for all lanes)
-        if (tx * TW >= bvw.x0 + bvw.w || tx * TW + TW <= bvw.x0 || ty * TH >= bvw.y0 + bvw.h || ty * TH + TH <= bvw.y0)
-          continue;
-      }
+    auto march = [&](const DevBrickView& bvw) {
       const DevBrick& br = a.bricks[bvw.brick];
       int64_t k0, k1;
       brick_krange(o, d, tin, a.step, n, br.lo, br.hi, br.closed, k0, k1);
-      if (k1 <= k0) continue;
+      if (k1 <= k0) return;
       touched = true;
       const double t0 = tin + ((double)k0 + 0.5) * a.step;
       const float px = (float)(o[0] + t0 * d[0] - (double)br.lo[0]);
@@ -416,9 +426,15 @@ __global__ __launch_bounds__(256) void k_march(MarchArgs a) {
         }
         if (stopped || !more) break;
       }
-      if (stopped) break;
-    }
+    };
+    if constexpr (THRU)
+      bricks_of_tile(a, tx * TW, ty * TH, TW, TH, [&] { return __any(meets && !stopped) != 0; },
+                     [&](const DevBrickView& bvw) {
+                       if (meets && !stopped) march(bvw);
+                     });
+    else if (meets) march(a.bv[lo]);
   }
+  if (THRU && !inside) return;
   // carried state: only a ray with samples here owns its pixel in this wave
   // (another brick of the wave whose rectangle holds the pixel may update it)
   if (!THRU && a.carry && !touched) return;
