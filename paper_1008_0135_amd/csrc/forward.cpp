@@ -70,21 +70,23 @@ int32_t gather_lanes(const Camera& cam) {
   return cam.S / (double)cam.W < 1.1 && (int64_t)cam.W * cam.H >= ((int64_t)1 << 16) ? 4 : 16;
 }
 
-MarchTimes march_times(const Camera& cam, const std::vector<Box>& boxes, double step, const FootShape* fs, int views) {
+void add_box(BoxSums& s, const Camera& cam, const Box& b, double step) {
+  const double pitch = cam.S / (double)cam.W;
+  const double* d = cam.e3;
+  const double e[3] = {(double)(b.hi[0] - b.lo[0]), (double)(b.hi[1] - b.lo[1]), (double)(b.hi[2] - b.lo[2])};
+  const double vol = e[0] * e[1] * e[2];
+  const double area = std::fabs(d[0]) * e[1] * e[2] + std::fabs(d[1]) * e[0] * e[2] + std::fabs(d[2]) * e[0] * e[1];
+  const double rays = std::min(area / (pitch * pitch), (double)cam.W * cam.H);
+  s.samples += rays * vol / std::max(area, 1.0) / step;
+  s.bytes += 4.0 * vol;
+  for (int i = 0; i < 3; i++) s.most[i] = std::max(s.most[i], b.hi[i] - b.lo[i]);
+}
+
+MarchTimes march_times(const Camera& cam, const BoxSums& boxes, const FootShape* fs, int views) {
   MarchTimes t;
   t.pitch = cam.S / (double)cam.W;
-  double samples = 0.0, bytes = 0.0;
-  int64_t layers = 0;
-  const double* d = cam.e3;
-  for (const Box& b : boxes) {
-    const double e[3] = {(double)(b.hi[0] - b.lo[0]), (double)(b.hi[1] - b.lo[1]), (double)(b.hi[2] - b.lo[2])};
-    const double vol = e[0] * e[1] * e[2];
-    const double area = std::fabs(d[0]) * e[1] * e[2] + std::fabs(d[1]) * e[0] * e[2] + std::fabs(d[2]) * e[0] * e[1];
-    const double rays = std::min(area / (t.pitch * t.pitch), (double)cam.W * cam.H);
-    samples += rays * vol / std::max(area, 1.0) / step;
-    bytes += 4.0 * vol;
-    if (fs) layers = std::max(layers, b.hi[fs->axis] - b.lo[fs->axis]);
-  }
+  const double samples = boxes.samples, bytes = boxes.bytes;
+  const int64_t layers = fs ? boxes.most[fs->axis] : 0;
   t.samples = samples;
   t.gather = 20e-6 + samples * std::pow(std::max(1.0, t.pitch / 1.2), 0.75) / (gather_lanes(cam) == 4 ? 230e9 : 182e9);
   if (!fs || t.pitch < 0.75) return t;
@@ -172,7 +174,7 @@ int32_t foot_brick(const Camera& cam, const FootShape& fs, const Box& box, DevBr
 // transparent brick), launch order (brick index order, which keeps
 // neighbouring bricks together), arena offsets and the front-to-back layers.
 void plan_bricked_view(const vr_volume* vol, const Camera& cam, const vr_params* p, int32_t tile_w,
-                       const float* tf, int32_t M, double vmin, double vmax, ViewPlan& vp, bool waves) {
+                       const float* tf, int32_t M, double vmin, double vmax, ViewPlan& vp) {
   const Partition& P = vol->part;
   const int32_t nb = (int32_t)P.boxes.size();
   const int32_t tile_h = 64 / tile_w;
@@ -211,29 +213,31 @@ void plan_bricked_view(const vr_volume* vol, const Camera& cam, const vr_params*
   vp.pixels = pix;
   vp.wave_begin.clear();
   vp.wave_tiles.clear();
-  if (waves) {
-    std::vector<int32_t> wave;
-    const int32_t nw = brick_waves(P, cam, wave);
-    std::vector<DevBrickView> by_wave;
-    by_wave.reserve(vp.bv.size());
-    for (int32_t w = 0; w < nw; w++) {
-      const int32_t first = (int32_t)by_wave.size();
-      int32_t t = 0;
-      for (const DevBrickView& b : vp.bv)
-        if (wave[b.brick] == w) {
-          DevBrickView c = b;
-          c.tile_begin = t;
-          t += c.tiles_x * ((c.h + tile_h - 1) / tile_h);
-          by_wave.push_back(c);
-        }
-      if (t == 0) continue;
-      vp.wave_begin.push_back(first);
-      vp.wave_tiles.push_back(t);
-    }
-    vp.wave_begin.push_back((int32_t)by_wave.size());
-    vp.bv.swap(by_wave);
-    vp.layers_order.clear();  // no brick images to composite
+}
+
+void plan_waves(const vr_volume* vol, const Camera& cam, int32_t tile_w, ViewPlan& vp) {
+  const int32_t tile_h = 64 / tile_w;
+  std::vector<int32_t> wave;
+  const int32_t nw = brick_waves(vol->part, cam, wave);
+  std::vector<DevBrickView> by_wave;
+  by_wave.reserve(vp.bv.size());
+  for (int32_t w = 0; w < nw; w++) {
+    const int32_t first = (int32_t)by_wave.size();
+    int32_t t = 0;
+    for (const DevBrickView& b : vp.bv)
+      if (wave[b.brick] == w) {
+        DevBrickView c = b;
+        c.tile_begin = t;
+        t += c.tiles_x * ((c.h + tile_h - 1) / tile_h);
+        by_wave.push_back(c);
+      }
+    if (t == 0) continue;
+    vp.wave_begin.push_back(first);
+    vp.wave_tiles.push_back(t);
   }
+  vp.wave_begin.push_back((int32_t)by_wave.size());
+  vp.bv.swap(by_wave);
+  vp.layers_order.clear();  // no brick images to composite
 }
 
 int render_forward(vr_ctx* ctx, vr_volume* vol, const vr_view* views, int32_t nviews, const vr_params* p,
@@ -280,7 +284,7 @@ int render_forward(vr_ctx* ctx, vr_volume* vol, const vr_view* views, int32_t nv
     make_camera(views[v], vol->n, cams[v]);
     ViewPlan& vp = plans[v];
     if (bricked) {
-      plan_bricked_view(vol, cams[v], p, tw, ctx->h_tf.data(), ctx->tf_m, vmin, vmax, vp, global);
+      plan_bricked_view(vol, cams[v], p, tw, ctx->h_tf.data(), ctx->tf_m, vmin, vmax, vp);
       if (!global) arena_pix = std::max(arena_pix, vp.pixels);
     } else {
       DevBrickView b;
@@ -321,45 +325,39 @@ int render_forward(vr_ctx* ctx, vr_volume* vol, const vr_view* views, int32_t nv
   // every ray through all its bricks in one launch: bricks front to back
   auto thru_order = [&](int32_t v) {
     ViewPlan& vp = plans[v];
-    plan_bricked_view(vol, cams[v], p, tw, ctx->h_tf.data(), ctx->tf_m, vmin, vmax, vp, false);
     std::vector<DevBrickView> o;
+    o.reserve(vp.bv.size());
     for (int32_t i : vp.layers_order) o.push_back(vp.bv[i]);
     vp.bv.swap(o);
     vp.layers_order.clear();
     vp.thru = true;
   };
-  auto view_boxes = [&](const ViewPlan& vp) {
-    std::vector<Box> boxes;
-    for (const DevBrickView& b : vp.bv) {
-      if (bricked) {
-        boxes.push_back(vol->part.boxes[b.brick]);
-        continue;
-      }
-      Box w;
-      for (int i = 0; i < 3; i++) {
-        w.lo[i] = 0;
-        w.hi[i] = vol->n[i] - 1;
-        w.closed[i] = 1;
-      }
-      boxes.push_back(w);
-    }
-    return boxes;
-  };
+  Box whole;
+  for (int i = 0; i < 3; i++) {
+    whole.lo[i] = 0;
+    whole.hi[i] = vol->n[i] - 1;
+    whole.closed[i] = 1;
+  }
+  std::vector<BoxSums> sums((size_t)nviews);
+  for (int32_t v = 0; v < nviews && pick; v++)
+    for (const DevBrickView& b : plans[v].bv) add_box(sums[v], cams[v], bricked ? vol->part.boxes[b.brick] : whole, p->step);
   for (int32_t v = 0; v < nviews; v++) {
     ViewPlan& vp = plans[v];
-    if (!pick || vp.bv.empty()) continue;
-    if (base.mc > 0) {
+    const bool choose = pick && !vp.bv.empty();
+    if (choose && base.mc > 0) {
       if (global) thru_order(v);
       vp.skip = true;
       gather_view(vp, 16);
-    } else if (global && !forced) {
-      const MarchTimes t = march_times(cams[v], view_boxes(vp), p->step, nullptr);
-      if (nviews == 1 || t.pitch < 1.0 || t.gather < kThruBelow) {
+    } else if (global) {
+      const MarchTimes t = march_times(cams[v], sums[v], nullptr);
+      if (choose && !forced && (nviews == 1 || t.pitch < 1.0 || t.gather < kThruBelow)) {
         thru_order(v);
         gather_view(vp, gather_lanes(cams[v]));
-      } else if (base.mask || vp.wave_begin.size() > 8) {
-        gather_view(vp, t.pitch < 2.0 ? 4 : 16);
+        continue;
       }
+      plan_waves(vol, cams[v], tw, vp);
+      if (choose && !forced && (base.mask || vp.wave_begin.size() > 8))
+        gather_view(vp, t.pitch < 2.0 ? 4 : 16);
     }
   }
   // perspective views: footprint cells sized per brick (the plain march of
@@ -367,10 +365,10 @@ int render_forward(vr_ctx* ctx, vr_volume* vol, const vr_view* views, int32_t nv
   // axis along which the eye lies outside its slab; the bricks neither axis
   // suits, and views with rays less than kPerspCellPitch voxels apart, by
   // gathers
-  auto persp_faster = [&](const Camera& cam, const ViewPlan& vp) {
+  auto persp_faster = [&](const Camera& cam, const BoxSums& boxes) {
     FootShape any;
     any.axis = std::fabs(cam.e3[1]) >= std::fabs(cam.e3[2]) ? 1 : 2;
-    const MarchTimes t = march_times(cam, view_boxes(vp), p->step, &any);
+    const MarchTimes t = march_times(cam, boxes, &any);
     return t.samples / kPerspCellRate + kPerspChains * t.chain <= t.gather;
   };
   for (int32_t v = 0; v < nviews; v++) {
@@ -378,7 +376,7 @@ int render_forward(vr_ctx* ctx, vr_volume* vol, const vr_view* views, int32_t nv
     if (!pick || !cams[v].persp || vp.bv.empty() || vp.deep || global) continue;
     const bool cells = bricked && ctx->persp_cells && (!base.mask || base.mask_n <= kCellsMaskMax) &&
                        ctx->ring_reg > 0 && ctx->ring_nslots != 3 &&
-                       (forced || (cams[v].S / W >= kPerspCellPitch && persp_faster(cams[v], vp)));
+                       (forced || (cams[v].S / W >= kPerspCellPitch && persp_faster(cams[v], sums[v])));
     const int first_axis = std::fabs(cams[v].e3[1]) >= std::fabs(cams[v].e3[2]) ? 1 : 2;
     std::vector<int32_t> axis(vp.bv.size(), 0);
     bool any = false;
@@ -448,12 +446,11 @@ int render_forward(vr_ctx* ctx, vr_volume* vol, const vr_view* views, int32_t nv
     // gathers for certain: their estimate is below the cells' best (the slab
     // axis with fewer layers), without sizing the cells on the host (80 us)
     if (!forced && !global && ctx->foot && !vp.bv.empty()) {
-      const std::vector<Box> boxes = view_boxes(vp);
       bool sure = true;
       for (int axis : {1, 2}) {
         FootShape any;
         any.axis = axis;
-        const MarchTimes t = march_times(cams[v], boxes, p->step, &any);
+        const MarchTimes t = march_times(cams[v], sums[v], &any);
         sure = sure && t.gather < t.cells;
       }
       if (sure) {
@@ -471,10 +468,11 @@ int render_forward(vr_ctx* ctx, vr_volume* vol, const vr_view* views, int32_t nv
     // staged windows read whole rows, past a narrow volume's end too
     if (cells && fs.reg)
       for (const DevBrickView& b : vp.bv) cells = cells && brick_rows_readable(vol, b.brick, (fs.nf + 3) & ~3);
-    if (cells)
-      for (const Box& b : view_boxes(vp)) cells = cells && samples_countable(cams[v], b, p->step);
+    Box widest = whole;
+    for (int i = 0; i < 3; i++) widest.hi[i] = sums[v].most[i];
+    cells = cells && samples_countable(cams[v], widest, p->step);
     if (!forced && !global && ctx->foot && !vp.bv.empty()) {
-      const MarchTimes t = march_times(cams[v], view_boxes(vp), p->step, cells ? &fs : nullptr);
+      const MarchTimes t = march_times(cams[v], sums[v], cells ? &fs : nullptr);
       if (ctx->debug_plan)
         std::fprintf(stderr, "[vr] view %d: estimated cells %.0f us, gathers %.0f us\n", v, t.cells * 1e6, t.gather * 1e6);
       if (t.gather < t.cells) {
@@ -483,12 +481,6 @@ int render_forward(vr_ctx* ctx, vr_volume* vol, const vr_view* views, int32_t nv
       }
     }
     if (!cells) continue;
-    Box whole;
-    for (int i = 0; i < 3; i++) {
-      whole.lo[i] = 0;
-      whole.hi[i] = vol->n[i] - 1;
-      whole.closed[i] = 1;
-    }
     // blocks of cells (the plain march, emission-absorption or MIP): one
     // workgroup per block, one window per layer; the window's rows must fit
     // inside every brick along axis 1

@@ -45,8 +45,14 @@ struct MarchTimes {
 // 0.7 1.23 ms and 1.00, at 1.35 414 us and 484; 256^2 rays through 128^3 59
 // and 59, fewer rays up to twice as slow with 4).
 int32_t gather_lanes(const Camera& cam);
-MarchTimes march_times(const Camera& cam, const std::vector<Box>& boxes, double step, const FootShape* fs,
-                       int views = 1);
+// What the estimates need of the boxes a view marches, gathered in one pass over
+// them (a volume may have 65536).
+struct BoxSums {
+  double samples = 0.0, bytes = 0.0;
+  int64_t most[3] = {0, 0, 0};  // largest extent along each axis, voxels
+};
+void add_box(BoxSums& s, const Camera& cam, const Box& box, double step);
+MarchTimes march_times(const Camera& cam, const BoxSums& boxes, const FootShape* fs, int views = 1);
 
 // Footprint-cell shape of one parallel view of a volume of size n, as the
 // forward picks it: plain = the plain march (no macrocell skipping, no mask),
@@ -69,7 +75,9 @@ void foot_args(const vr_ctx* ctx, const FootShape& fs, MarchArgs& a, int& wpb);
 int32_t foot_brick(const Camera& cam, const FootShape& fs, const Box& box, DevBrickView& b);
 
 void plan_bricked_view(const vr_volume* vol, const Camera& cam, const vr_params* p, int32_t tile_w,
-                       const float* tf, int32_t M, double vmin, double vmax, ViewPlan& vp, bool waves = false);
+                       const float* tf, int32_t M, double vmin, double vmax, ViewPlan& vp);
+// The planned bricks regrouped by front-to-back wave.
+void plan_waves(const vr_volume* vol, const Camera& cam, int32_t tile_w, ViewPlan& vp);
 int render_forward(vr_ctx* ctx, vr_volume* vol, const vr_view* views, int32_t nviews, const vr_params* p, float* out,
                    hipStream_t s);
 int validate_render(vr_ctx* ctx, const vr_volume* vol, const vr_view* views, int32_t nviews, const vr_params* p);

@@ -222,7 +222,9 @@ int render_with_state(vr_ctx* ctx, vr_volume* vol, const vr_view* views, int32_t
     // run at a time)
     FootShape fs;
     fs.axis = rv.axis;
-    const MarchTimes t = march_times(cams[v], {whole}, p->step, &fs, ctx->bwd_side ? std::min(nviews, 3) : 1);
+    BoxSums box;
+    add_box(box, cams[v], whole, p->step);
+    const MarchTimes t = march_times(cams[v], box, &fs, ctx->bwd_side ? std::min(nviews, 3) : 1);
     if (ctx->foot && (ctx->march_mode == 3 || t.cells <= t.gather) &&
         pick_foot(cams[v], vol->n, ctx->tf_m, true, ctx->ring_reg > 0, ctx->ring_nslots, ctx->foot_rays,
                   ctx->foot_pad, ctx->foot_kmax, fs, ctx->foot_maxpx, rv.axis) &&
