@@ -356,7 +356,7 @@ int render_forward(vr_ctx* ctx, vr_volume* vol, const vr_view* views, int32_t nv
         continue;
       }
       plan_waves(vol, cams[v], tw, vp);
-      if (choose && !forced && (base.mask || vp.wave_begin.size() > 8))
+      if (choose && !forced && (base.mask || cams[v].persp || vp.wave_begin.size() > 8))
         gather_view(vp, t.pitch < 2.0 ? 4 : 16);
     }
   }

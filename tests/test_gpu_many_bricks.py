@@ -26,3 +26,11 @@ def test_through_all_bricks(dims, brick, image, eye, mc):
             x, y = _both(dims, image, lambda vr: vr.grid_spec(brick, macrocell=mc), views, low if mc else _opaque, mask=m,
                          ert_scope=1, tau=0.95, shows=image == (70, 45))
             assert torch.equal(x, y)
+
+
+# several perspective views whose fronts are few and large
+def test_perspective_fronts():
+    import torch
+    x, y = _both((300, 280, 290), (300, 280), lambda vr: vr.grid_spec((150,) * 3), _views(2, 700.0), _opaque, ert_scope=1,
+                 tau=0.95)
+    assert torch.equal(x, y)
