@@ -132,16 +132,24 @@ __device__ __forceinline__ double quad_pick(int dl, double v0, double v1, double
   return dl & 2 ? hi : lo;
 }
 
+// Sums of a small table in LDS: lanes adding to one entry wait for each other, so
+// tables of up to half as many entries as this get several copies, a lane adds to
+// its own, until there are this many entries (8 KB).  Two views of 644 x 687 rays
+// through 257 x 408 x 111 voxels, half a voxel a sample, 2 / 16 / 32 / 64 entries:
+// 5.7 / 5.1 / 4.0 / 3.1 ms with one copy, 2.1 / 2.1 / 2.3 / 2.5 so; twice as many
+// entries 2.3 at 64, but 64^3 at 96^2 205 against 185 us (occupancy).
+constexpr int kTableEntries = 256;
 constexpr int kAhead = 3;  // layers of windows kept ahead in registers
 
 template <bool REPLAY, bool by>
 __global__ __launch_bounds__(256) __attribute__((amdgpu_waves_per_eu(4))) void k_bwd_ring(MarchArgs a, BwdArgs ba) {
   extern __shared__ double dsm[];
   const int M = a.M, L = ba.K;
-  // table gradients [4][M]: neighbouring entries in neighbouring banks (an
+  // table gradients [4][M][copies]: neighbouring entries in neighbouring banks (an
   // [M][4] layout makes entries 8 apart collide: 56 cycles per add against 33)
+  const int csh = ba.copy_shift;
   double* s_gtf = dsm;
-  float4* s_tf = reinterpret_cast<float4*>(dsm + 4 * M);  // [M]
+  float4* s_tf = reinterpret_cast<float4*>(dsm + (4 * M << csh));  // [M]
   const int slot = a.ring_slot;
   // The gradient windows hold doubles: on gfx950 one ds_add_f32 takes about
   // 195 cycles of a compute unit's LDS whatever its addresses (it retires
@@ -152,10 +160,8 @@ __global__ __launch_bounds__(256) __attribute__((amdgpu_waves_per_eu(4))) void k
   int* s_boff = reinterpret_cast<int*>(s_vox + (size_t)(L + 1) * slot);         // [32] window offsets
   int* s_range = s_boff + 32;                                                   // [8] layer ranges
   double* s_T = reinterpret_cast<double*>(s_boff + 64);                         // REPLAY: [blocks][64]
-  for (int i = threadIdx.x; i < M; i += blockDim.x) {
-    s_tf[i] = a.tf[i];
-    s_gtf[i] = s_gtf[M + i] = s_gtf[2 * M + i] = s_gtf[3 * M + i] = 0.0;
-  }
+  for (int i = threadIdx.x; i < M; i += blockDim.x) s_tf[i] = a.tf[i];
+  for (int i = threadIdx.x; i < 4 * M << csh; i += blockDim.x) s_gtf[i] = 0.0;
   for (int e = threadIdx.x; e < (L + 1) * slot; e += blockDim.x) s_grad[e] = 0.0;
 
   // same tile order as the forward
@@ -463,15 +469,16 @@ __global__ __launch_bounds__(256) __attribute__((amdgpu_waves_per_eu(4))) void k
         const double gr = gx * ta, gg = gy * ta, gb = gz * ta;
         const double ga = Tp * (h - Sk);
         const double w1 = e.w, w0 = 1.0 - e.w;
-        double* q = s_gtf + e.i;
+        double* q = s_gtf + ((e.i << csh) + (lane & ((1 << csh) - 1)));
+        const int q1 = 1 << csh, qm = M << csh;  // to the next entry, channel
         atomicAdd(q, w0 * gr);
-        atomicAdd(q + 1, w1 * gr);
-        atomicAdd(q + M, w0 * gg);
-        atomicAdd(q + M + 1, w1 * gg);
-        atomicAdd(q + 2 * M, w0 * gb);
-        atomicAdd(q + 2 * M + 1, w1 * gb);
-        atomicAdd(q + 3 * M, w0 * ga);
-        atomicAdd(q + 3 * M + 1, w1 * ga);
+        atomicAdd(q + q1, w1 * gr);
+        atomicAdd(q + qm, w0 * gg);
+        atomicAdd(q + qm + q1, w1 * gg);
+        atomicAdd(q + 2 * qm, w0 * gb);
+        atomicAdd(q + 2 * qm + q1, w1 * gb);
+        atomicAdd(q + 3 * qm, w0 * ga);
+        atomicAdd(q + 3 * qm + q1, w1 * ga);
         if (gvol && e.sraw > 0.0 && e.sraw < 1.0) {
           const double du = gr * ((double)e.t1.x - (double)e.t0.x) + gg * ((double)e.t1.y - (double)e.t0.y) +
                             gb * ((double)e.t1.z - (double)e.t0.z) + ga * ((double)e.t1.w - (double)e.t0.w);
@@ -538,7 +545,11 @@ __global__ __launch_bounds__(256) __attribute__((amdgpu_waves_per_eu(4))) void k
   }
   __syncthreads();
   double* part = ba.tf_part + ((int64_t)blockIdx.y * gridDim.x + blockIdx.x) * M * 4;
-  for (int i = threadIdx.x; i < M * 4; i += blockDim.x) part[i] = s_gtf[(i & 3) * M + (i >> 2)];
+  for (int i = threadIdx.x; i < M * 4; i += blockDim.x) {
+    double sum = 0.0;
+    for (int c = 0; c < 1 << csh; ++c) sum += s_gtf[(((i & 3) * M + (i >> 2)) << csh) + c];
+    part[i] = sum;
+  }
 }
 
 }  // namespace
@@ -564,7 +575,14 @@ hipError_t launch_bwd_ring(const MarchArgs& a, const BwdArgs& ba, hipStream_t s)
   if (a.tile_w != 8 || a.ring_slot <= 0 || (a.ring_slot & 3) != 0 || a.cam.persp != 0 || ba.K < 1 || ba.K > 31 ||
       ba.smax < 1)
     return hipErrorInvalidValue;
-  const size_t lds = bwd_ring_lds_bytes(a.M, ba.K, a.ring_slot, ba.smax, ba.replay != 0);
+  size_t lds = bwd_ring_lds_bytes(a.M, ba.K, a.ring_slot, ba.smax, ba.replay != 0);
+  BwdArgs bc = ba;
+  // each doubling of the sums' copies adds as many bytes as they take so far
+  while (bc.copy_shift < 6 && a.M << (bc.copy_shift + 1) <= kTableEntries &&
+         lds + ((size_t)32 * a.M << bc.copy_shift) <= 160 * 1024) {
+    lds += (size_t)32 * a.M << bc.copy_shift;
+    bc.copy_shift++;
+  }
   if (lds > 160 * 1024) return hipErrorInvalidValue;
   const bool by = a.slab_axis == 1;
   const auto f = ba.replay ? (by ? &k_bwd_ring<true, true> : &k_bwd_ring<true, false>)
@@ -576,7 +594,7 @@ hipError_t launch_bwd_ring(const MarchArgs& a, const BwdArgs& ba, hipStream_t s)
   if (ba.parts > 1 && (!ba.sums || ba.part_groups < 1)) return hipErrorInvalidValue;
   const int parts = std::max(1, ba.parts);
   const dim3 g(bwd_ring_blocks(a, ba) / parts, parts), b(256);
-  hipLaunchKernelGGL(f, g, b, lds, s, a, ba);
+  hipLaunchKernelGGL(f, g, b, lds, s, a, bc);
   return hipGetLastError();
 }
 

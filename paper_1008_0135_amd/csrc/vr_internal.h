@@ -329,6 +329,7 @@ struct BwdArgs {
   // estimated work.  band[8] == 0: equal counts of groups
   int32_t band[9];
   int32_t* flag;      // set to 1 when a ray's group held more than smax samples
+  int32_t copy_shift;  // ring adjoint: 2^copy_shift copies of the table sums in LDS (set at the launch)
   int32_t parts, part_groups;  // as SaveArgs
   const double4* sums;
 };
