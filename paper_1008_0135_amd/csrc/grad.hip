@@ -245,26 +245,26 @@ __global__ __launch_bounds__(256) void k_bwd(MarchArgs a, BwdArgs ba) {
 
 // grad_tf[e] (+)= sum over blocks of the partials, accumulated in double, in
 // two passes with a fixed order (the same bits on every run): slice s sums
-// blocks s, s + kSlices, ...; then each entry sums its slices in order.
-constexpr int kSlices = 256;
+// blocks s, s + slices, ...; then each entry sums its slices in order.
+constexpr int kSlices = 256;  // at most; one per block where there are fewer
 
 __global__ __launch_bounds__(256) void k_tf_slices(const double* part, int nblocks, int n, double* sl) {
   const int e = blockIdx.x * 256 + threadIdx.x;
   if (e >= n) return;
   double acc = 0.0;
 #pragma unroll 4
-  for (int b = (int)blockIdx.y; b < nblocks; b += kSlices) acc += part[(int64_t)b * n + e];
+  for (int b = (int)blockIdx.y; b < nblocks; b += (int)gridDim.y) acc += part[(int64_t)b * n + e];
   sl[(int64_t)blockIdx.y * n + e] = acc;
 }
 
 // One wavefront per entry: lane l sums slices l, l + 64, ..., then the lanes
 // are added pairwise (a fixed order).
-__global__ __launch_bounds__(256) void k_tf_reduce(const double* sl, int n, float* grad_tf) {
+__global__ __launch_bounds__(256) void k_tf_reduce(const double* sl, int slices, int n, float* grad_tf) {
   const int e = blockIdx.x * 4 + (threadIdx.x >> 6);
   if (e >= n) return;
   double acc = 0.0;
-#pragma unroll
-  for (int s = threadIdx.x & 63; s < kSlices; s += 64) acc += sl[(int64_t)s * n + e];
+#pragma unroll 4
+  for (int s = threadIdx.x & 63; s < slices; s += 64) acc += sl[(int64_t)s * n + e];
   for (int off = 32; off > 0; off >>= 1) acc += __shfl_xor(acc, off);
   if ((threadIdx.x & 63) == 0) grad_tf[e] = (float)((double)grad_tf[e] + acc);
 }
@@ -298,8 +298,9 @@ hipError_t launch_bwd(const MarchArgs& a, const BwdArgs& ba, hipStream_t s) {
 int tf_reduce_slices() { return kSlices; }
 
 hipError_t launch_tf_reduce(const double* part, int nblocks, int n, float* grad_tf, double* slices, hipStream_t s) {
-  hipLaunchKernelGGL(k_tf_slices, dim3((n + 255) / 256, kSlices), dim3(256), 0, s, part, nblocks, n, slices);
-  hipLaunchKernelGGL(k_tf_reduce, dim3((n + 3) / 4), dim3(256), 0, s, slices, n, grad_tf);
+  const int ns = nblocks < kSlices ? (nblocks > 0 ? nblocks : 1) : kSlices;
+  hipLaunchKernelGGL(k_tf_slices, dim3((n + 255) / 256, ns), dim3(256), 0, s, part, nblocks, n, slices);
+  hipLaunchKernelGGL(k_tf_reduce, dim3((n + 3) / 4), dim3(256), 0, s, slices, ns, n, grad_tf);
   return hipGetLastError();
 }
 
