@@ -60,7 +60,7 @@ struct RangePieces {
   std::vector<int64_t> cells, voxels;
   std::vector<int32_t> cell_brick, voxel_brick;
 };
-constexpr int64_t kRangePiece = 4096;
+constexpr int64_t kRangePiece = 4096, kRangePlanes = 4;
 bool range_pieces(const std::vector<int64_t>& sboxes, const int64_t n[3], int32_t mc, RangePieces& out);
 
 // Conservative pixel rectangle of the box's projection (corner bounding box
