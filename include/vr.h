@@ -348,8 +348,9 @@ int vr_composite(vr_ctx *ctx, const vr_brick_image *imgs, int32_t n, const int32
  * constant.  Each ray is walked back to front between its saved transmittance
  * checkpoints: inside a stretch the transmittance follows from its end by
  * division by the samples' 1 - alpha, or, for tables whose opacity exceeds 1/4
- * (and on the sample-segment layout), from a replay of the stretch from its
- * start.  ckpt_K bounds a stretch: on the ring-window layout (the default where
+ * (or changes by more than 1/32 per unit of the normalised value, in views whose
+ * forward marched footprint cells; and on the sample-segment layout), from a
+ * replay of the stretch from its start.  ckpt_K bounds a stretch: on the ring-window layout (the default where
  * its windows fit) a stretch is a group of L cell layers of the ray's 8 x 8
  * tile, L = round(ckpt_K step |d_b|) capped at 3 layers (the environment
  * variable VR_BWD_LAYERS sets the cap, 1 to 16: longer groups need more LDS per

@@ -26,6 +26,7 @@ struct vr_state {
   // others keep T before every K-th sample.
   struct View {
     bool ring = false;
+    bool exact = false;  // T of the adjoint's own samples (saved by gathers), not of the image's
     int32_t axis = 0, slot = 0, L = 0, smax = 0, ngrp = 0;
     int64_t off = 0;  // offset of this view's checkpoints in d_ckpt
     int32_t parts = 1, part_groups = 0;  // workgroups per tile and the groups each takes
@@ -57,6 +58,14 @@ float table_max_alpha(const vr_ctx* ctx) {
   float m = 0.f;
   for (int32_t i = 0; i < ctx->tf_m; i++) m = std::max(m, ctx->h_tf[4 * (size_t)i + 3]);
   return m;
+}
+
+// Largest change of the opacity per unit of the normalised value.
+float table_slope(const vr_ctx* ctx) {
+  float m = 0.f;
+  for (int32_t i = 0; i + 1 < ctx->tf_m; i++)
+    m = std::max(m, std::fabs(ctx->h_tf[4 * (size_t)i + 7] - ctx->h_tf[4 * (size_t)i + 3]));
+  return m * (float)(ctx->tf_m - 1);
 }
 
 // Device tables of one view of a whole-volume render: [DevBrick][DevBrickView].
@@ -237,6 +246,7 @@ int render_with_state(vr_ctx* ctx, vr_volume* vol, const vr_view* views, int32_t
       if (ctx->debug_plan) std::fprintf(stderr, "[vr] view %d: saved by cells of %.1f x %.1f\n", v, fs.Tf, fs.Tg);
       continue;
     }
+    rv.exact = true;
     // Few tiles leave most compute units without a workgroup of the adjoint, and
     // its time is one tile's chain of groups: parts of the groups side by side
     // until there are kPartBlocks workgroups (two views of 100 x 92 rays through
@@ -331,6 +341,8 @@ int render_with_state(vr_ctx* ctx, vr_volume* vol, const vr_view* views, int32_t
     sa.parts = rv.parts;
     sa.part_groups = rv.part_groups;
     sa.sums = st->d_sums + rv.sums;
+    sa.vmin = vmin;
+    sa.inv_range = vmax > vmin ? 1.0 / (vmax - vmin) : 0.0;
     if (rv.ring && ctx->bwd_bands)  // XCD bands of the adjoint
       xcd_bands(tile_costs(cams[v], base.hi, p->step, W, H), 1, st->vs[v].band);
     if (!side) rc = stage_begin(ctx, VR_STAGE_MARCH, s);
@@ -455,7 +467,10 @@ int vr_render_backward(vr_ctx* ctx, const vr_volume* vol, const vr_state* st, co
     bb.parts = rv.parts;
     pbase[v + 1] = pbase[v] + (rv.ring ? bwd_ring_blocks(a0, bb) : bwd_blocks(a0));
   }
-  const bool replay = table_max_alpha(ctx) > kMaxDivAlpha;
+  // T between checkpoints by division only where what it divides by is what the
+  // checkpoints were made of, or nearly
+  const bool opaque = table_max_alpha(ctx) > kMaxDivAlpha, steep = table_slope(ctx) > kMaxDivSlope;
+  bool replayed = false;
   const bool side = ctx->bwd_side && st->nviews > 1;
   int64_t nslots = 1;
   for (int32_t v = 0; v < st->nviews; v++) nslots = std::max(nslots, pbase[v + 1] - pbase[v]);
@@ -487,7 +502,8 @@ int vr_render_backward(vr_ctx* ctx, const vr_volume* vol, const vr_state* st, co
     ba.K = rv.ring ? rv.L : st->K;
     ba.npix = (int32_t)npix;
     ba.smax = rv.smax;
-    ba.replay = replay ? 1 : 0;
+    ba.replay = opaque || (steep && !rv.exact) ? 1 : 0;
+    replayed = replayed || ba.replay != 0;
     std::memcpy(ba.band, rv.band, sizeof ba.band);
     ba.flag = st->d_flag;
     ba.parts = rv.parts;
@@ -511,7 +527,7 @@ int vr_render_backward(vr_ctx* ctx, const vr_volume* vol, const vr_state* st, co
   // the replay's bound on the samples of one ray in one checkpoint group holds
   // by construction; a group that exceeded it is reported, not clamped (only
   // the replay can).  Either way the call ends with its stream idle.
-  if (!replay) {
+  if (!replayed) {
     VR_HIP(hipStreamSynchronize(s));
     return VR_OK;
   }

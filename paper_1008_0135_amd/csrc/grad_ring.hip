@@ -28,8 +28,8 @@
 // double precision), so S can start there.
 // T before a block comes from the group's end by division by its samples'
 // 1 - a (every sample is evaluated once), or, for tables whose opacity exceeds
-// kMaxDivAlpha, from a replay of the group from its start (REPLAY): dividing by
-// 1 - a multiplies the error of a by a / (1 - a).
+// kMaxDivAlpha (or, after a forward by cells, changes faster than kMaxDivSlope),
+// from a replay of the group from its start (REPLAY).
 // Samples are evaluated at double-precision positions (start + j step, one
 // rounding per axis; cell_d), with the trilinear value, the table lookup, the
 // recursion and the gradient algebra in double precision; which group a

@@ -136,12 +136,13 @@ __device__ __forceinline__ void spread_rays(int bank, int lane, int2* scratch, i
 
 // One sample of a lane at position q (q_b in the cell layer whose floor is fb):
 // corners from the two LDS windows at pl (lower voxel layer) and pu (upper),
-// each offset by the window's origin.
-template <bool MIP, bool BY, bool MASK>
+// each offset by the window's origin.  SAVE: Td is T as a double product, for the
+// adjoint's checkpoints (the image's T carries the roundings of its chain).
+template <bool MIP, bool BY, bool MASK, bool SAVE>
 __device__ __forceinline__ void take_sample(const MarchArgs& a, const DevBrick& br, const float4* s_tf, const float* s_mask,
                                             const float* pl,
                                             const float* pu, int pitch, const SamplePos& q, float& Cr, float& Cg,
-                                            float& Cb, float& T, float& mx) {
+                                            float& Cb, float& T, float& mx, [[maybe_unused]] double& Td) {
   const Cell cl = cell_of(q, br);
   const int at = __mul24(BY ? cl.iz : cl.iy, pitch) + cl.ix;
   pl += at;
@@ -161,24 +162,25 @@ __device__ __forceinline__ void take_sample(const MarchArgs& a, const DevBrick& 
     Classified kk = classify(val, a.vmin, a.inv_range, a.M, s_tf);
     if constexpr (MASK) kk.a *= w;
     accumulate(kk, Cr, Cg, Cb, T);
+    if constexpr (SAVE) Td = fma(-Td, (double)kk.a, Td);
   }
 }
 
 // The samples of one lane that fall in cell layer c, read from the two LDS
 // windows whose origins are wl (voxel layer c) and wu (layer c + 1).
-template <bool MIP, bool BY, bool MASK>
+template <bool MIP, bool BY, bool MASK, bool SAVE>
 __device__ __forceinline__ void sample_layer(const MarchArgs& a, const DevBrick& br, const CellRay& r,
                                              const float4* s_tf, const float* s_mask, const float* s_ring, int slot, int pitch, int c,
                                              const Window& wl, const Window& wu, int sl, int su, float fclo,
                                              float fchi, float& j, bool& done, float& Cr, float& Cg, float& Cb,
-                                             float& T, float& mx) {
+                                             float& T, float& mx, double& Td) {
   const float* baseL = s_ring + (sl * slot - wl.g0 * pitch - wl.f0);
   const float* baseU = s_ring + (su * slot - wu.g0 * pitch - wu.f0);
   const float fc = (float)c, fcnt = (float)r.cnt;
   while (!done) {
     const SamplePos q = sample_pos(j, r.px, r.py, r.pz, r.sx, r.sy, r.sz);
     if (floorf(__builtin_amdgcn_fmed3f(BY ? q.y : q.z, fclo, fchi)) != fc) break;
-    take_sample<MIP, BY, MASK>(a, br, s_tf, s_mask, baseL, baseU, pitch, q, Cr, Cg, Cb, T, mx);
+    take_sample<MIP, BY, MASK, SAVE>(a, br, s_tf, s_mask, baseL, baseU, pitch, q, Cr, Cg, Cb, T, mx, Td);
     j += 1.f;  // exact: the host leaves boxes whose rays could have 2^24 samples to other marches
     done = j >= fcnt || (MIP ? mx >= 1.f : T <= a.t_stop);
   }
@@ -365,6 +367,7 @@ __global__ __launch_bounds__(256) __attribute__((amdgpu_waves_per_eu(4))) void k
   }
   int s0 = 0;  // slot of V_k (V_{k+1} is in the other)
   [[maybe_unused]] int grp_end = 0;
+  [[maybe_unused]] double Td = 1.0;
   for (int k = 0; k < nlay; ++k) {
     const int c = up ? Lbeg + k : Lbeg - k;
     if constexpr (SAVE) {
@@ -372,14 +375,14 @@ __global__ __launch_bounds__(256) __attribute__((amdgpu_waves_per_eu(4))) void k
       // also what the group after their last one is to hold)
       const int m = up ? c - cloB : chiB - c, gi = uni(m / sa.K);
       if (k == 0 || gi == grp_end) {
-        if (r.cnt > 0) sa.ckpt[(int64_t)gi * sa.npix + r.pix] = T;
+        if (r.cnt > 0) sa.ckpt[(int64_t)gi * sa.npix + r.pix] = (float)Td;
         grp_end = gi + 1;
       }
     }
     const Window& wl = up ? w0 : w1;
     const Window& wu = up ? w1 : w0;
-    sample_layer<MIP, BY, MASK>(a, br, r, s_tf, s_mask, s_ring, slot, pitch, c, wl, wu, up ? s0 : s0 ^ 1,
-                                up ? s0 ^ 1 : s0, fclo, fchi, j, done, Cr, Cg, Cb, T, mx);
+    sample_layer<MIP, BY, MASK, SAVE>(a, br, r, s_tf, s_mask, s_ring, slot, pitch, c, wl, wu, up ? s0 : s0 ^ 1,
+                                      up ? s0 ^ 1 : s0, fclo, fchi, j, done, Cr, Cg, Cb, T, mx, Td);
     if (__all(done)) break;
     if (k + 1 < nlay) {
       rstore(s_ring + s0 * slot);  // V_{k+2} replaces V_k (same wavefront: LDS order holds)
@@ -394,7 +397,7 @@ __global__ __launch_bounds__(256) __attribute__((amdgpu_waves_per_eu(4))) void k
   }
   if constexpr (SAVE) {
     if (r.cnt > 0) {
-      sa.ckpt[(int64_t)grp_end * sa.npix + r.pix] = T;
+      sa.ckpt[(int64_t)grp_end * sa.npix + r.pix] = (float)Td;
       sa.nused[r.pix] = (int)j;
     }
   }
@@ -525,8 +528,9 @@ __global__ __launch_bounds__(512) __attribute__((amdgpu_waves_per_eu(4))) void k
     const int c = up ? Lbeg + k : Lbeg - k;
     const Window& wl = up ? w0 : w1;
     const Window& wu = up ? w1 : w0;
-    sample_layer<MIP, BY, false>(a, br, r, s_tf, nullptr, s_ring, slot, pitch, c, wl, wu, up ? s0 : s0 ^ 1, up ? s0 ^ 1 : s0,
-                          fclo, fchi, j, done, Cr, Cg, Cb, T, mx);
+    double unsaved = 1.0;
+    sample_layer<MIP, BY, false, false>(a, br, r, s_tf, nullptr, s_ring, slot, pitch, c, wl, wu, up ? s0 : s0 ^ 1,
+                                        up ? s0 ^ 1 : s0, fclo, fchi, j, done, Cr, Cg, Cb, T, mx, unsaved);
     // vote of the block (slot k & 1 is cleared for the next layer's vote
     // between the two barriers)
     const bool wave_live = __any(!done);  // over all lanes, before any branch on the lane

@@ -430,6 +430,7 @@ __global__ __launch_bounds__(256) void k_march_ring_ovf(MarchArgs a, SaveArgs sa
       const int cnt = (int)(k1b - k0b);
       float Cr = c0.x, Cg = c0.y, Cb = c0.z, T = c0.w, mx = 0.f;
       [[maybe_unused]] int grp = -1;
+      [[maybe_unused]] double Td = 1.0;  // T as the checkpoints have it: a double product
       int j = 0;
       while (j < cnt) {
         const Cell c = cell_of(sample_pos(j, px, py, pz, sx, sy, sz), br);
@@ -437,7 +438,7 @@ __global__ __launch_bounds__(256) void k_march_ring_ovf(MarchArgs a, SaveArgs sa
           const int b = a.slab_axis, ib = b == 1 ? c.iy : c.iz;
           const int gi = (a.cam.e3[b] > 0.0 ? ib - br.clo[b] : br.chi[b] - ib) / sa.K;
           // (the groups without a sample in front of it too, as k_march_save)
-          for (int g = grp < 0 ? gi : grp + 1; g <= gi; ++g) sa.ckpt[(int64_t)g * sa.npix + vv * a.cam.W + uu] = T;
+          for (int g = grp < 0 ? gi : grp + 1; g <= gi; ++g) sa.ckpt[(int64_t)g * sa.npix + vv * a.cam.W + uu] = (float)Td;
           grp = gi;
         }
         gfloat* p = gb + (c.iz * zs + c.iy * ys + c.ix);
@@ -452,11 +453,12 @@ __global__ __launch_bounds__(256) void k_march_ring_ovf(MarchArgs a, SaveArgs sa
           Classified k = classify(val, a.vmin, a.inv_range, a.M, s_tf);
           if constexpr (MASK) k.a *= channel_weight(a.mask, a.mask_axis, br.lo[a.mask_axis], c);
           accumulate(k, Cr, Cg, Cb, T);
+          if constexpr (SAVE) Td = fma(-Td, (double)k.a, Td);
           if (1.f - T >= a.tau) break;
         }
       }
       if constexpr (SAVE) {
-        sa.ckpt[(int64_t)(grp + 1) * sa.npix + vv * a.cam.W + uu] = T;
+        sa.ckpt[(int64_t)(grp + 1) * sa.npix + vv * a.cam.W + uu] = (float)Td;
         sa.nused[vv * a.cam.W + uu] = j;
       }
       if (a.carry || inr)

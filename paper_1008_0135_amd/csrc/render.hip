@@ -451,6 +451,27 @@ __device__ __forceinline__ double row_shr(double v) {
   return __hiloint2double(hi, lo);
 }
 
+// A sample as the adjoint evaluates it: opacity and colour in double precision at the
+// double-precision position, trilinear over the corners a00 (y, z) .. a11 of cell c.
+struct Sample64 {
+  double a, r, g, b;
+};
+__device__ __forceinline__ Sample64 sample64(int j, const double (&p0)[3], const double (&sv)[3], const Cell& c,
+                                             const f2u& a00, const f2u& a01, const f2u& a10, const f2u& a11,
+                                             double vmin, double inv_range, int M, const float4* s_tf) {
+  const double k = (double)j;
+  const double wx = fma(k, sv[0], p0[0]) - (double)c.ix, wy = fma(k, sv[1], p0[1]) - (double)c.iy,
+               wz = fma(k, sv[2], p0[2]) - (double)c.iz;
+  auto lerp = [](double w, double x, double y) { return fma(w, y - x, x); };
+  const double c0 = lerp(wy, lerp(wx, a00.x, a00.y), lerp(wx, a01.x, a01.y));
+  const double c1 = lerp(wy, lerp(wx, a10.x, a10.y), lerp(wx, a11.x, a11.y));
+  const double s = fmin(fmax((lerp(wz, c0, c1) - vmin) * inv_range, 0.0), 1.0), u = s * (double)(M - 1);
+  const int i = min((int)u, M - 2);
+  const double w = u - (double)i;
+  const float4 t0 = s_tf[i], t1 = s_tf[i + 1];
+  return Sample64{lerp(w, t0.w, t1.w), lerp(w, t0.x, t1.x), lerp(w, t0.y, t1.y), lerp(w, t0.z, t1.z)};
+}
+
 // Sum of v over the 16 lanes of a row, and over its lanes before lane dl.
 __device__ __forceinline__ double row_sum(double v) {
 #pragma unroll
@@ -469,7 +490,12 @@ __device__ __forceinline__ double row_before(double v, int dl) {
 
 // The checkpointing forward by gathers: k_march<16, 2> over the whole volume
 // that also stores T where a ray enters a group of sa.K cell layers along the
-// slab axis, T at its end, and the number of its samples.  For small views,
+// slab axis, T at its end, and the number of its samples.  These, and the sums of
+// parts, are made from each sample as the adjoint has it (double-precision position,
+// value and table lookup over the same eight corners), beside the image's own
+// single-precision chain: the adjoint divides by the samples' 1 - a between two
+// stored T and starts parts behind the sums, and what the two evaluations differ by
+// (a rounded position times the table's slope) would be in every gradient.  For small views,
 // whose rays a wavefront of 64 rays would walk one sample at a time (100 x 92
 // rays through 61 x 83 x 72 voxels: 135 us by windows of one ray per lane).
 template <bool BY, bool PARTS>
@@ -496,9 +522,10 @@ __global__ __launch_bounds__(256) void k_march_save(MarchArgs a, SaveArgs sa) {
   if (k1 > k0) {
     const float sx = (float)(a.step * d[0]), sy = (float)(a.step * d[1]), sz = (float)(a.step * d[2]);
     const double t0 = tin + ((double)k0 + 0.5) * a.step;
-    const float px = (float)(o[0] + t0 * d[0] - (double)br.lo[0]);
-    const float py = (float)(o[1] + t0 * d[1] - (double)br.lo[1]);
-    const float pz = (float)(o[2] + t0 * d[2] - (double)br.lo[2]);
+    const double p0[3] = {o[0] + t0 * d[0] - (double)br.lo[0], o[1] + t0 * d[1] - (double)br.lo[1],
+                          o[2] + t0 * d[2] - (double)br.lo[2]};
+    const double sv[3] = {a.step * d[0], a.step * d[1], a.step * d[2]};
+    const float px = (float)p0[0], py = (float)p0[1], pz = (float)p0[2];
     const int cnt = (int)(k1 - k0);
     const int ys = br.sy, zs = br.sz;
     gfloat* base = (gfloat*)br.base;
@@ -527,12 +554,11 @@ __global__ __launch_bounds__(256) void k_march_save(MarchArgs a, SaveArgs sa) {
     // what this lane's samples add to the ray (parts: summed over the 16 lanes
     // where a part begins and at the end)
     double4 own = make_double4(0.0, 0.0, 0.0, 0.0);
-    // T by double products: what the adjoint starts from keeps only the errors of
-    // the opacities, not those of a chain of single-precision roundings
     double Td = 1.0;
     for (int jb = D;; jb += D) {
       const float val = trilerp(a00.x, a00.y, a01.x, a01.y, a10.x, a10.y, a11.x, a11.y, c);
       const int jc = j, gi = group(BY ? c.iy : c.iz);
+      const Sample64 k64 = sample64(jc, p0, sv, c, a00, a01, a10, a11, sa.vmin, sa.inv_range, a.M, s_tf);
       const bool more = jb < cnt;
       if (more) load(jb);
       Classified k = classify(val, a.vmin, a.inv_range, a.M, s_tf);
@@ -542,7 +568,7 @@ __global__ __launch_bounds__(256) void k_march_save(MarchArgs a, SaveArgs sa) {
       const bool stopped = accumulate_group<D>(k, a.tau, Cr, Cg, Cb, T, &taken);
       used = stopped ? jb - D + taken : min(jb, cnt);
       // T before this lane's sample: the product over the lanes before
-      const double e = jc < used ? 1.0 - (double)k.a : 1.0;
+      const double e = jc < used ? 1.0 - k64.a : 1.0;
       double q = e;
       q *= row_shr<1>(q);
       q *= row_shr<2>(q);
@@ -559,8 +585,8 @@ __global__ __launch_bounds__(256) void k_march_save(MarchArgs a, SaveArgs sa) {
       if (begins)
         for (int g = from; g <= gi; ++g) sa.ckpt[(int64_t)g * sa.npix + pix] = (float)Tb;
       if constexpr (PARTS) {
-        const double w = jc < used ? Tb * (double)k.a : 0.0;
-        const double4 add = make_double4(w * (double)k.r, w * (double)k.g, w * (double)k.b, w);
+        const double w = jc < used ? Tb * k64.a : 0.0;
+        const double4 add = make_double4(w * k64.r, w * k64.g, w * k64.b, w);
         // the part that begins at one of these groups (the last, if several do)
         const int pg = gi - gi % sa.part_groups;
         const bool part = begins && pg >= from;

@@ -41,7 +41,7 @@ def test_skipped_groups_past_the_cells(step, capfd):
             for k in env:
                 del os.environ[k]
         h = vr.vr_volume_wrap(c, a, dims)
-        vr.vr_tf_set(c, _table(64, 0.2), float(a.min()), float(a.max()))
+        vr.vr_tf_set(c, _table(64, 0.03), float(a.min()), float(a.max()))  # (taken by division)
         out = torch.empty((3, H, W, 4), device="cuda")
         capfd.readouterr()
         st = vr.vr_render(c, h, views, vr.make_params(step=step, tau=2.0, ess=0), out, save=True)
