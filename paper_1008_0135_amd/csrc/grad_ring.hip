@@ -214,10 +214,14 @@ __global__ __launch_bounds__(256) __attribute__((amdgpu_waves_per_eu(4))) void k
   auto layer_of = [&](int j) {
     return (int)floorf(__builtin_amdgcn_fmed3f(fmaf((float)j, sb, pb), (float)cloB, (float)chiB));
   };
+  // the tile's layers end with the last sample any of its rays took (rays that
+  // stopped early leave the groups behind empty: 1024^2 rays of 256^3, stopped after
+  // some 20 samples, 2.6 ms with them, 1.2 without)
+  const int used = valid ? ba.nused[pix] : 0;
   int c_first = up ? 0x7fffffff : -0x7fffffff, c_last = up ? -0x7fffffff : 0x7fffffff;
-  if (cnt > 0) {
+  if (used > 0) {
     c_first = layer_of(0);
-    c_last = layer_of(cnt - 1);
+    c_last = layer_of(used - 1);
   }
   c_first = up ? wave_imin(c_first) : wave_imax(c_first);
   c_last = up ? wave_imax(c_last) : wave_imin(c_last);
@@ -281,7 +285,6 @@ __global__ __launch_bounds__(256) __attribute__((amdgpu_waves_per_eu(4))) void k
     const int nwin = NG * pitch;
 
     // per-ray state of the backward walk
-    const int used = valid ? ba.nused[pix] : 0;
     float4 gf = valid ? ba.gout[pix] : make_float4(0.f, 0.f, 0.f, 0.f);
     const double dvs = (double)(M - 1) * ba.inv_range;  // du/dv inside the window
     double S = 0.0;
