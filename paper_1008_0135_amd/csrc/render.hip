@@ -320,7 +320,12 @@ __global__ __launch_bounds__(256) void k_march(MarchArgs a) {
 
   constexpr int TH = 64 / D / TW;
   const int nblk = (a.ntiles + 3) >> 2;
-  const int lb = xcd_block();
+  // one lane per ray, tiles in rows: a contiguous eighth for each XCD (its tiles
+  // have no shared corners to gain from short runs: 276 x 97 x 295 in perspective
+  // at 665 x 349, tiles of 4 x 16, 434 us in runs of eight blocks, 336 so)
+  const int per = (nblk + 7) >> 3, hw = grid_block();
+  if (D == 1 && hw >= 8 * per) return;
+  const int lb = D > 1 ? xcd_block() : (hw & 7) * per + (hw >> 3);
   if (lb >= nblk) return;
   int tile = __builtin_amdgcn_readfirstlane(lb * 4 + (int)(threadIdx.x >> 6));
   if (tile >= a.ntiles) return;
@@ -369,7 +374,7 @@ __global__ __launch_bounds__(256) void k_march(MarchArgs a) {
   {
     const float sx = (float)(a.step * d[0]), sy = (float)(a.step * d[1]), sz = (float)(a.step * d[2]);
     auto march = [&](const DevBrickView& bvw) {
-      const DevBrick& br = a.bricks[bvw.brick];
+      const DevBrick br = a.bricks[bvw.brick];
       int64_t k0, k1;
       brick_krange(o, d, tin, a.step, n, br.lo, br.hi, br.closed, k0, k1);
       if (k1 <= k0) return;
@@ -385,7 +390,9 @@ __global__ __launch_bounds__(256) void k_march(MarchArgs a) {
       if constexpr (MASK) mask = (gfloat*)(a.mask + br.lo[a.mask_axis]);
       // the corners (and mask weights) of the next samples are loaded while
       // these are composited; loads return in order, so a load of its own in
-      // the middle of a sample would wait for the next corners too
+      // the middle of a sample would wait for the next corners too.  One lane per
+      // ray loads its sample where it takes it: a view of many rays is bound by
+      // instructions, of which the copies were a quarter (the view above 336 -> 310)
       int j;
       Cell c;
       f2u a00, a01, a10, a11;
@@ -400,14 +407,16 @@ __global__ __launch_bounds__(256) void k_march(MarchArgs a) {
         a11 = ld_pair(p + zs + ys);
         if constexpr (MASK) mw = ld_pair(mask + (a.mask_axis == 2 ? c.iz : c.iy));
       };
-      load(0);
-      for (int jb = D;; jb += D) {
+      if constexpr (D > 1) load(0);
+      for (int jb = 0;;) {
+        if constexpr (D == 1) load(jb);
         const float val = trilerp(a00.x, a00.y, a01.x, a01.y, a10.x, a10.y, a11.x, a11.y, c);
         [[maybe_unused]] float w = 1.f;
         if constexpr (MASK) w = channel_weight(mw.x, mw.y, a.mask_axis, c);
         const bool past = D > 1 && j >= cnt;
+        jb += D;
         const bool more = jb < cnt;
-        if (more) load(jb);
+        if (D > 1 && more) load(jb);
         if (MIP) {
           float s = norm_value(val, a.vmin, a.inv_range);
           if constexpr (MASK) s *= w;
