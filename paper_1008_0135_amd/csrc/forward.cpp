@@ -66,8 +66,18 @@ constexpr double kThruBelow = 0.4e-3;
 //     0.75 voxels apart, where the narrowest cells hold more than 64 of them,
 //     are left to the gathers (300^3 at 800^2, 0.65 voxels: 1.1 ms by cells,
 //     0.49 by gathers).
-int32_t gather_lanes(const Camera& cam) {
-  return cam.S / (double)cam.W < 1.1 && (int64_t)cam.W * cam.H >= ((int64_t)1 << 16) ? 4 : 16;
+static bool near_rays(const Camera& cam) {
+  return cam.S / (double)cam.W < 1.1 && (int64_t)cam.W * cam.H >= ((int64_t)1 << 16);
+}
+
+// Few samples (most rays miss the volume or cross a thin one): a wavefront's setup
+// costs more than its samples, and 16 lanes per ray set up four times the wavefronts
+// (10 x 301 x 393 in perspective, three 486 x 450 views at step 2.7, 0.8 samples a
+// pixel: 143 us with 16 lanes, 61 with 4; 362 x 11 x 284 in perspective at 858 x 1099, 1.1 a
+// pixel: 176 and 64).  Below 2^15 pixels the two are as fast (27 to 30 us).
+int32_t gather_lanes(const Camera& cam, double samples) {
+  const int64_t pixels = (int64_t)cam.W * cam.H;
+  return near_rays(cam) || (pixels >= ((int64_t)1 << 15) && samples < 16.0 * (double)pixels) ? 4 : 16;
 }
 
 void add_box(BoxSums& s, const Camera& cam, const Box& b, double step) {
@@ -88,7 +98,7 @@ MarchTimes march_times(const Camera& cam, const BoxSums& boxes, const FootShape*
   const double samples = boxes.samples, bytes = boxes.bytes;
   const int64_t layers = fs ? boxes.most[fs->axis] : 0;
   t.samples = samples;
-  t.gather = 20e-6 + samples * std::pow(std::max(1.0, t.pitch / 1.2), 0.75) / (gather_lanes(cam) == 4 ? 230e9 : 182e9);
+  t.gather = 20e-6 + samples * std::pow(std::max(1.0, t.pitch / 1.2), 0.75) / (near_rays(cam) ? 230e9 : 182e9);
   if (!fs || t.pitch < 0.75) return t;
   t.chain = (double)layers * (0.9e-6 + 0.13e-6 * t.pitch) * (1.0 + std::max(0.0, t.pitch - 4.0) / 4.0);
   t.cells = std::max(std::max(samples / 300e9, 2.3 * bytes / 7.2e12), t.chain / (double)std::max(1, views));
@@ -352,7 +362,7 @@ int render_forward(vr_ctx* ctx, vr_volume* vol, const vr_view* views, int32_t nv
       const MarchTimes t = march_times(cams[v], sums[v], nullptr);
       if (choose && !forced && (nviews == 1 || t.pitch < 1.0 || t.gather < kThruBelow)) {
         thru_order(v);
-        gather_view(vp, gather_lanes(cams[v]));
+        gather_view(vp, gather_lanes(cams[v], sums[v].samples));
         continue;
       }
       plan_waves(vol, cams[v], tw, vp);
@@ -407,7 +417,7 @@ int render_forward(vr_ctx* ctx, vr_volume* vol, const vr_view* views, int32_t nv
       }
     }
     if (!any) {
-      gather_view(vp, gather_lanes(cams[v]));
+      gather_view(vp, gather_lanes(cams[v], sums[v].samples));
       continue;
     }
     std::vector<DevBrickView> grouped;
@@ -454,7 +464,7 @@ int render_forward(vr_ctx* ctx, vr_volume* vol, const vr_view* views, int32_t nv
         sure = sure && t.gather < t.cells;
       }
       if (sure) {
-        gather_view(vp, gather_lanes(cams[v]));
+        gather_view(vp, gather_lanes(cams[v], sums[v].samples));
         continue;
       }
     }
@@ -476,7 +486,7 @@ int render_forward(vr_ctx* ctx, vr_volume* vol, const vr_view* views, int32_t nv
       if (ctx->debug_plan)
         std::fprintf(stderr, "[vr] view %d: estimated cells %.0f us, gathers %.0f us\n", v, t.cells * 1e6, t.gather * 1e6);
       if (t.gather < t.cells) {
-        gather_view(vp, gather_lanes(cams[v]));
+        gather_view(vp, gather_lanes(cams[v], sums[v].samples));
         continue;
       }
     }

@@ -44,7 +44,7 @@ struct MarchTimes {
 // views of 201 x 187 x 333 at 0.8 voxels 405 us with 16, 330 with 4; 400^3 at
 // 0.7 1.23 ms and 1.00, at 1.35 414 us and 484; 256^2 rays through 128^3 59
 // and 59, fewer rays up to twice as slow with 4).
-int32_t gather_lanes(const Camera& cam);
+int32_t gather_lanes(const Camera& cam, double samples);
 // What the estimates need of the boxes a view marches, gathered in one pass over
 // them (a volume may have 65536).
 struct BoxSums {
