@@ -374,7 +374,8 @@ __global__ __launch_bounds__(256) void k_march(MarchArgs a) {
   {
     const float sx = (float)(a.step * d[0]), sy = (float)(a.step * d[1]), sz = (float)(a.step * d[2]);
     auto march = [&](const DevBrickView& bvw) {
-      const DevBrick br = a.bricks[bvw.brick];
+      // (a copy costs two masked 768^2 views of 512^3 in 64 bricks, four lanes per ray, 2.29 -> 2.48 ms)
+      std::conditional_t<D == 1, const DevBrick, const DevBrick&> br = a.bricks[bvw.brick];
       int64_t k0, k1;
       brick_krange(o, d, tin, a.step, n, br.lo, br.hi, br.closed, k0, k1);
       if (k1 <= k0) return;
