@@ -47,6 +47,11 @@ constexpr double kPerspCellRate = 106e9, kPerspChains = 5.0;
 // of bricks, each working on a compact part of the volume, the views' side by
 // side (two views of 1024 x 1024 x 512 6.2 ms against 6.9)
 constexpr double kThruBelow = 0.4e-3;
+// what a view by cells costs beside its march: their size is searched on the host
+// and the launch takes more kernels (checkpointing forward, three views of 35 x 40
+// rays through 16 x 6 x 57 voxels 181 us by cells, 81 by gathers; masked 21 x 29
+// view of 24 x 23 x 14 voxels 105 and 28)
+constexpr double kCellsFixed = 60e-6;
 
 }  // namespace
 
@@ -103,6 +108,7 @@ MarchTimes march_times(const Camera& cam, const BoxSums& boxes, const FootShape*
   t.chain = (double)layers * (0.9e-6 + 0.13e-6 * t.pitch) * (1.0 + std::max(0.0, t.pitch - 4.0) / 4.0);
   t.cells = std::max(std::max(samples / 300e9, 2.3 * bytes / 7.2e12), t.chain / (double)std::max(1, views));
   if (fs->waves > 0) t.cells *= std::max(1.0, 12.0 / (double)fs->waves);
+  t.cells += kCellsFixed;
   return t;
 }
 

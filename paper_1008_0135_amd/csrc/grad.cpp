@@ -46,10 +46,6 @@ namespace vr {
 namespace {
 
 constexpr int32_t kPartBlocks = 4096, kMaxParts = 16;
-// what a view by cells costs beside its march: their size is searched on the host
-// and the launch takes four more kernels (three views of 35 x 40 rays through
-// 16 x 6 x 57 voxels: forward 181 us by cells, 81 by gathers)
-constexpr double kCellsFixed = 60e-6;
 // tables with (nearly) opaque entries: no parts.  Behind a sample of opacity 1
 // the forward's sums hold nothing, but its own gradient needs what lies there.
 constexpr float kPartAlpha = 0.99f;
@@ -238,7 +234,7 @@ int render_with_state(vr_ctx* ctx, vr_volume* vol, const vr_view* views, int32_t
     BoxSums box;
     add_box(box, cams[v], whole, p->step);
     const MarchTimes t = march_times(cams[v], box, &fs, ctx->bwd_side ? std::min(nviews, 3) : 1);
-    if (ctx->foot && (ctx->march_mode == 3 || t.cells + kCellsFixed <= t.gather) &&
+    if (ctx->foot && (ctx->march_mode == 3 || t.cells <= t.gather) &&
         pick_foot(cams[v], vol->n, ctx->tf_m, true, ctx->ring_reg > 0, ctx->ring_nslots, ctx->foot_rays,
                   ctx->foot_pad, ctx->foot_kmax, fs, ctx->foot_maxpx, rv.axis) &&
         fs.reg && brick_rows_readable(vol, 0, (fs.nf + 3) & ~3) && samples_countable(cams[v], whole, p->step)) {
