@@ -461,6 +461,7 @@ int vr_render_backward(vr_ctx* ctx, const vr_volume* vol, const vr_state* st, co
     std::memset(&bb, 0, sizeof bb);
     std::memcpy(bb.band, rv.band, sizeof bb.band);
     bb.parts = rv.parts;
+    bb.run = bwd_ring_run(a0.ntiles, M);
     pbase[v + 1] = pbase[v] + (rv.ring ? bwd_ring_blocks(a0, bb) : bwd_blocks(a0));
   }
   // T between checkpoints by division only where what it divides by is what the
@@ -503,6 +504,7 @@ int vr_render_backward(vr_ctx* ctx, const vr_volume* vol, const vr_state* st, co
     std::memcpy(ba.band, rv.band, sizeof ba.band);
     ba.flag = st->d_flag;
     ba.parts = rv.parts;
+    ba.run = bwd_ring_run(a.ntiles, M);
     ba.part_groups = rv.part_groups;
     ba.sums = st->d_sums + rv.sums;
     if (rv.ring) {

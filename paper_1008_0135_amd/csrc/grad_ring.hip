@@ -140,8 +140,16 @@ __device__ __forceinline__ double quad_pick(int dl, double v0, double v1, double
 // entries 2.3 at 64, but 64^3 at 96^2 205 against 185 us (occupancy).
 constexpr int kTableEntries = 256;
 constexpr int kAhead = 3;  // layers of windows kept ahead in registers
+// A workgroup clears and writes out its table sums (32 bytes an entry) once for all
+// its tiles.  With large tables that is a good part of a tile's time and of the
+// memory a call takes, so views of many tiles give each workgroup several (RUN),
+// as long as kRunBlocks workgroups remain: three 900^2 views of 64 x 60 x 70, 2048
+// entries, 11.3 ms with one tile, 10.1, 9.4 and 9.5 with two, four and eight; of
+// noise of 128 x 120 x 130 13.1 -> 12.0, of a smooth 256^3 cube 18.7 -> 19.2.  1024
+// entries 6.5 -> 6.2 and 12.2 -> 12.8, 256 entries 5.9 -> 6.1: one tile each.
+constexpr int kRunEntries = 2048, kRunBlocks = 3072, kRunMax = 4;
 
-template <bool REPLAY, bool by>
+template <bool REPLAY, bool by, bool RUN>
 __global__ __launch_bounds__(256) __attribute__((amdgpu_waves_per_eu(4))) void k_bwd_ring(MarchArgs a, BwdArgs ba) {
   extern __shared__ double dsm[];
   const int M = a.M, L = ba.K;
@@ -165,13 +173,13 @@ __global__ __launch_bounds__(256) __attribute__((amdgpu_waves_per_eu(4))) void k
   for (int e = threadIdx.x; e < (L + 1) * slot; e += blockDim.x) s_grad[e] = 0.0;
 
   // same tile order as the forward
-  int tile;
-  if (ba.band[8] > 0) {
-    const int x = (int)(blockIdx.x & 7), g = ba.band[x] + (int)(blockIdx.x >> 3);
-    tile = g < ba.band[x + 1] ? g : a.ntiles;
-  } else {
-    tile = (int)(blockIdx.x & 7) * ((a.ntiles + 7) >> 3) + (int)(blockIdx.x >> 3);
-  }
+  const int xcd = (int)(blockIdx.x & 7), per = (a.ntiles + 7) >> 3;
+  const bool bands = ba.band[8] > 0;
+  const int run = RUN ? ba.run : 1;
+  const int tile0 = (bands ? ba.band[xcd] : xcd * per) + (int)(blockIdx.x >> 3) * run;
+  const int tile_end = min(tile0 + run, bands ? ba.band[xcd + 1] : min((xcd + 1) * per, a.ntiles));
+  int tile = tile0 < tile_end ? tile0 : a.ntiles;
+  do {  // (one tile; the body keeps its indent)
   const int tid = threadIdx.x, wave = uni(tid >> 6), lane = tid & 63, dl = tid & 3;
   // a wavefront's 16 rays are every other pixel of the tile both ways: rays
   // next to each other would add to the same voxels (8 views 14.8 ms against
@@ -546,7 +554,8 @@ __global__ __launch_bounds__(256) __attribute__((amdgpu_waves_per_eu(4))) void k
       }
     }
   }
-  __syncthreads();
+  __syncthreads();  // (the windows and the layer ranges are the next tile's)
+  } while (RUN && ++tile < tile_end);
   double* part = ba.tf_part + ((int64_t)blockIdx.y * gridDim.x + blockIdx.x) * M * 4;
   for (int i = threadIdx.x; i < M * 4; i += blockDim.x) {
     double sum = 0.0;
@@ -561,22 +570,26 @@ size_t bwd_ring_lds_bytes(int M, int L, int slot, int smax, bool replay) {
   return sizeof(double) * 4 * (size_t)M + sizeof(float4) * (size_t)M + sizeof(float) * tile_floats(L, slot, smax, replay);
 }
 
+int bwd_ring_run(int ntiles, int M) {
+  return M < kRunEntries ? 1 : std::max(1, std::min(kRunMax, ntiles / kRunBlocks));
+}
+
 int bwd_ring_blocks(const MarchArgs& a, const BwdArgs& ba) {
   if (a.ntiles <= 0) return 0;
   const int parts = std::max(1, ba.parts);
+  int widest = (a.ntiles + 7) / 8;
   if (ba.band[8] > 0) {
-    int widest = 0;
+    widest = 0;
     for (int x = 0; x < 8; x++) widest = std::max(widest, ba.band[x + 1] - ba.band[x]);
-    return 8 * widest * parts;
   }
-  return ((a.ntiles + 7) / 8) * 8 * parts;
+  return 8 * ((widest + ba.run - 1) / ba.run) * parts;
 }
 
 hipError_t launch_bwd_ring(const MarchArgs& a, const BwdArgs& ba, hipStream_t s) {
   if (a.ntiles <= 0) return hipSuccess;
   // (the offsets of L + 1 windows have 32 places)
   if (a.tile_w != 8 || a.ring_slot <= 0 || (a.ring_slot & 3) != 0 || a.cam.persp != 0 || ba.K < 1 || ba.K > 31 ||
-      ba.smax < 1)
+      ba.smax < 1 || ba.run < 1)
     return hipErrorInvalidValue;
   size_t lds = bwd_ring_lds_bytes(a.M, ba.K, a.ring_slot, ba.smax, ba.replay != 0);
   BwdArgs bc = ba;
@@ -588,8 +601,12 @@ hipError_t launch_bwd_ring(const MarchArgs& a, const BwdArgs& ba, hipStream_t s)
   }
   if (lds > 160 * 1024) return hipErrorInvalidValue;
   const bool by = a.slab_axis == 1;
-  const auto f = ba.replay ? (by ? &k_bwd_ring<true, true> : &k_bwd_ring<true, false>)
-                           : (by ? &k_bwd_ring<false, true> : &k_bwd_ring<false, false>);
+  using Kernel = void (*)(MarchArgs, BwdArgs);
+  const Kernel one[2][2] = {{&k_bwd_ring<false, false, false>, &k_bwd_ring<false, true, false>},
+                            {&k_bwd_ring<true, false, false>, &k_bwd_ring<true, true, false>}};
+  const Kernel several[2][2] = {{&k_bwd_ring<false, false, true>, &k_bwd_ring<false, true, true>},
+                                {&k_bwd_ring<true, false, true>, &k_bwd_ring<true, true, true>}};
+  const Kernel f = (ba.run > 1 ? several : one)[ba.replay != 0][by];
   if (lds > 64 * 1024) {  // dynamic LDS beyond the default limit
     const hipError_t e = hipFuncSetAttribute(reinterpret_cast<const void*>(f), hipFuncAttributeMaxDynamicSharedMemorySize, 160 * 1024);
     if (e != hipSuccess) return e;

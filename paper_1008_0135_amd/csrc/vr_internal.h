@@ -326,9 +326,10 @@ struct BwdArgs {
   int32_t smax;       // layer groups: samples of one ray in one group, at most
   int32_t replay;     // layer groups: T from a replay of the group (else by division from its end)
   // ring adjoint: tiles of XCD x (workgroup b runs on XCD b % 8 and takes
-  // tile band[x] + b / 8 while below band[x + 1]); contiguous bands of equal
-  // estimated work.  band[8] == 0: equal counts of groups
+  // `run` tiles from band[x] + b / 8 * run on while below band[x + 1]); contiguous
+  // bands of equal estimated work.  band[8] == 0: equal counts of groups
   int32_t band[9];
+  int32_t run;        // ring adjoint: tiles a workgroup takes one after another
   int32_t* flag;      // set to 1 when a ray's group held more than smax samples
   int32_t copy_shift;  // ring adjoint: 2^copy_shift copies of the table sums in LDS (set at the launch)
   int32_t parts, part_groups;  // as SaveArgs
@@ -413,6 +414,7 @@ size_t block_lds_bytes(const MarchArgs& a);
 constexpr float kMaxDivAlpha = 0.25f, kMaxDivSlope = 1.f / 32.f;
 hipError_t launch_bwd_ring(const MarchArgs& a, const BwdArgs& ba, hipStream_t s);
 size_t bwd_ring_lds_bytes(int M, int L, int slot, int smax, bool replay);
+int bwd_ring_run(int ntiles, int M);  // BwdArgs::run of a view
 int bwd_ring_blocks(const MarchArgs& a, const BwdArgs& ba);
 hipError_t launch_march_lds(const MarchArgs& a, hipStream_t s);
 hipError_t launch_composite(const CompArgs& a, hipStream_t s);
