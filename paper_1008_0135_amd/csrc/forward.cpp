@@ -79,9 +79,13 @@ static bool near_rays(const Camera& cam) {
 // costs more than its samples, and 16 lanes per ray set up four times the wavefronts
 // (10 x 301 x 393 in perspective, three 486 x 450 views at step 2.7, 0.8 samples a
 // pixel: 143 us with 16 lanes, 61 with 4; 362 x 11 x 284 in perspective at 858 x 1099, 1.1 a
-// pixel: 176 and 64).  Below 2^15 pixels the two are as fast (27 to 30 us).
+// pixel: 176 and 64).  Below 2^15 pixels the two are as fast (27 to 30 us).  Views of
+// 2^19 pixels and more, with fewer still: one lane per ray (pixels, samples a pixel,
+// four lanes, one: 0.7 M 1.3 59 and 42 us; 1.1 M 2.1 89 and 53; 0.9 M 3.4 67 and 100;
+// 0.3 M 1.3 33 and 42).
 int32_t gather_lanes(const Camera& cam, double samples) {
   const int64_t pixels = (int64_t)cam.W * cam.H;
+  if (pixels >= ((int64_t)1 << 19) && samples < 2.5 * (double)pixels) return 1;
   return near_rays(cam) || (pixels >= ((int64_t)1 << 15) && samples < 16.0 * (double)pixels) ? 4 : 16;
 }
 
@@ -330,7 +334,9 @@ int render_forward(vr_ctx* ctx, vr_volume* vol, const vr_view* views, int32_t nv
     return t;
   };
   auto gather_view = [&](ViewPlan& vp, int32_t depth) {
+    if (vp.thru) depth = std::max(depth, 4);
     vp.deep = depth;
+    if (depth == 1) return;  // 8 x 8 pixels, as planned
     const int32_t e = vp.skip ? 8 : depth == 16 ? 2 : 4;
     if (global && !vp.thru)
       for (size_t w = 0; w + 1 < vp.wave_begin.size(); w++)
