@@ -324,7 +324,6 @@ int build_macrocells(vr_volume* vol, int32_t mc, const vr_volume* src, hipStream
     dev_give(vol->d_mc_mm, vol->mc_mm_bytes);
     vol->d_mc_mm = nullptr;
     vol->d_mc_clear = nullptr;
-    vol->d_mc_clear = nullptr;
     return fail(VR_ENOMEM, "hipMalloc for %lld macrocells failed", (long long)count);
   }
   vol->d_mc_count = reinterpret_cast<unsigned int*>(vol->d_mc_clear + cbytes);

@@ -237,7 +237,7 @@ int render_batch(vr_ctx* ctx, const vr_request* reqs, int32_t n, const vr_params
     a.reqs = b->d_reqs;
     a.nreq = n;
     a.total_items = items;
-      a.max_M = maxM;
+    a.max_M = maxM;
     a.step = p->step;
     a.tau = b->tau;
     VR_HIP(hipStreamBeginCapture(b->cap, hipStreamCaptureModeThreadLocal));

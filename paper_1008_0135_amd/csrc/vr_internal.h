@@ -399,8 +399,6 @@ hipError_t launch_march_cells(const MarchArgs& a, int wpb, hipStream_t s, const 
 size_t cells_lds_bytes(const MarchArgs& a, int wpb);
 hipError_t launch_march_block(const MarchArgs& a, hipStream_t s);
 size_t block_lds_bytes(const MarchArgs& a);
-// Differentiable forward on the ring layout (whole volume): also stores the
-// per-group checkpoints of sa (layer groups of sa.K cell layers).
 // Adjoint on the ring layout (grad_ring.hip): layer groups of ba.K cell layers.
 // T by division by 1 - a only for tables whose opacity stays at most this (an error
 // of a enters T multiplied by a / (1 - a)), and, where the checkpoints hold the
