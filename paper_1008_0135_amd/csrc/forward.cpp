@@ -320,8 +320,6 @@ int render_forward(vr_ctx* ctx, vr_volume* vol, const vr_view* views, int32_t nv
       vp.pixels = (int64_t)W * H;
     }
   }
-  // work items of a view marched by gathers: 64 / D pixels each (8 x 8 with
-  // macrocell skipping)
   // tiles of e x e pixels, numbered by blocks of 2 x 2
   auto gather_tiles = [](ViewPlan& vp, int32_t first, int32_t last, int32_t e) {
     int32_t t = 0;
@@ -333,6 +331,7 @@ int render_forward(vr_ctx* ctx, vr_volume* vol, const vr_view* views, int32_t nv
     }
     return t;
   };
+  // a view marched by gathers: 64 / depth pixels a wavefront (8 x 8 with macrocell skipping)
   auto gather_view = [&](ViewPlan& vp, int32_t depth) {
     if (vp.thru) depth = std::max(depth, 4);
     vp.deep = depth;

@@ -23,7 +23,7 @@ struct ViewPlan {
   // brick with slab axis class_axis[c] (1 or 2), then those marched by gathers
   // (class_axis 0); empty: one launch for the view
   std::vector<int32_t> class_begin, class_tiles, class_axis;
-  // gather march: lanes per ray (4 or 16; 0: another march), with macrocells
+  // gather march: lanes per ray (1, 4 or 16; 0: another march), with macrocells
   // passed over ray by ray (skip), or every ray through all its bricks (thru;
   // bv front to back)
   int32_t deep = 0;
@@ -43,7 +43,8 @@ struct MarchTimes {
 // voxels apart, sixteen lanes shorten the chain of a ray where there are few (two
 // views of 201 x 187 x 333 at 0.8 voxels 405 us with 16, 330 with 4; 400^3 at
 // 0.7 1.23 ms and 1.00, at 1.35 414 us and 484; 256^2 rays through 128^3 59
-// and 59, fewer rays up to twice as slow with 4).
+// and 59, fewer rays up to twice as slow with 4).  Fewer lanes, too, for views of
+// few of the `samples` per pixel.
 int32_t gather_lanes(const Camera& cam, double samples);
 // What the estimates need of the boxes a view marches, gathered in one pass over
 // them (a volume may have 65536).

@@ -104,9 +104,10 @@ struct vr_ctx {
   std::vector<Timed> timed;
   std::vector<hipEvent_t> event_pool;
   hipStream_t prof_stream = nullptr;
-  // march selection: 0 = automatic (per-layer ring when its windows fit, else
-  // LDS-staged slabs when a slab fits, else gather); 1 = gather only;
-  // 2 = LDS-staged slabs (else gather); 3 = same as 0
+  // march selection: 0 = automatic (footprint cells or gathers, whichever is
+  // estimated faster for the view); 1 = gathers with one lane per ray;
+  // 2 = LDS-staged slabs (else gather); 3 = windows in LDS wherever they fit,
+  // whatever the estimates say
   int32_t march_mode = 0;
   int32_t lds_budget = 4096;  // floats of LDS for one slab's voxel box
   int32_t bwd_layer_cap = 3;  // adjoint on the ring layout: cell layers per checkpoint group, at most
