@@ -53,7 +53,52 @@ constexpr double kThruBelow = 0.4e-3;
 // view of 24 x 23 x 14 voxels 105 and 28)
 constexpr double kCellsFixed = 60e-6;
 
+bool near_rays(const Camera& cam) {
+  return cam.S / (double)cam.W < 1.1 && (int64_t)cam.W * cam.H >= ((int64_t)1 << 16);
+}
+
+// Estimated time of a view's gathers with D lanes per ray: the wavefronts' set-up
+// (pixels x D / 64 of them, 0.87 ns each over the device, more with the table each
+// workgroup copies), the longest ray's chain of loads (0.5 us for D samples) and the
+// samples at 182 G/s, falling with the distance of the rays, faster the fewer lanes
+// lie along a ray.  Calibrated on 765 views of one volume (6 to 700 voxels a side,
+// 30 k to 1.7 M pixels, 64 to 4096 entries, each measured with 1, 4 and 16 lanes):
+// chosen so, a view takes 1.06 times its best number's time on average and at worst
+// 1.16 times its time with 16 lanes (rays 1.1 voxels apart or more; 1.17 times the best
+// with 16 always).  10 x 301 x 393 in perspective, three 486 x 450 views at step 2.7:
+// 143 us with 16 lanes, 61 with 4; two 287 x 821 views of 143 x 117 x 812: 149 and
+// 315; two 1130 x 1179 views of 8 x 9 x 7: 157 with 4, 76 with 1.
+double lanes_time(const Camera& cam, const BoxSums& boxes, double step, int32_t M, int32_t D) {
+  const double waves = (double)cam.W * cam.H * D / 64.0, apart = std::max(1.0, cam.S / (double)cam.W / 1.2);
+  const double chord = cam.persp ? 1.5 * boxes.chord : boxes.chord;  // (other rays' ways are longer)
+  return waves * 0.87e-9 * (1.0 + M / 1500.0) + chord / step / D * 0.5e-6 +
+         boxes.samples * (D == 16 ? std::sqrt(apart) : apart) / 182e9;
+}
+
 }  // namespace
+
+int32_t gather_lanes(const Camera& cam, const BoxSums& boxes, double step, int32_t M) {
+  const int64_t pixels = (int64_t)cam.W * cam.H;
+  auto time = [&](int32_t D) { return lanes_time(cam, boxes, step, M, D); };
+  // (few rays fill the device with 16 lanes only, below 2^18 not with one)
+  if (!near_rays(cam) && (pixels < ((int64_t)1 << 15) || time(4) >= 0.95 * time(16))) return 16;
+  return pixels >= ((int64_t)1 << 18) && time(1) < 0.7 * time(4) ? 1 : 4;
+}
+
+void add_box(BoxSums& s, const Camera& cam, const Box& b, double step) {
+  const double pitch = cam.S / (double)cam.W;
+  const double* d = cam.e3;
+  const double e[3] = {(double)(b.hi[0] - b.lo[0]), (double)(b.hi[1] - b.lo[1]), (double)(b.hi[2] - b.lo[2])};
+  const double vol = e[0] * e[1] * e[2];
+  const double area = std::fabs(d[0]) * e[1] * e[2] + std::fabs(d[1]) * e[0] * e[2] + std::fabs(d[2]) * e[0] * e[1];
+  const double rays = std::min(area / (pitch * pitch), (double)cam.W * cam.H);
+  s.samples += rays * vol / std::max(area, 1.0) / step;
+  s.bytes += 4.0 * vol;
+  double way = 1e30;
+  for (int i = 0; i < 3; i++) way = std::min(way, e[i] / std::max(std::fabs(d[i]), 1e-9));
+  s.chord = std::max(s.chord, way);
+  for (int i = 0; i < 3; i++) s.most[i] = std::max(s.most[i], b.hi[i] - b.lo[i]);
+}
 
 // Estimated times of a view (seconds) by the cell march with the shape fs
 // (infinite when null) and by gathers, for boxes marched side by side (and
@@ -71,36 +116,6 @@ constexpr double kCellsFixed = 60e-6;
 //     0.75 voxels apart, where the narrowest cells hold more than 64 of them,
 //     are left to the gathers (300^3 at 800^2, 0.65 voxels: 1.1 ms by cells,
 //     0.49 by gathers).
-static bool near_rays(const Camera& cam) {
-  return cam.S / (double)cam.W < 1.1 && (int64_t)cam.W * cam.H >= ((int64_t)1 << 16);
-}
-
-// Few samples (most rays miss the volume or cross a thin one): a wavefront's setup
-// costs more than its samples, and 16 lanes per ray set up four times the wavefronts
-// (10 x 301 x 393 in perspective, three 486 x 450 views at step 2.7, 0.8 samples a
-// pixel: 143 us with 16 lanes, 61 with 4; 362 x 11 x 284 in perspective at 858 x 1099, 1.1 a
-// pixel: 176 and 64).  Below 2^15 pixels the two are as fast (27 to 30 us).  Views of
-// 2^19 pixels and more, with fewer still: one lane per ray (pixels, samples a pixel,
-// four lanes, one: 0.7 M 1.3 59 and 42 us; 1.1 M 2.1 89 and 53; 0.9 M 3.4 67 and 100;
-// 0.3 M 1.3 33 and 42).
-int32_t gather_lanes(const Camera& cam, double samples) {
-  const int64_t pixels = (int64_t)cam.W * cam.H;
-  if (pixels >= ((int64_t)1 << 19) && samples < 2.5 * (double)pixels) return 1;
-  return near_rays(cam) || (pixels >= ((int64_t)1 << 15) && samples < 16.0 * (double)pixels) ? 4 : 16;
-}
-
-void add_box(BoxSums& s, const Camera& cam, const Box& b, double step) {
-  const double pitch = cam.S / (double)cam.W;
-  const double* d = cam.e3;
-  const double e[3] = {(double)(b.hi[0] - b.lo[0]), (double)(b.hi[1] - b.lo[1]), (double)(b.hi[2] - b.lo[2])};
-  const double vol = e[0] * e[1] * e[2];
-  const double area = std::fabs(d[0]) * e[1] * e[2] + std::fabs(d[1]) * e[0] * e[2] + std::fabs(d[2]) * e[0] * e[1];
-  const double rays = std::min(area / (pitch * pitch), (double)cam.W * cam.H);
-  s.samples += rays * vol / std::max(area, 1.0) / step;
-  s.bytes += 4.0 * vol;
-  for (int i = 0; i < 3; i++) s.most[i] = std::max(s.most[i], b.hi[i] - b.lo[i]);
-}
-
 MarchTimes march_times(const Camera& cam, const BoxSums& boxes, const FootShape* fs, int views) {
   MarchTimes t;
   t.pitch = cam.S / (double)cam.W;
@@ -373,7 +388,10 @@ int render_forward(vr_ctx* ctx, vr_volume* vol, const vr_view* views, int32_t nv
       const MarchTimes t = march_times(cams[v], sums[v], nullptr);
       if (choose && !forced && (nviews == 1 || t.pitch < 1.0 || t.gather < kThruBelow)) {
         thru_order(v);
-        gather_view(vp, gather_lanes(cams[v], sums[v].samples));
+        BoxSums rays = sums[v], all;
+        add_box(all, cams[v], whole, p->step);
+        rays.chord = all.chord;  // a ray's chain runs through all its bricks
+        gather_view(vp, gather_lanes(cams[v], rays, p->step, base.M));
         continue;
       }
       plan_waves(vol, cams[v], tw, vp);
@@ -428,7 +446,7 @@ int render_forward(vr_ctx* ctx, vr_volume* vol, const vr_view* views, int32_t nv
       }
     }
     if (!any) {
-      gather_view(vp, gather_lanes(cams[v], sums[v].samples));
+      gather_view(vp, gather_lanes(cams[v], sums[v], p->step, base.M));
       continue;
     }
     std::vector<DevBrickView> grouped;
@@ -475,7 +493,7 @@ int render_forward(vr_ctx* ctx, vr_volume* vol, const vr_view* views, int32_t nv
         sure = sure && t.gather < t.cells;
       }
       if (sure) {
-        gather_view(vp, gather_lanes(cams[v], sums[v].samples));
+        gather_view(vp, gather_lanes(cams[v], sums[v], p->step, base.M));
         continue;
       }
     }
@@ -497,7 +515,7 @@ int render_forward(vr_ctx* ctx, vr_volume* vol, const vr_view* views, int32_t nv
       if (ctx->debug_plan)
         std::fprintf(stderr, "[vr] view %d: estimated cells %.0f us, gathers %.0f us\n", v, t.cells * 1e6, t.gather * 1e6);
       if (t.gather < t.cells) {
-        gather_view(vp, gather_lanes(cams[v], sums[v].samples));
+        gather_view(vp, gather_lanes(cams[v], sums[v], p->step, base.M));
         continue;
       }
     }

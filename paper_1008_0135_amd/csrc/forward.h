@@ -38,20 +38,21 @@ struct MarchTimes {
   double samples = 0.0, chain = 0.0;  // samples, and the part of cells that is a wavefront's chain
   double pitch = 0.0;                 // voxels between rays
 };
+// What the estimates need of the boxes a view marches, gathered in one pass over
+// them (a volume may have 65536).
+struct BoxSums {
+  double samples = 0.0, bytes = 0.0;
+  double chord = 0.0;           // longest way along the view direction through a box, voxels
+  int64_t most[3] = {0, 0, 0};  // largest extent along each axis, voxels
+};
 // Lanes per ray of a view's gathers: 4 x 4 rays of four consecutive samples
 // touch fewer lines than 2 x 2 rays of sixteen where rays are less than 1.1
 // voxels apart, sixteen lanes shorten the chain of a ray where there are few (two
 // views of 201 x 187 x 333 at 0.8 voxels 405 us with 16, 330 with 4; 400^3 at
 // 0.7 1.23 ms and 1.00, at 1.35 414 us and 484; 256^2 rays through 128^3 59
-// and 59, fewer rays up to twice as slow with 4).  Fewer lanes, too, for views of
-// few of the `samples` per pixel.
-int32_t gather_lanes(const Camera& cam, double samples);
-// What the estimates need of the boxes a view marches, gathered in one pass over
-// them (a volume may have 65536).
-struct BoxSums {
-  double samples = 0.0, bytes = 0.0;
-  int64_t most[3] = {0, 0, 0};  // largest extent along each axis, voxels
-};
+// and 59, fewer rays up to twice as slow with 4); otherwise whichever number is
+// estimated faster, 1 among them.
+int32_t gather_lanes(const Camera& cam, const BoxSums& boxes, double step, int32_t M);
 void add_box(BoxSums& s, const Camera& cam, const Box& box, double step);
 MarchTimes march_times(const Camera& cam, const BoxSums& boxes, const FootShape* fs, int views = 1);
 
