@@ -855,6 +855,7 @@ static int brick_volume(vr_volume* vol, Partition& P, bool materialize, int32_t 
     r.vmin = mm[2 * b];
     r.vmax = mm[2 * b + 1];
     r.slack = (mat || vol->owned) ? 1 : 0;
+    r.wlo = mat ? r.clo[0] : -r.lo[0];
     vr_brick_desc& d = vol->bdesc[b];
     for (int i = 0; i < 3; i++) {
       d.lo[i] = bx.lo[i];

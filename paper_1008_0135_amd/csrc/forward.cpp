@@ -152,7 +152,10 @@ bool brick_rows_readable(const vr_volume* vol, int32_t brick, int32_t pitch) {
     if (!vol->bricked) continue;
     lo[i] = vol->bdesc[brick].slo[i];
     hi[i] = vol->bdesc[brick].shi[i];
-    if (!vol->materialized) continue;
+    if (!vol->materialized) {
+      if (i == 0) lo[0] = std::min(lo[0], std::max<int64_t>(0, hi[0] + 1 - pitch));  // DevBrick::wlo
+      continue;
+    }
     hi[i] -= lo[i];  // storage of its own
     lo[i] = 0;
     n[i] = hi[i] + 1;

@@ -296,7 +296,7 @@ __global__ __launch_bounds__(256) __attribute__((amdgpu_waves_per_eu(4))) void k
       glo = max((int)floorf(Ag_lo + Pg - arg - 0.05f), cloG);
       w.fb = w.gb = 0;
     }
-    w.f0 = uni(max(cloF, min(flo, chiF + 2 - pitch)));
+    w.f0 = uni(max(br.wlo, min(flo, chiF + 2 - pitch)));
     w.g0 = uni(max(cloG, min(glo, chiG + 2 - NG)));
     if constexpr (PERSP) {
       w.fb = uni(w.fb - w.f0);
@@ -478,7 +478,7 @@ __global__ __launch_bounds__(512) __attribute__((amdgpu_waves_per_eu(4))) void k
     const float Pf = (float)V * rf, Pg = (float)V * rg;
     const int flo = max((int)floorf(Af_lo + Pf - arf - 0.05f), cloF);
     const int glo = max((int)floorf(Ag_lo + Pg - arg - 0.05f), cloG);
-    w.f0 = uni(max(cloF, min(flo, chiF + 2 - pitch)));
+    w.f0 = uni(max(br.wlo, min(flo, chiF + 2 - pitch)));
     w.g0 = uni(max(cloG, min(glo, chiG + 2 - NG)));
     w.fb = w.gb = 0;
     return w;

@@ -190,6 +190,8 @@ struct DevBrick {
   int32_t clo[3], chi[3]; // clamps of the local cell index (global [0, n-2] shifted by -lo)
   float vmin, vmax;       // range of the stored voxels
   int32_t slack;          // 1: the storage is followed by >= 64 readable floats (row tails may be over-read)
+  int32_t wlo;            // a window's row may start here along axis 1 at the earliest (<= clo[0]: a brick
+                          // narrower than the row reads its neighbour's voxels, not past the storage's end)
 };
 
 // Per (view, rendered brick) record, in launch order.
