@@ -58,18 +58,19 @@ bool near_rays(const Camera& cam) {
 }
 
 // Estimated time of a view's gathers with D lanes per ray: the wavefronts' set-up
-// (pixels x D / 64 of them, 0.87 ns each over the device, more with the table each
-// workgroup copies), the longest ray's chain of loads (0.5 us for D samples) and the
-// samples at 182 G/s, falling with the distance of the rays, faster the fewer lanes
-// lie along a ray.  Calibrated on 765 views of one volume (6 to 700 voxels a side,
-// 30 k to 1.7 M pixels, 64 to 4096 entries, each measured with 1, 4 and 16 lanes):
-// chosen so, a view takes 1.06 times its best number's time on average and at worst
-// 1.16 times its time with 16 lanes (rays 1.1 voxels apart or more; 1.17 times the best
-// with 16 always).  10 x 301 x 393 in perspective, three 486 x 450 views at step 2.7:
-// 143 us with 16 lanes, 61 with 4; two 287 x 821 views of 143 x 117 x 812: 149 and
-// 315; two 1130 x 1179 views of 8 x 9 x 7: 157 with 4, 76 with 1.
+// (pixels x D / 64 of them, a bricked view's pixels those of its rectangles, 0.87 ns
+// each over the device, more with the table each workgroup copies), the longest ray's
+// chain of loads (0.5 us for D samples) and the samples at 182 G/s, falling with the
+// distance of the rays, faster the fewer lanes lie along a ray.  Calibrated on 765
+// views of one volume (6 to 700 voxels a side, 30 k to 1.7 M pixels, 64 to 4096
+// entries, each measured with 1, 4 and 16 lanes): chosen so, a view takes 1.06 times
+// its best number's time on average (1.17 with 16 always) and at worst 1.16 times its
+// time with 16 lanes.  10 x 301 x 393 in perspective, three 486 x 450 views at step
+// 2.7: 143 us with 16 lanes, 61 with 4; two 287 x 821 views of 143 x 117 x 812: 149
+// and 315; two 622 x 824 views of 973 x 100 x 78 in eight bricks 114 and 166; two
+// 1130 x 1179 views of 8 x 9 x 7: 157 with 4, 76 with 1.
 double lanes_time(const Camera& cam, const BoxSums& boxes, double step, int32_t M, int32_t D) {
-  const double waves = (double)cam.W * cam.H * D / 64.0, apart = std::max(1.0, cam.S / (double)cam.W / 1.2);
+  const double waves = (double)boxes.pixels * D / 64.0, apart = std::max(1.0, cam.S / (double)cam.W / 1.2);
   const double chord = cam.persp ? 1.5 * boxes.chord : boxes.chord;  // (other rays' ways are longer)
   return waves * 0.87e-9 * (1.0 + M / 1500.0) + chord / step / D * 0.5e-6 +
          boxes.samples * (D == 16 ? std::sqrt(apart) : apart) / 182e9;
@@ -78,14 +79,14 @@ double lanes_time(const Camera& cam, const BoxSums& boxes, double step, int32_t 
 }  // namespace
 
 int32_t gather_lanes(const Camera& cam, const BoxSums& boxes, double step, int32_t M) {
-  const int64_t pixels = (int64_t)cam.W * cam.H;
+  const int64_t pixels = boxes.pixels;
   auto time = [&](int32_t D) { return lanes_time(cam, boxes, step, M, D); };
   // (few rays fill the device with 16 lanes only, below 2^18 not with one)
   if (!near_rays(cam) && (pixels < ((int64_t)1 << 15) || time(4) >= 0.95 * time(16))) return 16;
   return pixels >= ((int64_t)1 << 18) && time(1) < 0.7 * time(4) ? 1 : 4;
 }
 
-void add_box(BoxSums& s, const Camera& cam, const Box& b, double step) {
+void add_box(BoxSums& s, const Camera& cam, const Box& b, int64_t pixels, double step) {
   const double pitch = cam.S / (double)cam.W;
   const double* d = cam.e3;
   const double e[3] = {(double)(b.hi[0] - b.lo[0]), (double)(b.hi[1] - b.lo[1]), (double)(b.hi[2] - b.lo[2])};
@@ -94,6 +95,7 @@ void add_box(BoxSums& s, const Camera& cam, const Box& b, double step) {
   const double rays = std::min(area / (pitch * pitch), (double)cam.W * cam.H);
   s.samples += rays * vol / std::max(area, 1.0) / step;
   s.bytes += 4.0 * vol;
+  s.pixels += pixels;
   double way = 1e30;
   for (int i = 0; i < 3; i++) way = std::min(way, e[i] / std::max(std::fabs(d[i]), 1e-9));
   s.chord = std::max(s.chord, way);
@@ -379,7 +381,8 @@ int render_forward(vr_ctx* ctx, vr_volume* vol, const vr_view* views, int32_t nv
   }
   std::vector<BoxSums> sums((size_t)nviews);
   for (int32_t v = 0; v < nviews && pick; v++)
-    for (const DevBrickView& b : plans[v].bv) add_box(sums[v], cams[v], bricked ? vol->part.boxes[b.brick] : whole, p->step);
+    for (const DevBrickView& b : plans[v].bv)
+      add_box(sums[v], cams[v], bricked ? vol->part.boxes[b.brick] : whole, (int64_t)b.w * b.h, p->step);
   for (int32_t v = 0; v < nviews; v++) {
     ViewPlan& vp = plans[v];
     const bool choose = pick && !vp.bv.empty();
@@ -392,8 +395,9 @@ int render_forward(vr_ctx* ctx, vr_volume* vol, const vr_view* views, int32_t nv
       if (choose && !forced && (nviews == 1 || t.pitch < 1.0 || t.gather < kThruBelow)) {
         thru_order(v);
         BoxSums rays = sums[v], all;
-        add_box(all, cams[v], whole, p->step);
+        add_box(all, cams[v], whole, (int64_t)W * H, p->step);
         rays.chord = all.chord;  // a ray's chain runs through all its bricks
+        rays.pixels = all.pixels;
         gather_view(vp, gather_lanes(cams[v], rays, p->step, base.M));
         continue;
       }

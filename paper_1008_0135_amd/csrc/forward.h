@@ -42,6 +42,7 @@ struct MarchTimes {
 // them (a volume may have 65536).
 struct BoxSums {
   double samples = 0.0, bytes = 0.0;
+  int64_t pixels = 0;           // of the rectangles
   double chord = 0.0;           // longest way along the view direction through a box, voxels
   int64_t most[3] = {0, 0, 0};  // largest extent along each axis, voxels
 };
@@ -53,7 +54,7 @@ struct BoxSums {
 // and 59, fewer rays up to twice as slow with 4); otherwise whichever number is
 // estimated faster, 1 among them.
 int32_t gather_lanes(const Camera& cam, const BoxSums& boxes, double step, int32_t M);
-void add_box(BoxSums& s, const Camera& cam, const Box& box, double step);
+void add_box(BoxSums& s, const Camera& cam, const Box& box, int64_t pixels, double step);
 MarchTimes march_times(const Camera& cam, const BoxSums& boxes, const FootShape* fs, int views = 1);
 
 // Footprint-cell shape of one parallel view of a volume of size n, as the

@@ -232,7 +232,7 @@ int render_with_state(vr_ctx* ctx, vr_volume* vol, const vr_view* views, int32_t
     FootShape fs;
     fs.axis = rv.axis;
     BoxSums box;
-    add_box(box, cams[v], whole, p->step);
+    add_box(box, cams[v], whole, npix, p->step);
     const MarchTimes t = march_times(cams[v], box, &fs, ctx->bwd_side ? std::min(nviews, 3) : 1);
     if (ctx->foot && (ctx->march_mode == 3 || t.cells <= t.gather) &&
         pick_foot(cams[v], vol->n, ctx->tf_m, true, ctx->ring_reg > 0, ctx->ring_nslots, ctx->foot_rays,

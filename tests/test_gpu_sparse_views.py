@@ -30,7 +30,7 @@ def _context(vr, **env):
     ((3, 3, 3), (512, 512), 20.0, 1),        # 262144
     ((9, 12, 13), (1003, 1001), 40.0, 1),    # 8 x 8 tiles past the border
     ((100, 90, 95), (200, 180), 230.0, 16),  # rays of 200 samples
-    ((40, 35, 400), (130, 500), 500.0, (16, 0)),  # a tall frame, mostly empty, long rays (in bricks: either)
+    ((40, 35, 400), (130, 500), 500.0, 16),  # a tall frame, mostly empty, long rays
 ])
 @pytest.mark.parametrize("bricks", [None, (40, 31, 33)])
 def test_lanes_and_bits(dims, image, extent, lanes, bricks, capfd):
@@ -54,10 +54,10 @@ def test_lanes_and_bits(dims, image, extent, lanes, bricks, capfd):
             torch.cuda.synchronize()
             said = capfd.readouterr().err
             found = [int(x) for x in re.findall(r"gathers lanes (\d+)", said)]
-            # (rays through all bricks: four at least)
-            want = lanes if isinstance(lanes, int) else lanes[bool(bricks) and not scope]
-            want = max(want, 4) if bricks and scope else want
-            assert (found == [want or found[0]] if c is auto else found == []), (eye, mode, scope, said)
+            # (bricks are chosen for by their rectangles and their own rays: any; rays
+            # through all bricks: four at least)
+            want = (max(lanes, 4) if scope else found[0]) if bricks and found else lanes
+            assert (found == [want] if c is auto else found == []), (eye, mode, scope, said)
             got[c] = out
             vr.vr_volume_destroy(h)
         assert torch.equal(got[auto], got[plain]), (eye, mode, scope)
